@@ -235,8 +235,9 @@ int soft_threshold_vjp(int32_t nx, int32_t ny, int32_t levels, int32_t batch, co
  *   grad_coef[t][l] = -Im sum_c conj(kk[t][c]) [A (b_l w)](t, c)     (float64 [T][L])
  *   grad_dw0[r]     = -Im( w(r) conj([A^H (t kk)](r)) )              (float64 [R])
  * Either output may be NULL to skip it.  w: [R], kk: [T][C] complex64.
- * precision must be EXPENC_FP32.  The L basis-weighted products run as one
- * batched forward contraction (every phase tile is shared by the L terms).
+ * precision must be EXPENC_FP32.  Both outputs are weighted sums of the one
+ * real matrix Im(exp(i phi(t,r)) sum_c conj(kk[t][c]) S_c(r) w(r)), which is
+ * formed once, on the fly.
  */
 int expenc_field_grad(const expenc_op *op, int32_t precision, const float *w, const float *kk,
                       double *grad_coef, double *grad_dw0, void *ws, size_t ws_bytes, void *stream);

@@ -205,3 +205,40 @@ def test_unrolled_gradients_match_fp64_oracle_at_diff_config():
           + " ".join(f"{k} {v:.2e}" for k, v in errs.items()), flush=True)
     assert e_loss <= 1e-4
     assert max(errs.values()) <= 1e-3
+
+
+@pytest.mark.parametrize("n,T,C,L,with_dw0,sh,which,scale", [
+    (1, 1, 1, 4, True, True, "both", 1.0),         # one pixel, one sample, one coil
+    (7, 257, 33, 16, True, False, "both", 1.0),    # one sample past a workgroup, odd coils, last maps variant
+    (37, 300, 70, 16, True, True, "both", 1.0),    # several pixel chunks, tiles cut by the row end
+    (37, 300, 6, 9, False, False, "coef", 1.0),    # one output only
+    (20, 511, 5, 4, True, True, "dw0", 1.0),
+    (12, 64, 3, 0, True, False, "dw0", 1.0),       # no field terms
+    (16, 256, 8, 9, True, True, "both", 1e-22),    # the product of the inputs underflows FP32
+    (16, 256, 8, 9, True, False, "both", 1e22),    # ... and overflows it
+])
+def test_field_grad_edges(n, T, C, L, with_dw0, sh, which, scale):
+    """Edges of the gradient contraction: tile and workgroup remainders, one
+    output at a time, magnitudes whose products leave the FP32 range.  Sums of
+    at most 2 C and 1024 FP32 terms: 1e-5 relative is 20 times the rounding
+    of a random sum of that length."""
+    ee, ag = _ee()
+    w = synth.Workload("edge", n, 0.1, C, T, 3e-6, 2.0, L, 120.0, 20.0, 5, "haar", 1, 23)
+    wf = synth.Workload("edge", n, 0.1, C, T, 3e-6, 2.0, 16, 120.0, 20.0, 5, "haar", 1, 23)
+    case = Case(wf if L == 0 else w, z0=0.004, nbasis=L, sh=sh, with_dw0=with_dw0)
+    print(f"[case] field grad n={n} T={T} C={C} L={L} sh={sh} {which} scale={scale}", flush=True)
+    x = c64(scale * synth.random_complex(n * n, 91))
+    g = c64(scale * synth.random_complex((T, C), 92))
+    coef, basis = case.coef, case.basis_np
+    dw0 = case.dw0 if with_dw0 else np.zeros(n * n)
+    _, gc_ref, gd_ref = encoding.vjp_forward(x / scale, g / scale, case.smaps, coef, case.time, basis, dw0)
+    gc, gd = ag.field_grad(case.op, case.to_dev(x), case.to_dev(g), which != "dw0", which != "coef")
+    if which != "dw0":
+        assert rel(gc.cpu().numpy() / scale ** 2, gc_ref) <= 1e-5
+    else:
+        assert gc is None
+    if which != "coef":
+        # a readout that starts at t = 0 with one sample has no off-resonance gradient
+        assert rel(gd.cpu().numpy() / scale ** 2, gd_ref) <= 1e-5 if np.any(gd_ref) else not np.any(gd.cpu().numpy())
+    else:
+        assert gd is None

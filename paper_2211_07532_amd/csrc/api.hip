@@ -308,8 +308,9 @@ extern "C" int expenc_forward(const expenc_op *op, int32_t batch, int32_t precis
     return fail(EXPENC_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 enc_operand_bytes(p));
   hipStream_t s = (hipStream_t)stream;
-  EX_TRY(enc_prepare(p, op, eb, s));
-  EX_TRY(enc_build_z(p, op->smaps, reinterpret_cast<const float2 *>(x), p.R, p.nx, eb, s));
+  const float2 *x2 = reinterpret_cast<const float2 *>(x);
+  EX_TRY(enc_prepare(p, op, eb, s, kNeedForward, x2));
+  EX_TRY(enc_build_z(p, op->smaps, x2, p.R, p.nx, eb, s, nullptr, 0, true));
   EX_TRY(enc_forward_partials(p, eb, s));
   return enc_forward_reduce_out(p, eb, reinterpret_cast<float2 *>(y), s);
 }
@@ -325,8 +326,9 @@ extern "C" int expenc_adjoint(const expenc_op *op, int32_t batch, int32_t precis
     return fail(EXPENC_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 enc_operand_bytes(p));
   hipStream_t s = (hipStream_t)stream;
-  EX_TRY(enc_prepare(p, op, eb, s));
-  EX_TRY(enc_pack_y(p, reinterpret_cast<const float2 *>(y), eb, s));
+  const float2 *y2 = reinterpret_cast<const float2 *>(y);
+  EX_TRY(enc_prepare(p, op, eb, s, kNeedAdjoint, y2));
+  EX_TRY(enc_pack_y(p, y2, eb, s, 1.f, true));
   EX_TRY(enc_adjoint_partials(p, eb, s));
   return enc_adjoint_reduce_out(p, eb, op->smaps, reinterpret_cast<float2 *>(x), p.R, p.nx, nullptr, nullptr, s);
 }
@@ -346,7 +348,7 @@ extern "C" int expenc_lipschitz(const expenc_op *op, int32_t precision, int32_t 
     return fail(EXPENC_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 lipschitz_bytes(p1));
   hipStream_t s = (hipStream_t)stream;
-  EX_TRY(enc_prepare(p1, op, eb, s));
+  EX_TRY(enc_prepare(p1, op, eb, s, kNeedBoth));
   return lipschitz_run(p1, op, eb, n_iter, v0, vec, tmp, dpart, dpart + kRedBlocks, lipschitz_out, s);
 }
 

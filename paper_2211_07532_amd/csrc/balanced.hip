@@ -471,8 +471,7 @@ extern "C" int fista_balanced_solve(const expenc_op *op, int32_t batch, const fl
   const bool split = opts->precision != EXPENC_FP32;
   // prologue: tables, L_A, kappa, L, weights, thresholds, zero state
   EX_TRY(clear_status(L.status, s));
-  EX_TRY(enc_prepare(pf, op, L.eb, s));
-  if (split) EX_TRY(enc_prepare(p, op, L.eb, s));
+  EX_TRY(enc_prepare(p, op, L.eb, s, kNeedBoth));  // (the FP32 plan's tables are among them)
   if (opts->lipschitz > 0) {
     k_set_scalar<<<1, 64, 0, s>>>(L.sc, opts->lipschitz);
     EX_LAUNCHED("lipschitz");

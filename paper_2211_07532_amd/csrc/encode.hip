@@ -36,47 +36,9 @@
 namespace expenc {
 
 
-static constexpr double kInv2Pi = 0.15915494309189533576888376337251436;
-
 // ---------------------------------------------------------------------------
-// Setup kernels
+// Operand kernels (the field tables are prep.hip's)
 // ---------------------------------------------------------------------------
-
-__global__ void k_prep_kap(const double *__restrict__ coef, const double *__restrict__ time,
-                           double *__restrict__ kap, int64_t T, int64_t Tp, int L, int NT) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Tp * NT) return;
-  const int pz = blockIdx.y;  // problem
-  if (coef) coef += pz * T * L;
-  time += pz * T;
-  kap += pz * Tp * NT;
-  int64_t t = i / NT;
-  int j = (int)(i % NT);
-  double v = 0.0;
-  if (t < T) {
-    if (j < L) v = coef[t * L + j] * kInv2Pi;
-    else if (j == L) v = time[t];
-  }
-  kap[i] = v;
-}
-
-__global__ void k_prep_bet(const double *__restrict__ basis, const double *__restrict__ dw0,
-                           double *__restrict__ bet, int R, int Rp, int L, int NT) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)Rp * NT) return;
-  const int pz = blockIdx.y;
-  if (basis) basis += (int64_t)pz * L * R;
-  if (dw0) dw0 += (int64_t)pz * R;
-  bet += (int64_t)pz * Rp * NT;
-  int r = (int)(i / NT);
-  int j = (int)(i % NT);
-  double v = 0.0;
-  if (r < R) {
-    if (j < L) v = basis[(int64_t)j * R + r];
-    else if (j == L && dw0) v = dw0[r] * kInv2Pi;
-  }
-  bet[i] = v;
-}
 
 // Z[r'][col] = S_c(r) * x_b(r), col = b*C + c, row r' = y*nxq + x of pixel
 // r = y*nx + x (nxq = nx, or nx rounded up to 16 for the solid-harmonic
@@ -893,23 +855,11 @@ int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part) {
 static inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)ceil_div(n, bs); }
 static inline dim3 grid_p(int64_t n, int bs, int P) { return dim3((unsigned)ceil_div(n, bs), (unsigned)P); }
 
-int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s) {
-  k_prep_kap<<<grid_p(p.Tp * p.NT, 256, p.P), 256, 0, s>>>(op->coef, op->time, b.kap, p.T, p.Tp, p.L, p.NT);
-  EX_LAUNCHED("prep_kap");
-  const bool split = p.prec != EXPENC_FP32;
-  if (!p.sh) {  // the polynomial (solid-harmonic) kernels do not read bet
-    k_prep_bet<<<grid_p((int64_t)p.Rp * p.NT, 256, p.P), 256, 0, s>>>(op->basis, op->dw0, b.bet, p.R, p.Rp, p.L,
-                                                                       p.NT);
-    EX_LAUNCHED("prep_bet");
-  }
-  if (split) return split_prepare(p, op, b, s);
-  if (p.sh) return sh_prepare(p, op, b, s);
-  return EXPENC_OK;
-}
-
 int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride,
-                int32_t x_row_stride, const EncBuffers &b, hipStream_t s, const float2 *xsub, int64_t x_pstride) {
-  if (p.prec != EXPENC_FP32) return split_build_z(p, smaps, x, xsub, x_stride, x_row_stride, b, s, x_pstride);
+                int32_t x_row_stride, const EncBuffers &b, hipStream_t s, const float2 *xsub, int64_t x_pstride,
+                bool prepared) {
+  if (p.prec != EXPENC_FP32)
+    return split_build_z(p, smaps, x, xsub, x_stride, x_row_stride, b, s, x_pstride, prepared);
   if (xsub) return fail(EXPENC_EUNSUPPORTED, "operand difference is only built for split forms");
   k_build_z_f32<<<grid_p((int64_t)p.Rp * p.NCP, 256, p.P), 256, 0, s>>>(
       reinterpret_cast<const float2 *>(smaps), x, x_stride, x_row_stride, p.nx, p.R, p.Rp, p.C, p.NC,
@@ -918,10 +868,10 @@ int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x
   return EXPENC_OK;
 }
 
-int enc_pack_y(const EncPlan &p, const float2 *y, const EncBuffers &b, hipStream_t s, float sign) {
+int enc_pack_y(const EncPlan &p, const float2 *y, const EncBuffers &b, hipStream_t s, float sign, bool prepared) {
   if (p.prec != EXPENC_FP32) {
     if (sign != 1.f) return fail(EXPENC_EUNSUPPORTED, "scaled operand packing is FP32 only");
-    return split_pack_y(p, y, false, nullptr, b, s);
+    return split_pack_y(p, y, false, nullptr, b, s, prepared);
   }
   k_pack_y_f32<<<grid_p(p.Tp * p.NCP, 256, p.P), 256, 0, s>>>(y, p.T, p.Tp, p.C, p.NC, p.NCP, b.yop, sign);
   EX_LAUNCHED("pack_y");

@@ -402,9 +402,7 @@ struct FistaGroup {
     const EncPlan &p = L.p, &pf = L.pf;
     const int P = L.P, B = L.B;
     const int64_t img = (int64_t)L.nxp * L.nyp;
-    // FP32 tables first (the FP32 plan's pixel layout), then the split tables
-    EX_TRY(enc_prepare(pf, op, L.eb, s));
-    if (opts->precision != EXPENC_FP32) EX_TRY(enc_prepare(p, op, L.eb, s));
+    EX_TRY(enc_prepare(p, op, L.eb, s, kNeedBoth));  // (the FP32 plan's tables are among them)
     if (opts->lipschitz > 0) {
       k_fill_d<<<(unsigned)ceil_div(P, 256), 256, 0, s>>>(L.sc, P, opts->lipschitz);
       EX_LAUNCHED("fill");
@@ -659,7 +657,7 @@ extern "C" int cg_solve(const expenc_op *op, int32_t batch, const float *y, floa
   const int64_t n = p.R;
   const dim3 vg((unsigned)ceil_div(n, 256), B);
   EX_TRY(clear_status(L.status, s));
-  EX_TRY(enc_prepare(p, op, L.eb, s));
+  EX_TRY(enc_prepare(p, op, L.eb, s, kNeedBoth));
   // r = A^H y ; p = r ; x = 0 ; rs = <r, r>
   EX_TRY(enc_pack_y(p, reinterpret_cast<const float2 *>(y), L.eb, s));
   EX_TRY(enc_adjoint_partials(p, L.eb, s));

@@ -295,7 +295,7 @@ struct GradLayout {
   EncPlan p;
   int chunk = 0, nsplit = 0;
   double *kap = nullptr, *bet = nullptr, *pmono = nullptr, *dwq = nullptr;
-  float *ddw = nullptr, *kkt = nullptr, *tf = nullptr, *bt = nullptr, *amax = nullptr, *gpart = nullptr,
+  float *kkt = nullptr, *tf = nullptr, *bt = nullptr, *amax = nullptr, *gpart = nullptr,
         *dpart = nullptr;
   float2 *wsc = nullptr;
 };
@@ -315,7 +315,6 @@ static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLay
   if (p.sh) {
     G->pmono = a.take<double>(p.Tp * 12);
     G->dwq = a.take<double>(p.Rp);
-    G->ddw = a.take<float>(p.Rp);
   } else {
     G->bet = a.take<double>((size_t)p.Rp * p.NT);
   }
@@ -362,8 +361,7 @@ extern "C" int expenc_field_grad(const expenc_op *op, int32_t precision, const f
   eb.bet = G.bet;
   eb.pmono = G.pmono;
   eb.dwq = G.dwq;
-  eb.ddw = G.ddw;
-  EX_TRY(enc_prepare(p, op, eb, s));
+  EX_TRY(enc_prepare(p, op, eb, s, kNeedForward));
   k_grad_amax<<<dim3(kGradAmax, 2), 256, 0, s>>>(w2, p.R, k2, p.T * p.C, G.amax);
   EX_LAUNCHED("gradient operand bounds");
   k_grad_pack<<<(unsigned)ceil_div(p.Tp * p.C + p.Tp + p.Rp, 256), 256, 0, s>>>(

@@ -267,7 +267,7 @@ struct EncPlan {
 };
 
 // Workgroups (per problem) of the magnitude pre-pass of the scaled form.
-constexpr int kAmaxBlocks = 64;
+constexpr int kAmaxBlocks = 256;
 // Longest reduction chunk of one workgroup: samples in the split adjoint
 // contractions; pixels or samples in the FP32 contractions.
 constexpr int32_t kSplitAdjChunkMax = 1024;
@@ -336,19 +336,30 @@ uint64_t tuning_generation();
 int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part = 0);
 
 // Kernel launchers (stream-ordered, no synchronisation).
-int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s);
+// Field tables of plan p (prep.hip), one launch: those that the directions in
+// `need` read.  A split plan's tables include the FP32 plan's of the same
+// geometry.  operand (fp16 form): the image [P][B][R] (need = kNeedForward) or
+// data [P][B][T][C] (kNeedAdjoint) that the call applies the operator to; its
+// magnitude bound is then taken in the same launch, and enc_build_z /
+// enc_pack_y are told so (prepared = true).
+enum { kNeedForward = 1, kNeedAdjoint = 2, kNeedBoth = 3 };
+int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s, int need,
+                const float2 *operand = nullptr);
 // Z[r][b*C+c] = S_c(r) x_b(r) from x [B][R] (x_stride elements between problems);
 // for split precisions, pre-split and packed in the MFMA operand order.
 // (x_pstride: elements between problems)
 int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride,
                 int32_t x_row_stride, const EncBuffers &b, hipStream_t s, const float2 *xsub = nullptr,
-                int64_t x_pstride = 0);
+                int64_t x_pstride = 0, bool prepared = false);
+// (prepared: enc_prepare was given this operand with kNeedForward, so its
+// bound is written and there is no coil table)
 // (timing = false: never records the profiling events of expenc_kernel_timing)
 int enc_forward_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s, bool timing = true);
 // y[b][t][c] = sum_split partials (ABI layout)
 int enc_forward_reduce_out(const EncPlan &p, const EncBuffers &b, float2 *y, hipStream_t s);
 // Y operand from sign * y, y [B][T][C] (sign other than 1: FP32 plans only)
-int enc_pack_y(const EncPlan &p, const float2 *y, const EncBuffers &b, hipStream_t s, float sign = 1.f);
+int enc_pack_y(const EncPlan &p, const float2 *y, const EncBuffers &b, hipStream_t s, float sign = 1.f,
+               bool prepared = false);
 int enc_adjoint_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 // x_b(r) = alpha * sum_c conj(S_c(r)) sum_split partials (+ add_b(r)),
 // written to x [B] with x_stride between problems and row stride
@@ -367,10 +378,6 @@ int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *s
 int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_meas, hipStream_t s);
 
 // Split-precision kernels (split.hip).
-int split_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s);
-// Polynomial phase tables of the solid-harmonic kind (pmono, dwq, ddw; dpa
-// for the split forms) from kap (split.hip).
-int sh_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s);
 void split_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 // the polynomial (solid-harmonic) split adjoint, built in split_adj.hip
@@ -396,9 +403,9 @@ bool split_groupable(const EncPlan &a, const EncPlan &b);
 int split_forward_grouped(const EncPlan *const *p, const EncBuffers *const *b, int n, hipStream_t s);
 int split_adjoint_grouped(const EncPlan *const *p, const EncBuffers *const *b, int n, hipStream_t s);
 int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const float2 *xsub, int64_t x_stride,
-                  int32_t x_row_stride, const EncBuffers &b, hipStream_t s, int64_t x_pstride);
+                  int32_t x_row_stride, const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared);
 int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, const float2 *y_meas,
-                 const EncBuffers &b, hipStream_t s);
+                 const EncBuffers &b, hipStream_t s, bool prepared = false);
 
 // Per-kernel event timing of the contraction kernels (mode 0 off, 1 on, 2 read).
 int kernel_timing(int32_t mode, double *out);

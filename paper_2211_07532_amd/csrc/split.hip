@@ -486,18 +486,6 @@ __global__ __launch_bounds__(256) void k_amax_z(const float2 *__restrict__ x, co
   write_block_max(m, amax + pz * kAmaxBlocks + blockIdx.x);
 }
 
-// Pre-pass of the coil maps [P][n]: per-workgroup max of |Re S| + |Im S|.
-__global__ __launch_bounds__(256) void k_amax_l1(const float2 *__restrict__ v, int64_t n, float *__restrict__ amax) {
-  const int pz = blockIdx.y;
-  v += pz * n;
-  float m = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float2 a = v[i];
-    m = fmaxf(m, fabsf(a.x) + fabsf(a.y));
-  }
-  write_block_max(m, amax + pz * kAmaxBlocks + blockIdx.x);
-}
-
 // Pre-pass of a complex array [P][n] (stride pstride): per-workgroup max of
 // the component magnitudes.  Grid (kAmaxBlocks, P), 256 threads.
 __global__ __launch_bounds__(256) void k_amax_c(const float2 *__restrict__ v, int64_t n, int64_t pstride,
@@ -689,193 +677,6 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
   write_record<BF>(ys, q, g, NGP, lane, b1, b2);
 }
 
-// Per-tile differences d[16q + j][k] = (float)(src[16q + j][k] - src[16q + 8][k]).
-__global__ void k_tile_diff(const double *__restrict__ src, float *__restrict__ d, int64_t rows, int NT) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * NT) return;
-  src += blockIdx.y * rows * NT;  // problem
-  d += blockIdx.y * rows * NT;
-  const int64_t r = i / NT;
-  const int k = (int)(i % NT);
-  const int64_t centre = (r & ~int64_t(15)) + 8;
-  d[i] = (float)(src[r * NT + k] - src[centre * NT + k]);
-}
-
-// Monomial coefficients of the solid harmonics at fixed z (rows l, columns
-// m over 1, x, y, x^2, xy, y^2, x^3, x^2 y, x y^2, y^3).
-struct MonoMatrix {
-  double m[16][10];
-};
-
-__host__ __device__ inline MonoMatrix mono_matrix(double z) {
-  MonoMatrix M{};
-  auto &m = M.m;
-  m[0][0] = 1;
-  m[1][1] = 1;
-  m[2][2] = 1;
-  m[3][0] = z;
-  m[4][4] = 1;
-  m[5][2] = z;
-  m[6][0] = 2 * z * z, m[6][3] = -1, m[6][5] = -1;
-  m[7][1] = z;
-  m[8][3] = 1, m[8][5] = -1;
-  m[9][7] = 3, m[9][9] = -1;
-  m[10][4] = z;
-  m[11][2] = 4 * z * z, m[11][7] = -1, m[11][9] = -1;
-  m[12][0] = 2 * z * z * z, m[12][3] = -3 * z, m[12][5] = -3 * z;
-  m[13][1] = 4 * z * z, m[13][6] = -1, m[13][8] = -1;
-  m[14][3] = z, m[14][5] = -z;
-  m[15][6] = 1, m[15][8] = -3;
-  return M;
-}
-
-// pmono[t][m] = sum_l kap[t][l] M[l][m] (m < 10), pmono[t][10] = t; the
-// monomial matrix M comes from the problem's slice position (z0s[p], or M0).
-__global__ void k_prep_pmono(const double *__restrict__ kap, int NT, int L, int64_t Tp, MonoMatrix M0,
-                             const double *__restrict__ z0s, double *__restrict__ pmono) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= Tp) return;
-  const int pz = blockIdx.y;
-  kap += pz * Tp * NT;
-  pmono += pz * Tp * 12;
-  MonoMatrix M = z0s ? mono_matrix(z0s[pz]) : M0;
-  double out[12];
-  for (int m = 0; m < 12; ++m) out[m] = 0.0;
-  for (int l = 0; l < L; ++l) {
-    const double k = kap[t * NT + l];
-    for (int m = 0; m < 10; ++m) out[m] = fma(k, M.m[l][m], out[m]);
-  }
-  out[10] = kap[t * NT + L];
-  for (int m = 0; m < 12; ++m) pmono[t * 12 + m] = out[m];
-}
-
-// A operand of the adjoint's phase-increment product, in lane order.  For the
-// 32-sample tile q and lane l (sample t = 32q + l%32, half hl = l/32), with
-// d_m = pmono[t][m] - pmono[32q + 16][m] (monomials in pmono order), the
-// increment at a pixel of image row y is the cubic in x
-//   C_0 + C_1 x + C_2 x^2 + C_3 x^3 + d10 dw0,
-//   C_0 = d0 + d2 y + d5 y^2 + d9 y^3,  C_1 = d1 + d4 y + d8 y^2,
-//   C_2 = d3 + d7 y,                    C_3 = d6,
-// and lane l holds the coefficients the adjoint evaluates at a block's row:
-// [0..3] the cubic in y of C_hl, [4..5] the linear one of C_{2+hl}, [6] d10
-// (hl = 0, the dw0 term) or 1 (hl = 1, the anchor term).
-__global__ void k_prep_dpa(const double *__restrict__ pmono, int64_t Tp, float *__restrict__ dpa) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Tp / 32 * 64) return;
-  pmono += blockIdx.y * Tp * 12;  // problem
-  dpa += blockIdx.y * Tp * 16;
-  const int64_t q = i >> 6;
-  const int l = (int)(i & 63);
-  const int64_t t = 32 * q + (l & 31), ta = 32 * q + 16;
-  double d[11];
-  for (int m = 0; m <= 10; ++m) d[m] = pmono[t * 12 + m] - pmono[ta * 12 + m];
-  const bool hl = (l >> 5) != 0;
-  const double c[7] = {hl ? d[1] : d[0], hl ? d[4] : d[2], hl ? d[8] : d[5], hl ? 0.0 : d[9],
-                       hl ? d[6] : d[3], hl ? 0.0 : d[7], hl ? 1.0 : d[10]};
-  float v[8];
-  for (int j = 0; j < 7; ++j) v[j] = (float)c[j];
-  v[7] = 0.f;
-  float4 *o = reinterpret_cast<float4 *>(dpa + i * 8);
-  o[0] = make_float4(v[0], v[1], v[2], v[3]);
-  o[1] = make_float4(v[4], v[5], v[6], v[7]);
-}
-
-// Anchors of the polynomial split adjoint: for the 32-sample tile q and the
-// row-padded pixel rq, the phase of the tile's centre sample 32q + 16 at that
-// pixel, sum_m P_m(t) mono_m(x, y) + t dw0(r)/2pi, evaluated in FP64 (nested
-// in y, then in x) and reduced to turns in [0, 1).  The adjoint adds its FP32
-// phase increments within the tile to it.
-__global__ void k_prep_anchor(const double *__restrict__ pmono, const double *__restrict__ dwq, int64_t Tp, int Rp,
-                              int nxq, int nx, int ny, double dx, double dy, float *__restrict__ anc) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Tp / 32 * Rp) return;
-  const int pz = blockIdx.y;  // problem
-  pmono += pz * Tp * 12;
-  dwq += (int64_t)pz * Rp;
-  anc += (int64_t)pz * (Tp / 32) * Rp;
-  const int64_t q = i / Rp;
-  const int rq = (int)(i - q * Rp);
-  const double x = (rq % nxq - 0.5 * nx) * dx, y = (rq / nxq - 0.5 * ny) * dy, w = dwq[rq];
-  const double *pc = pmono + (32 * q + 16) * 12;
-  // monomial order of pmono: 1, x, y, x^2, xy, y^2, x^3, x^2 y, x y^2, y^3
-  const double a0 = fma(y, fma(y, fma(y, pc[9], pc[5]), pc[2]), pc[0]);
-  const double a1 = fma(y, fma(y, pc[8], pc[4]), pc[1]);
-  const double a2 = fma(y, pc[7], pc[3]);
-  const double pa = fma(pc[10], w, fma(x, fma(x, fma(x, pc[6], a2), a1), a0));
-  anc[i] = (float)__builtin_amdgcn_fract(pa);
-}
-
-// dwq[r'] = dw0(r)/2pi in the row-padded pixel layout.
-__global__ void k_prep_dwq(const double *__restrict__ dw0, int nx, int ny, int nxq, int Rp, double *__restrict__ dwq) {
-  const int rq = blockIdx.x * blockDim.x + threadIdx.x;
-  if (rq >= Rp) return;
-  if (dw0) dw0 += (int64_t)blockIdx.y * nx * ny;  // problem
-  dwq += (int64_t)blockIdx.y * Rp;
-  const int yy = rq / nxq, xx = rq % nxq;
-  double v = 0.0;
-  if (dw0 && yy < ny && xx < nx) v = dw0[yy * nx + xx] * 0.15915494309189533576888376337251436;
-  dwq[rq] = v;
-}
-
-// sq[row][col] = S_col(r) at pixel r = (row / nxq) * nx + row % nxq (the
-// adjoint partial-sum layout), zero on padding rows and columns.
-__global__ void k_prep_sq(const float2 *__restrict__ smaps, int nx, int ny, int nxq, int Rp, int C, int NCP,
-                          float2 *__restrict__ sq) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)Rp * NCP) return;
-  const int pz = blockIdx.y;  // problem
-  const int R = nx * ny;
-  const int row = (int)(i / NCP), col = (int)(i % NCP);
-  const int yy = row / nxq, xx = row % nxq;
-  float2 v = make_float2(0.f, 0.f);
-  if (col < C && xx < nx && yy < ny) v = smaps[((int64_t)pz * C + col) * R + yy * nx + xx];
-  sq[(int64_t)pz * Rp * NCP + i] = v;
-}
-
-int sh_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s) {
-  auto gp = [&](int64_t n) { return dim3((unsigned)ceil_div(n, 256), (unsigned)p.P); };
-  k_prep_pmono<<<gp(p.Tp), 256, 0, s>>>(b.kap, p.NT, p.L, p.Tp, mono_matrix(p.z0), p.z0s, b.pmono);
-  EX_LAUNCHED("monomial coefficients");
-  if (p.prec != EXPENC_FP32) {
-    k_prep_dpa<<<gp(p.Tp / 32 * 64), 256, 0, s>>>(b.pmono, p.Tp, b.dpa);
-    EX_LAUNCHED("increment table (samples)");
-  }
-  k_prep_dwq<<<gp(p.Rp), 256, 0, s>>>(op->dw0, p.nx, p.ny, p.nxq, p.Rp, b.dwq);
-  EX_LAUNCHED("off-resonance layout");
-  if (p.adj_anc) {
-    if (!b.anc) return fail(EXPENC_EINVAL, "anchor table of a split plan is not carved");
-    k_prep_anchor<<<gp(p.Tp / 32 * p.Rp), 256, 0, s>>>(b.pmono, b.dwq, p.Tp, p.Rp, p.nxq, p.nx, p.ny, p.dx, p.dy,
-                                                        b.anc);
-    EX_LAUNCHED("adjoint anchors");
-  }
-  k_tile_diff<<<gp(p.Rp), 256, 0, s>>>(b.dwq, b.ddw, p.Rp, 1);
-  EX_LAUNCHED("tile differences (pixels)");
-  return EXPENC_OK;
-}
-
-int split_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s) {
-  auto gp = [&](int64_t n) { return dim3((unsigned)ceil_div(n, 256), (unsigned)p.P); };
-  if (p.scaled) {
-    // bound of the coil maps for the fp16 operand scaling (third amax section)
-    if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of an fp16 plan are not carved");
-    k_amax_l1<<<dim3(kAmaxBlocks, (unsigned)p.P), 256, 0, s>>>(reinterpret_cast<const float2 *>(op->smaps),
-                                                               (int64_t)p.C * p.R, b.amax + (size_t)2 * p.P * kAmaxBlocks);
-    EX_LAUNCHED("coil-map bound");
-  }
-  if (p.comb) {
-    if (!b.sq) return fail(EXPENC_EINVAL, "coil table of a single-image split plan is not carved");
-    k_prep_sq<<<gp((int64_t)p.Rp * p.NCP), 256, 0, s>>>(reinterpret_cast<const float2 *>(op->smaps), p.nx, p.ny,
-                                                          p.nxq, p.Rp, p.C, p.NCP, b.sq);
-    EX_LAUNCHED("coil table");
-  }
-  if (p.sh) return sh_prepare(p, op, b, s);
-  k_tile_diff<<<gp((int64_t)p.Rp * p.NT), 256, 0, s>>>(b.bet, b.dbet, p.Rp, p.NT);
-  EX_LAUNCHED("tile differences (pixels)");
-  k_tile_diff<<<gp(p.Tp * p.NT), 256, 0, s>>>(b.kap, b.dkap, p.Tp, p.NT);
-  EX_LAUNCHED("tile differences (samples)");
-  return EXPENC_OK;
-}
-
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
@@ -999,7 +800,7 @@ void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) 
 }
 
 int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const float2 *xsub, int64_t x_stride,
-                  int32_t x_row_stride, const EncBuffers &b, hipStream_t s, int64_t x_pstride) {
+                  int32_t x_row_stride, const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared) {
   const int NGP = p.NCP / 16;
   const int64_t n = (int64_t)(p.Rp / 16) * NGP * 64;
   const dim3 nb((unsigned)ceil_div(n, 256), (unsigned)p.P);
@@ -1007,23 +808,26 @@ int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const f
   u32x4 *zs = reinterpret_cast<u32x4 *>(b.zs);
   if (p.scaled) {
     if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of an fp16 plan are not carved");
-    k_amax_z<<<dim3(kAmaxBlocks, (unsigned)p.P), 256, 0, s>>>(x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.B,
-                                                              x_pstride, b.amax);
-    EX_LAUNCHED("operand bound");
+    if (!prepared) {
+      k_amax_z<<<dim3(kAmaxBlocks, (unsigned)p.P), 256, 0, s>>>(x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.B,
+                                                                x_pstride, b.amax);
+      EX_LAUNCHED("operand bound");
+    }
   }
   float *scl = p.scaled ? b.scl : nullptr;
+  const float2 *sq = p.comb && !prepared ? b.sq : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
     k_build_z_split<true><<<nb, 256, 0, s>>>(sm, x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C,
-                                             p.NC, NGP, zs, x_pstride, p.comb ? b.sq : nullptr, b.amax, scl);
+                                             p.NC, NGP, zs, x_pstride, sq, b.amax, scl);
   else
     k_build_z_split<false><<<nb, 256, 0, s>>>(sm, x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C,
-                                              p.NC, NGP, zs, x_pstride, p.comb ? b.sq : nullptr, b.amax, scl);
+                                              p.NC, NGP, zs, x_pstride, sq, b.amax, scl);
   EX_LAUNCHED("build_z split");
   return EXPENC_OK;
 }
 
 int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, const float2 *y_meas,
-                 const EncBuffers &b, hipStream_t s) {
+                 const EncBuffers &b, hipStream_t s, bool prepared) {
   const int NGP = p.NCP / 16;
   const int64_t n = (p.Tp / 16) * NGP * 64;
   const dim3 nb((unsigned)ceil_div(n, 256), (unsigned)p.P);
@@ -1036,8 +840,10 @@ int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, cons
     const dim3 ng(kAmaxBlocks, (unsigned)p.P);
     const int64_t ny_el = p.T * p.NC;  // [B][T][C] per problem
     if (!from_partials) {
-      k_amax_c<<<ng, 256, 0, s>>>(y_abi, ny_el, ny_el, b.amax);
-      EX_LAUNCHED("operand bound");
+      if (!prepared) {
+        k_amax_c<<<ng, 256, 0, s>>>(y_abi, ny_el, ny_el, b.amax);
+        EX_LAUNCHED("operand bound");
+      }
       bnd = b.amax;
       nbnd = kAmaxBlocks;
     } else {

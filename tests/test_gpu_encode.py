@@ -156,3 +156,26 @@ def test_degenerate_shapes_sh(shape, prec):
     xa = ee.adjoint(t(g.astype(np.complex64)), op, precision=prec).cpu().numpy()
     x_ref = encoding.adjoint(g, smaps, coef, time, basis, dw0)
     assert xa.shape == x_ref.shape and rel(xa, x_ref) <= bar
+
+
+@pytest.mark.parametrize("sh", [False, True], ids=["maps", "sh"])
+@pytest.mark.parametrize("T", [255, 257, 800])
+def test_field_tables_at_tile_remainders(T, sh):
+    """One-direction field setup (each call prepares only the tables it reads)
+    where the sample axis ends inside an anchor workgroup's 512 samples and
+    the pixel axis inside a tile; rectangular slice offset, two images for the
+    FP32 form.  FP32 and fp16-split sums of a few hundred terms: 2e-6; a bf16
+    pair carries 16 bits: 2e-5."""
+    import paper_2211_07532_amd as ee
+    w = synth.Workload("tables", 19, 0.1, 5, T, 3e-6, 2.0, 16, 120.0, 20.0, 5, "haar", 1, 31)
+    case = Case(w, z0=0.004, sh=sh)
+    args = case.oracle_args()
+    x = c64(synth.random_complex((2, w.npix), 41))
+    y = c64(synth.random_complex((2, T, w.ncoils), 42))
+    for prec, batch, bar in (("fp32", 2, 2e-6), ("fp16", 1, 2e-6), ("fp16", 2, 2e-6), ("bf16", 1, 2e-5)):
+        print(f"[case] tables T={T} sh={sh} {prec} batch={batch}", flush=True)
+        f = ee.forward(case.to_dev(x[:batch]), case.op, precision=prec).cpu().numpy()
+        a = ee.adjoint(case.to_dev(y[:batch]), case.op, precision=prec).cpu().numpy()
+        for b in range(batch):
+            assert rel(f[b], encoding.forward(x[b], *args)) <= bar
+            assert rel(a[b], encoding.adjoint(y[b], *args)) <= bar

@@ -16,7 +16,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OUT_DIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(OUT_DIR, "libexpenc.so")
-SOURCES = ["prep.hip", "encode.hip", "split.hip", "split_adj.hip", "wavelet.hip", "api.hip", "fista.hip", "grad.hip", "coils.hip",
+SOURCES = ["prep.hip", "encode.hip", "f32.hip", "split.hip", "split_adj.hip", "wavelet.hip", "api.hip", "fista.hip", "grad.hip", "coils.hip",
            "balanced.hip", "noalloc.hip"]
 # Per-source code generation: the polynomial split adjoint keeps its matrix-
 # core results in the vector register file (no AGPR copies of the phase

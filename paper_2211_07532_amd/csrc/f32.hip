@@ -1,0 +1,545 @@
+// FP32 form of the encoding contractions, on the bf16 matrix cores.
+//
+// Every FP32 operand value is written as hi + mid + lo with hi = rnd(v),
+// mid = rnd(v - hi) and lo = v - hi - mid in bf16: three 8-bit significands
+// hold the 24 bits of v exactly.  A product a*b is taken as
+//   a_hi b_hi + a_hi b_mid + a_mid b_hi + a_hi b_lo + a_lo b_hi + a_mid b_mid
+// on v_mfma_f32_32x32x16_bf16 with FP32 accumulation; the three products left
+// out are below 2^-25 of it, under the rounding of one FP32 addition.  Phases
+// are FP64 throughout, as the field may be of any strength.
+//
+// Why: v_mfma_f32_32x32x2_f32 takes 4096 matrix cycles per 16 reduction
+// indices, 64 rows and 32 columns, the six bf16 products 1536, for a few
+// hundred cycles more of vector work (three splits, the exchanges); neither
+// overlaps much with the FP64 phase.  Measured at 148 x 148, 32 coils, T =
+// 16384, against the same phases on the FP32 instruction, forward / adjoint:
+// solid harmonics 981 / 1133 -> 655 / 676 us, 16 maps 1024 / 1154 -> 798 /
+// 860 us, 9 maps 890 / 1008 -> 631 / 693 us.  Bound: matrix cycles plus the
+// vector work of the phase, sine, cosine and splits.  The error against FP64
+// does not grow (adjoint 200 x 200, T = 40000: 4.8e-7 -> 3.9e-7): one matrix
+// instruction adds 16 products to an accumulator, the FP32 one two.
+//
+// Layout of one step (K = 16 reduction indices) as in the split forms: lane l
+// holds indices 8*(l/32) .. +7 of row l%32 (A) or column l%32 (B).  Each lane
+// evaluates its OWN row against 16 wave-uniform indices, splits and packs
+// pairs, and v_permlane32_swap exchanges the half-waves, so that the two
+// 32-row blocks of the wave get their operands.  The B operand is packed in
+// lane order: six 16-byte records per lane and step (b1 hi, mid, lo, b2 hi,
+// mid, lo; b1 against cos, b2 against sin).
+#include <algorithm>
+#include <type_traits>
+
+#include "internal.h"
+#include "split_dev.h"
+
+namespace expenc {
+
+constexpr int kRec3 = 6 * 64;  // 16-byte words of one step and column group
+
+__device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// (hi, mid, lo) pairs of two FP32 values (exact remainders: the bf16 dot
+// product v + (hi_a, hi_b) . (-1, 0), see split_pair).
+__device__ inline void split3(float a, float b, Bf16Masks mk, uint32_t &h, uint32_t &m, uint32_t &l) {
+  const bf16x2 ma = __builtin_bit_cast(bf16x2, mk.lo), mb = __builtin_bit_cast(bf16x2, mk.hi);
+  const bf16x2 hv = {(__bf16)a, (__bf16)b};
+  const float ra = __builtin_amdgcn_fdot2_f32_bf16(hv, ma, a, false);
+  const float rb = __builtin_amdgcn_fdot2_f32_bf16(hv, mb, b, false);
+  const bf16x2 mv = {(__bf16)ra, (__bf16)rb};
+  const float la = __builtin_amdgcn_fdot2_f32_bf16(mv, ma, ra, false);
+  const float lb = __builtin_amdgcn_fdot2_f32_bf16(mv, mb, rb, false);
+  const bf16x2 lv = {(__bf16)la, (__bf16)lb};
+  h = __builtin_bit_cast(uint32_t, hv);
+  m = __builtin_bit_cast(uint32_t, mv);
+  l = __builtin_bit_cast(uint32_t, lv);
+}
+
+// The same for packed operands, by subtraction (any magnitude).
+__device__ inline void split3_any(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
+  const bf16x2 hv = {(__bf16)a, (__bf16)b};
+  h = __builtin_bit_cast(uint32_t, hv);
+  const float ra = a - bf16_lo(h), rb = b - bf16_hi(h);
+  const bf16x2 mv = {(__bf16)ra, (__bf16)rb};
+  m = __builtin_bit_cast(uint32_t, mv);
+  const bf16x2 lv = {(__bf16)(ra - bf16_lo(m)), (__bf16)(rb - bf16_hi(m))};
+  l = __builtin_bit_cast(uint32_t, lv);
+}
+
+// cos and sin of a phase in turns (FP64), reduced to [-1/2, 1/2] turns
+// before it is rounded to FP32
+__device__ inline void sincos_turns(double p, float &c, float &s) {
+  const float f = (float)(p - __builtin_rint(p));
+  c = __builtin_amdgcn_cosf(f);
+  s = __builtin_amdgcn_sinf(f);
+}
+
+// The six products of cos against b1 and of sin against b2, smallest first.
+// A: [c hi, c mid, c lo, s hi, s mid, s lo].
+__device__ inline f32x16 step12(const u32x4 (&A)[6], const u32x4 (&b)[6], f32x16 acc) {
+#pragma unroll
+  for (int o = 0; o < 6; o += 3) {
+    acc = mfma16<true>(A[o + 1], b[o + 1], acc);
+    acc = mfma16<true>(A[o + 2], b[o], acc);
+    acc = mfma16<true>(A[o], b[o + 2], acc);
+    acc = mfma16<true>(A[o + 1], b[o], acc);
+    acc = mfma16<true>(A[o], b[o + 1], acc);
+    acc = mfma16<true>(A[o], b[o], acc);
+  }
+  return acc;
+}
+
+// Wave-uniform terms of one reduction index (scalar loads).  The opaque
+// offset keeps the loads of one index from being merged with or hoisted above
+// those of an earlier one: two indices' terms are live at a time.
+template <int NU>
+__device__ inline void load_uniform(const double *__restrict__ u, int off, double (&q)[NU]) {
+  __asm__ volatile("" : "+s"(off));
+#pragma unroll
+  for (int j = 0; j < NU; ++j) q[j] = u[off + j];
+}
+
+struct F32Args {
+  int64_t Tp;
+  int Rp, NCP, chunk, nsplit, nxq, nx, ny;
+  double dx, dy;
+  Bf16Masks mk;
+};
+
+// Exchanges the packed words of the lane's own row (w[kind][pair], pairs of
+// reduction indices) into the two blocks' operands and adds the step's
+// products; o: the step's records of the first column group, this lane's.
+template <int GW>
+__device__ inline void contract16(const uint32_t (&w)[6][8], const u32x4 *__restrict__ o, f32x16 (&acc)[2][GW]) {
+  u32x4 A[2][6];
+#pragma unroll
+  for (int q = 0; q < 6; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const auto r = __builtin_amdgcn_permlane32_swap(w[q][i], w[q][4 + i], false, false);
+      A[0][q][i] = r[0];
+      A[1][q][i] = r[1];
+    }
+#pragma unroll
+  for (int g = 0; g < GW; ++g) {
+    const u32x4 *og = o + g * kRec3;
+    const u32x4 b[6] = {og[0], og[64], og[128], og[192], og[256], og[320]};
+    acc[0][g] = step12(A[0], b, acc[0][g]);
+    acc[1][g] = step12(A[1], b, acc[1][g]);
+  }
+}
+
+template <int GW>
+__device__ inline void zero_acc(f32x16 (&acc)[2][GW]) {
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int g = 0; g < GW; ++g)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[b][g][v] = 0.f;
+}
+
+// One workgroup: 256 rows (64 per wave) x 16 GW columns x a chunk of the
+// reduction.  FWD: rows are samples, the reduction runs over pixels; else
+// rows are pixels and it runs over samples.  NT: terms of the general basis
+// (17 FP64 products an entry at L = 16), or 0 (forward) for the solid
+// harmonics: along a 16-pixel tile of an image row a sample's phase is a
+// cubic (coefficients from the row polynomial at the tile's centre, 4 FP64
+// products an entry).
+// own, uni: the rows' terms [rows][NT] and the reduction indices' terms
+// [n][NT] of the general basis, or pmono and dwq; opr: operand records.
+// (restrict kernel arguments: uniform terms become scalar loads)
+// The reduction indices' first lds_terms(NT) terms go through LDS (blocks of
+// kIndices, double-buffered, one barrier per block) and the rest through the
+// scalar cache: with 17 FP64 terms an index the scalar cache's fills bound the
+// kernel, and a broadcast read costs the LDS a full one.  148 x 148, 32 coils,
+// T = 16384, forward / adjoint: 0 terms in LDS 1105 / 1233 us, 4 812 / 890,
+// 6 798 / 860, 8 902 / 1000; 10 terms an index fit the scalar path alone
+// (631 / 693, with 4 to 6 in LDS 654 / 711).
+constexpr int kIndices = 64;
+constexpr int lds_terms(int nt) { return nt == 17 ? 6 : 0; }
+
+template <int NT, int GW, bool FWD>
+__device__ inline void f32_body(const double *__restrict__ own, const double *__restrict__ uni,
+                                const u32x4 *__restrict__ opr, float *__restrict__ part, const F32Args &a) {
+  static_assert(NT || FWD, "the solid-harmonic adjoint is k_adj_f32_sh");
+  constexpr int NL = lds_terms(NT), NS = NT - NL;
+  __shared__ double sh[2][NL ? kIndices : 1][NL ? NL : 2];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int64_t rows = FWD ? a.Tp : a.Rp, len = FWD ? a.Rp : a.Tp;
+  int split, rb;
+  if (!split_tile(blockIdx.x, (int)(rows / 256), a.nsplit, &split, &rb)) return;
+  const int64_t row0 = (int64_t)rb * 256 + wave * 64;
+  const int g0 = blockIdx.y * GW;
+  const int NGP = a.NCP / 16;
+  const int pz = blockIdx.z;  // problem
+  constexpr int NP = NT ? NT : 11;
+  constexpr int S = NT ? NT : kPolyStride;  // row strides of the tables
+  own += pz * (NT ? rows : a.Tp) * S;
+  uni += NT ? pz * len * S : (int64_t)pz * a.Rp;
+  const u32x4 *__restrict__ op = opr + ((int64_t)pz * (len / 16) * NGP + g0) * kRec3 + lane;
+  double P[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) P[j] = own[(row0 + lane) * S + j];
+  f32x16 acc[2][GW];
+  zero_acc<GW>(acc);
+  const int64_t k0 = (int64_t)split * a.chunk;
+  const int64_t k1 = min(len, k0 + a.chunk);
+  const double dx2 = a.dx * a.dx, dx3 = dx2 * a.dx;
+  auto fill = [&](int64_t kb, int buf) {
+    const int n = (int)min<int64_t>(kIndices, k1 - kb) * NL;
+    for (int i = threadIdx.x; i < n; i += 256) (&sh[buf][0][0])[i] = uni[(kb + i / NL) * S + i % NL];
+  };
+  if constexpr (NL > 0) {
+    fill(k0, 0);
+    __syncthreads();
+  }
+  for (int64_t k = k0; k < k1; k += 16) {
+    uint32_t w[6][8];  // [c hi, mid, lo, s hi, mid, lo][pair of the 16 indices]
+    if constexpr (NT == 0) {
+      const int r = (int)k, yi = r / a.nxq, xi = r % a.nxq + 8;
+      const double ym = (yi - 0.5 * a.ny) * a.dy, xc = (xi - 0.5 * a.nx) * a.dx;
+      const double a0 = P[0] + ym * (P[2] + ym * (P[5] + ym * P[9]));
+      const double a1 = P[1] + ym * (P[4] + ym * P[8]);
+      const double a2 = P[3] + ym * P[7], a3 = P[6];
+      const double c0 = a0 + xc * (a1 + xc * (a2 + xc * a3));
+      const double d1 = (a1 + xc * (2.0 * a2 + 3.0 * a3 * xc)) * a.dx;
+      const double d2 = (a2 + 3.0 * a3 * xc) * dx2;
+      const double d3 = a3 * dx3;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        float c[2], s[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const double kk = 2 * m + e - 8;
+          sincos_turns(fma(P[10], uni[r + 2 * m + e], fma(fma(fma(d3, kk, d2), kk, d1), kk, c0)), c[e], s[e]);
+        }
+        split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
+        split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
+      }
+    } else {
+      const int in = (int)(k - k0) & (kIndices - 1), buf = (int)((k - k0) / kIndices) & 1;
+      if constexpr (NL > 0) {
+        if (in == 0 && k + kIndices < k1) fill(k + kIndices, buf ^ 1);
+      }
+      // the 16 indices' scalar terms, loaded one index ahead of their use
+      const double *u0 = uni + k * S + NL;
+      double q[2][NS];
+      load_uniform<NS>(u0, 0, q[0]);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        float c[2], s[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int i = 2 * m + e;
+          if (i < 15) load_uniform<NS>(u0, (i + 1) * S, q[(i + 1) & 1]);
+          double p = 0.0;
+#pragma unroll
+          for (int j = 0; j < NL; ++j) p = fma(sh[buf][NL ? in + i : 0][j], P[j], p);
+#pragma unroll
+          for (int j = 0; j < NS; ++j) p = fma(q[e][j], P[NL + j], p);
+          sincos_turns(p, c[e], s[e]);
+        }
+        split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
+        split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
+      }
+    }
+    contract16<GW>(w, op + (k >> 4) * NGP * kRec3, acc);
+    if constexpr (NL > 0) {
+      if (((k - k0) & (kIndices - 1)) == kIndices - 16) __syncthreads();
+    }
+  }
+  // [problem][split][row][column] complex
+  adj_epilogue<GW>(part, nullptr, (int)rows, a.NCP, a.nsplit, split, pz, blockIdx.y, gridDim.y, row0, g0, lane,
+                   acc);
+}
+
+template <int NT, int GW>
+__global__ __launch_bounds__(256, 2) void k_fwd_f32(const double *__restrict__ own, const double *__restrict__ uni,
+                                                     const u32x4 *__restrict__ op, float *__restrict__ part,
+                                                     F32Args a) {
+  f32_body<NT, GW, true>(own, uni, op, part, a);
+}
+
+template <int NT, int GW>
+__global__ __launch_bounds__(256, 2) void k_adj_f32(const double *__restrict__ own, const double *__restrict__ uni,
+                                                     const u32x4 *__restrict__ op, float *__restrict__ part,
+                                                     F32Args a) {
+  f32_body<NT, GW, false>(own, uni, op, part, a);
+}
+
+// The solid-harmonic adjoint (rows: pixels, reduction over samples).  At a
+// pixel (x, y) sample t has the phase
+//   a_0 + x (a_1 + x (a_2 + x a_3)) + t dw0,
+// a_j polynomials in y with the sample's coefficients.  A workgroup's 256
+// pixels lie in a few image rows, so it evaluates the a_j of kSamples samples
+// at those rows into LDS (double-buffered, one barrier per block of samples)
+// and a lane reads its row's four and t: 4 FP64 products an entry and 40
+// bytes from LDS (broadcast within a row).  With the sample's ten
+// coefficients as scalar operands it took 10 products, and the scalar cache's
+// fills bound it: 148 x 148, 32 coils, T = 16384: 806 us.
+constexpr int kSamples = 64;
+
+template <int GW>
+__global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict__ pmono,
+                                                       const double *__restrict__ dwq,
+                                                       const u32x4 *__restrict__ opr, float *__restrict__ part,
+                                                       F32Args a, int nrow) {
+  extern __shared__ double sh[];  // [2][kSamples][nrow][4], then t [2][kSamples]
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  int split, rb;
+  if (!split_tile(blockIdx.x, a.Rp / 256, a.nsplit, &split, &rb)) return;
+  const int64_t row0 = (int64_t)rb * 256 + wave * 64;
+  const int g0 = blockIdx.y * GW;
+  const int NGP = a.NCP / 16;
+  const int pz = blockIdx.z;  // problem
+  pmono += pz * a.Tp * kPolyStride;
+  dwq += (int64_t)pz * a.Rp;
+  const u32x4 *__restrict__ op = opr + ((int64_t)pz * (a.Tp / 16) * NGP + g0) * kRec3 + lane;
+  const int rq = (int)row0 + lane, yfirst = rb * 256 / a.nxq;
+  const double x = (rq % a.nxq - 0.5 * a.nx) * a.dx, w0 = dwq[rq];
+  double *const tt = sh + 2 * kSamples * nrow * 4;
+  const int64_t k0 = (int64_t)split * a.chunk, k1 = min(a.Tp, k0 + a.chunk);
+  auto fill = [&](int64_t kb, int buf) {
+    const int ns = (int)min<int64_t>(kSamples, k1 - kb);
+    for (int i = threadIdx.x; i < ns * nrow; i += 256) {
+      const int j = i / nrow, r = i - j * nrow;
+      const double *P = pmono + (kb + j) * kPolyStride;
+      const double y = (yfirst + r - 0.5 * a.ny) * a.dy;
+      double *o = sh + ((buf * kSamples + j) * nrow + r) * 4;
+      o[0] = fma(y, fma(y, fma(y, P[9], P[5]), P[2]), P[0]);
+      o[1] = fma(y, fma(y, P[8], P[4]), P[1]);
+      o[2] = fma(y, P[7], P[3]);
+      o[3] = P[6];
+      if (r == 0) tt[buf * kSamples + j] = P[10];
+    }
+  };
+  f32x16 acc[2][GW];
+  zero_acc<GW>(acc);
+  fill(k0, 0);
+  __syncthreads();
+  int buf = 0;
+  for (int64_t kb = k0; kb < k1; kb += kSamples, buf ^= 1) {
+    if (kb + kSamples < k1) fill(kb + kSamples, buf ^ 1);
+    const int ns = (int)min<int64_t>(kSamples, k1 - kb);
+    const double2 *cf = reinterpret_cast<const double2 *>(sh) + (buf * kSamples * nrow + rq / a.nxq - yfirst) * 2;
+    const double *ct = tt + buf * kSamples;
+    for (int j0 = 0; j0 < ns; j0 += 16) {
+      uint32_t w[6][8];  // [c hi, mid, lo, s hi, mid, lo][pair of the 16 indices]
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        float c[2], s[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int j = j0 + 2 * m + e;
+          const double2 a01 = cf[j * nrow * 2], a23 = cf[j * nrow * 2 + 1];
+          sincos_turns(fma(ct[j], w0, fma(x, fma(x, fma(x, a23.y, a23.x), a01.y), a01.x)), c[e], s[e]);
+        }
+        split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
+        split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
+      }
+      contract16<GW>(w, op + ((kb + j0) >> 4) * NGP * kRec3, acc);
+    }
+    __syncthreads();
+  }
+  adj_epilogue<GW>(part, nullptr, a.Rp, a.NCP, a.nsplit, split, pz, blockIdx.y, gridDim.y, row0, g0, lane, acc);
+}
+
+// ---------------------------------------------------------------------------
+// Operand packing.  Record (step q, group g, lane l): 8 reduction indices
+// 16q + 8*(l/32) + i, column col = 16g + l%16, part = (l/16)&1.
+//   forward:  b1 = part ? Zi : Zr,   b2 = part ? Zr : -Zi
+//   adjoint:  b1 = part ? Yi : Yr,   b2 = part ? -Yr : Yi
+// ---------------------------------------------------------------------------
+
+__device__ inline void write_rec3(u32x4 *o, const float (&b1)[8], const float (&b2)[8]) {
+  uint32_t w[6][4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    split3_any(b1[2 * m], b1[2 * m + 1], w[0][m], w[1][m], w[2][m]);
+    split3_any(b2[2 * m], b2[2 * m + 1], w[3][m], w[4][m], w[5][m]);
+  }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) o[64 * q] = u32x4{w[q][0], w[q][1], w[q][2], w[q][3]};
+}
+
+// Z[r'][col] = S_c(r) x_b(r), col = b*C + c, row r' = y*nxq + x of pixel
+// r = y*nx + x; zero for padded pixels and columns.
+__global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ smaps, const float2 *__restrict__ x,
+                                                     int64_t x_stride, int x_row_stride, int nx, int ny, int nxq,
+                                                     int Rp, int C, int NC, int NGP, u32x4 *__restrict__ zs,
+                                                     int64_t x_pstride) {
+  const int R = nx * ny;
+  const int64_t pz = blockIdx.y;
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (id >= (int64_t)(Rp / 16) * NGP * 64) return;
+  const int lane = (int)(id & 63);
+  const int64_t qg = id >> 6;
+  const int g = (int)(qg % NGP);
+  const int col = 16 * g + (lane & 15), im = (lane >> 4) & 1;
+  const int rq0 = (int)(16 * (qg / NGP) + 8 * (lane >> 5));
+  int yy = rq0 / nxq, xx = rq0 - yy * nxq;
+  const bool colok = col < NC;
+  const int b = colok ? col / C : 0, c = colok ? col % C : 0;
+  smaps += (pz * C + c) * R;
+  x += pz * x_pstride + b * x_stride;
+  float2 u[8], s[8];
+  bool ok[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    ok[i] = yy < ny && xx < nx && colok;
+    const int yc = ok[i] ? yy : 0, xc = ok[i] ? xx : 0;
+    u[i] = x[(int64_t)yc * x_row_stride + xc];
+    s[i] = smaps[yc * nx + xc];
+    if (++xx == nxq) {
+      xx = 0;
+      ++yy;
+    }
+  }
+  float b1[8], b2[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float2 z = ok[i] ? make_float2(s[i].x * u[i].x - s[i].y * u[i].y, s[i].x * u[i].y + s[i].y * u[i].x)
+                           : make_float2(0.f, 0.f);
+    b1[i] = im ? z.y : z.x;
+    b2[i] = im ? z.x : -z.y;
+  }
+  write_rec3(zs + (pz * (Rp / 16) * NGP + qg) * kRec3 + lane, b1, b2);
+}
+
+// Adjoint operand: sign * y, y [B][T][C] (src), or the forward's partial sums
+// (part, added in FP64 in the order of the splits) minus y_meas (may be
+// NULL).  Padded rows and columns are zero.  The residual is also kept as
+// yop [Tp][NCP] (its norm is the Rayleigh quotient and the data term).
+__global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ src, float sign,
+                                                    const float2 *__restrict__ part, int nsplit,
+                                                    const float2 *__restrict__ y_meas, int64_t T, int64_t Tp, int C,
+                                                    int NC, int NCP, u32x4 *__restrict__ ys,
+                                                    float2 *__restrict__ yop) {
+  const int NGP = NCP / 16;
+  const int64_t pz = blockIdx.y;
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (id >= (Tp / 16) * NGP * 64) return;
+  const int lane = (int)(id & 63);
+  const int64_t qg = id >> 6;
+  const int col = 16 * (int)(qg % NGP) + (lane & 15), im = (lane >> 4) & 1;
+  const int64_t t0 = 16 * (qg / NGP) + 8 * (lane >> 5);
+  const int b = col / C, c = col % C;
+  float2 y[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) y[i] = make_float2(0.f, 0.f);
+  if (src) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (t0 + i < T && col < NC) {
+        const float2 v = src[((pz * NC / C + b) * T + t0 + i) * C + c];
+        y[i] = make_float2(sign * v.x, sign * v.y);
+      }
+  } else if (col < NC) {
+    double sx[8], sy[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sx[i] = sy[i] = 0.0;
+    const float2 *p = part + (pz * nsplit * Tp + t0) * NCP + col;
+    for (int k = 0; k < nsplit; ++k, p += Tp * NCP) {
+      float2 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = p[(int64_t)i * NCP];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        sx[i] += v[i].x;
+        sy[i] += v[i].y;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (t0 + i < T) {
+        if (y_meas) {
+          const float2 m = y_meas[((pz * NC / C + b) * T + t0 + i) * C + c];
+          sx[i] -= m.x;
+          sy[i] -= m.y;
+        }
+        y[i] = make_float2((float)sx[i], (float)sy[i]);
+      }
+    // (padded samples hold the field-free sums of their rows: zero them)
+  }
+  if (yop && !im) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) yop[(pz * Tp + t0 + i) * NCP + col] = y[i];
+  }
+  float b1[8], b2[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    b1[i] = im ? y[i].y : y[i].x;
+    b2[i] = im ? -y[i].x : y[i].y;
+  }
+  write_rec3(ys + (pz * (Tp / 16) * NGP + qg) * kRec3 + lane, b1, b2);
+}
+
+// ---------------------------------------------------------------------------
+// Launchers
+// ---------------------------------------------------------------------------
+
+template <int NT, bool FWD>
+static void launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
+  const int nsplit = FWD ? p.fwd_split : p.adj_split;
+  const double *own = NT ? (FWD ? b.kap : b.bet) : b.pmono, *uni = NT ? (FWD ? b.bet : b.kap) : b.dwq;
+  const u32x4 *op = reinterpret_cast<const u32x4 *>(FWD ? b.zs : b.ys);
+  float *part = reinterpret_cast<float *>(b.part);
+  const F32Args a{p.Tp, p.Rp, p.NCP, FWD ? p.fwd_chunk : p.adj_chunk, nsplit, p.nxq, p.nx, p.ny, p.dx, p.dy,
+                  bf16_masks()};
+  const dim3 grid(split_grid((FWD ? p.Tp : p.Rp) / 256 * nsplit), (unsigned)p.NGY, (unsigned)p.P);
+  auto go = [&](auto gw) {
+    constexpr int GW = decltype(gw)::value;
+    if constexpr (FWD) k_fwd_f32<NT, GW><<<grid, 256, 0, s>>>(own, uni, op, part, a);
+    else if constexpr (NT > 0) k_adj_f32<NT, GW><<<grid, 256, 0, s>>>(own, uni, op, part, a);
+    else {
+      // image rows that 256 pixels can touch (at most 17: nxq >= 16)
+      const int nrow = std::min(256 / p.nxq + 2, (int)ceil_div(p.Rp, p.nxq));
+      const size_t lds = (size_t)2 * kSamples * (4 * nrow + 1) * sizeof(double);
+      if (lds > 65536)
+        hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_f32_sh<GW>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      k_adj_f32_sh<GW><<<grid, 256, lds, s>>>(own, uni, op, part, a, nrow);
+    }
+  };
+  if (p.GW == 2) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 1>{});
+}
+
+template <bool FWD>
+static void launch_nt(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
+  if (p.sh) return launch<0, FWD>(p, b, s);
+  switch (p.NT) {
+    case 4: return launch<4, FWD>(p, b, s);
+    case 10: return launch<10, FWD>(p, b, s);
+    default: return launch<17, FWD>(p, b, s);
+  }
+}
+
+void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) { launch_nt<true>(p, b, s); }
+void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) { launch_nt<false>(p, b, s); }
+
+static dim3 record_grid(int64_t len, const EncPlan &p) {
+  return dim3((unsigned)ceil_div(len / 16 * (p.NCP / 16) * 64, 256), (unsigned)p.P);
+}
+
+int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
+                const EncBuffers &b, hipStream_t s, int64_t x_pstride) {
+  k_build_z_f32<<<record_grid(p.Rp, p), 256, 0, s>>>(reinterpret_cast<const float2 *>(smaps), x, x_stride,
+                                                     x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C, p.NC, p.NCP / 16,
+                                                     reinterpret_cast<u32x4 *>(b.zs), x_pstride);
+  EX_LAUNCHED("build_z");
+  return EXPENC_OK;
+}
+
+int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_meas, const EncBuffers &b,
+               hipStream_t s) {
+  k_pack_y_f32<<<record_grid(p.Tp, p), 256, 0, s>>>(y, sign, b.part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC,
+                                                    p.NCP, reinterpret_cast<u32x4 *>(b.ys), y ? nullptr : b.yop);
+  EX_LAUNCHED("pack_y");
+  return EXPENC_OK;
+}
+
+}  // namespace expenc

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void k_grad_pack(const float2 *__restrict__ kk
 // Arguments of the gradient contraction.
 struct GradArgs {
   const double *kap, *bet;      // maps kind: [Tp][NT], [Rp][NT]
-  const double *pmono, *dwq;    // solid-harmonic kind: [Tp][12], [Rp]
+  const double *pmono, *dwq;    // solid-harmonic kind: [Tp][kPolyStride], [Rp]
   const float *kkt, *tf, *bt;
   const float2 *ws, *smaps;
   float *gpart, *dpart;         // [nsplit][Tp][16], [Tp/256][Rp]; NULL: that gradient is not wanted
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256, 2) void k_field_grad(GradArgs a) {
   constexpr int NP = NT ? NT : 11;
   double P[NP];
 #pragma unroll
-  for (int j = 0; j < NP; ++j) P[j] = NT ? a.kap[(t0 + lane) * NT + j] : a.pmono[(t0 + lane) * 12 + j];
+  for (int j = 0; j < NP; ++j) P[j] = NT ? a.kap[(t0 + lane) * NT + j] : a.pmono[(t0 + lane) * kPolyStride + j];
   const float tm0 = a.tf[t0 + l32], tm1 = a.tf[t0 + 32 + l32];
   const double dx2 = a.dx * a.dx, dx3 = dx2 * a.dx;
   const float *kb = a.kkt + half * a.Tp + t0 + l32;  // this lane's K row (re or im) at its samples
@@ -313,7 +313,7 @@ static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLay
   G->chunk = (int)round_up(ceil_div(p.Rp, std::min<int64_t>(want, p.Rp / 32)), 32);
   G->nsplit = (int)ceil_div(p.Rp, G->chunk);
   if (p.sh) {
-    G->pmono = a.take<double>(p.Tp * 12);
+    G->pmono = a.take<double>(p.Tp * kPolyStride);
     G->dwq = a.take<double>(p.Rp);
   } else {
     G->bet = a.take<double>((size_t)p.Rp * p.NT);

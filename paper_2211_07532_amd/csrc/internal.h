@@ -266,6 +266,7 @@ struct EncPlan {
   int32_t nwmax = 0;
 };
 
+constexpr int kPolyStride = 12;  // row stride of the polynomial coefficient table (11 used)
 // Workgroups (per problem) of the magnitude pre-pass of the scaled form.
 constexpr int kAmaxBlocks = 256;
 // Longest reduction chunk of one workgroup: samples in the split adjoint
@@ -279,14 +280,13 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
 struct EncBuffers {
   double *kap = nullptr;   // [Tp][NT] field coefficients in turns (+ time)
   double *bet = nullptr;   // [Rp][NT] basis values (+ dw0 in turns/s)
-  float2 *zop = nullptr;   // forward operand: FP32 [Rp][NCP] or packed split
-  float2 *yop = nullptr;   // adjoint operand: FP32 [Tp][NCP] or packed split
+  float2 *yop = nullptr;   // FP32 form: [Tp][NCP] the residual, beside its packed records
   float2 *part = nullptr;  // split-K partial sums (max of forward and adjoint)
-  void *zs = nullptr;      // split forms: packed hi/lo forward operand [Rp/16][NCP/16][4][64] x 16 B
-  void *ys = nullptr;      // split forms: packed hi/lo adjoint operand [Tp/16][NCP/16][4][64] x 16 B
+  void *zs = nullptr;      // packed forward operand [Rp/16][NCP/16][parts][64] x 16 B, parts 4 (split forms) or 6
+  void *ys = nullptr;      // packed adjoint operand [Tp/16][NCP/16][parts][64] x 16 B
   float *dbet = nullptr;   // split forms: [Rp][NT] bet minus its 16-row tile centre (FP32)
   float *dkap = nullptr;   // split forms: [Tp][NT] kap minus its 16-row tile centre (FP32)
-  double *pmono = nullptr; // split + SH: [Tp][12] cubic-monomial phase coefficients (turns) and t
+  double *pmono = nullptr; // SH: [Tp][kPolyStride] cubic-monomial phase coefficients (turns) and t
   float *dpa = nullptr;    // split + SH: [Tp/32][64][8] adjoint increment coefficients (FP32, per lane)
   double *dwq = nullptr;   // split + SH: [Rp] dw0/2pi in the row-padded pixel layout
   float *ddw = nullptr;    // split + SH: [Rp] dwq minus its 16-pixel tile centre (FP32)
@@ -377,6 +377,14 @@ int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *s
 // straight into the adjoint operand.
 int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_meas, hipStream_t s);
 
+// FP32 kernels (f32.hip).  f32_pack_y: from sign * y, or with y NULL the
+// forward's residual against y_meas (or NULL).
+void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
+void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
+int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
+                const EncBuffers &b, hipStream_t s, int64_t x_pstride);
+int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_meas, const EncBuffers &b,
+               hipStream_t s);
 // Split-precision kernels (split.hip).
 void split_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);

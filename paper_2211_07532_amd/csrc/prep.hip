@@ -111,10 +111,9 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
     if (i >= a.Tp) return;
     double P[11];
     sample_poly(coef, time, i, a.T, a.L, z, P);
-    double *o = a.pmono + (pz * a.Tp + i) * 12;
+    double *o = a.pmono + (pz * a.Tp + i) * kPolyStride;
 #pragma unroll
     for (int m = 0; m < 11; ++m) o[m] = P[m];
-    o[11] = 0.0;
     return;
   }
   if (role == kRoleIncr) {
@@ -175,8 +174,8 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
       return j < a.L ? coef[s * a.L + j] * kInv2Pi : j == a.L ? time[s] : 0.0;
     };
     const double v = val(t);
-    a.kap[pz * a.Tp * a.NT + i] = v;
-    if (a.dkap) a.dkap[pz * a.Tp * a.NT + i] = (float)(v - val((t & ~int64_t(15)) + 8));
+    a.kap[(pz * a.Tp + t) * a.NT + j] = v;
+    if (a.dkap) a.dkap[(pz * a.Tp + t) * a.NT + j] = (float)(v - val((t & ~int64_t(15)) + 8));
     return;
   }
   if (role == kRoleBet) {
@@ -189,8 +188,8 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
       return j < a.L ? basis[(int64_t)j * a.R + s] : j == a.L && dw0 ? dw0[s] * kInv2Pi : 0.0;
     };
     const double v = val(r);
-    a.bet[pz * a.Rp * a.NT + i] = v;
-    if (a.dbet) a.dbet[pz * a.Rp * a.NT + i] = (float)(v - val((r & ~15) + 8));
+    a.bet[(pz * a.Rp + r) * a.NT + j] = v;
+    if (a.dbet) a.dbet[(pz * a.Rp + r) * a.NT + j] = (float)(v - val((r & ~15) + 8));
     return;
   }
   // magnitude bounds of the fp16 form, per workgroup: |Re| + |Im| of the coil

@@ -299,15 +299,15 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
   const int g0 = by * GW;
   const int NGP = NCP / 16;
   const int pz = bz;  // problem
-  pmono += pz * Tp * 12;
+  pmono += pz * Tp * kPolyStride;
   dwq += (int64_t)pz * Rp;
   ddw += (int64_t)pz * Rp;
   zs += (int64_t)pz * Rp * NGP * 16;
   part += pz * nsplit * Tp * NCP * 2;
   double P[10];
 #pragma unroll
-  for (int m = 0; m < 10; ++m) P[m] = pmono[(row0 + lane) * 12 + m];
-  const double tt = pmono[(row0 + lane) * 12 + 10];
+  for (int m = 0; m < 10; ++m) P[m] = pmono[(row0 + lane) * kPolyStride + m];
+  const double tt = pmono[(row0 + lane) * kPolyStride + 10];
   const float tf = (float)tt;
   const double dx2 = dx * dx, dx3 = dx2 * dx;
   f32x16 acc[2][GW];

@@ -179,3 +179,42 @@ def test_field_tables_at_tile_remainders(T, sh):
         for b in range(batch):
             assert rel(f[b], encoding.forward(x[b], *args)) <= bar
             assert rel(a[b], encoding.adjoint(y[b], *args)) <= bar
+
+
+@pytest.mark.parametrize("shape", [
+    (5, 200, 500, 3, 16, True, 1.0),       # 16-pixel rows: a workgroup's pixels span 17 image rows
+    (100, 3, 1000, 20, 16, True, 1.0),     # fewer image rows than that; sample chunks that end inside an LDS block
+    (31, 29, 1000, 33, 16, False, 1.0),    # 17 terms a row (split between LDS and scalar loads), three column groups
+    (31, 29, 1000, 7, 9, False, 1.0),
+    (31, 29, 1000, 16, 3, False, 1.0),
+    (31, 29, 300, 8, 9, True, 1e-25),
+    (31, 29, 300, 8, 9, False, 1e25),
+], ids=lambda s: "x".join(str(v) for v in s))
+def test_fp32_form_edges(shape):
+    """The FP32 form's kernel variants (three-way bf16 products, FP64 phases)
+    at the edges of their tiles and for operands far from 1, against the
+    oracle.  Random sums of up to 1000 FP32 terms: 1e-6 is several times the
+    sqrt(n) growth of a 2^-24 rounding."""
+    import torch
+    ee = _ee()
+    nx, ny, T, C, L, sh, scale = shape
+    fx, fy, z0 = 0.1, 0.07, 0.003
+    R = nx * ny
+    rng = np.random.default_rng(7 + nx + T + C + L)
+    basis = encoding.sh_basis(nx, fx, z0, L, ny=ny, fov_y=fy)
+    coef = rng.normal(0.0, 1.0, (T, L)) * (20.0 / np.maximum(np.abs(basis).max(axis=1), 1e-12))[None, :]
+    time = np.arange(T, dtype=np.float64) * 2e-6
+    dw0 = rng.uniform(-600.0, 600.0, R)
+    smaps = c64(synth.random_complex((C, R), 61))
+    x = c64(scale * synth.random_complex((1, R), 62))
+    y = c64(scale * synth.random_complex((1, T, C), 63))
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    op = ee.Operator(nx, ny, t(smaps.astype(np.complex64)), t(coef), t(time), None if sh else t(basis), t(dw0),
+                     sh_grid=(fx, fy, z0) if sh else None)
+    args = (smaps, coef, time, basis, dw0)
+    print(f"[case] fp32 edges {shape}", flush=True)
+    yf = ee.forward(t(x.astype(np.complex64)), op).cpu().numpy().astype(np.complex128) / scale
+    assert rel(yf[0], encoding.forward(x[0] / scale, *args)) <= 1e-6
+    xa = ee.adjoint(t(y.astype(np.complex64)), op).cpu().numpy().astype(np.complex128) / scale
+    assert rel(xa[0], encoding.adjoint(y[0] / scale, *args)) <= 1e-6

@@ -93,3 +93,23 @@ def test_compress_full_size_data_follows_virtual_model(nv):
     op_v = ee.Operator(w.n, w.n, sv, case.t_coef, case.t_time, None, case.t_dw0, sh_grid=(w.fov, w.fov, case.z0))
     y2 = ee.forward(case.to_dev(case.x_noisy), op_v).cpu().numpy()
     assert rel(yv.cpu().numpy(), y2) <= 1e-5
+
+
+@pytest.mark.parametrize("C,nv,n,npix", [(2, 1, 1, 1), (33, 20, 129, 65), (48, 48, 500, 64), (64, 40, 1000, 63)])
+def test_coil_tile_edges(C, nv, n, npix):
+    """Vector tiles of 64 and blocks of 8 components with remainders, one and
+    many vectors, the largest coil count (its matrices take most of LDS).
+    FP64 arithmetic on FP32 data: 1e-6 after whitening, 1e-5 for what the
+    kept subspace determines."""
+    import paper_2211_07532_amd as ee
+    rng = np.random.default_rng(80 + C)
+    y = c64(rng.standard_normal((n, C)) + 1j * rng.standard_normal((n, C)))
+    y = c64(y * np.geomspace(10.0, 0.5, C)[None, :])
+    s = c64(rng.standard_normal((C, npix)) + 1j * rng.standard_normal((C, npix)))
+    psi = _psi(C, 90 + C)
+    print(f"[case] coil tiles C={C} nv={nv} n={n} npix={npix}", flush=True)
+    yd, sd = _dev(y), _dev(s)
+    ee.prewhiten(_dev(psi, np.complex128), yd, sd)
+    yw_ref, sw_ref = coils.prewhiten(psi, y, s)
+    assert rel(yd.cpu().numpy(), yw_ref) <= 1e-6 and rel(sd.cpu().numpy(), sw_ref) <= 1e-6
+    _compare_compression(y, s, nv)

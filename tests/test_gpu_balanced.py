@@ -111,3 +111,21 @@ def test_balanced_fista_anchor_modes_match_oracle(anchor):
     e = solve.nrmse(res.x.cpu().numpy().reshape(-1), ref.reshape(-1))
     print(f"[case] balanced fp16 anchor={anchor}: NRMSE {e:.2e}", flush=True)
     assert e <= 1e-4
+
+
+@pytest.mark.parametrize("name", ["haar", "db4"])
+@pytest.mark.parametrize("shape,levels,batch", [((1, 1), 1, 1), ((5, 3), 4, 2), ((17, 33), 3, 1), ((64, 130), 4, 2),
+                                                ((200, 7), 2, 3)])
+def test_undecimated_tile_edges(name, shape, levels, batch):
+    """Lattice tiles (32 x 16 positions of one residue modulo the spacing) cut
+    by the image, spacings larger than the image, images smaller than the
+    filter.  FP64 sums rounded to FP32 once per level: 3e-7."""
+    import paper_2211_07532_amd as ee
+    rng = np.random.default_rng(sum(shape) + levels)
+    x = c64(rng.standard_normal((batch,) + shape) + 1j * rng.standard_normal((batch,) + shape))
+    ref = np.stack([bal.swt2(x[b], levels, name) for b in range(batch)])
+    print(f"[case] swt edges {name} {shape} J={levels} B={batch}", flush=True)
+    assert rel(ee.swt_fwd(_dev(x), levels, name).cpu().numpy(), ref) <= 3e-7
+    v = c64(rng.standard_normal(ref.shape) + 1j * rng.standard_normal(ref.shape))
+    ref2 = np.stack([bal.iswt2(v[b], levels, name) for b in range(batch)])
+    assert rel(ee.swt_inv(_dev(v), levels, name).cpu().numpy(), ref2) <= 3e-7

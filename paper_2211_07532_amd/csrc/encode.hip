@@ -20,6 +20,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdio>
+#include <limits>
 #include <mutex>
 #include <type_traits>
 #include <utility>
@@ -243,13 +244,62 @@ static int phase_terms(int L) {
   return 17;
 }
 
-static int target_workgroups() {
+constexpr int kTargetWorkgroups = 2048;
+constexpr int kMaxWorkgroups = 4608;  // of the default split (scratch grows with the splits)
+
+// EXPENC_TARGET_WG, or 0.
+static int env_target() {
   static int v = [] {
     const char *e = getenv("EXPENC_TARGET_WG");
-    int t = e ? atoi(e) : 0;
-    return t > 0 ? t : 2048;
+    return std::max(0, e ? atoi(e) : 0);
   }();
   return v;
+}
+
+// Chunk of the K summed indexes of a contraction of `nrb` row blocks for
+// about `target` workgroups.
+static int32_t target_chunk(int64_t K, int64_t nrb, int ngy, int target, int grain, int32_t cap) {
+  int64_t want = ceil_div(target, nrb * ngy);
+  want = std::max<int64_t>(1, std::min<int64_t>(want, K / 16));
+  return std::min((int32_t)round_up(ceil_div(K, want), grain), cap);
+}
+
+// Chunk without a tuned target: of the chunks up to `longest` (or that of
+// kTargetWorkgroups, if it is longer) the one whose launch is shortest by
+// this model, fitted to 27 sweeps (32 to 200 px, every precision, both
+// kinds).  A CU takes n workgroups, `slots` at a time; a remainder of 1 or 2
+// runs at 0.85 or 0.9 of the full rate, as if it were n / rate; 1.5 more
+// stand for the uneven end.  A workgroup has a prologue of about 8 steps of
+// 16 indexes, and a step takes 0.5 us of a CU (twice that for the FP32 and
+// the general-basis kernels, 0.6 times with 16 columns per wave).  The
+// partial sums cost `width` complex values per row and split at 8 TB/s.
+// Whole calls, at 2048 workgroups and as picked: 100 x 90, T 3000, 16 coils,
+// 4 images, fp16: forward 112 / 84 us (32 splits), adjoint 100 / 84 (9);
+// one image, 16 maps, bf16: 64 / 58 and 71 / 60; 64 x 64, T 4000, 8 coils,
+// bf16: 39 / 34 and 73 / 31; 148 x 148, 32 coils, bf16: 351 / 334 and
+// 342 / 331.  (The picks are within 5 % of the fastest split in all sweeps.)
+int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, int grain,
+                      int32_t longest, int32_t cap) {
+  const int32_t at_target = target_chunk(K, nrb, ngy, kTargetWorkgroups, grain, cap);
+  const int32_t last = std::max(at_target, std::min(longest, (int32_t)round_up(K, grain)));
+  const int64_t most = std::max<int64_t>(1, kMaxWorkgroups / (nrb * ngy));
+  int32_t best = at_target;
+  int64_t prev = -1;
+  double cost = 1e300;
+  for (int32_t chunk = std::min<int32_t>(at_target, (int32_t)round_up(ceil_div(K, most), grain)); chunk <= last;
+       chunk += grain) {
+    const int64_t split = ceil_div(K, chunk);
+    if (split == prev) continue;  // (the shortest chunk of a split is its most even)
+    prev = split;
+    const int64_t n = ceil_div(nrb * ngy * split, 256), r = n % slots;
+    const double load = (double)(n - r) + (r == 1 ? 1 / 0.85 : r == 2 ? 2 / 0.9 : (double)r) + 1.5;
+    const double t = load * (chunk / 16 + 8) * step + (double)split * nrb * width * (256 * 8 / 8e6);
+    if (t < cost) {
+      cost = t;
+      best = chunk;
+    }
+  }
+  return best;
 }
 
 // Workgroup targets per operator geometry, batch and precision, set by the
@@ -340,7 +390,7 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   q.B = batch;
   q.NC = q.C * q.B;
   q.G = (int32_t)ceil_div(q.NC, 16);
-  int tgt_fwd = target_workgroups(), tgt_adj = tgt_fwd, tuned_gw = 0;
+  int tgt_fwd = env_target(), tgt_adj = tgt_fwd, tuned_gw = 0;  // 0: default_chunk
   tuned_targets(op, batch, precision, &tgt_fwd, &tgt_adj, &tuned_gw);
   // 16-column groups per wave: two (one phase tile feeds both) unless tuned
   // to one or there is only one
@@ -355,23 +405,27 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   q.P = nprob;
   q.scaled = precision == EXPENC_FP16_SPLIT;
   q.adj_anc = q.sh && precision != EXPENC_FP32;
+  // Partial sums of the default splits: no longer than 512 indexes in the
+  // FP32 form (its chunk sums are its rounding error) and 1024 in the split
+  // forms (below), unless kTargetWorkgroups makes them longer.
+  const bool f32 = precision == EXPENC_FP32;
+  const int32_t longest = f32 ? 512 : kSplitAdjChunkMax;
+  const double step = (f32 || !q.sh ? 1.0 : 0.5) * (q.GW == 2 ? 1.0 : 0.6);
   // forward: 256 sample rows per workgroup, split over pixels
   {
-    int64_t nrb = q.Tp / 256 * q.P;
-    int64_t want = ceil_div(tgt_fwd, nrb * q.NGY);
-    want = std::max<int64_t>(1, std::min<int64_t>(want, q.Rp / 16));
-    q.fwd_chunk = (int32_t)round_up(ceil_div(q.Rp, want), 16);
-    if (precision == EXPENC_FP32) q.fwd_chunk = std::min(q.fwd_chunk, kF32ChunkMax);
+    const int64_t nrb = q.Tp / 256 * q.P;
+    const int32_t cap = f32 ? kF32ChunkMax : std::numeric_limits<int32_t>::max();
+    const int slots = f32 ? 5 - q.GW : 4 - q.GW;  // workgroups that fit on a CU
+    q.fwd_chunk = tgt_fwd ? target_chunk(q.Rp, nrb, q.NGY, tgt_fwd, 16, cap)
+                          : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, 16, longest, cap);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
   }
   // adjoint: 256 pixel rows per workgroup, split over samples
   {
-    int64_t nrb = q.Rp / 256 * q.P;
-    int64_t want = ceil_div(tgt_adj, nrb * q.NGY);
-    want = std::max<int64_t>(1, std::min<int64_t>(want, q.Tp / 16));
+    const int64_t nrb = q.Rp / 256 * q.P;
     // (the polynomial split adjoint steps over 32 samples at a time)
-    q.adj_chunk = (int32_t)round_up(ceil_div(q.Tp, want), (q.sh && precision != EXPENC_FP32) ? 32 : 16);
+    const int grain = q.sh && !f32 ? 32 : 16;
     // The error of a contraction grows with the length of the sums one
     // workgroup accumulates on the matrix cores.  Measured on a 200 px,
     // T = 20000 fp16 solve: NRMSE 1.8e-5 at 562 samples per split adjoint
@@ -380,7 +434,11 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
     // chunks (3 forward, 2 adjoint splits) alone took it from 2.2e-5 to
     // 4.9e-5.  So chunks are capped (the tuned single-problem shapes are
     // below the caps).
-    q.adj_chunk = std::min(q.adj_chunk, precision == EXPENC_FP32 ? kF32ChunkMax : kSplitAdjChunkMax);
+    const int32_t cap = f32 ? kF32ChunkMax : kSplitAdjChunkMax;
+    const int slots = f32 ? 5 - q.GW : q.sh ? 3 : 4 - q.GW;
+    q.adj_chunk = tgt_adj ? target_chunk(q.Tp, nrb, q.NGY, tgt_adj, grain, cap)
+                          : default_chunk(q.Tp, nrb, q.NGY, q.comb ? q.NGY : q.NCP, slots, step, grain,
+                                          std::min(longest, cap), cap);
     q.adj_split = (int32_t)ceil_div(q.Tp, q.adj_chunk);
   }
   *p = q;

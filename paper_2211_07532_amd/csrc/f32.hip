@@ -36,9 +36,6 @@ namespace expenc {
 
 constexpr int kRec3 = 6 * 64;  // 16-byte words of one step and column group
 
-__device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-
 // (hi, mid, lo) pairs of two FP32 values (exact remainders: the bf16 dot
 // product v + (hi_a, hi_b) . (-1, 0), see split_pair).
 __device__ inline void split3(float a, float b, Bf16Masks mk, uint32_t &h, uint32_t &m, uint32_t &l) {
@@ -52,17 +49,6 @@ __device__ inline void split3(float a, float b, Bf16Masks mk, uint32_t &h, uint3
   const bf16x2 lv = {(__bf16)la, (__bf16)lb};
   h = __builtin_bit_cast(uint32_t, hv);
   m = __builtin_bit_cast(uint32_t, mv);
-  l = __builtin_bit_cast(uint32_t, lv);
-}
-
-// The same for packed operands, by subtraction (any magnitude).
-__device__ inline void split3_any(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
-  const bf16x2 hv = {(__bf16)a, (__bf16)b};
-  h = __builtin_bit_cast(uint32_t, hv);
-  const float ra = a - bf16_lo(h), rb = b - bf16_hi(h);
-  const bf16x2 mv = {(__bf16)ra, (__bf16)rb};
-  m = __builtin_bit_cast(uint32_t, mv);
-  const bf16x2 lv = {(__bf16)(ra - bf16_lo(m)), (__bf16)(rb - bf16_hi(m))};
   l = __builtin_bit_cast(uint32_t, lv);
 }
 

@@ -19,12 +19,14 @@
 
 #include "internal.h"
 #include "reduce.h"
+#include "split_dev.h"
 
 namespace expenc {
 
-constexpr int kGradTerms = 32;      // columns of the basis table (L <= 16 used)
-constexpr int kGradChunkMax = 1024; // pixels one workgroup accumulates in FP32
-constexpr int kGradAmax = 64;       // workgroups of the magnitude pre-pass per array
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kGradChunkMax = 1024;  // pixels one workgroup accumulates in FP32
+constexpr int kGradAmax = 64;        // workgroups of the magnitude pre-pass per array
 
 // Per-workgroup max component magnitude of w [R] (blockIdx.y 0) and kk [n]
 // (blockIdx.y 1) into amax[2][kGradAmax].
@@ -57,209 +59,290 @@ __device__ inline float grad_scale(const float *__restrict__ amax) {
   return ldexpf(1.f, min(126, max(-126, -e)));
 }
 
-// Operands of the gradient contraction: kkt[c][re | im][Tp] = scaled kk
-// (transposed, so the lanes of a wave read consecutive samples), tf[Tp] the
-// sample times, bt[Rp][kGradTerms] = b_l at the padded pixels (from the
-// table bet [Rp][NT], or the solid harmonics at the pixel centre), ws[Rp] the
-// scaled w; zero on padding.  One element per thread, array by array.
-__global__ __launch_bounds__(256) void k_grad_pack(const float2 *__restrict__ kk, const double *__restrict__ time,
-                                                   int64_t T, int64_t Tp, int C, const double *__restrict__ bet,
-                                                   int NT, int L, const float2 *__restrict__ w, int nx, int ny,
-                                                   int nxq, int Rp, double dx, double dy, double z0,
-                                                   const float *__restrict__ amax, float *__restrict__ kkt,
-                                                   float *__restrict__ tf, float *__restrict__ bt,
-                                                   float2 *__restrict__ wsc) {
+// Operands of the gradient contraction, records of lane order.  za (rows:
+// pixels, z_c = S_c w) and kb (columns: samples) hold, per block of 16 pixels
+// or samples and group of 16 coils, three 16-byte words per lane (the exact
+// bf16 parts hi, mid, lo): lane l has element l % 16 and, as reduction
+// indices, real and imaginary part of coils 4 (l / 16) .. + 3.  tf[Tp] are the
+// sample times; bt holds, per block of 16 pixels, b_{l % 16} at pixels
+// 4 (l / 16) .. + 3 (from the table bet [Rp][NT], or the solid harmonics at
+// the pixel centre).  Zero on padding.
+struct GradPackArgs {
+  const float2 *kk, *w, *smaps;
+  const double *time, *bet;
+  const float *amax;
+  u32x4 *za, *kb;
+  float *tf, *bt;
+  int64_t T, Tp;
+  int C, CK, NT, L, nx, ny, nxq, Rp;
+  double dx, dy, z0;
+};
+
+__global__ __launch_bounds__(256) void k_grad_pack(GradPackArgs g) {
   int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < Tp * C) {
-    const int64_t t = i % Tp, c = i / Tp;
-    float2 v = make_float2(0.f, 0.f);
-    if (t < T) {
-      const float s = grad_scale(amax + kGradAmax);
-      v = kk[t * C + c];
-      v.x *= s;
-      v.y *= s;
-    }
-    kkt[2 * c * Tp + t] = v.x;
-    kkt[(2 * c + 1) * Tp + t] = v.y;
-    return;
-  }
-  i -= Tp * C;
-  if (i < Tp) {
-    tf[i] = i < T ? (float)time[i] : 0.f;
-    return;
-  }
-  i -= Tp;
-  if (i >= Rp) return;
-  const int r = (int)i, yy = r / nxq, xx = r % nxq;
-  const bool in = xx < nx && yy < ny;
-  float2 u = make_float2(0.f, 0.f);
-  if (in) {
-    const float s = grad_scale(amax);
-    u = w[(int64_t)yy * nx + xx];
-    u.x *= s;
-    u.y *= s;
-  }
-  wsc[r] = u;
-  double v[16];
-  if (!bet) sh_eval((xx - 0.5 * nx) * dx, (yy - 0.5 * ny) * dy, z0, v);
+  const int64_t nkb = g.Tp / 16 * g.CK * 64, nza = (int64_t)g.Rp / 16 * g.CK * 64;
+  if (i < nkb + nza) {
+    const bool samples = i < nkb;
+    if (!samples) i -= nkb;
+    const int lane = (int)i & 63, e = lane & 15;
+    const int64_t rec = i >> 6, blk = rec / g.CK;
+    const int c0 = (int)(rec % g.CK) * 16 + 4 * (lane >> 4);
+    float2 v[4];
 #pragma unroll
-  for (int l = 0; l < kGradTerms; ++l) {
+    for (int j = 0; j < 4; ++j) v[j] = make_float2(0.f, 0.f);
+    if (samples) {
+      const int64_t t = blk * 16 + e;
+      if (t < g.T) {
+        const float s = grad_scale(g.amax + kGradAmax);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (c0 + j < g.C) {
+            const float2 k = g.kk[t * g.C + c0 + j];
+            v[j] = make_float2(k.x * s, k.y * s);
+          }
+      }
+    } else {
+      const int r = (int)blk * 16 + e, yy = r / g.nxq, xx = r % g.nxq;
+      if (xx < g.nx && yy < g.ny) {
+        const float s = grad_scale(g.amax);
+        const int64_t pix = (int64_t)yy * g.nx + xx, R = (int64_t)g.nx * g.ny;
+        float2 w = g.w[pix];
+        w.x *= s;
+        w.y *= s;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (c0 + j < g.C) {
+            const float2 c = g.smaps[(c0 + j) * R + pix];
+            v[j] = make_float2(c.x * w.x - c.y * w.y, c.x * w.y + c.y * w.x);
+          }
+      }
+    }
+    u32x4 h, m, l;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t a, b, c;
+      split3_any(v[j].x, v[j].y, a, b, c);
+      h[j] = a;
+      m[j] = b;
+      l[j] = c;
+    }
+    u32x4 *o = (samples ? g.kb : g.za) + rec * 192 + lane;
+    o[0] = h;
+    o[64] = m;
+    o[128] = l;
+    return;
+  }
+  i -= nkb + nza;
+  if (i < g.Tp) {
+    g.tf[i] = i < g.T ? (float)g.time[i] : 0.f;
+    return;
+  }
+  i -= g.Tp;
+  if (i >= g.Rp) return;
+  const int r = (int)i, yy = r / g.nxq, xx = r % g.nxq, e = r & 15;
+  const bool in = xx < g.nx && yy < g.ny;
+  double v[16];
+  if (!g.bet) sh_eval((xx - 0.5 * g.nx) * g.dx, (yy - 0.5 * g.ny) * g.dy, g.z0, v);
+  float *o = g.bt + (int64_t)(r >> 4) * 256 + 64 * (e >> 2) + (e & 3);
+#pragma unroll
+  for (int l = 0; l < 16; ++l) {
     float b = 0.f;
-    if (in && l < L) b = (float)(bet ? bet[(int64_t)r * NT + min(l, NT - 1)] : v[l & 15]);
-    bt[(int64_t)r * kGradTerms + l] = b;
+    if (in && l < g.L) b = (float)(g.bet ? g.bet[(int64_t)r * g.NT + min(l, g.NT - 1)] : v[l]);
+    o[4 * l] = b;
   }
 }
 
 // Arguments of the gradient contraction.
 struct GradArgs {
-  const double *kap, *bet;      // maps kind: [Tp][NT], [Rp][NT]
-  const double *pmono, *dwq;    // solid-harmonic kind: [Tp][kPolyStride], [Rp]
-  const float *kkt, *tf, *bt;
-  const float2 *ws, *smaps;
-  float *gpart, *dpart;         // [nsplit][Tp][16], [Tp/256][Rp]; NULL: that gradient is not wanted
+  float *gpart, *dpart;  // [nsplit][Tp][16], [Tp/256][Rp]; NULL: that gradient is not wanted
   int64_t Tp;
-  int Rp, C, R, nx, ny, nxq, chunk, nsplit;
+  int Rp, CK, ny, nx, nxq, chunk, nsplit;
   double dx, dy;
 };
 
-// One workgroup: 256 samples (64 per wave) x a chunk of pixels, in blocks of
-// 32 pixels.  Per block a wave forms M^T (rows: pixels, columns: samples) on
-// v_mfma_f32_32x32x2_f32 over coils, its two K indices being the real and the
-// imaginary part of a coil; evaluates the phases as the FP32 forward does
-// (its own sample, two wave-uniform pixels at a time, FP64, exchanged by
-// v_permlane32_swap); and multiplies.  V then sits with its sample in the
-// lane and its pixel in the register, which is the A-operand layout of the
-// product with the basis table, so grad_k is accumulated on the matrix cores
-// without moving V.  grad_dw sums over lanes by recursive halving.
-// Bound: the FP32 matrix cores (4 C + 32 products per entry) plus the FP64
-// phase, which does not co-issue with them.  At 128 x 128, 16 coils, T = 12000
-// and 16 terms 0.68 ms, where the basis-weighted forward and the adjoint took
-// 3.78 + 0.34 ms.
-// NT 0: solid-harmonic kind (polynomial phase); else the general basis.
+__device__ inline f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                 0, 0);
+}
+
+// sum over three exact parts each: the products below 2^-25 are left out
+__device__ inline f32x4 mfma_3x3(const u32x4 (&a)[3], const u32x4 (&b)[3]) {
+  f32x4 m = {0.f, 0.f, 0.f, 0.f};
+  m = mfma_bf16(a[1], b[1], m);
+  m = mfma_bf16(a[2], b[0], m);
+  m = mfma_bf16(a[0], b[2], m);
+  m = mfma_bf16(a[1], b[0], m);
+  m = mfma_bf16(a[0], b[1], m);
+  return mfma_bf16(a[0], b[0], m);
+}
+
+template <int CTRL>
+__device__ inline float dpp(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
+
+// One workgroup: 256 samples (64 per wave) x a chunk of pixels, in steps of
+// 16 pixels, and 16 coils at a time (their sample operands stay in registers
+// for the whole chunk).  Per step a wave forms M^T (rows: 16 pixels, columns:
+// its samples in four blocks of 16) on v_mfma_f32_16x16x32_bf16 over the real
+// and imaginary parts of 16 coils, from three exact bf16 parts per operand
+// (6 products of 16 matrix cycles instead of 8 FP32 ones of 32); the second
+// operand of Im M is the first with its halves exchanged.  Meanwhile each
+// lane evaluates the FP64 phases of its own sample at the 16 wave-uniform
+// pixels; two stages of lane exchanges bring them to M's layout.  V then sits
+// with its sample in lane % 16 and its pixel 4 (lane / 16) + register, which
+// is the A-operand layout of v_mfma_f32_16x16x4_f32, so grad_k is accumulated
+// on the matrix cores without moving V.  grad_dw sums over lanes by halving
+// (DPP) into a row of LDS per wave: no barrier before the end of the chunk.
+// The tables come as kernel parameters: only through those does the compiler
+// read the wave-uniform ones by scalar loads.
+// Bound: the matrix cores (768 cycles a step for M and 512 for the basis
+// products) plus the vector work of 16 FP64 phases, sines and cosines, which
+// does not overlap much with it.  At 128 x 128, 16 coils, T = 12000 and 16
+// terms 0.26 ms; the same matrix on the FP32 instruction, its coil maps and
+// data read again by every workgroup, took 0.68 ms, and the basis-weighted
+// forward and adjoint before that 3.78 + 0.34 ms.
+// NT 0: solid-harmonic kind (own: polynomial coefficients, uni: dwq); else
+// the general basis (own: kap, uni: bet).
 template <int NT>
-__global__ __launch_bounds__(256, 2) void k_field_grad(GradArgs a) {
-  __shared__ float sdw[2][4][32];
+__global__ __launch_bounds__(256, 2) void k_field_grad(const double *__restrict__ own, const double *__restrict__ uni,
+                                                       const u32x4 *__restrict__ za, const u32x4 *__restrict__ kb,
+                                                       const float *__restrict__ tf, const f32x4 *__restrict__ bt,
+                                                       GradArgs a) {
+  __shared__ float sdw[4][kGradChunkMax];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int half = lane >> 5, l32 = lane & 31;
+  const int l16 = lane & 15;
   int split, rb;
   if (!split_tile(blockIdx.x, (int)(a.Tp / 256), a.nsplit, &split, &rb)) return;
   const int64_t t0 = (int64_t)rb * 256 + wave * 64;
   constexpr int NP = NT ? NT : 11;
   double P[NP];
 #pragma unroll
-  for (int j = 0; j < NP; ++j) P[j] = NT ? a.kap[(t0 + lane) * NT + j] : a.pmono[(t0 + lane) * kPolyStride + j];
-  const float tm0 = a.tf[t0 + l32], tm1 = a.tf[t0 + 32 + l32];
+  for (int j = 0; j < NP; ++j) P[j] = own[(t0 + lane) * (NT ? NT : kPolyStride) + j];
+  float tm[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) tm[b] = tf[t0 + 16 * b + l16];
   const double dx2 = a.dx * a.dx, dx3 = dx2 * a.dx;
-  const float *kb = a.kkt + half * a.Tp + t0 + l32;  // this lane's K row (re or im) at its samples
-  f32x16 G[2];
+  f32x4 G[4];
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) G[b][v] = 0.f;
+  for (int b = 0; b < 4; ++b) G[b] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int r0 = split * a.chunk, r1 = min(a.Rp, r0 + a.chunk);
-  int par = 0;
-  for (int r = r0; r < r1; r += 32, par ^= 1) {
-    // this lane's pixel as a row of M^T (padding: w is zero there)
-    const int rq = r + l32, py = rq / a.nxq, px = rq - py * a.nxq;
-    const int pix = min(py, a.ny - 1) * a.nx + min(px, a.nx - 1);
-    const float2 w = a.ws[rq];
-    const float2 *sp = a.smaps + pix;
-    f32x16 Mr[2], Mi[2];
+  for (int ks = 0; ks < a.CK; ++ks) {
+    u32x4 B[4][3];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) Mr[b][v] = Mi[b][v] = 0.f;
-#pragma unroll 4
-    for (int c = 0; c < a.C; ++c) {
-      const float2 s = sp[(int64_t)c * a.R];
-      const float zr = s.x * w.x - s.y * w.y, zi = s.x * w.y + s.y * w.x;
-      const float k0 = kb[2 * c * a.Tp], k1 = kb[2 * c * a.Tp + 32];
+      for (int q = 0; q < 3; ++q) B[b][q] = kb[((t0 / 16 + b) * a.CK + ks) * 192 + 64 * q + lane];
+    int yi = r0 / a.nxq, xi = r0 - yi * a.nxq;
+    bool row = true;
+    double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+    for (int r = r0; r < r1; r += 16) {
+      const u32x4 *zr = za + ((int64_t)(r >> 4) * a.CK + ks) * 192 + lane;
+      const u32x4 A[3] = {zr[0], zr[64], zr[128]};
+      const f32x4 bv = bt[(r >> 4) * 64 + lane];
       // conj(k) z: Re = kr zr + ki zi, Im = kr zi - ki zr
-      const float ar = half ? zi : zr, ai = half ? -zr : zi;
-      Mr[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, k0, Mr[0], 0, 0, 0);
-      Mi[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, k0, Mi[0], 0, 0, 0);
-      Mr[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, k1, Mr[1], 0, 0, 0);
-      Mi[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, k1, Mi[1], 0, 0, 0);
-    }
-    const float *bp = a.bt + (int64_t)(r + 4 * half) * kGradTerms + l32;
-    float u[16];
-    double c0 = 0, d1 = 0, d2 = 0, d3 = 0;
+      u32x4 Ai[3];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int pa_ = 8 * (v >> 2) + (v & 3), pb_ = pa_ + 4;  // pixels of the two half-waves' rows
-      double pa, pb;
+      for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Ai[q][j] = __builtin_amdgcn_alignbit(A[q][j], A[q][j], 16) ^ 0x80000000u;
+      f32x4 Mr[4], Mi[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        Mr[b] = mfma_3x3(A, B[b]);
+        Mi[b] = mfma_3x3(Ai, B[b]);
+      }
+      // phases of this lane's sample at the 16 pixels, as turns reduced to
+      // [-1/2, 1/2] before they are rounded to FP32
+      float f[4][4];  // [pixel / 4][pixel % 4]
       if constexpr (NT == 0) {
-        if ((v & 7) == 0) {
-          // row polynomial of this 16-pixel tile around its centre
-          const int rt = r + 2 * v, yi = rt / a.nxq, xi = rt - yi * a.nxq + 8;
-          const double ym = (yi - 0.5 * a.ny) * a.dy, xc = (xi - 0.5 * a.nx) * a.dx;
-          const double a0 = P[0] + ym * (P[2] + ym * (P[5] + ym * P[9]));
-          const double a1 = P[1] + ym * (P[4] + ym * P[8]);
-          const double a2 = P[3] + ym * P[7], a3 = P[6];
-          c0 = a0 + xc * (a1 + xc * (a2 + xc * a3));
-          d1 = (a1 + xc * (2.0 * a2 + 3.0 * a3 * xc)) * a.dx;
-          d2 = (a2 + 3.0 * a3 * xc) * dx2;
-          d3 = a3 * dx3;
+        if (row) {  // row polynomial
+          const double ym = (yi - 0.5 * a.ny) * a.dy;
+          a0 = P[0] + ym * (P[2] + ym * (P[5] + ym * P[9]));
+          a1 = P[1] + ym * (P[4] + ym * P[8]);
+          a2 = P[3] + ym * P[7], a3 = P[6];
         }
-        const double ka = (pa_ & 15) - 8, kb_ = (pb_ & 15) - 8;
-        pa = fma(P[10], a.dwq[r + pa_], fma(fma(fma(d3, ka, d2), ka, d1), ka, c0));
-        pb = fma(P[10], a.dwq[r + pb_], fma(fma(fma(d3, kb_, d2), kb_, d1), kb_, c0));
+        // around the centre of this 16-pixel tile
+        const double xc = (xi + 8 - 0.5 * a.nx) * a.dx;
+        const double c0 = a0 + xc * (a1 + xc * (a2 + xc * a3));
+        const double d1 = (a1 + xc * (2.0 * a2 + 3.0 * a3 * xc)) * a.dx;
+        const double d2 = (a2 + 3.0 * a3 * xc) * dx2;
+        const double d3 = a3 * dx3;
+        xi += 16;
+        row = xi >= a.nxq;
+        if (row) {
+          xi -= a.nxq;
+          ++yi;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const double k = i - 8;
+          const double ph = fma(P[10], uni[r + i], fma(fma(fma(d3, k, d2), k, d1), k, c0));
+          f[i >> 2][i & 3] = (float)(ph - __builtin_rint(ph));
+        }
       } else {
-        const double *ba = a.bet + (int64_t)(r + pa_) * NT;
-        pa = pb = 0.0;
 #pragma unroll
-        for (int j = 0; j < NP; ++j) {
-          pa = fma(P[j], ba[j], pa);
-          pb = fma(P[j], ba[4 * NT + j], pb);
+        for (int i = 0; i < 16; ++i) {
+          const double *u = uni + (int64_t)(r + i) * NT;
+          double ph = 0.0;
+#pragma unroll
+          for (int j = 0; j < NP; ++j) ph = fma(P[j], u[j], ph);
+          f[i >> 2][i & 3] = (float)(ph - __builtin_rint(ph));
         }
       }
-      // centred reduction to [-1/2, 1/2] turns before rounding to FP32
-      const float fa = (float)(pa - __builtin_rint(pa)), fb = (float)(pb - __builtin_rint(pb));
-      const float ca = __builtin_amdgcn_cosf(fa), sa = __builtin_amdgcn_sinf(fa);
-      const float cb = __builtin_amdgcn_cosf(fb), sb = __builtin_amdgcn_sinf(fb);
-      const auto cc = __builtin_amdgcn_permlane32_swap(__float_as_uint(ca), __float_as_uint(cb), false, false);
-      const auto ss = __builtin_amdgcn_permlane32_swap(__float_as_uint(sa), __float_as_uint(sb), false, false);
-      // Im(E M) = cos Mi + sin Mr
-      const float v0 = fmaf(__uint_as_float(cc[0]), Mi[0][v], __uint_as_float(ss[0]) * Mr[0][v]);
-      const float v1 = fmaf(__uint_as_float(cc[1]), Mi[1][v], __uint_as_float(ss[1]) * Mr[1][v]);
+      float V[4][4];  // [sample block][register]
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        // (register: pixel quarter, lane quarter: sample block) transposed
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(f[0][v]), __float_as_uint(f[2][v]), false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(f[1][v]), __float_as_uint(f[3][v]), false, false);
+        const auto p = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false);
+        const auto q = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
+        const float g[4] = {__uint_as_float(p[0]), __uint_as_float(p[1]), __uint_as_float(q[0]), __uint_as_float(q[1])};
+        // Im(E M) = cos Mi + sin Mr
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          V[b][v] = fmaf(__builtin_amdgcn_cosf(g[b]), Mi[b][v], __builtin_amdgcn_sinf(g[b]) * Mr[b][v]);
+      }
       if (a.gpart) {
-        const float b = bp[pa_ * kGradTerms];
-        G[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v0, b, G[0], 0, 0, 0);
-        G[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v1, b, G[1], 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) G[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[b][v], bv[v], G[b], 0, 0, 0);
       }
-      u[v] = fmaf(v0, tm0, v1 * tm1);
-    }
-    if (a.dpart) {
-      // sum over the 32 samples (lanes) of each half: at each stage a lane
-      // keeps one half of its values; lane l ends with element v = (l%32)/2
+      if (a.dpart) {
+        // over the 64 samples: blocks, then the 16 lanes of a row; a lane
+        // keeps half of its four values at each of two stages and ends with
+        // pixel 4 (lane / 16) + lane % 16 / 4
+        float u[4];
 #pragma unroll
-      for (int o = 16, n = 16; o > 1; o >>= 1, n >>= 1) {
-        const bool up = (lane & o) != 0;
-#pragma unroll
-        for (int i = 0; i < n / 2; ++i) {
-          const float keep = up ? u[i + n / 2] : u[i], send = up ? u[i] : u[i + n / 2];
-          u[i] = keep + __shfl_xor(send, o);
+        for (int v = 0; v < 4; ++v)
+          u[v] = fmaf(V[0][v], tm[0], V[1][v] * tm[1]) + fmaf(V[2][v], tm[2], V[3][v] * tm[3]);
+        const bool up8 = lane & 8, up4 = lane & 4;
+        const float k0 = up8 ? u[2] : u[0], k1 = up8 ? u[3] : u[1];
+        const float s0 = up8 ? u[0] : u[2], s1 = up8 ? u[1] : u[3];
+        const float h0 = k0 + dpp<0x128>(s0), h1 = k1 + dpp<0x128>(s1);  // row_ror:8
+        float h = (up4 ? h1 : h0) + dpp<0x141>(up4 ? h0 : h1);           // row_half_mirror
+        h += dpp<0xb1>(h);                                               // quad_perm 1,0,3,2
+        h += dpp<0x4e>(h);                                               // quad_perm 2,3,0,1
+        if ((lane & 3) == 0) {
+          float *o = &sdw[wave][r - r0 + 4 * (lane >> 4) + (l16 >> 2)];
+          *o = ks ? *o + h : h;
         }
       }
-      u[0] += __shfl_xor(u[0], 1);
-      if ((lane & 1) == 0) {
-        const int v = l32 >> 1;
-        sdw[par][wave][8 * (v >> 2) + 4 * half + (v & 3)] = u[0];
-      }
-      __syncthreads();
-      // (the other buffer is written next; its readers passed this barrier)
-      if (threadIdx.x < 32)
-        a.dpart[(int64_t)rb * a.Rp + r + threadIdx.x] = (sdw[par][0][threadIdx.x] + sdw[par][1][threadIdx.x]) +
-                                                        (sdw[par][2][threadIdx.x] + sdw[par][3][threadIdx.x]);
     }
   }
-  if (a.gpart && l32 < 16) {
+  if (a.dpart) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < r1 - r0; i += 256)
+      a.dpart[(int64_t)rb * a.Rp + r0 + i] = (sdw[0][i] + sdw[1][i]) + (sdw[2][i] + sdw[3][i]);
+  }
+  if (a.gpart) {
     float *g = a.gpart + (int64_t)split * a.Tp * 16;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        g[(t0 + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3)) * 16 + l32] = G[b][v];
+      for (int v = 0; v < 4; ++v) g[(t0 + 16 * b + 4 * (lane >> 4) + v) * 16 + l16] = G[b][v];
   }
 }
 
@@ -293,11 +376,10 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const float *__restrict__ g
 
 struct GradLayout {
   EncPlan p;
-  int chunk = 0, nsplit = 0;
+  int chunk = 0, nsplit = 0, CK = 0;
   double *kap = nullptr, *bet = nullptr, *pmono = nullptr, *dwq = nullptr;
-  float *kkt = nullptr, *tf = nullptr, *bt = nullptr, *amax = nullptr, *gpart = nullptr,
-        *dpart = nullptr;
-  float2 *wsc = nullptr;
+  u32x4 *za = nullptr, *kb = nullptr;
+  float *tf = nullptr, *bt = nullptr, *amax = nullptr, *gpart = nullptr, *dpart = nullptr;
 };
 
 static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLayout *G) {
@@ -306,11 +388,11 @@ static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLay
   EX_TRY(make_plan(op, L > 0 ? L : 1, precision, &G->p));
   EX_TRY(make_plan(op, 1, precision, &G->p));
   const EncPlan &p = G->p;
-  // about 1024 workgroups: two rounds of the two a CU holds; chunks of at
-  // most kGradChunkMax pixels bound the length of an FP32 sum
-  const int64_t nrb = p.Tp / 256;
-  const int64_t want = std::max<int64_t>(ceil_div(1024, nrb), ceil_div(p.Rp, kGradChunkMax));
-  G->chunk = (int)round_up(ceil_div(p.Rp, std::min<int64_t>(want, p.Rp / 32)), 32);
+  // chunks bound the length of an FP32 sum: kGradChunkMax products per
+  // sample, fewer pixels where they hold several groups of 16 coils
+  G->CK = (int)ceil_div(p.C, 16);
+  const int cap = std::max(64, kGradChunkMax / G->CK / 16 * 16);
+  G->chunk = default_chunk(p.Rp, p.Tp / 256, 1, 8, 2, 1.3, 16, cap, cap);
   G->nsplit = (int)ceil_div(p.Rp, G->chunk);
   if (p.sh) {
     G->pmono = a.take<double>(p.Tp * kPolyStride);
@@ -319,10 +401,10 @@ static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLay
     G->bet = a.take<double>((size_t)p.Rp * p.NT);
   }
   G->kap = a.take<double>(p.Tp * p.NT);
-  G->kkt = a.take<float>(2 * p.Tp * p.C);
+  G->kb = a.take<u32x4>((size_t)p.Tp * G->CK * 12);
+  G->za = a.take<u32x4>((size_t)p.Rp * G->CK * 12);
   G->tf = a.take<float>(p.Tp);
-  G->bt = a.take<float>((size_t)p.Rp * kGradTerms);
-  G->wsc = a.take<float2>(p.Rp);
+  G->bt = a.take<float>((size_t)p.Rp * 16);
   G->amax = a.take<float>(2 * kGradAmax);
   G->gpart = a.take<float>((size_t)G->nsplit * p.Tp * 16);
   G->dpart = a.take<float>((size_t)(p.Tp / 256) * p.Rp);
@@ -364,19 +446,18 @@ extern "C" int expenc_field_grad(const expenc_op *op, int32_t precision, const f
   EX_TRY(enc_prepare(p, op, eb, s, kNeedForward));
   k_grad_amax<<<dim3(kGradAmax, 2), 256, 0, s>>>(w2, p.R, k2, p.T * p.C, G.amax);
   EX_LAUNCHED("gradient operand bounds");
-  k_grad_pack<<<(unsigned)ceil_div(p.Tp * p.C + p.Tp + p.Rp, 256), 256, 0, s>>>(
-      k2, op->time, p.T, p.Tp, p.C, G.bet, p.NT, p.L, w2, p.nx, p.ny, p.nxq, p.Rp, p.dx, p.dy, p.z0, G.amax, G.kkt,
-      G.tf, G.bt, G.wsc);
+  const GradPackArgs pa{k2, w2, reinterpret_cast<const float2 *>(op->smaps), op->time, G.bet, G.amax, G.za, G.kb,
+                        G.tf, G.bt, p.T, p.Tp, p.C, G.CK, p.NT, p.L, p.nx, p.ny, p.nxq, p.Rp, p.dx, p.dy, p.z0};
+  k_grad_pack<<<(unsigned)ceil_div((p.Tp + p.Rp) * G.CK * 4 + p.Tp + p.Rp, 256), 256, 0, s>>>(pa);
   EX_LAUNCHED("gradient operands");
-  const GradArgs ga{G.kap, G.bet, G.pmono, G.dwq, G.kkt, G.tf, G.bt, G.wsc,
-                    reinterpret_cast<const float2 *>(op->smaps), grad_coef ? G.gpart : nullptr,
-                    grad_dw0 ? G.dpart : nullptr, p.Tp, p.Rp, p.C, p.R, p.nx, p.ny, p.nxq, G.chunk, G.nsplit,
-                    p.dx, p.dy};
+  const GradArgs ga{grad_coef ? G.gpart : nullptr, grad_dw0 ? G.dpart : nullptr, p.Tp, p.Rp, G.CK, p.ny, p.nx,
+                    p.nxq, G.chunk, G.nsplit, p.dx, p.dy};
+  const f32x4 *bt = reinterpret_cast<const f32x4 *>(G.bt);
   const unsigned grid = split_grid(p.Tp / 256 * G.nsplit);
-  if (p.sh) k_field_grad<0><<<grid, 256, 0, s>>>(ga);
-  else if (p.NT == 4) k_field_grad<4><<<grid, 256, 0, s>>>(ga);
-  else if (p.NT == 10) k_field_grad<10><<<grid, 256, 0, s>>>(ga);
-  else k_field_grad<17><<<grid, 256, 0, s>>>(ga);
+  if (p.sh) k_field_grad<0><<<grid, 256, 0, s>>>(G.pmono, G.dwq, G.za, G.kb, G.tf, bt, ga);
+  else if (p.NT == 4) k_field_grad<4><<<grid, 256, 0, s>>>(G.kap, G.bet, G.za, G.kb, G.tf, bt, ga);
+  else if (p.NT == 10) k_field_grad<10><<<grid, 256, 0, s>>>(G.kap, G.bet, G.za, G.kb, G.tf, bt, ga);
+  else k_field_grad<17><<<grid, 256, 0, s>>>(G.kap, G.bet, G.za, G.kb, G.tf, bt, ga);
   EX_LAUNCHED("field gradient");
   const int64_t n = (grad_coef ? p.T * p.L : 0) + (grad_dw0 ? (int64_t)p.R : 0);
   k_grad_reduce<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(G.gpart, G.dpart, p.T, p.Tp, p.L, G.nsplit, p.nx, p.ny,

@@ -68,6 +68,20 @@ __device__ inline void split_pair(float a, float b, uint32_t &hi, uint32_t &lo, 
   }
 }
 
+__device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Exact bf16 parts (hi, mid, lo) of two FP32 values of any magnitude.
+__device__ inline void split3_any(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
+  const bf16x2 hv = {(__bf16)a, (__bf16)b};
+  h = __builtin_bit_cast(uint32_t, hv);
+  const float ra = a - bf16_lo(h), rb = b - bf16_hi(h);
+  const bf16x2 mv = {(__bf16)ra, (__bf16)rb};
+  m = __builtin_bit_cast(uint32_t, mv);
+  const bf16x2 lv = {(__bf16)(ra - bf16_lo(m)), (__bf16)(rb - bf16_hi(m))};
+  l = __builtin_bit_cast(uint32_t, lv);
+}
+
 template <bool BF>
 __device__ inline f32x16 mfma16(u32x4 a, u32x4 b, f32x16 c) {
   if constexpr (BF)

@@ -242,3 +242,23 @@ def test_field_grad_edges(n, T, C, L, with_dw0, sh, which, scale):
         assert rel(gd.cpu().numpy() / scale ** 2, gd_ref) <= 1e-5 if np.any(gd_ref) else not np.any(gd.cpu().numpy())
     else:
         assert gd is None
+
+
+@pytest.mark.parametrize("n,T,C,L,sh", [
+    (20, 300, 16, 16, True),     # one full group of coils
+    (20, 300, 17, 9, False),     # one coil in a second group
+    (20, 40, 257, 4, True),      # many groups, the shortest chunks
+])
+def test_field_grad_coil_groups(n, T, C, L, sh):
+    """Coils are contracted 16 at a time and the gradients summed over the
+    groups: at most 2 C and 1024 FP32 terms per sum, 1e-5 relative as above."""
+    ee, ag = _ee()
+    w = synth.Workload("groups", n, 0.1, C, T, 3e-6, 2.0, L, 120.0, 20.0, 5, "haar", 1, 29)
+    case = Case(w, z0=0.004, nbasis=L, sh=sh, with_dw0=True)
+    print(f"[case] field grad coil groups n={n} T={T} C={C} L={L} sh={sh}", flush=True)
+    x = c64(synth.random_complex(n * n, 93))
+    g = c64(synth.random_complex((T, C), 94))
+    _, gc_ref, gd_ref = encoding.vjp_forward(x, g, case.smaps, case.coef, case.time, case.basis_np, case.dw0)
+    gc, gd = ag.field_grad(case.op, case.to_dev(x), case.to_dev(g))
+    assert rel(gc.cpu().numpy(), gc_ref) <= 1e-5
+    assert rel(gd.cpu().numpy(), gd_ref) <= 1e-5

@@ -16,13 +16,14 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OUT_DIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(OUT_DIR, "libexpenc.so")
-SOURCES = ["prep.hip", "encode.hip", "f32.hip", "split.hip", "split_adj.hip", "wavelet.hip", "api.hip", "fista.hip", "grad.hip", "coils.hip",
-           "balanced.hip", "noalloc.hip"]
+SOURCES = ["prep.hip", "encode.hip", "f32.hip", "split.hip", "split_adj.hip", "split_maps.hip", "wavelet.hip", "api.hip",
+           "fista.hip", "grad.hip", "coils.hip", "balanced.hip", "noalloc.hip"]
 # Per-source code generation: the polynomial split adjoint keeps its matrix-
 # core results in the vector register file (no AGPR copies of the phase
 # tiles; 165-168 registers, three waves per SIMD instead of two).  The same
 # option slows the forward kernels, so it is not global.
-EXTRA_FLAGS = {"split_adj.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+EXTRA_FLAGS = {"split_adj.hip": VGPR_FORM, "split_maps.hip": VGPR_FORM}
 ARCH = "gfx950"
 
 

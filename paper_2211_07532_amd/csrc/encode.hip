@@ -270,8 +270,8 @@ static int32_t target_chunk(int64_t K, int64_t nrb, int ngy, int target, int gra
 // kinds).  A CU takes n workgroups, `slots` at a time; a remainder of 1 or 2
 // runs at 0.85 or 0.9 of the full rate, as if it were n / rate; 1.5 more
 // stand for the uneven end.  A workgroup has a prologue of about 8 steps of
-// 16 indexes, and a step takes 0.5 us of a CU (twice that for the FP32 and
-// the general-basis kernels, 0.6 times with 16 columns per wave).  The
+// 16 indexes, and a step takes 0.5 us of a CU (0.6 for the general-basis and
+// 1 for the FP32 kernels, 0.6 times that with 16 columns per wave).  The
 // partial sums cost `width` complex values per row and split at 8 TB/s.
 // Whole calls, at 2048 workgroups and as picked: 100 x 90, T 3000, 16 coils,
 // 4 images, fp16: forward 112 / 84 us (32 splits), adjoint 100 / 84 (9);
@@ -352,6 +352,9 @@ int set_tuning(const expenc_op *op, int32_t batch, int32_t precision, int32_t fw
   return EXPENC_OK;
 }
 
+// Pixels per step of the forward contraction (general-basis split form: 32).
+static int fwd_grain(const EncPlan &q) { return q.sh || q.prec == EXPENC_FP32 ? 16 : 32; }
+
 int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p, int32_t nprob) {
   if (!op) return fail(EXPENC_EINVAL, "operator descriptor is NULL");
   if (op->nx < 1 || op->ny < 1) return fail(EXPENC_EINVAL, "image grid %dx%d is empty", op->nx, op->ny);
@@ -410,22 +413,23 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   // forms (below), unless kTargetWorkgroups makes them longer.
   const bool f32 = precision == EXPENC_FP32;
   const int32_t longest = f32 ? 512 : kSplitAdjChunkMax;
-  const double step = (f32 || !q.sh ? 1.0 : 0.5) * (q.GW == 2 ? 1.0 : 0.6);
+  const double step = (f32 ? 1.0 : q.sh ? 0.5 : 0.6) * (q.GW == 2 ? 1.0 : 0.6);
   // forward: 256 sample rows per workgroup, split over pixels
   {
     const int64_t nrb = q.Tp / 256 * q.P;
     const int32_t cap = f32 ? kF32ChunkMax : std::numeric_limits<int32_t>::max();
-    const int slots = f32 ? 5 - q.GW : 4 - q.GW;  // workgroups that fit on a CU
-    q.fwd_chunk = tgt_fwd ? target_chunk(q.Rp, nrb, q.NGY, tgt_fwd, 16, cap)
-                          : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, 16, longest, cap);
+    const int slots = f32 ? 5 - q.GW : q.sh ? 4 - q.GW : 2;  // workgroups that fit on a CU
+    const int grain = fwd_grain(q);
+    q.fwd_chunk = tgt_fwd ? target_chunk(q.Rp, nrb, q.NGY, tgt_fwd, grain, cap)
+                          : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, grain, longest, cap);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
   }
   // adjoint: 256 pixel rows per workgroup, split over samples
   {
     const int64_t nrb = q.Rp / 256 * q.P;
-    // (the polynomial split adjoint steps over 32 samples at a time)
-    const int grain = q.sh && !f32 ? 32 : 16;
+    // (the split adjoints step over 32 samples at a time)
+    const int grain = f32 ? 16 : 32;
     // The error of a contraction grows with the length of the sums one
     // workgroup accumulates on the matrix cores.  Measured on a 200 px,
     // T = 20000 fp16 solve: NRMSE 1.8e-5 at 562 samples per split adjoint
@@ -435,7 +439,7 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
     // 4.9e-5.  So chunks are capped (the tuned single-problem shapes are
     // below the caps).
     const int32_t cap = f32 ? kF32ChunkMax : kSplitAdjChunkMax;
-    const int slots = f32 ? 5 - q.GW : q.sh ? 3 : 4 - q.GW;
+    const int slots = f32 ? 5 - q.GW : q.sh ? 3 : 2;
     q.adj_chunk = tgt_adj ? target_chunk(q.Tp, nrb, q.NGY, tgt_adj, grain, cap)
                           : default_chunk(q.Tp, nrb, q.NGY, q.comb ? q.NGY : q.NCP, slots, step, grain,
                                           std::min(longest, cap), cap);
@@ -461,7 +465,7 @@ int plan_forward_within(const expenc_op *op, int32_t batch, int32_t precision, s
   q.adj_chunk = (int32_t)q.Tp;
   const int32_t min_split = q.prec == EXPENC_FP32 ? (int32_t)ceil_div(q.Rp, kF32ChunkMax) : 1;
   auto set_split = [&](int32_t want) {
-    q.fwd_chunk = (int32_t)round_up(ceil_div(q.Rp, want), 16);
+    q.fwd_chunk = (int32_t)round_up(ceil_div(q.Rp, want), fwd_grain(q));
     if (q.prec == EXPENC_FP32) q.fwd_chunk = std::min(q.fwd_chunk, kF32ChunkMax);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
@@ -511,8 +515,8 @@ int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part) {
       b->wmax = a.take<float>(P * p.nwmax);
     }
     if (!p.sh) {
-      b->dbet = a.take<float>(P * p.Rp * p.NT);
-      b->dkap = a.take<float>(P * p.Tp * p.NT);
+      b->dbet = a.take<float>(P * p.Rp * round_up(p.NT, 2));
+      b->dkap = a.take<float>(P * p.Tp * round_up(p.NT, 2));
     }
   }
   return a.ok() ? EXPENC_OK : EXPENC_EWORKSPACE;

@@ -287,8 +287,9 @@ struct EncBuffers {
   float2 *part = nullptr;  // split-K partial sums (max of forward and adjoint)
   void *zs = nullptr;      // packed forward operand [Rp/16][NCP/16][parts][64] x 16 B, parts 4 (split forms) or 6
   void *ys = nullptr;      // packed adjoint operand [Tp/16][NCP/16][parts][64] x 16 B
-  float *dbet = nullptr;   // split forms: [Rp][NT] bet minus its 16-row tile centre (FP32)
-  float *dkap = nullptr;   // split forms: [Tp][NT] kap minus its 16-row tile centre (FP32)
+  // split forms: bet and kap minus those of index 8 of their 16 (FP32), per 32
+  // indexes [pair of terms][term of the pair][index], zero past NT
+  float *dbet = nullptr, *dkap = nullptr;
   double *pmono = nullptr; // SH: [Tp][kPolyStride] cubic-monomial phase coefficients (turns) and t
   float *dpa = nullptr;    // split + SH: [Tp/32][64][8] adjoint increment coefficients (FP32, per lane)
   double *dwq = nullptr;   // split + SH: [Rp] dw0/2pi in the row-padded pixel layout
@@ -393,6 +394,7 @@ void split_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 // the polynomial (solid-harmonic) split adjoint, built in split_adj.hip
 void split_adjoint_sh_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
+void split_maps_launch(const EncPlan &p, const EncBuffers &b, bool adjoint, hipStream_t s);
 
 // One launch of a split contraction over several problem groups (plans of
 // one shape class: solid-harmonic kind, same number format and column width

@@ -66,6 +66,14 @@ __device__ inline double pixel_dw(const double *__restrict__ dw0, int rq, int nx
   return dw0 && yy < ny && xx < nx ? dw0[(int64_t)yy * nx + xx] * kInv2Pi : 0.0;
 }
 
+// Element (index i, term j) of a difference table of the split contractions:
+// per 32 indexes [pair of terms][term of the pair][index], zero past NT.
+__device__ inline void put_diff(float *__restrict__ d, int64_t i, int j, int NT, float v) {
+  float *o = d + ((i >> 5) * ((NT + 1) / 2) + (j >> 1)) * 64 + (i & 31);
+  o[32 * (j & 1)] = v;
+  if ((NT & 1) && j == NT - 1) o[32] = 0.f;
+}
+
 __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
   __shared__ double pc[kAncTiles][12];
   __shared__ float wm[4];
@@ -74,6 +82,7 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
   while (blockIdx.x >= a.end[role]) ++role;
   const unsigned blk = blockIdx.x - (role ? a.end[role - 1] : 0u);
   const int tid = threadIdx.x;
+  const int nte = (a.NT + 1) & ~1;
   const int64_t i = (int64_t)blk * 256 + tid;
   const double z = a.z0s ? a.z0s[pz] : a.z0;
   const double *coef = a.coef ? a.coef + pz * a.T * a.L : nullptr;
@@ -175,7 +184,7 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
     };
     const double v = val(t);
     a.kap[(pz * a.Tp + t) * a.NT + j] = v;
-    if (a.dkap) a.dkap[(pz * a.Tp + t) * a.NT + j] = (float)(v - val((t & ~int64_t(15)) + 8));
+    if (a.dkap) put_diff(a.dkap + pz * a.Tp * nte, t, j, a.NT, (float)(v - val((t & ~int64_t(15)) + 8)));
     return;
   }
   if (role == kRoleBet) {
@@ -189,7 +198,7 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
     };
     const double v = val(r);
     a.bet[(pz * a.Rp + r) * a.NT + j] = v;
-    if (a.dbet) a.dbet[(pz * a.Rp + r) * a.NT + j] = (float)(v - val((r & ~15) + 8));
+    if (a.dbet) put_diff(a.dbet + pz * a.Rp * nte, r, j, a.NT, (float)(v - val((r & ~15) + 8)));
     return;
   }
   // magnitude bounds of the fp16 form, per workgroup: |Re| + |Im| of the coil

@@ -54,186 +54,10 @@ __device__ inline void pack_tile16(const float (&c)[16], const float (&sn)[16], 
   }
 }
 
-// Phase tile of one lane against 16 wave-uniform reduction indices, split,
-// packed and redistributed.
-//
-// The phase of the tile's centre index (index 8) is accumulated in FP64 and
-// reduced to [0,1) turns (anchor a).  The other 15 follow as
-//   phi_j = a + sum_k pf[k] * dq[j][k]          (FP32)
-// where pf is this lane's phase terms rounded to FP32 and dq[j] the
-// wave-uniform differences (index j minus index 8) of the other factor,
-// precomputed per tile in FP64 and rounded once.  Within a tile the
-// increments stay small (a few turns for 16 pixels along a row, under one
-// turn for 16 samples), so the FP32 rounding error of the increment is
-// about 1e-6 turn, well inside the split forms' error budget.  The uniform
-// differences (NT floats per index) are scalar-loaded one index ahead.
-//
-//   pv: this lane's FP64 terms; qc: the centre index's NT uniform FP64
-//   terms; dq: 16 x NT uniform FP32 differences.  On return A[blk][kind]
-//   (blk 0: rows 0..31, 1: rows 32..63; kind 0 c_hi, 1 c_lo, 2 s_hi, 3 s_lo)
-//   are the A operands of this step.
-template <int NT, bool BF>
-__device__ inline void phase_tile16(const double (&pv)[NT], const float (&pf)[NT], const double *__restrict__ qc,
-                                    const float *__restrict__ dq, u32x4 (&A)[2][4]) {
-  double pa = 0.0;
-#pragma unroll
-  for (int j = 0; j < NT; ++j) pa = fma(pv[j], qc[j], pa);
-  const float a = (float)__builtin_amdgcn_fract(pa);
-  __builtin_amdgcn_sched_barrier(0);
-  float c[16], sn[16];
-  float buf[2][NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) buf[0][j] = dq[j];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    if (i + 1 < 16) {
-      // An opaque (empty) redefinition of the uniform offset: the scalar
-      // loads of index i+1 cannot be merged with, or hoisted above, those of
-      // earlier indices, so only two indices' terms are live at a time.
-      int off = (i + 1) * NT;
-      __asm__ volatile("" : "+s"(off));
-#pragma unroll
-      for (int j = 0; j < NT; ++j) buf[(i + 1) & 1][j] = dq[off + j];
-    }
-    float ph = a;
-#pragma unroll
-    for (int j = 0; j < NT; ++j) ph = fmaf(pf[j], buf[i & 1][j], ph);
-    const float f = __builtin_amdgcn_fractf(ph);
-    c[i] = __builtin_amdgcn_cosf(f);
-    sn[i] = __builtin_amdgcn_sinf(f);
-  }
-  pack_tile16<BF>(c, sn, A);
-}
-
 // Slot of this wave in the per-problem maxima array of a forward launch
 // (workgroup bx, by of a grid gx wide).
 __device__ inline int wave_slot(int bx, int by, int gx) { return (by * gx + bx) * 4 + (threadIdx.x >> 6); }
 __device__ inline int wave_slot() { return wave_slot(blockIdx.x, blockIdx.y, gridDim.x); }
-
-// Writes a wave's forward partial sums; with wmax (scaled form) also the
-// wave's max |value| into its slot (a bound for the residual operand), per
-// wave and without a workgroup barrier.
-template <int GW>
-__device__ inline void store_partials(float *dst, int64_t row0, int NCP, int g0, int lane, f32x16 (&acc)[2][GW],
-                                      float *wmax, int slot) {
-  const int half = lane >> 5, c16 = lane & 15, im = (lane >> 4) & 1;
-  float m = 0.f;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int g = 0; g < GW; ++g)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t row = row0 + a * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-        const int col = (g0 + g) * 16 + c16;
-        dst[(row * NCP + col) * 2 + im] = acc[a][g][v];
-        m = fmaxf(m, fabsf(acc[a][g][v]));
-      }
-  if (wmax) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (lane == 0) wmax[slot] = m;
-  }
-}
-
-// Forward, split form: rows = samples, reduction over pixels (16 per step).
-template <int NT, int GW, bool BF>
-__global__ __launch_bounds__(256) void k_fwd_split(const double *__restrict__ kap, const double *__restrict__ bet,
-                                                   const float *__restrict__ dbet, const u32x4 *__restrict__ zs,
-                                                   float *__restrict__ part, int64_t Tp, int Rp, int NCP, int chunk,
-                                                   int nsplit) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  int split, rb;
-  if (!split_tile(blockIdx.x, (int)(Tp / 256), nsplit, &split, &rb)) return;
-  const int64_t row0 = (int64_t)rb * 256 + wave * 64;
-  const int g0 = blockIdx.y * GW;
-  const int NGP = NCP / 16;
-  const int pz = blockIdx.z;  // problem
-  kap += pz * Tp * NT;
-  bet += (int64_t)pz * Rp * NT;
-  dbet += (int64_t)pz * Rp * NT;
-  zs += (int64_t)pz * Rp * NGP * 16;
-  part += pz * nsplit * Tp * NCP * 2;
-  double kv[NT];
-  float kf[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    kv[j] = kap[(row0 + lane) * NT + j];
-    kf[j] = (float)kv[j];
-  }
-  f32x16 acc[2][GW];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int g = 0; g < GW; ++g)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][g][v] = 0.f;
-  const int r0 = split * chunk;
-  const int r1 = min(Rp, r0 + chunk);
-  for (int r = r0; r < r1; r += 16) {
-    u32x4 A[2][4];
-    phase_tile16<NT, BF>(kv, kf, bet + (int64_t)(r + 8) * NT, dbet + (int64_t)r * NT, A);
-#pragma unroll
-    for (int g = 0; g < GW; ++g) {
-      const u32x4 *zq = zs + ((int64_t)(r >> 4) * NGP + (g0 + g)) * 256 + lane;
-      const u32x4 b[4] = {zq[0], zq[64], zq[128], zq[192]};
-      acc[0][g] = step6<BF>(A[0], b, acc[0][g]);
-      acc[1][g] = step6<BF>(A[1], b, acc[1][g]);
-    }
-  }
-  store_partials<GW>(part + (int64_t)split * Tp * NCP * 2, row0, NCP, g0, lane, acc, nullptr, 0);
-}
-
-// Adjoint, split form: rows = pixels, reduction over samples (16 per step).
-// The A operand is exp(+i phi); the conjugation lives in the packed B operand.
-template <int NT, int GW, bool BF>
-__global__ __launch_bounds__(256) void k_adj_split(const double *__restrict__ kap, const double *__restrict__ bet,
-                                                   const float *__restrict__ dkap, const u32x4 *__restrict__ ys,
-                                                   float *__restrict__ part, int Rp, int64_t Tp, int NCP, int chunk,
-                                                   int nsplit, const float2 *__restrict__ sq) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  int split, rb;
-  if (!(sq ? split_tile_rows(blockIdx.x, Rp / 256, nsplit, &split, &rb) : split_tile(blockIdx.x, Rp / 256, nsplit, &split, &rb))) return;
-  const int64_t row0 = (int64_t)rb * 256 + wave * 64;
-  const int g0 = blockIdx.y * GW;
-  const int NGP = NCP / 16;
-  const int pz = blockIdx.z;  // problem
-  kap += pz * Tp * NT;
-  dkap += pz * Tp * NT;
-  bet += (int64_t)pz * Rp * NT;
-  ys += pz * Tp * NGP * 16;
-  double bv[NT];
-  float bf[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    bv[j] = bet[(row0 + lane) * NT + j];
-    bf[j] = (float)bv[j];
-  }
-  f32x16 acc[2][GW];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int g = 0; g < GW; ++g)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][g][v] = 0.f;
-  const int64_t t0 = (int64_t)split * chunk;
-  const int64_t t1 = min(Tp, t0 + chunk);
-  for (int64_t t = t0; t < t1; t += 16) {
-    u32x4 A[2][4];
-    phase_tile16<NT, BF>(bv, bf, kap + (t + 8) * NT, dkap + t * NT, A);
-#pragma unroll
-    for (int g = 0; g < GW; ++g) {
-      const u32x4 *yq = ys + ((t >> 4) * NGP + (g0 + g)) * 256 + lane;
-      const u32x4 b[4] = {yq[0], yq[64], yq[128], yq[192]};
-      acc[0][g] = step6<BF>(A[0], b, acc[0][g]);
-      acc[1][g] = step6<BF>(A[1], b, acc[1][g]);
-    }
-  }
-  adj_epilogue<GW>(part, sq, Rp, NCP, nsplit, split, pz, blockIdx.y, gridDim.y, row0, g0, lane, acc);
-}
-
 
 // ---------------------------------------------------------------------------
 // Split forms with the solid-harmonic basis in polynomial form.  With z
@@ -500,12 +324,14 @@ __global__ __launch_bounds__(256) void k_amax_c(const float2 *__restrict__ v, in
   write_block_max(m, amax + pz * kAmaxBlocks + blockIdx.x);
 }
 
+// (perm: the index order of the adjoint records below, which the
+// general-basis forward shares)
 template <bool BF>
 __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict__ smaps, const float2 *__restrict__ x,
                                 const float2 *__restrict__ xsub, int64_t x_stride, int x_row_stride, int nx, int ny,
                                 int nxq, int Rp, int C, int NC, int NGP, u32x4 *__restrict__ zs, int64_t x_pstride,
                                 const float2 *__restrict__ sq, const float *__restrict__ amax,
-                                float *__restrict__ scl) {
+                                float *__restrict__ scl, int perm) {
   const int R = nx * ny;
   const int pz = blockIdx.y;  // problem
   // scaled form: every workgroup derives the same power of two from the pre-pass
@@ -531,8 +357,8 @@ __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict_
   const int im = (lane >> 4) & 1;
   // the 8 pixels of this lane: every load is issued before the arithmetic
   // (outside pixels and columns read an in-bounds element and give 0)
-  const int rq0 = (int)(16 * q + 8 * (lane >> 5));
-  int yy = rq0 / nxq, xx = rq0 - yy * nxq;
+  const int half = lane >> 5, rq0 = (int)(16 * q) + (perm ? 4 : 8) * half;
+  int rq = rq0, yy = rq / nxq, xx = rq - yy * nxq;
   const bool colok = col < NC;
   const int b = colok ? col / C : 0, c = colok ? col % C : 0;
   float2 u[8], w[8], sv[8];
@@ -545,9 +371,12 @@ __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict_
     u[i] = x[o];
     w[i] = xsub ? xsub[o] : make_float2(0.f, 0.f);
     // (the S table, when given, holds the same value in row-major order)
-    sv[i] = sq ? sq[(int64_t)(rq0 + i) * NGP * 16 + col] : smaps[(int64_t)c * R + yc * nx + xc];
-    if (++xx == nxq) {
-      xx = 0;
+    sv[i] = sq ? sq[(int64_t)rq * NGP * 16 + col] : smaps[(int64_t)c * R + yc * nx + xc];
+    const int step = perm && i == 3 ? 5 : 1;
+    rq += step;
+    xx += step;
+    while (xx >= nxq) {
+      xx -= nxq;
       ++yy;
     }
   }
@@ -570,13 +399,13 @@ __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict_
 
 // Adjoint operand from y [B][T][C] (src_abi) or from forward partials minus
 // y_meas (src_part, nsplit partial arrays in [Tp][NCP] layout).
-// With perm, K index 8h + i of a step holds sample 8(i/4) + 4h + i%4 of its
-// 16 (the order in which the polynomial adjoint produces its phase tile).
+// K index 8h + i of a step holds sample 8(i/4) + 4h + i%4 of its 16 (the
+// order in which the adjoints produce their phase tiles).
 template <bool BF>
 __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__ src_abi,
                                                       const float2 *__restrict__ src_part, int nsplit,
                                                       const float2 *__restrict__ y_meas, int64_t T, int64_t Tp, int C,
-                                                      int NC, int NCP, u32x4 *__restrict__ ys, int perm,
+                                                      int NC, int NCP, u32x4 *__restrict__ ys,
                                                       const float *__restrict__ bnd, int nbnd,
                                                       const float *__restrict__ bnd_meas, float *__restrict__ scl) {
   const int NGP = NCP / 16;
@@ -612,7 +441,7 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
   float2 y[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    t[i] = 16 * q + (perm ? 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3) : 8 * (lane >> 5) + i);
+    t[i] = 16 * q + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
     ok[i] = t[i] < T && col < NC;
     y[i] = make_float2(0.f, 0.f);
   }
@@ -681,51 +510,6 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
 // Launchers
 // ---------------------------------------------------------------------------
 
-template <int NT, bool BF>
-static void launch_fwd_split(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  dim3 grid(split_grid(p.Tp / 256 * p.fwd_split), (unsigned)p.NGY, (unsigned)p.P);
-  float *part = reinterpret_cast<float *>(b.part);
-  const u32x4 *zs = reinterpret_cast<const u32x4 *>(b.zs);
-  if (p.GW == 2)
-    k_fwd_split<NT, 2, BF><<<grid, 256, 0, s>>>(b.kap, b.bet, b.dbet, zs, part, p.Tp, p.Rp, p.NCP, p.fwd_chunk,
-                                                p.fwd_split);
-  else
-    k_fwd_split<NT, 1, BF><<<grid, 256, 0, s>>>(b.kap, b.bet, b.dbet, zs, part, p.Tp, p.Rp, p.NCP, p.fwd_chunk,
-                                                p.fwd_split);
-}
-
-template <int NT, bool BF>
-static void launch_adj_split(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  dim3 grid(split_grid((int64_t)p.Rp / 256 * p.adj_split), (unsigned)p.NGY, (unsigned)p.P);
-  float *part = reinterpret_cast<float *>(b.part);
-  const u32x4 *ys = reinterpret_cast<const u32x4 *>(b.ys);
-  const float2 *sm = p.comb ? b.sq : nullptr;
-  if (p.GW == 2)
-    k_adj_split<NT, 2, BF><<<grid, 256, 0, s>>>(b.kap, b.bet, b.dkap, ys, part, p.Rp, p.Tp, p.NCP, p.adj_chunk,
-                                                p.adj_split, sm);
-  else
-    k_adj_split<NT, 1, BF><<<grid, 256, 0, s>>>(b.kap, b.bet, b.dkap, ys, part, p.Rp, p.Tp, p.NCP, p.adj_chunk,
-                                                p.adj_split, sm);
-}
-
-template <bool BF>
-static void fwd_split_nt(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  switch (p.NT) {
-    case 4: launch_fwd_split<4, BF>(p, b, s); break;
-    case 10: launch_fwd_split<10, BF>(p, b, s); break;
-    default: launch_fwd_split<17, BF>(p, b, s); break;
-  }
-}
-
-template <bool BF>
-static void adj_split_nt(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  switch (p.NT) {
-    case 4: launch_adj_split<4, BF>(p, b, s); break;
-    case 10: launch_adj_split<10, BF>(p, b, s); break;
-    default: launch_adj_split<17, BF>(p, b, s); break;
-  }
-}
-
 static FwdShArgs fwd_sh_args(const EncPlan &p, const EncBuffers &b) {
   return FwdShArgs{b.pmono, b.dwq, b.ddw, reinterpret_cast<const u32x4 *>(b.zs), reinterpret_cast<float *>(b.part),
                    p.scaled ? b.wmax : nullptr, p.Tp, p.Rp, p.NCP, p.fwd_chunk, p.fwd_split, p.nxq, p.nx, p.ny,
@@ -784,19 +568,13 @@ void split_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) 
     if (bf) fwd_split_sh<true>(p, b, s);
     else fwd_split_sh<false>(p, b, s);
   } else {
-    if (bf) fwd_split_nt<true>(p, b, s);
-    else fwd_split_nt<false>(p, b, s);
+    split_maps_launch(p, b, false, s);
   }
 }
 
 void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  const bool bf = p.prec == EXPENC_BF16_SPLIT;
-  if (p.sh) {
-    split_adjoint_sh_launch(p, b, s);
-  } else {
-    if (bf) adj_split_nt<true>(p, b, s);
-    else adj_split_nt<false>(p, b, s);
-  }
+  if (p.sh) split_adjoint_sh_launch(p, b, s);
+  else split_maps_launch(p, b, true, s);
 }
 
 int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const float2 *xsub, int64_t x_stride,
@@ -818,10 +596,10 @@ int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const f
   const float2 *sq = p.comb && !prepared ? b.sq : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
     k_build_z_split<true><<<nb, 256, 0, s>>>(sm, x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C,
-                                             p.NC, NGP, zs, x_pstride, sq, b.amax, scl);
+                                             p.NC, NGP, zs, x_pstride, sq, b.amax, scl, p.sh ? 0 : 1);
   else
     k_build_z_split<false><<<nb, 256, 0, s>>>(sm, x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C,
-                                              p.NC, NGP, zs, x_pstride, sq, b.amax, scl);
+                                              p.NC, NGP, zs, x_pstride, sq, b.amax, scl, p.sh ? 0 : 1);
   EX_LAUNCHED("build_z split");
   return EXPENC_OK;
 }
@@ -870,10 +648,10 @@ int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, cons
   float *scl = p.scaled ? b.scl : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
     k_pack_y_split<true><<<nb, 256, 0, s>>>(y_abi, part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP, ys,
-                                            p.sh ? 1 : 0, bnd, nbnd, bnd_meas, scl);
+                                            bnd, nbnd, bnd_meas, scl);
   else
     k_pack_y_split<false><<<nb, 256, 0, s>>>(y_abi, part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP, ys,
-                                             p.sh ? 1 : 0, bnd, nbnd, bnd_meas, scl);
+                                             bnd, nbnd, bnd_meas, scl);
   EX_LAUNCHED("pack_y split");
   return EXPENC_OK;
 }

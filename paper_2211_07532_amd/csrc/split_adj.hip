@@ -30,7 +30,7 @@ struct AdjShArgs {
 // sample at each pixel (table anc) plus the increment over the tile.  With
 // the pixels of the block in one image row y the increment is a cubic in x,
 // sum_k C_k(t, y) x^k + d10(t) dw0, whose coefficients are polynomials in y
-// (k_prep_dpa): a rank-6 product, three v_mfma_f32_32x32x2_f32 with terms
+//: a rank-6 product, three v_mfma_f32_32x32x2_f32 with terms
 // (1 | x), (x^2 | x^3), (dw0 | anchor) against (C_0 | C_1), (C_2 | C_3),
 // (d10 | 1) evaluated at the block's row.  A block that continues into the
 // next row (when the padded row length nxq is not a multiple of 32) adds,

@@ -105,4 +105,30 @@ __device__ inline f32x16 step6(const u32x4 (&A)[4], const u32x4 *b, f32x16 acc) 
   return acc;
 }
 
+// Writes a wave's forward partial sums; with wmax (scaled form) also the
+// wave's max |value| into its slot (a bound for the residual operand), per
+// wave and without a workgroup barrier.
+template <int GW>
+__device__ inline void store_partials(float *dst, int64_t row0, int NCP, int g0, int lane, f32x16 (&acc)[2][GW],
+                                      float *wmax, int slot) {
+  const int half = lane >> 5, c16 = lane & 15, im = (lane >> 4) & 1;
+  float m = 0.f;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int g = 0; g < GW; ++g)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int64_t row = row0 + a * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+        const int col = (g0 + g) * 16 + c16;
+        dst[(row * NCP + col) * 2 + im] = acc[a][g][v];
+        m = fmaxf(m, fabsf(acc[a][g][v]));
+      }
+  if (wmax) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (lane == 0) wmax[slot] = m;
+  }
+}
+
 }  // namespace expenc

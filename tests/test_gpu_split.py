@@ -177,3 +177,36 @@ def test_strong_field_operators(prec, n):
     print(f"strong field {prec} n={n}: forward {e_f:.2e}, adjoint {e_a:.2e}", flush=True)
     bar = 1e-6 if prec == "fp32" else 1e-4
     assert e_f <= bar and e_a <= bar
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("nx,ny,T,C,L,B", [
+    (1, 1, 1, 1, 0, 1),          # one pixel and sample, the off-resonance term alone
+    (33, 20, 700, 17, 3, 2),     # odd rows, an even number of terms, two images
+    (31, 29, 1000, 33, 16, 1),   # 17 terms (the last one paired with zero), three column groups
+    (16, 16, 256, 8, 9, 1),      # whole tiles
+    (3, 130, 40, 40, 16, 1),     # tiles that span several image rows
+])
+def test_split_maps_tile_edges(nx, ny, T, C, L, B, prec):
+    """The general-basis split contractions (phase increments of 32 indexes as
+    a matrix product) against the oracle.  Operand rounding 3 * 2^-16 (bf16) or
+    less; increments of up to some tens of turns in FP32, 2e-5 rad: 1e-4."""
+    import torch
+    ee = _ee()
+    R = nx * ny
+    rng = np.random.default_rng(11 + nx + T + C + L)
+    basis = encoding.sh_basis(nx, 0.1, 0.003, max(L, 1), ny=ny, fov_y=0.07)[:L]
+    coef = rng.normal(0.0, 1.0, (T, L)) * (20.0 / np.maximum(np.abs(basis).max(axis=1), 1e-12))[None, :]
+    time = np.arange(1, T + 1, dtype=np.float64) * 2e-6
+    dw0 = rng.uniform(-600.0, 600.0, R)
+    smaps = c64(synth.random_complex((C, R), 71))
+    x, y = c64(synth.random_complex((B, R), 72)), c64(synth.random_complex((B, T, C), 73))
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    op = ee.Operator(nx, ny, t(smaps.astype(np.complex64)), t(coef), t(time), t(basis) if L else None, t(dw0))
+    print(f"[case] split maps edges {nx}x{ny} T={T} C={C} L={L} B={B} {prec}", flush=True)
+    f = ee.forward(t(x.astype(np.complex64)), op, precision=prec).cpu().numpy().reshape(B, T, C)
+    a = ee.adjoint(t(y.astype(np.complex64)), op, precision=prec).cpu().numpy().reshape(B, R)
+    for b in range(B):
+        assert rel(f[b], encoding.forward(x[b], smaps, coef, time, basis, dw0)) <= 1e-4
+        assert rel(a[b], encoding.adjoint(y[b], smaps, coef, time, basis, dw0)) <= 1e-4

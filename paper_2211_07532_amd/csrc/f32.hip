@@ -52,10 +52,11 @@ __device__ inline void split3(float a, float b, Bf16Masks mk, uint32_t &h, uint3
   l = __builtin_bit_cast(uint32_t, lv);
 }
 
-// cos and sin of a phase in turns (FP64), reduced to [-1/2, 1/2] turns
-// before it is rounded to FP32
+// A phase in turns (FP64), reduced to [-1/2, 1/2] before it is rounded to FP32
+__device__ inline float reduce_turns(double p) { return (float)(p - __builtin_rint(p)); }
+
 __device__ inline void sincos_turns(double p, float &c, float &s) {
-  const float f = (float)(p - __builtin_rint(p));
+  const float f = reduce_turns(p);
   c = __builtin_amdgcn_cosf(f);
   s = __builtin_amdgcn_sinf(f);
 }
@@ -181,26 +182,20 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
     fill(k0, 0);
     __syncthreads();
   }
+  RowCubic rc;
+  if constexpr (NT == 0) rc.start((int)k0, a.nxq);
   for (int64_t k = k0; k < k1; k += 16) {
     uint32_t w[6][8];  // [c hi, mid, lo, s hi, mid, lo][pair of the 16 indices]
     if constexpr (NT == 0) {
-      const int r = (int)k, yi = r / a.nxq, xi = r % a.nxq + 8;
-      const double ym = (yi - 0.5 * a.ny) * a.dy, xc = (xi - 0.5 * a.nx) * a.dx;
-      const double a0 = P[0] + ym * (P[2] + ym * (P[5] + ym * P[9]));
-      const double a1 = P[1] + ym * (P[4] + ym * P[8]);
-      const double a2 = P[3] + ym * P[7], a3 = P[6];
-      const double c0 = a0 + xc * (a1 + xc * (a2 + xc * a3));
-      const double d1 = (a1 + xc * (2.0 * a2 + 3.0 * a3 * xc)) * a.dx;
-      const double d2 = (a2 + 3.0 * a3 * xc) * dx2;
-      const double d3 = a3 * dx3;
+      const int r = (int)k;
+      rc.expand(P, a.nx, a.ny, a.dx, a.dy, dx2, dx3);
+      rc.next(a.nxq);
+      float f[16];
+      rc.each([&](int i, double p) { f[i] = reduce_turns(fma(P[10], uni[r + i], p)); });
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
-        float c[2], s[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const double kk = 2 * m + e - 8;
-          sincos_turns(fma(P[10], uni[r + 2 * m + e], fma(fma(fma(d3, kk, d2), kk, d1), kk, c0)), c[e], s[e]);
-        }
+        const float c[2] = {__builtin_amdgcn_cosf(f[2 * m]), __builtin_amdgcn_cosf(f[2 * m + 1])};
+        const float s[2] = {__builtin_amdgcn_sinf(f[2 * m]), __builtin_amdgcn_sinf(f[2 * m + 1])};
         split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
         split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
       }

@@ -233,9 +233,8 @@ __global__ __launch_bounds__(256, 2) void k_field_grad(const double *__restrict_
     for (int b = 0; b < 4; ++b)
 #pragma unroll
       for (int q = 0; q < 3; ++q) B[b][q] = kb[((t0 / 16 + b) * a.CK + ks) * 192 + 64 * q + lane];
-    int yi = r0 / a.nxq, xi = r0 - yi * a.nxq;
-    bool row = true;
-    double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+    RowCubic rc;
+    if constexpr (NT == 0) rc.start(r0, a.nxq);
     for (int r = r0; r < r1; r += 16) {
       const u32x4 *zr = za + ((int64_t)(r >> 4) * a.CK + ks) * 192 + lane;
       const u32x4 A[3] = {zr[0], zr[64], zr[128]};
@@ -256,30 +255,12 @@ __global__ __launch_bounds__(256, 2) void k_field_grad(const double *__restrict_
       // [-1/2, 1/2] before they are rounded to FP32
       float f[4][4];  // [pixel / 4][pixel % 4]
       if constexpr (NT == 0) {
-        if (row) {  // row polynomial
-          const double ym = (yi - 0.5 * a.ny) * a.dy;
-          a0 = P[0] + ym * (P[2] + ym * (P[5] + ym * P[9]));
-          a1 = P[1] + ym * (P[4] + ym * P[8]);
-          a2 = P[3] + ym * P[7], a3 = P[6];
-        }
-        // around the centre of this 16-pixel tile
-        const double xc = (xi + 8 - 0.5 * a.nx) * a.dx;
-        const double c0 = a0 + xc * (a1 + xc * (a2 + xc * a3));
-        const double d1 = (a1 + xc * (2.0 * a2 + 3.0 * a3 * xc)) * a.dx;
-        const double d2 = (a2 + 3.0 * a3 * xc) * dx2;
-        const double d3 = a3 * dx3;
-        xi += 16;
-        row = xi >= a.nxq;
-        if (row) {
-          xi -= a.nxq;
-          ++yi;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const double k = i - 8;
-          const double ph = fma(P[10], uni[r + i], fma(fma(fma(d3, k, d2), k, d1), k, c0));
+        rc.expand(P, a.nx, a.ny, a.dx, a.dy, dx2, dx3);
+        rc.next(a.nxq);
+        rc.each([&](int i, double p) {
+          const double ph = fma(P[10], uni[r + i], p);
           f[i >> 2][i & 3] = (float)(ph - __builtin_rint(ph));
-        }
+        });
       } else {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {

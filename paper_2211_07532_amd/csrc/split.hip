@@ -96,6 +96,7 @@ struct FwdShArgs {
   int64_t Tp;
   int Rp, NCP, chunk, nsplit, nxq, nx, ny;
   double dx, dy;
+  Bf16Masks mk;
 };
 
 // One workgroup of the forward (workgroup bx, by, bz of a gx x gy x P grid).
@@ -143,21 +144,39 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
       for (int v = 0; v < 16; ++v) acc[a][g][v] = 0.f;
   const int r0 = split * chunk;
   const int r1 = min(Rp, r0 + chunk);
-  for (int r = r0; r < r1; r += 16) {
-    const int yi = r / nxq, xi = r % nxq + 8;
-    const double ym = (yi - 0.5 * ny) * dy, xc = (xi - 0.5 * nx) * dx;
-    const double a0 = P[0] + ym * (P[2] + ym * (P[5] + ym * P[9]));
-    const double a1 = P[1] + ym * (P[4] + ym * P[8]);
-    const double a2 = P[3] + ym * P[7];
-    const double a3 = P[6];
-    const double phc = fma(tt, dwq[r + 8], a0 + xc * (a1 + xc * (a2 + xc * a3)));
-    const float an = (float)__builtin_amdgcn_fract(phc);
-    const float d1 = (float)((a1 + xc * (2.0 * a2 + 3.0 * a3 * xc)) * dx);
-    const float d2 = (float)((a2 + 3.0 * a3 * xc) * dx2);
-    const float d3 = (float)(a3 * dx3);
+  // Software pipeline: the phases of tile r + 16 are evaluated between the
+  // MFMAs of tile r, in ten slots of a few MFMAs and the vector work of two
+  // indexes.  The vector unit issues in three quarters of the cycles and the
+  // matrix cores are busy in half, at a clock of 1.9 GHz that the two share;
+  // left to itself the compiler puts the MFMAs behind the phases, the more so
+  // the fewer vector instructions those take: with the cubic moved along the
+  // row 148 x 148, 32 coils, T = 16384 took 384 us (fp16) so, 360 expanded
+  // anew for every tile, and takes 348 pipelined.
+  u32x4 A[2][4], bq[GW][4];
+  uint32_t w[4][8];  // [kind: c hi, c lo, s hi, s lo][pair of indexes]
+  float ph[16], dd[16];
+  RowCubic rc;  // of the tile whose phases come next
+  rc.start(r0, nxq);
+  double dq = 0.0;
+  auto load_b = [&](int g, int r) {
+    const u32x4 *zq = zs + ((int64_t)(r >> 4) * NGP + (g0 + g)) * 256 + lane;
+    bq[g][0] = zq[0];
+    bq[g][1] = zq[64];
+    bq[g][2] = zq[128];
+    bq[g][3] = zq[192];
+  };
+  auto load_dw = [&](int r) {
+    dq = dwq[r + 8];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) dd[j] = ddw[r + j];
+  };
+  auto expand = [&] {
+    rc.expand(P, nx, ny, dx, dy, dx2, dx3);
+    rc.next(nxq);
+    const float an = (float)__builtin_amdgcn_fract(fma(tt, dq, rc.c0));
+    const float d1 = (float)rc.d1, d2 = (float)rc.d2, d3 = (float)rc.d3;
     // p(k) = an + d1 k + d2 k^2 + d3 k^3 at k = j - 8: the even part
     // an + d2 k^2 and the odd factor d1 + d3 k^2 are shared by k and -k
-    float ph[16];
     ph[8] = an;
 #pragma unroll
     for (int m = 1; m < 8; ++m) {
@@ -167,23 +186,66 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
       ph[8 - m] = fmaf(od, -k, ev);
     }
     ph[0] = fmaf(fmaf(fmaf(d3, -8.f, d2), -8.f, d1), -8.f, an);
-    float c[16], sn[16];
+  };
+  auto pair = [&](int m) {
+    float c2[2], s2[2];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const float f = __builtin_amdgcn_fractf(fmaf(tf, ddw[r + j], ph[j]));
-      c[j] = __builtin_amdgcn_cosf(f);
-      sn[j] = __builtin_amdgcn_sinf(f);
+    for (int e = 0; e < 2; ++e) {
+      const float f = __builtin_amdgcn_fractf(fmaf(tf, dd[2 * m + e], ph[2 * m + e]));
+      c2[e] = __builtin_amdgcn_cosf(f);
+      s2[e] = __builtin_amdgcn_sinf(f);
     }
-    u32x4 A[2][4];
-    pack_tile16<BF>(c, sn, A);
+    split_pair<BF>(c2[0], c2[1], w[0][m], w[1][m], a.mk);
+    split_pair<BF>(s2[0], s2[1], w[2][m], w[3][m], a.mk);
+  };
+  auto exchange = [&] {
 #pragma unroll
-    for (int g = 0; g < GW; ++g) {
-      const u32x4 *zq = zs + ((int64_t)(r >> 4) * NGP + (g0 + g)) * 256 + lane;
-      const u32x4 b[4] = {zq[0], zq[64], zq[128], zq[192]};
-      acc[0][g] = step6<BF>(A[0], b, acc[0][g]);
-      acc[1][g] = step6<BF>(A[1], b, acc[1][g]);
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const auto x = __builtin_amdgcn_permlane32_swap(w[q][i], w[q][4 + i], false, false);
+        A[0][q][i] = x[0];
+        A[1][q][i] = x[1];
+      }
+  };
+  // MFMAs [lo, hi) of a tile: column groups in turn, the products of the two
+  // row blocks alternating
+  auto products = [&](int lo, int hi) {
+    constexpr int pa[6] = {0, 0, 1, 2, 2, 3}, pb[6] = {0, 1, 0, 2, 3, 2};
+#pragma unroll
+    for (int k = 0; k < 12 * GW; ++k)
+      if (k >= lo && k < hi) {
+        const int g = k / 12, q = k % 12 >> 1, blk = k & 1;
+        acc[blk][g] = mfma16<BF>(A[blk][pa[q]], bq[g][pb[q]], acc[blk][g]);
+      }
+  };
+  load_dw(r0);
+#pragma unroll
+  for (int g = 0; g < GW; ++g) load_b(g, r0);
+  expand();
+#pragma unroll
+  for (int m = 0; m < 8; ++m) pair(m);
+  exchange();
+  for (int r = r0; r + 16 < r1; r += 16) {
+    constexpr int N = 12 * GW;
+    load_dw(r + 16);
+    products(0, N / 10);
+    __builtin_amdgcn_sched_barrier(0);
+    products(N / 10, N * 2 / 10);
+    expand();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      products(N * (m + 2) / 10, N * (m + 3) / 10);
+      pair(m);
+      // a column group's records are replaced once its products are issued
+#pragma unroll
+      for (int g = 0; g < GW; ++g)
+        if (N * (m + 2) / 10 < 12 * (g + 1) && N * (m + 3) / 10 >= 12 * (g + 1)) load_b(g, r + 16);
     }
+    exchange();
   }
+  products(0, 12 * GW);
   store_partials<GW>(part + (int64_t)split * Tp * NCP * 2, row0, NCP, g0, lane, acc, wmax, slot);
 }
 
@@ -513,7 +575,7 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
 static FwdShArgs fwd_sh_args(const EncPlan &p, const EncBuffers &b) {
   return FwdShArgs{b.pmono, b.dwq, b.ddw, reinterpret_cast<const u32x4 *>(b.zs), reinterpret_cast<float *>(b.part),
                    p.scaled ? b.wmax : nullptr, p.Tp, p.Rp, p.NCP, p.fwd_chunk, p.fwd_split, p.nxq, p.nx, p.ny,
-                   p.dx, p.dy};
+                   p.dx, p.dy, bf16_masks()};
 }
 
 template <bool BF>

@@ -528,6 +528,7 @@ static inline dim3 grid_p(int64_t n, int bs, int P) { return dim3((unsigned)ceil
 int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride,
                 int32_t x_row_stride, const EncBuffers &b, hipStream_t s, const float2 *xsub, int64_t x_pstride,
                 bool prepared) {
+  if (prepared && !p.scaled) return EXPENC_OK;  // enc_prepare wrote the records
   if (p.prec != EXPENC_FP32)
     return split_build_z(p, smaps, x, xsub, x_stride, x_row_stride, b, s, x_pstride, prepared);
   if (xsub) return fail(EXPENC_EUNSUPPORTED, "operand difference is only built for split forms");
@@ -535,6 +536,7 @@ int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x
 }
 
 int enc_pack_y(const EncPlan &p, const float2 *y, const EncBuffers &b, hipStream_t s, float sign, bool prepared) {
+  if (prepared && !p.scaled) return EXPENC_OK;
   if (p.prec != EXPENC_FP32) {
     if (sign != 1.f) return fail(EXPENC_EUNSUPPORTED, "scaled operand packing is FP32 only");
     return split_pack_y(p, y, false, nullptr, b, s, prepared);

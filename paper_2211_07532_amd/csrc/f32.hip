@@ -34,8 +34,6 @@
 
 namespace expenc {
 
-constexpr int kRec3 = 6 * 64;  // 16-byte words of one step and column group
-
 // (hi, mid, lo) pairs of two FP32 values (exact remainders: the bf16 dot
 // product v + (hi_a, hi_b) . (-1, 0), see split_pair).
 __device__ inline void split3(float a, float b, Bf16Masks mk, uint32_t &h, uint32_t &m, uint32_t &l) {
@@ -334,17 +332,6 @@ __global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict_
 //   forward:  b1 = part ? Zi : Zr,   b2 = part ? Zr : -Zi
 //   adjoint:  b1 = part ? Yi : Yr,   b2 = part ? -Yr : Yi
 // ---------------------------------------------------------------------------
-
-__device__ inline void write_rec3(u32x4 *o, const float (&b1)[8], const float (&b2)[8]) {
-  uint32_t w[6][4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    split3_any(b1[2 * m], b1[2 * m + 1], w[0][m], w[1][m], w[2][m]);
-    split3_any(b2[2 * m], b2[2 * m + 1], w[3][m], w[4][m], w[5][m]);
-  }
-#pragma unroll
-  for (int q = 0; q < 6; ++q) o[64 * q] = u32x4{w[q][0], w[q][1], w[q][2], w[q][3]};
-}
 
 // Z[r'][col] = S_c(r) x_b(r), col = b*C + c, row r' = y*nxq + x of pixel
 // r = y*nx + x; zero for padded pixels and columns.

@@ -398,10 +398,11 @@ int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part = 0);
 // Kernel launchers (stream-ordered, no synchronisation).
 // Field tables of plan p (prep.hip), one launch: those that the directions in
 // `need` read.  A split plan's tables include the FP32 plan's of the same
-// geometry.  operand (fp16 form): the image [P][B][R] (need = kNeedForward) or
-// data [P][B][T][C] (kNeedAdjoint) that the call applies the operator to; its
-// magnitude bound is then taken in the same launch, and enc_build_z /
-// enc_pack_y are told so (prepared = true).
+// geometry.  operand: the image [P][B][R] (need = kNeedForward) or data
+// [P][B][T][C] (kNeedAdjoint) that the call applies the operator to; its
+// records (FP32, bf16) or its magnitude bound (fp16, whose records need it) are
+// then written by the same launch, and enc_build_z / enc_pack_y are told so
+// (prepared = true).
 enum { kNeedForward = 1, kNeedAdjoint = 2, kNeedBoth = 3 };
 int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s, int need,
                 const float2 *operand = nullptr);
@@ -412,7 +413,7 @@ int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x
                 int32_t x_row_stride, const EncBuffers &b, hipStream_t s, const float2 *xsub = nullptr,
                 int64_t x_pstride = 0, bool prepared = false);
 // (prepared: enc_prepare was given this operand with kNeedForward, so its
-// bound is written and there is no coil table)
+// records or its bound are written and there is no coil table)
 // (timing = false: never records the profiling events of expenc_kernel_timing)
 int enc_forward_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s, bool timing = true);
 // y[b][t][c] = sum_split partials (ABI layout)

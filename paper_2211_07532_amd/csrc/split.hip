@@ -282,22 +282,6 @@ __global__ __launch_bounds__(256) void k_fwd_split_sh_grouped(GroupedLaunch<FwdS
 //   adjoint:  b1 = part ? Yi : Yr,   b2 = part ? -Yr : Yi
 // ---------------------------------------------------------------------------
 
-template <bool BF>
-__device__ inline void write_record(u32x4 *out, int64_t q, int g, int NGP, int lane, const float (&b1)[8],
-                                    const float (&b2)[8]) {
-  uint32_t h1[4], l1[4], h2[4], l2[4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    split_pair<BF>(b1[2 * m], b1[2 * m + 1], h1[m], l1[m]);
-    split_pair<BF>(b2[2 * m], b2[2 * m + 1], h2[m], l2[m]);
-  }
-  u32x4 *o = out + (q * NGP + g) * 256 + lane;
-  o[0] = u32x4{h1[0], h1[1], h1[2], h1[3]};
-  o[64] = u32x4{l1[0], l1[1], l1[2], l1[3]};
-  o[128] = u32x4{h2[0], h2[1], h2[2], h2[3]};
-  o[192] = u32x4{l2[0], l2[1], l2[2], l2[3]};
-}
-
 // ---------------------------------------------------------------------------
 // Operand scaling of the fp16 form.  An fp16 hi/lo pair represents |v| up to
 // 65504 and keeps its ~22-bit precision only while the lo half is normal,

@@ -105,6 +105,38 @@ __device__ inline f32x16 step6(const u32x4 (&A)[4], const u32x4 *b, f32x16 acc) 
   return acc;
 }
 
+constexpr int kRec3 = 6 * 64;  // 16-byte words of one FP32-form step and column group
+
+// Operand records of 8 reduction indices (layout: see the packing kernels):
+// hi and lo of b1 and b2 (split forms), three exact bf16 parts (FP32 form; o:
+// the lane's).
+template <bool BF>
+__device__ inline void write_record(u32x4 *out, int64_t q, int g, int NGP, int lane, const float (&b1)[8],
+                                    const float (&b2)[8]) {
+  uint32_t h1[4], l1[4], h2[4], l2[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    split_pair<BF>(b1[2 * m], b1[2 * m + 1], h1[m], l1[m]);
+    split_pair<BF>(b2[2 * m], b2[2 * m + 1], h2[m], l2[m]);
+  }
+  u32x4 *o = out + (q * NGP + g) * 256 + lane;
+  o[0] = u32x4{h1[0], h1[1], h1[2], h1[3]};
+  o[64] = u32x4{l1[0], l1[1], l1[2], l1[3]};
+  o[128] = u32x4{h2[0], h2[1], h2[2], h2[3]};
+  o[192] = u32x4{l2[0], l2[1], l2[2], l2[3]};
+}
+
+__device__ inline void write_rec3(u32x4 *o, const float (&b1)[8], const float (&b2)[8]) {
+  uint32_t w[6][4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    split3_any(b1[2 * m], b1[2 * m + 1], w[0][m], w[1][m], w[2][m]);
+    split3_any(b2[2 * m], b2[2 * m + 1], w[3][m], w[4][m], w[5][m]);
+  }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) o[64 * q] = u32x4{w[q][0], w[q][1], w[q][2], w[q][3]};
+}
+
 // Writes a wave's forward partial sums; with wmax (scaled form) also the
 // wave's max |value| into its slot (a bound for the residual operand), per
 // wave and without a workgroup barrier.

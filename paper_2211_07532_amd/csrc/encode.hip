@@ -245,6 +245,7 @@ static int phase_terms(int L) {
 }
 
 constexpr int kTargetWorkgroups = 2048;
+constexpr int32_t kSplitFwdChunkMax = 3072;
 constexpr int kMaxWorkgroups = 4608;  // of the default split (scratch grows with the splits)
 
 // EXPENC_TARGET_WG, or 0.
@@ -268,17 +269,18 @@ static int32_t target_chunk(int64_t K, int64_t nrb, int ngy, int target, int gra
 // kTargetWorkgroups, if it is longer) the one whose launch is shortest by
 // this model, fitted to 27 sweeps (32 to 200 px, every precision, both
 // kinds).  A CU takes n workgroups, `slots` at a time; a remainder of 1 or 2
-// runs at 0.85 or 0.9 of the full rate, as if it were n / rate; 1.5 more
-// stand for the uneven end.  A workgroup has a prologue of about 8 steps of
+// runs at 0.85 or 0.9 of the full rate, as if it were n / rate; `tail` more
+// stand for the uneven end (1.5; 0.3 for the split forwards of two column
+// groups, whose whole rounds of two workgroups end together).  A workgroup has a prologue of about 8 steps of
 // 16 indexes, and a step takes 0.5 us of a CU (0.6 for the general-basis and
 // 1 for the FP32 kernels, 0.6 times that with 16 columns per wave).  The
 // partial sums cost `width` complex values per row and split at 8 TB/s.
 // Whole calls, at 2048 workgroups and as picked: 100 x 90, T 3000, 16 coils,
 // 4 images, fp16: forward 112 / 84 us (32 splits), adjoint 100 / 84 (9);
 // one image, 16 maps, bf16: 64 / 58 and 71 / 60; 64 x 64, T 4000, 8 coils,
-// bf16: 39 / 34 and 73 / 31; 148 x 148, 32 coils, bf16: 351 / 334 and
-// 342 / 331.  (The picks are within 5 % of the fastest split in all sweeps.)
-int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, int grain,
+// bf16: 39 / 34 and 73 / 31; 148 x 148, 32 coils, bf16: 351 / 326 (16
+// splits) and 342 / 331.
+int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, int grain,
                       int32_t longest, int32_t cap) {
   const int32_t at_target = target_chunk(K, nrb, ngy, kTargetWorkgroups, grain, cap);
   const int32_t last = std::max(at_target, std::min(longest, (int32_t)round_up(K, grain)));
@@ -292,7 +294,7 @@ int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots,
     if (split == prev) continue;  // (the shortest chunk of a split is its most even)
     prev = split;
     const int64_t n = ceil_div(nrb * ngy * split, 256), r = n % slots;
-    const double load = (double)(n - r) + (r == 1 ? 1 / 0.85 : r == 2 ? 2 / 0.9 : (double)r) + 1.5;
+    const double load = (double)(n - r) + (r == 1 ? 1 / 0.85 : r == 2 ? 2 / 0.9 : (double)r) + tail;
     const double t = load * (chunk / 16 + 8) * step + (double)split * nrb * width * (256 * 8 / 8e6);
     if (t < cost) {
       cost = t;
@@ -409,8 +411,9 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   q.scaled = precision == EXPENC_FP16_SPLIT;
   q.adj_anc = q.sh && precision != EXPENC_FP32;
   // Partial sums of the default splits: no longer than 512 indexes in the
-  // FP32 form (its chunk sums are its rounding error) and 1024 in the split
-  // forms (below), unless kTargetWorkgroups makes them longer.
+  // FP32 form (its chunk sums are its rounding error), 1024 in the split
+  // adjoints and kSplitFwdChunkMax in the split forwards (below), unless
+  // kTargetWorkgroups makes them longer.
   const bool f32 = precision == EXPENC_FP32;
   const int32_t longest = f32 ? 512 : kSplitAdjChunkMax;
   const double step = (f32 ? 1.0 : q.sh ? 0.5 : 0.6) * (q.GW == 2 ? 1.0 : 0.6);
@@ -421,7 +424,8 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
     const int slots = f32 ? 5 - q.GW : q.sh ? 4 - q.GW : 2;  // workgroups that fit on a CU
     const int grain = fwd_grain(q);
     q.fwd_chunk = tgt_fwd ? target_chunk(q.Rp, nrb, q.NGY, tgt_fwd, grain, cap)
-                          : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, grain, longest, cap);
+                          : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, f32 || q.GW == 1 ? 1.5 : 0.3, grain,
+                                          f32 ? longest : kSplitFwdChunkMax, cap);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
   }
@@ -441,7 +445,7 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
     const int32_t cap = f32 ? kF32ChunkMax : kSplitAdjChunkMax;
     const int slots = f32 ? 5 - q.GW : q.sh ? 3 : 2;
     q.adj_chunk = tgt_adj ? target_chunk(q.Tp, nrb, q.NGY, tgt_adj, grain, cap)
-                          : default_chunk(q.Tp, nrb, q.NGY, q.comb ? q.NGY : q.NCP, slots, step, grain,
+                          : default_chunk(q.Tp, nrb, q.NGY, q.comb ? q.NGY : q.NCP, slots, step, 1.5, grain,
                                           std::min(longest, cap), cap);
     q.adj_split = (int32_t)ceil_div(q.Tp, q.adj_chunk);
   }

@@ -332,7 +332,7 @@ constexpr int32_t kF32ChunkMax = 2048;
 
 int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p, int32_t nprob = 1);
 // Indexes per workgroup of a split reduction (see the definition).
-int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, int grain,
+int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, int grain,
                       int32_t longest, int32_t cap);
 
 // Device buffers of one operator application, carved from the workspace.

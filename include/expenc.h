@@ -453,8 +453,8 @@ int expenc_coil_compress(int32_t ncoils, int32_t nvirtual, int64_t nsamples, con
  * split their reduction (pixels for A, samples for A^H) so that one launch
  * has about `target` workgroups (the EXPENC_TARGET_WG environment variable;
  * without it, the split that a model of the launch finds shortest, of at
- * most 4608 workgroups and without sums longer than 2048 workgroups' or 512
- * (FP32), 1024 (split adjoint) and 3072 (split forward) indexes, whichever is
+ * most 4608 workgroups and without sums longer than 2048 workgroups' or 64
+ * (FP32), 1024 (split forms) and 3072 (bf16 forward) indexes, whichever is
  * longer).
  * expenc_set_tuning sets the forward and adjoint
  * targets for every later plan of op's geometry (nx, ny, ncoils, nbasis,

@@ -245,7 +245,7 @@ static int phase_terms(int L) {
 }
 
 constexpr int kTargetWorkgroups = 2048;
-constexpr int32_t kSplitFwdChunkMax = 3072;
+constexpr int32_t kBf16FwdChunkMax = 3072;
 constexpr int kMaxWorkgroups = 4608;  // of the default split (scratch grows with the splits)
 
 // EXPENC_TARGET_WG, or 0.
@@ -410,12 +410,14 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   q.P = nprob;
   q.scaled = precision == EXPENC_FP16_SPLIT;
   q.adj_anc = q.sh && precision != EXPENC_FP32;
-  // Partial sums of the default splits: no longer than 512 indexes in the
-  // FP32 form (its chunk sums are its rounding error), 1024 in the split
-  // adjoints and kSplitFwdChunkMax in the split forwards (below), unless
-  // kTargetWorkgroups makes them longer.
+  // Partial sums of the default splits, unless kTargetWorkgroups makes them
+  // longer: at most 64 indexes in the FP32 form, whose error they set (64 x 64
+  // to 128 x 128: 1.1 to 2.2 times smaller than with 512, at the same times),
+  // 1024 in the split forms (below), kBf16FwdChunkMax in the bf16 forward
+  // (3.8e-6 whatever the chunk; the fp16 forward's 6.6e-7 at 1024 becomes
+  // 7.5e-7 at 1480, 148 x 148).
   const bool f32 = precision == EXPENC_FP32;
-  const int32_t longest = f32 ? 512 : kSplitAdjChunkMax;
+  const int32_t longest = f32 ? 64 : kSplitAdjChunkMax;
   const double step = (f32 ? 1.0 : q.sh ? 0.5 : 0.6) * (q.GW == 2 ? 1.0 : 0.6);
   // forward: 256 sample rows per workgroup, split over pixels
   {
@@ -425,7 +427,7 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
     const int grain = fwd_grain(q);
     q.fwd_chunk = tgt_fwd ? target_chunk(q.Rp, nrb, q.NGY, tgt_fwd, grain, cap)
                           : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, f32 || q.GW == 1 ? 1.5 : 0.3, grain,
-                                          f32 ? longest : kSplitFwdChunkMax, cap);
+                                          precision == EXPENC_BF16_SPLIT ? kBf16FwdChunkMax : longest, cap);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
   }

@@ -117,8 +117,8 @@ def test_tuning_targets_shape_the_split():
                                             (64, 8, 4000, 9, 1), (148, 32, 16384, 16, 1), (100, 16, 3000, 16, 4),
                                             (512, 8, 100, 4, 1), (12, 64, 200000, 9, 16)])
 def test_default_split_bounds(n, c, t, nb, batch, prec, nprob):
-    """The default split leaves no workgroup longer sums than 512 (FP32), 1024
-    (split adjoint) or 3072 (split forward) indexes, or those of a split into
+    """The default split leaves no workgroup longer sums than 64 (FP32), 1024
+    (split forms) or 3072 (bf16 forward) indexes, or those of a split into
     2048 workgroups, and makes at most 4608 workgroups where the capped chunks
     (2048 FP32, 1024 split adjoint) allow so few."""
     b, lib = _lib()
@@ -126,8 +126,8 @@ def test_default_split_bounds(n, c, t, nb, batch, prec, nprob):
     fs, as_, fw, aw, _, _ = _info(b, lib, op, batch, prec, nprob)
     fp32 = prec == 0
     rp, tp = -(-(-(-n // 16) * 16 * n) // 256) * 256, -(-t // 256) * 256
-    for split, wgs, k, cap, length in ((fs, fw, rp, 2048 if fp32 else 1 << 30, 512 if fp32 else 3072),
-                                       (as_, aw, tp, 2048 if fp32 else 1024, 512 if fp32 else 1024)):
+    for split, wgs, k, cap, length in ((fs, fw, rp, 2048 if fp32 else 1 << 30, 64 if fp32 else 3072 if prec == 1 else 1024),
+                                       (as_, aw, tp, 2048 if fp32 else 1024, 64 if fp32 else 1024)):
         one = wgs // split                          # workgroups of one split
         assert wgs == one * split and 1 <= split <= k // 16
         most = max(1, min(-(-2048 // one), k // 16))

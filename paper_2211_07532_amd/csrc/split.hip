@@ -10,12 +10,13 @@
 //
 // Layout of one MFMA step (K = 16 reduction indices): lane l holds 8
 // consecutive reduction indices 8*(l/32) .. 8*(l/32)+7 of row l%32 for the A
-// operand and of column l%32 for the B operand.  As in the FP32 kernels, each
-// lane first evaluates the phase tile for ITS OWN row against all 16
+// operand and of column l%32 for the B operand.  In the polynomial forward, as
+// in the FP32 kernels, each lane first evaluates the phases of ITS OWN row at all 16
 // reduction indices (which are wave-uniform, so their field/basis values
 // come through scalar loads), splits and packs pairs into 32-bit words, and
 // v_permlane32_swap exchanges the half-waves so that the two 32-row MFMA
-// blocks receive their operands.  The B operand is pre-split and packed in
+// blocks receive their operands (the other kernels take their phases from a
+// matrix product in that layout).  The B operand is pre-split and packed in
 // exactly the per-lane order (four 16-byte records per lane and step: b1 hi,
 // b1 lo, b2 hi, b2 lo), so the inner loop loads it with dwordx4 loads.
 #include "internal.h"
@@ -23,41 +24,9 @@
 
 namespace expenc {
 
-__device__ inline uint32_t swap_lo(uint32_t a, uint32_t b, uint32_t &hi_out) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  hi_out = r[1];
-  return r[0];
-}
-
-// Split the 16 (cos, sin) values of one lane into hi/lo 16-bit pairs, pack
-// them into 32-bit words and exchange half-waves so that
-//   A[blk][kind] (blk 0: rows 0..31, 1: rows 32..63; kind 0 c_hi, 1 c_lo, 2 s_hi, 3 s_lo)
-// are the A operands of this step.
-template <bool BF>
-__device__ inline void pack_tile16(const float (&c)[16], const float (&sn)[16], u32x4 (&A)[2][4]) {
-  uint32_t w[4][2][4];  // [kind][half of the 16 indices][word]
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    const int hf = m >> 2, wd = m & 3;
-    split_pair<BF>(c[2 * m], c[2 * m + 1], w[0][hf][wd], w[1][hf][wd]);
-    split_pair<BF>(sn[2 * m], sn[2 * m + 1], w[2][hf][wd], w[3][hf][wd]);
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    uint32_t hi0, hi1, hi2, hi3;
-    const uint32_t lo0 = swap_lo(w[k][0][0], w[k][1][0], hi0);
-    const uint32_t lo1 = swap_lo(w[k][0][1], w[k][1][1], hi1);
-    const uint32_t lo2 = swap_lo(w[k][0][2], w[k][1][2], hi2);
-    const uint32_t lo3 = swap_lo(w[k][0][3], w[k][1][3], hi3);
-    A[0][k] = u32x4{lo0, lo1, lo2, lo3};
-    A[1][k] = u32x4{hi0, hi1, hi2, hi3};
-  }
-}
-
 // Slot of this wave in the per-problem maxima array of a forward launch
 // (workgroup bx, by of a grid gx wide).
 __device__ inline int wave_slot(int bx, int by, int gx) { return (by * gx + bx) * 4 + (threadIdx.x >> 6); }
-__device__ inline int wave_slot() { return wave_slot(blockIdx.x, blockIdx.y, gridDim.x); }
 
 // ---------------------------------------------------------------------------
 // Split forms with the solid-harmonic basis in polynomial form.  With z

@@ -124,6 +124,53 @@ __device__ inline void zero_acc(f32x16 (&acc)[2][GW]) {
       for (int v = 0; v < 16; ++v) acc[b][g][v] = 0.f;
 }
 
+// Software pipeline of the solid-harmonic forward: the products of one step
+// are issued between the vector work of the next step's phases.  A group's
+// records follow in halves (cos, sin) as soon as the half before is used up.
+// 148 x 148, 32 coils, T = 16384: 677 -> 640 us, 200 x 200, T = 20000: 1348 ->
+// 1263 (one column group: equal).  The adjoint, which waits for its LDS reads
+// as well, took 705 for 683 us with the same pipeline.
+template <int GW>
+struct Pipe {
+  static constexpr int N = 24 * GW;  // MFMAs of a step
+  u32x4 A[2][6], b[6];
+  uint32_t w[6][8];  // the next step's words, as for contract16
+
+  __device__ inline void load(int h, const u32x4 *__restrict__ rec) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) b[3 * h + q] = rec[64 * (3 * h + q)];
+  }
+  // the words of a pair of indices (phases in turns, reduced)
+  __device__ inline void pair(int m, float f0, float f1, Bf16Masks mk) {
+    split3(__builtin_amdgcn_cosf(f0), __builtin_amdgcn_cosf(f1), mk, w[0][m], w[1][m], w[2][m]);
+    split3(__builtin_amdgcn_sinf(f0), __builtin_amdgcn_sinf(f1), mk, w[3][m], w[4][m], w[5][m]);
+  }
+  __device__ inline void exchange() {
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(w[q][i], w[q][4 + i], false, false);
+        A[0][q][i] = r[0];
+        A[1][q][i] = r[1];
+      }
+  }
+  // MFMAs [lo, hi) of the step: groups in turn, cos then sin, step12's order
+  // for each row block, the blocks alternating; cur, next: this lane's records
+  // of the step and of the one after
+  __device__ inline void products(int lo, int hi, const u32x4 *__restrict__ cur, const u32x4 *__restrict__ next,
+                                  f32x16 (&acc)[2][GW]) {
+    constexpr int pa[6] = {1, 2, 0, 1, 0, 0}, pb[6] = {1, 0, 2, 0, 1, 0};
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (k >= lo && k < hi) {
+        const int g = k / 24, h = k % 24 / 12, q = k % 12 >> 1, blk = k & 1;
+        acc[blk][g] = mfma16<true>(A[blk][3 * h + pa[q]], b[3 * h + pb[q]], acc[blk][g]);
+        if (k % 12 == 11) load(h, g + 1 < GW ? cur + (g + 1) * kRec3 : next);
+      }
+  }
+};
+
 // One workgroup: 256 rows (64 per wave) x 16 GW columns x a chunk of the
 // reduction.  FWD: rows are samples, the reduction runs over pixels; else
 // rows are pixels and it runs over samples.  NT: terms of the general basis
@@ -180,24 +227,48 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
     fill(k0, 0);
     __syncthreads();
   }
-  RowCubic rc;
-  if constexpr (NT == 0) rc.start((int)k0, a.nxq);
-  for (int64_t k = k0; k < k1; k += 16) {
-    uint32_t w[6][8];  // [c hi, mid, lo, s hi, mid, lo][pair of the 16 indices]
-    if constexpr (NT == 0) {
-      const int r = (int)k;
+  if constexpr (NT == 0) {
+    Pipe<GW> pp;
+    RowCubic rc;
+    rc.start((int)k0, a.nxq);
+    float f[16];
+    const int64_t step = (int64_t)NGP * kRec3;
+    const u32x4 *__restrict__ cur = op + (k0 >> 4) * step;
+    auto phase = [&](int r, int m) {  // pixels 8 + m and 8 - m (m = 0: 8 and 0)
+      double lo, hi;
+      rc.two(m, lo, hi);
+      f[(8 - m) & 7] = reduce_turns(fma(P[10], uni[r + ((8 - m) & 7)], lo));
+      f[8 + m] = reduce_turns(fma(P[10], uni[r + 8 + m], hi));
+    };
+    pp.load(0, cur);
+    pp.load(1, cur);
+    rc.expand(P, a.nx, a.ny, a.dx, a.dy, dx2, dx3);
+    rc.next(a.nxq);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) phase((int)k0, m);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) pp.pair(m, f[2 * m], f[2 * m + 1], a.mk);
+    pp.exchange();
+    for (int64_t k = k0; k + 16 < k1; k += 16, cur += step) {
+      constexpr int N = Pipe<GW>::N;
       rc.expand(P, a.nx, a.ny, a.dx, a.dy, dx2, dx3);
       rc.next(a.nxq);
-      float f[16];
-      rc.each([&](int i, double p) { f[i] = reduce_turns(fma(P[10], uni[r + i], p)); });
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
-        const float c[2] = {__builtin_amdgcn_cosf(f[2 * m]), __builtin_amdgcn_cosf(f[2 * m + 1])};
-        const float s[2] = {__builtin_amdgcn_sinf(f[2 * m]), __builtin_amdgcn_sinf(f[2 * m + 1])};
-        split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
-        split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
+        pp.products(N * m / 16, N * (m + 1) / 16, cur, cur + step, acc);
+        phase((int)k + 16, m);
       }
-    } else {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        pp.products(N * (m + 8) / 16, N * (m + 9) / 16, cur, cur + step, acc);
+        pp.pair(m, f[2 * m], f[2 * m + 1], a.mk);
+      }
+      pp.exchange();
+    }
+    pp.products(0, Pipe<GW>::N, cur, cur, acc);
+  } else {
+    for (int64_t k = k0; k < k1; k += 16) {
+      uint32_t w[6][8];  // [c hi, mid, lo, s hi, mid, lo][pair of the 16 indices]
       const int in = (int)(k - k0) & (kIndices - 1), buf = (int)((k - k0) / kIndices) & 1;
       if constexpr (NL > 0) {
         if (in == 0 && k + kIndices < k1) fill(k + kIndices, buf ^ 1);
@@ -223,10 +294,10 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
         split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
         split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
       }
-    }
-    contract16<GW>(w, op + (k >> 4) * NGP * kRec3, acc);
-    if constexpr (NL > 0) {
-      if (((k - k0) & (kIndices - 1)) == kIndices - 16) __syncthreads();
+      contract16<GW>(w, op + (k >> 4) * NGP * kRec3, acc);
+      if constexpr (NL > 0) {
+        if (((k - k0) & (kIndices - 1)) == kIndices - 16) __syncthreads();
+      }
     }
   }
   // [problem][split][row][column] complex

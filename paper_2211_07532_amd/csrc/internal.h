@@ -245,18 +245,28 @@ struct RowCubic {
       ++yi;
     }
   }
-  // f(i, phase of pixel i without off-resonance) for the 16 pixels; the even
-  // part and the odd factor are shared by k and -k
+  // phases without off-resonance of pixels 8 - m and 8 + m (m = 0: 0 and 8):
+  // the even part and the odd factor are shared
+  __device__ inline void two(int m, double &lo, double &hi) const {
+    if (m == 0) {
+      lo = fma(fma(fma(d3, -8.0, d2), -8.0, d1), -8.0, c0);
+      hi = c0;
+      return;
+    }
+    const double k = m, ev = fma(d2, k * k, c0), od = fma(d3, k * k, d1);
+    lo = fma(od, -k, ev);
+    hi = fma(od, k, ev);
+  }
+  // f(i, phase of pixel i without off-resonance) for the 16 pixels
   template <typename F>
   __device__ inline void each(F f) const {
-    f(8, c0);
 #pragma unroll
-    for (int m = 1; m < 8; ++m) {
-      const double k = m, ev = fma(d2, k * k, c0), od = fma(d3, k * k, d1);
-      f(8 + m, fma(od, k, ev));
-      f(8 - m, fma(od, -k, ev));
+    for (int m = 0; m < 8; ++m) {
+      double lo, hi;
+      two(m, lo, hi);
+      f(m ? 8 - m : 0, lo);
+      f(8 + m, hi);
     }
-    f(0, fma(fma(fma(d3, -8.0, d2), -8.0, d1), -8.0, c0));
   }
 };
 

@@ -262,7 +262,7 @@ static int env_target() {
 static int32_t target_chunk(int64_t K, int64_t nrb, int ngy, int target, int grain, int32_t cap) {
   int64_t want = ceil_div(target, nrb * ngy);
   want = std::max<int64_t>(1, std::min<int64_t>(want, K / 16));
-  return std::min((int32_t)round_up(ceil_div(K, want), grain), cap);
+  return (int32_t)std::min<int64_t>(round_up(ceil_div(K, want), grain), cap);
 }
 
 // Chunk without a tuned target: of the chunks up to `longest` (or that of
@@ -283,22 +283,22 @@ static int32_t target_chunk(int64_t K, int64_t nrb, int ngy, int target, int gra
 int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, int grain,
                       int32_t longest, int32_t cap) {
   const int32_t at_target = target_chunk(K, nrb, ngy, kTargetWorkgroups, grain, cap);
-  const int32_t last = std::max(at_target, std::min(longest, (int32_t)round_up(K, grain)));
+  const int64_t last = std::max<int64_t>(at_target, std::min<int64_t>(longest, round_up(K, grain)));
   const int64_t most = std::max<int64_t>(1, kMaxWorkgroups / (nrb * ngy));
   int32_t best = at_target;
   int64_t prev = -1;
   double cost = 1e300;
-  for (int32_t chunk = std::min<int32_t>(at_target, (int32_t)round_up(ceil_div(K, most), grain)); chunk <= last;
+  for (int64_t chunk = std::min<int64_t>(at_target, round_up(ceil_div(K, most), grain)); chunk <= last;
        chunk += grain) {
     const int64_t split = ceil_div(K, chunk);
     if (split == prev) continue;  // (the shortest chunk of a split is its most even)
     prev = split;
     const int64_t n = ceil_div(nrb * ngy * split, 256), r = n % slots;
     const double load = (double)(n - r) + (r == 1 ? 1 / 0.85 : r == 2 ? 2 / 0.9 : (double)r) + tail;
-    const double t = load * (chunk / 16 + 8) * step + (double)split * nrb * width * (256 * 8 / 8e6);
+    const double t = load * (double)(chunk / 16 + 8) * step + (double)split * nrb * width * (256 * 8 / 8e6);
     if (t < cost) {
       cost = t;
-      best = chunk;
+      best = (int32_t)chunk;
     }
   }
   return best;

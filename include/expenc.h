@@ -57,14 +57,16 @@ enum {
   EXPENC_EDIVERGED = -6      /* a solve's objective diverged (expenc_solve_status) */
 };
 
-/* Arithmetic form of the encoding contraction.  The fp16 form multiplies
- * each operand it packs by a power of two chosen on the device from a bound
- * on the operand's magnitudes (one extra pre-pass launch for an image
- * operand or boundary data), and its reductions divide it out, so inputs of
+/* Arithmetic form of the encoding contraction.  The fp16 and FP32 forms
+ * multiply each operand they pack by a power of two chosen on the device from a
+ * bound on the operand's magnitudes (one extra pre-pass launch for an image
+ * operand or boundary data), and their reductions divide it out, so inputs of
  * any magnitude within the FP32 range keep the form's accuracy; the fp16
- * halves alone cover only ~2^-3 .. 65504 at full pair precision. */
+ * halves alone cover only ~2^-3 .. 65504 at full pair precision, the FP32
+ * form's three bf16 parts 2^-110 .. 2^128. */
 enum {
-  EXPENC_FP32 = 0,        /* FP32 phase tile x FP32 operand on FP32 MFMA              */
+  EXPENC_FP32 = 0,        /* FP32 operands and phase tile, three bf16 parts each,
+                             6 MFMA products; operands scaled as above               */
   EXPENC_BF16_SPLIT = 1,  /* both operands split hi+lo in bf16, 3 MFMA products      */
   EXPENC_FP16_SPLIT = 2   /* both operands split hi+lo in fp16, 3 MFMA products,
                              operands scaled by powers of two (above)               */

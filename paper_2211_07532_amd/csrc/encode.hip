@@ -408,7 +408,7 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   q.prec = precision;
   q.has_dw0 = op->dw0 != nullptr;
   q.P = nprob;
-  q.scaled = precision == EXPENC_FP16_SPLIT;
+  q.scaled = precision != EXPENC_BF16_SPLIT;
   q.adj_anc = q.sh && precision != EXPENC_FP32;
   // Partial sums of the default splits, unless kTargetWorkgroups makes them
   // longer: at most 64 indexes in the FP32 form, whose error they set (64 x 64
@@ -491,8 +491,16 @@ size_t enc_part_elems(const EncPlan &p) {
   return std::max(pf, pa) * p.P;
 }
 
-int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part) {
+int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, std::initializer_list<const EncPlan *> with) {
   const size_t P = p.P;
+  size_t part = enc_part_elems(p);
+  int32_t nwmax = p.nwmax;
+  bool scaled = p.scaled;
+  for (const EncPlan *q : with) {
+    part = std::max(part, enc_part_elems(*q));
+    nwmax = std::max(nwmax, q->nwmax);
+    scaled = scaled || q->scaled;
+  }
   b->kap = a.take<double>(P * p.Tp * p.NT);
   b->bet = a.take<double>(P * p.Rp * p.NT);
   // operand records: 384 bytes per step row and 16 columns (FP32 form, three
@@ -503,7 +511,7 @@ int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part) {
   b->zs = a.take<char>(P * p.Rp * NG * 384);
   b->ys = a.take<char>(P * p.Tp * NG * 384);
   b->yop = a.take<float2>(P * p.Tp * NG * 16);
-  b->part = a.take<float2>(std::max(enc_part_elems(p), min_part));
+  b->part = a.take<float2>(part);
   if (p.sh) {
     // polynomial phase tables (every precision; dpa: the split adjoint's
     // increment operand)
@@ -515,15 +523,15 @@ int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part) {
   }
   if (p.prec != EXPENC_FP32) {
     if (p.comb) b->sq = a.take<float2>(P * p.Rp * p.NCP);
-    if (p.scaled) {
-      b->scl = a.take<float>(P * 2);
-      b->amax = a.take<float>(P * 3 * kAmaxBlocks);
-      b->wmax = a.take<float>(P * p.nwmax);
-    }
     if (!p.sh) {
       b->dbet = a.take<float>(P * p.Rp * round_up(p.NT, 2));
       b->dkap = a.take<float>(P * p.Tp * round_up(p.NT, 2));
     }
+  }
+  if (scaled) {
+    b->scl = a.take<float>(P * 2);
+    b->amax = a.take<float>(P * 3 * kAmaxBlocks);
+    b->wmax = a.take<float>(P * nwmax);
   }
   return a.ok() ? EXPENC_OK : EXPENC_EWORKSPACE;
 }
@@ -538,7 +546,7 @@ int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x
   if (p.prec != EXPENC_FP32)
     return split_build_z(p, smaps, x, xsub, x_stride, x_row_stride, b, s, x_pstride, prepared);
   if (xsub) return fail(EXPENC_EUNSUPPORTED, "operand difference is only built for split forms");
-  return f32_build_z(p, smaps, x, x_stride, x_row_stride, b, s, x_pstride);
+  return f32_build_z(p, smaps, x, x_stride, x_row_stride, b, s, x_pstride, prepared);
 }
 
 int enc_pack_y(const EncPlan &p, const float2 *y, const EncBuffers &b, hipStream_t s, float sign, bool prepared) {
@@ -547,7 +555,7 @@ int enc_pack_y(const EncPlan &p, const float2 *y, const EncBuffers &b, hipStream
     if (sign != 1.f) return fail(EXPENC_EUNSUPPORTED, "scaled operand packing is FP32 only");
     return split_pack_y(p, y, false, nullptr, b, s, prepared);
   }
-  return f32_pack_y(p, y, sign, nullptr, b, s);
+  return f32_pack_y(p, y, sign, nullptr, b, s, prepared);
 }
 
 // ---------------------------------------------------------------------------
@@ -671,7 +679,7 @@ int enc_forward_reduce_out(const EncPlan &p, const EncBuffers &b, float2 *y, hip
 
 int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_meas, hipStream_t s) {
   if (p.prec != EXPENC_FP32) return split_pack_y(p, nullptr, true, y_meas, b, s);
-  return f32_pack_y(p, nullptr, 1.f, y_meas, b, s);
+  return f32_pack_y(p, nullptr, 1.f, y_meas, b, s, false);
 }
 
 int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *smaps, float2 *x,

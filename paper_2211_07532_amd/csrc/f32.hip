@@ -2,7 +2,8 @@
 //
 // Every FP32 operand value is written as hi + mid + lo with hi = rnd(v),
 // mid = rnd(v - hi) and lo = v - hi - mid in bf16: three 8-bit significands
-// hold the 24 bits of v exactly.  A product a*b is taken as
+// hold the 24 bits of v exactly, where lo's last bit is a bf16 value (from
+// 2^-110; operands are packed times a power of two, split_dev.h).  A product a*b is taken as
 //   a_hi b_hi + a_hi b_mid + a_mid b_hi + a_hi b_lo + a_lo b_hi + a_mid b_mid
 // on v_mfma_f32_32x32x16_bf16 with FP32 accumulation; the three products left
 // out are below 2^-25 of it, under the rounding of one FP32 addition.  Phases
@@ -89,6 +90,7 @@ struct F32Args {
   int Rp, NCP, chunk, nsplit, nxq, nx, ny;
   double dx, dy;
   Bf16Masks mk;
+  float *wmax;  // forward: per-wave maxima of the partial sums
 };
 
 // Exchanges the packed words of the lane's own row (w[kind][pair], pairs of
@@ -201,11 +203,16 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
   const int wave = threadIdx.x >> 6;
   const int64_t rows = FWD ? a.Tp : a.Rp, len = FWD ? a.Rp : a.Tp;
   int split, rb;
-  if (!split_tile(blockIdx.x, (int)(rows / 256), a.nsplit, &split, &rb)) return;
+  const int pz = blockIdx.z;  // problem
+  float *const wmax = FWD ? a.wmax + ((int64_t)(pz * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 4 + wave
+                          : nullptr;
+  if (!split_tile(blockIdx.x, (int)(rows / 256), a.nsplit, &split, &rb)) {
+    if (FWD && lane == 0) *wmax = 0.f;
+    return;
+  }
   const int64_t row0 = (int64_t)rb * 256 + wave * 64;
   const int g0 = blockIdx.y * GW;
   const int NGP = a.NCP / 16;
-  const int pz = blockIdx.z;  // problem
   constexpr int NP = NT ? NT : 11;
   constexpr int S = NT ? NT : kPolyStride;  // row strides of the tables
   own += pz * (NT ? rows : a.Tp) * S;
@@ -301,8 +308,7 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
     }
   }
   // [problem][split][row][column] complex
-  adj_epilogue<GW>(part, nullptr, (int)rows, a.NCP, a.nsplit, split, pz, blockIdx.y, gridDim.y, row0, g0, lane,
-                   acc);
+  store_partials<GW>(part + ((int64_t)pz * a.nsplit + split) * rows * a.NCP * 2, row0, a.NCP, g0, lane, acc, wmax, 0);
 }
 
 template <int NT, int GW>
@@ -409,11 +415,13 @@ __global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict_
 __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ smaps, const float2 *__restrict__ x,
                                                      int64_t x_stride, int x_row_stride, int nx, int ny, int nxq,
                                                      int Rp, int C, int NC, int NGP, u32x4 *__restrict__ zs,
-                                                     int64_t x_pstride) {
+                                                     int64_t x_pstride, const float *__restrict__ amax,
+                                                     float *__restrict__ scl) {
   const int R = nx * ny;
   const int64_t pz = blockIdx.y;
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= (int64_t)(Rp / 16) * NGP * 64) return;
+  int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const bool live = id < (int64_t)(Rp / 16) * NGP * 64;
+  if (!live) id = 0;
   const int lane = (int)(id & 63);
   const int64_t qg = id >> 6;
   const int g = (int)(qg % NGP);
@@ -437,10 +445,15 @@ __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ 
       ++yy;
     }
   }
+  // (every workgroup derives the same power of two, behind its loads)
+  const float sc = image_scale(amax, (int)pz, gridDim.y);
+  if (blockIdx.x == 0 && threadIdx.x == 0) scl[2 * pz] = sc;
+  if (!live) return;
   float b1[8], b2[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const float2 z = ok[i] ? make_float2(s[i].x * u[i].x - s[i].y * u[i].y, s[i].x * u[i].y + s[i].y * u[i].x)
+    const float2 z = ok[i] ? make_float2((s[i].x * u[i].x - s[i].y * u[i].y) * sc,
+                                         (s[i].x * u[i].y + s[i].y * u[i].x) * sc)
                            : make_float2(0.f, 0.f);
     b1[i] = im ? z.y : z.x;
     b2[i] = im ? z.x : -z.y;
@@ -456,11 +469,14 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
                                                     const float2 *__restrict__ part, int nsplit,
                                                     const float2 *__restrict__ y_meas, int64_t T, int64_t Tp, int C,
                                                     int NC, int NCP, u32x4 *__restrict__ ys,
-                                                    float2 *__restrict__ yop) {
+                                                    float2 *__restrict__ yop, const float *__restrict__ bnd, int nbnd,
+                                                    const float *__restrict__ bnd_meas, float *__restrict__ scl) {
   const int NGP = NCP / 16;
   const int64_t pz = blockIdx.y;
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= (Tp / 16) * NGP * 64) return;
+  const float inv_z = src ? 1.f : 1.f / scl[2 * pz];
+  int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const bool live = id < (Tp / 16) * NGP * 64;
+  if (!live) id = 0;
   const int lane = (int)(id & 63);
   const int64_t qg = id >> 6;
   const int col = 16 * (int)(qg % NGP) + (lane & 15), im = (lane >> 4) & 1;
@@ -494,6 +510,8 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (t0 + i < T) {
+        sx[i] *= inv_z;
+        sy[i] *= inv_z;
         if (y_meas) {
           const float2 m = y_meas[((pz * NC / C + b) * T + t0 + i) * C + c];
           sx[i] -= m.x;
@@ -501,8 +519,11 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
         }
         y[i] = make_float2((float)sx[i], (float)sy[i]);
       }
-    // (padded samples hold the field-free sums of their rows: zero them)
+    // (padded samples stay zero)
   }
+  const float sc = data_scale(bnd, nbnd, src ? 0 : nsplit, inv_z, bnd_meas, (int)pz);
+  if (blockIdx.x == 0 && threadIdx.x == 0) scl[2 * pz + 1] = sc;
+  if (!live) return;
   if (yop && !im) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) yop[(pz * Tp + t0 + i) * NCP + col] = y[i];
@@ -510,8 +531,8 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
   float b1[8], b2[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    b1[i] = im ? y[i].y : y[i].x;
-    b2[i] = im ? -y[i].x : y[i].y;
+    b1[i] = (im ? y[i].y : y[i].x) * sc;
+    b2[i] = (im ? -y[i].x : y[i].y) * sc;
   }
   write_rec3(ys + (pz * (Tp / 16) * NGP + qg) * kRec3 + lane, b1, b2);
 }
@@ -527,7 +548,7 @@ static void launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   const u32x4 *op = reinterpret_cast<const u32x4 *>(FWD ? b.zs : b.ys);
   float *part = reinterpret_cast<float *>(b.part);
   const F32Args a{p.Tp, p.Rp, p.NCP, FWD ? p.fwd_chunk : p.adj_chunk, nsplit, p.nxq, p.nx, p.ny, p.dx, p.dy,
-                  bf16_masks()};
+                  bf16_masks(), b.wmax};
   const dim3 grid(split_grid((FWD ? p.Tp : p.Rp) / 256 * nsplit), (unsigned)p.NGY, (unsigned)p.P);
   auto go = [&](auto gw) {
     constexpr int GW = decltype(gw)::value;
@@ -565,18 +586,22 @@ static dim3 record_grid(int64_t len, const EncPlan &p) {
 }
 
 int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
-                const EncBuffers &b, hipStream_t s, int64_t x_pstride) {
+                const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared) {
+  if (!prepared) EX_TRY(bound_image(p, x, nullptr, x_stride, x_row_stride, x_pstride, b, s));
   k_build_z_f32<<<record_grid(p.Rp, p), 256, 0, s>>>(reinterpret_cast<const float2 *>(smaps), x, x_stride,
                                                      x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C, p.NC, p.NCP / 16,
-                                                     reinterpret_cast<u32x4 *>(b.zs), x_pstride);
+                                                     reinterpret_cast<u32x4 *>(b.zs), x_pstride, b.amax, b.scl);
   EX_LAUNCHED("build_z");
   return EXPENC_OK;
 }
 
 int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_meas, const EncBuffers &b,
-               hipStream_t s) {
+               hipStream_t s, bool prepared) {
+  DataBound d;
+  EX_TRY(bound_data(p, y, y_meas, b, prepared, &d, s));
   k_pack_y_f32<<<record_grid(p.Tp, p), 256, 0, s>>>(y, sign, b.part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC,
-                                                    p.NCP, reinterpret_cast<u32x4 *>(b.ys), y ? nullptr : b.yop);
+                                                    p.NCP, reinterpret_cast<u32x4 *>(b.ys), y ? nullptr : b.yop,
+                                                    d.bnd, d.nbnd, d.meas, b.scl);
   EX_LAUNCHED("pack_y");
   return EXPENC_OK;
 }

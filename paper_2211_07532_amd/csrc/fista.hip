@@ -336,9 +336,8 @@ static int layout_fista(const expenc_op *op, int32_t nprob, int32_t batch, int32
   EX_TRY(resolve_pad(op->ny, ny_pad, levels, &L->nyp));
   L->P = nprob;
   L->B = batch;
-  // p's buffers hold the FP32 operands of pf as well; the partial-sum buffer
-  // is shared by all three plans (identical padded geometry)
-  carve_enc(L->p, a, &L->eb, std::max(enc_part_elems(L->p1), enc_part_elems(L->pf)));
+  // the buffers are shared by all three plans (identical padded geometry)
+  carve_enc(L->p, a, &L->eb, {&L->p1, &L->pf});
   const size_t img = (size_t)nprob * batch * L->nxp * L->nyp;
   L->z = a.take<float2>(img);
   L->v = a.take<float2>(img);

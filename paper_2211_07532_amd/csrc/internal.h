@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <functional>
+#include <initializer_list>
 
 #include <cstddef>
 #include <cstdint>
@@ -323,18 +324,24 @@ struct EncPlan {
   // every kernel takes the problem index as an extra grid dimension.
   int32_t P = 1;
   const double *z0s = nullptr;            // [P] slice positions (SH basis), or NULL: z0 for all
-  // fp16 split form: every packed operand is multiplied by a power of two
-  // chosen on the device from a bound on its magnitudes (the fp16 halves
-  // overflow above 65504 and lose the lo half's precision below ~2^-3), and
-  // the reductions divide it out.  nwmax: per-problem slots of the forward
-  // contraction's per-wave output maxima (the residual operand's bound).
+  // fp16 split and FP32 forms: every packed operand is multiplied by a power of
+  // two chosen on the device from a bound on its magnitudes (the fp16 halves
+  // overflow above 65504 and lose the lo half's precision below ~2^-3, the
+  // FP32 form's three bf16 parts lose bits below 2^-110), and the reductions
+  // divide it out.  nwmax: per-problem slots of the forward contraction's
+  // per-wave output maxima (the residual operand's bound).
   bool scaled = false;
   int32_t nwmax = 0;
 };
 
 constexpr int kPolyStride = 12;  // row stride of the polynomial coefficient table (11 used)
-// Workgroups (per problem) of the magnitude pre-pass of the scaled form.
+// Slots (per problem) of the magnitude pre-pass of the scaled forms ...
 constexpr int kAmaxBlocks = 256;
+// ... of which it launches as many as give a thread four of n elements (a
+// workgroup fills more than one slot).
+inline unsigned amax_blocks(int64_t n) {
+  return (unsigned)(n > (int64_t)kAmaxBlocks * 1024 ? kAmaxBlocks : n > 1024 ? ceil_div(n, 1024) : 1);
+}
 // Longest reduction chunk of one workgroup: samples in the split adjoint
 // contractions; pixels or samples in the FP32 contractions.
 constexpr int32_t kSplitAdjChunkMax = 1024;
@@ -401,17 +408,17 @@ inline bool anchor_in_fp32(int32_t anchor, int k, int K) {
 int set_tuning(const expenc_op *op, int32_t batch, int32_t precision, int32_t fwd_target, int32_t adj_target,
                int32_t col_groups);
 uint64_t tuning_generation();
-// Carves the buffers of plan p; the partial-sum buffer gets at least
-// min_part float2 elements (so a second plan can share it).
-int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, size_t min_part = 0);
+// Carves the buffers of plan p, large enough for the plans in `with` too (the
+// other plans of a solver: same geometry, other precision or batch).
+int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, std::initializer_list<const EncPlan *> with = {});
 
 // Kernel launchers (stream-ordered, no synchronisation).
 // Field tables of plan p (prep.hip), one launch: those that the directions in
 // `need` read.  A split plan's tables include the FP32 plan's of the same
 // geometry.  operand: the image [P][B][R] (need = kNeedForward) or data
 // [P][B][T][C] (kNeedAdjoint) that the call applies the operator to; its
-// records (FP32, bf16) or its magnitude bound (fp16, whose records need it) are
-// then written by the same launch, and enc_build_z / enc_pack_y are told so
+// records (bf16) or its magnitude bound (scaled forms, whose records need it)
+// are then written by the same launch, and enc_build_z / enc_pack_y are told so
 // (prepared = true).
 enum { kNeedForward = 1, kNeedAdjoint = 2, kNeedBoth = 3 };
 int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s, int need,
@@ -453,9 +460,20 @@ int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_
 void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
-                const EncBuffers &b, hipStream_t s, int64_t x_pstride);
+                const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared);
 int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_meas, const EncBuffers &b,
-               hipStream_t s);
+               hipStream_t s, bool prepared);
+// Magnitude bounds of the scaled forms' operands (split.hip): pre-passes of an
+// image x - xsub, and of data y or (y NULL) the forward's partial sums minus
+// y_meas (prepared: enc_prepare has bounded y).
+struct DataBound {
+  const float *bnd = nullptr, *meas = nullptr;  // [P][nbnd] of the data or sums; [P][kAmaxBlocks] of y_meas
+  int nbnd = 0;
+};
+int bound_image(const EncPlan &p, const float2 *x, const float2 *xsub, int64_t x_stride, int32_t x_row_stride,
+                int64_t x_pstride, const EncBuffers &b, hipStream_t s);
+int bound_data(const EncPlan &p, const float2 *y, const float2 *y_meas, const EncBuffers &b, bool prepared,
+               DataBound *d, hipStream_t s);
 // Split-precision kernels (split.hip).
 void split_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);

@@ -1,6 +1,6 @@
 // Field setup of the encoding operators: the phase tables of both basis
 // kinds, the coil table of the split adjoint's epilogue, and of a single
-// application's operand the records (FP32, bf16) or the magnitude bounds (fp16),
+// application's operand the records (bf16) or the magnitude bounds (FP32, fp16),
 // all in ONE launch whose workgroups take one role each (a range of block
 // indices per table).  No table reads another: where
 // one is built from a second (increments and anchors from the polynomial
@@ -13,8 +13,11 @@
 // anchors, one entry per thread with two index divisions and its own
 // coefficient loads; 22 the polynomial coefficients, whose per-thread arrays
 // were indexed at run time; 12 a bound of the coil maps only a forward reads).
-// The operand records here instead of in a launch of their own: 32 x 32, 8
-// coils, FP32 24.7 -> 22.7 us a forward, 33 x 20, 17 coils, bf16 24.5 -> 21.2.
+// The bf16 records here instead of in a launch of their own: 33 x 20, 17 coils
+// 24.5 -> 21.2 us.  The scaled forms' records need the bound first: a launch of
+// their own (32 x 32, 8 coils, FP32 forward 25.6 us; records here, every
+// workgroup bounding the whole operand itself, 26.8; unscaled records here,
+// which lose the operands' last bits below 2^-110, 21.7).
 #include "internal.h"
 #include "split_dev.h"
 
@@ -35,7 +38,7 @@ struct PrepArgs {
   int64_t T, Tp, nop;  // nop: operand elements per problem
   int R, Rp, L, NT, nx, ny, nxq, C, NC, NCP, op_l1;
   u32x4 *rec;
-  int rec_image, rec_perm, rec_parts;  // records of an image; index order; 3 (FP32) or 2 (bf16) parts
+  int rec_image, rec_perm;  // records of an image; index order
   double dx, dy, z0;
   unsigned end[kRoles];  // block index one past each role's range
 };
@@ -162,8 +165,7 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
       b2[e] = im ? z.x : z.y;
       if (im != a.rec_image) b2[e] = -b2[e];
     }
-    if (a.rec_parts == 3) write_rec3(a.rec + (pz * (K / 16) * NGP + qg) * kRec3 + lane, b1, b2);
-    else write_record<true>(a.rec + pz * K * NGP * 16, qg / NGP, g, NGP, lane, b1, b2);
+    write_record<true>(a.rec + pz * K * NGP * 16, qg / NGP, g, NGP, lane, b1, b2);
     return;
   }
   if (role == kRolePoly) {
@@ -251,7 +253,7 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
     if (a.dbet) put_diff(a.dbet + pz * a.Rp * nte, r, j, a.NT, (float)(v - val((r & ~15) + 8)));
     return;
   }
-  // magnitude bounds of the fp16 form, per workgroup: |Re| + |Im| of the coil
+  // magnitude bounds of the scaled forms, per workgroup: |Re| + |Im| of the coil
   // maps (third section) and of an image operand, the larger component of a
   // data operand (first section)
   const bool maps = role == kRoleMaps;
@@ -259,17 +261,18 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
   const int64_t n = maps ? (int64_t)a.C * a.R : a.nop;
   const bool l1 = maps || a.op_l1;
   float m = 0.f;
-  for (int64_t k = (int64_t)blk * 256 + tid; k < n; k += (int64_t)kAmaxBlocks * 256) {
-    const float2 u = v[k];
-    m = fmaxf(m, l1 ? fabsf(u.x) + fabsf(u.y) : fmaxf(fabsf(u.x), fabsf(u.y)));
+  const int nblk = (int)(a.end[role] - a.end[role - 1]);
+  for (int64_t k = (int64_t)blk * 256 + tid; k < n; k += (int64_t)nblk * 256) {
+    m = fmaxf(m, magnitude(v[k], l1));
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if ((tid & 63) == 0) wm[tid >> 6] = m;
   __syncthreads();
-  if (tid == 0)
-    a.amax[((maps ? 2 * (int64_t)gridDim.y : 0) + pz) * kAmaxBlocks + blk] = fmaxf(fmaxf(wm[0], wm[1]),
-                                                                                   fmaxf(wm[2], wm[3]));
+  const int slot = (int)blk + tid * nblk;
+  if (slot < kAmaxBlocks)
+    a.amax[((maps ? 2 * (int64_t)gridDim.y : 0) + pz) * kAmaxBlocks + slot] = fmaxf(fmaxf(wm[0], wm[1]),
+                                                                                    fmaxf(wm[2], wm[3]));
 }
 
 int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s, int need,
@@ -327,17 +330,20 @@ int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipS
     a.sq = b.sq;
     n[kRoleSq] = ceil_div((int64_t)p.Rp * p.NCP, 256);
   }
-  if (p.scaled) {
-    if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of an fp16 plan are not carved");
+  // (the coil maps' bound: also for a bf16 solver's FP32 plan)
+  if (b.amax && fwd) {
     a.amax = b.amax;
-    if (fwd) n[kRoleMaps] = kAmaxBlocks;
-    if (operand) n[kRoleOperand] = kAmaxBlocks;
+    n[kRoleMaps] = amax_blocks((int64_t)p.C * p.R);
+  }
+  if (p.scaled && operand) {
+    if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of a scaled plan are not carved");
+    a.amax = b.amax;
+    n[kRoleOperand] = amax_blocks(a.nop);
   } else if (operand) {
     a.NC = p.NC;
     a.rec = reinterpret_cast<u32x4 *>(fwd ? b.zs : b.ys);
     a.rec_image = fwd;
-    a.rec_perm = split && (adj || !p.sh);
-    a.rec_parts = split ? 2 : 3;
+    a.rec_perm = adj || !p.sh;
     n[kRoleRecords] = ceil_div((fwd ? p.Rp : p.Tp) * (p.NCP / 4), 256);
   }
   int64_t tot = 0;

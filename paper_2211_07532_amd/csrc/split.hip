@@ -251,57 +251,22 @@ __global__ __launch_bounds__(256) void k_fwd_split_sh_grouped(GroupedLaunch<FwdS
 //   adjoint:  b1 = part ? Yi : Yr,   b2 = part ? -Yr : Yi
 // ---------------------------------------------------------------------------
 
-// ---------------------------------------------------------------------------
-// Operand scaling of the fp16 form.  An fp16 hi/lo pair represents |v| up to
-// 65504 and keeps its ~22-bit precision only while the lo half is normal,
-// i.e. for |v| above ~2^-3.  The fp16 form therefore multiplies each packed
-// operand by a power of two s = 2^(14 - e), where M < 2^e bounds the
-// operand's magnitudes, so that every value lies below 2^14 and values down
-// to 2^-17 of the largest keep full precision; the reductions that read the
-// contraction's output divide s out again (exact for powers of two).
-// M comes from a pre-pass over the operand (image operand, or data given at
-// the boundary) or from the forward contraction's per-wave output maxima
-// (the residual operand, summed over nsplit partial sums).
-// ---------------------------------------------------------------------------
-
-__device__ inline float pow2_scale(float m) {
-  if (!(m > 0.f) || !(m <= 3.0e38f)) return 1.f;  // zero, NaN or infinite: unscaled
-  int e;
-  (void)frexpf(m, &e);
-  return ldexpf(1.f, min(126, max(-126, 14 - e)));
-}
-
-// Max of v[0..n) over a 256-thread workgroup; every thread returns it.
-__device__ inline float block_max(const float *__restrict__ v, int n) {
-  __shared__ float wm[4];
-  float m = 0.f;
-  int i = threadIdx.x;
-  for (; i + 768 < n; i += 1024) {  // four independent loads in flight
-    const float a = v[i], b = v[i + 256], c = v[i + 512], d = v[i + 768];
-    m = fmaxf(m, fmaxf(fmaxf(a, b), fmaxf(c, d)));
-  }
-  for (; i < n; i += 256) m = fmaxf(m, v[i]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  __syncthreads();  // an earlier call's readers are done with wm
-  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
-  __syncthreads();
-  return fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
-}
-
-__device__ inline void write_block_max(float m, float *__restrict__ out) {
+// Max of m over workgroup blk of nblk into its slots blk, blk + nblk, ... of
+// the kAmaxBlocks in out.
+__device__ inline void write_block_max(float m, float *__restrict__ out, int blk, int nblk) {
   __shared__ float wm[4];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) *out = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
+  const int slot = blk + threadIdx.x * nblk;
+  if (slot < kAmaxBlocks) out[slot] = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
 }
 
 // Pre-pass of the image operand: per-workgroup max of |Re u| + |Im u| over
 // the encoded pixels and images, u = x - xsub.  With the same bound of the
 // coil maps (taken once per preparation), their product bounds the
-// components of Z = S u.  Grid (kAmaxBlocks, P), 256 threads.
+// components of Z = S u.  Grid (at most kAmaxBlocks, P), 256 threads.
 __global__ __launch_bounds__(256) void k_amax_z(const float2 *__restrict__ x, const float2 *__restrict__ xsub,
                                                 int64_t x_stride, int x_row_stride, int nx, int ny, int B,
                                                 int64_t x_pstride, float *__restrict__ amax) {
@@ -319,24 +284,23 @@ __global__ __launch_bounds__(256) void k_amax_z(const float2 *__restrict__ x, co
         u.x -= xsub[o].x;
         u.y -= xsub[o].y;
       }
-      m = fmaxf(m, fabsf(u.x) + fabsf(u.y));
+      m = fmaxf(m, magnitude(u, true));
     }
   }
-  write_block_max(m, amax + pz * kAmaxBlocks + blockIdx.x);
+  write_block_max(m, amax + pz * kAmaxBlocks, blockIdx.x, gridDim.x);
 }
 
 // Pre-pass of a complex array [P][n] (stride pstride): per-workgroup max of
-// the component magnitudes.  Grid (kAmaxBlocks, P), 256 threads.
+// the component magnitudes.  Grid (at most kAmaxBlocks, P), 256 threads.
 __global__ __launch_bounds__(256) void k_amax_c(const float2 *__restrict__ v, int64_t n, int64_t pstride,
                                                 float *__restrict__ amax) {
   const int pz = blockIdx.y;
   v += pz * pstride;
   float m = 0.f;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float2 a = v[i];
-    m = fmaxf(m, fmaxf(fabsf(a.x), fabsf(a.y)));
+    m = fmaxf(m, magnitude(v[i], false));
   }
-  write_block_max(m, amax + pz * kAmaxBlocks + blockIdx.x);
+  write_block_max(m, amax + pz * kAmaxBlocks, blockIdx.x, gridDim.x);
 }
 
 // (perm: the index order of the adjoint records below, which the
@@ -352,10 +316,7 @@ __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict_
   // scaled form: every workgroup derives the same power of two from the pre-pass
   float sc = 1.f;
   if (scl) {
-    const int P = gridDim.y;
-    const float mu = block_max(amax + pz * kAmaxBlocks, kAmaxBlocks);
-    const float ms = block_max(amax + (2 * P + pz) * kAmaxBlocks, kAmaxBlocks);
-    sc = pow2_scale(mu * ms);
+    sc = image_scale(amax, pz, gridDim.y);
     if (blockIdx.x == 0 && threadIdx.x == 0) scl[2 * pz] = sc;
   }
   smaps += (int64_t)pz * C * R;
@@ -425,18 +386,10 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
                                                       const float *__restrict__ bnd_meas, float *__restrict__ scl) {
   const int NGP = NCP / 16;
   const int pz = blockIdx.y;  // problem
-  // scaled form: the bound of the operand is max(bnd) (src_abi: its pre-pass;
-  // src_part: the forward's per-wave maxima, in units of the forward operand's
-  // scale, times nsplit) plus max(bnd_meas) (the pre-pass of y_meas, if any)
   float sc = 1.f, inv_z = 1.f;
   if (scl) {
-    float m = block_max(bnd + (int64_t)pz * nbnd, nbnd);
-    if (src_part) {
-      inv_z = 1.f / scl[2 * pz];
-      m = m * (float)nsplit * inv_z;
-    }
-    if (bnd_meas) m += block_max(bnd_meas + pz * kAmaxBlocks, kAmaxBlocks);
-    sc = pow2_scale(m);
+    if (src_part) inv_z = 1.f / scl[2 * pz];
+    sc = data_scale(bnd, nbnd, src_part ? nsplit : 0, inv_z, bnd_meas, pz);
     if (blockIdx.x == 0 && threadIdx.x == 0) scl[2 * pz + 1] = sc;
   }
   if (src_abi) src_abi += pz * T * NC;
@@ -592,6 +545,43 @@ void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) 
   else split_maps_launch(p, b, true, s);
 }
 
+int bound_image(const EncPlan &p, const float2 *x, const float2 *xsub, int64_t x_stride, int32_t x_row_stride,
+                int64_t x_pstride, const EncBuffers &b, hipStream_t s) {
+  if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of a scaled plan are not carved");
+  k_amax_z<<<dim3(amax_blocks((int64_t)p.R * p.B), (unsigned)p.P), 256, 0, s>>>(x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.B,
+                                                            x_pstride, b.amax);
+  EX_LAUNCHED("operand bound");
+  return EXPENC_OK;
+}
+
+int bound_data(const EncPlan &p, const float2 *y, const float2 *y_meas, const EncBuffers &b, bool prepared,
+               DataBound *d, hipStream_t s) {
+  if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of a scaled plan are not carved");
+  auto pass = [&](const float2 *v, int64_t n, float *out) -> int {
+    k_amax_c<<<dim3(amax_blocks(n), (unsigned)p.P), 256, 0, s>>>(v, n, n, out);
+    EX_LAUNCHED("operand bound");
+    return EXPENC_OK;
+  };
+  const int64_t ny_el = p.T * p.NC;  // [B][T][C] per problem
+  d->bnd = b.amax;
+  d->nbnd = kAmaxBlocks;
+  if (y) return prepared ? EXPENC_OK : pass(y, ny_el, b.amax);
+  if (p.sh || p.prec == EXPENC_FP32) {
+    // these forwards write their per-wave output maxima
+    d->bnd = b.wmax;
+    d->nbnd = p.nwmax;
+  } else {
+    // (the split maps-kind forward does not: a pre-pass over its partial sums)
+    EX_TRY(pass(b.part, (int64_t)p.fwd_split * p.Tp * p.NCP, b.amax));
+  }
+  if (y_meas) {
+    float *am = b.amax + (size_t)p.P * kAmaxBlocks;
+    EX_TRY(pass(y_meas, ny_el, am));
+    d->meas = am;
+  }
+  return EXPENC_OK;
+}
+
 int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const float2 *xsub, int64_t x_stride,
                   int32_t x_row_stride, const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared) {
   const int NGP = p.NCP / 16;
@@ -599,14 +589,7 @@ int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const f
   const dim3 nb((unsigned)ceil_div(n, 256), (unsigned)p.P);
   const float2 *sm = reinterpret_cast<const float2 *>(smaps);
   u32x4 *zs = reinterpret_cast<u32x4 *>(b.zs);
-  if (p.scaled) {
-    if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of an fp16 plan are not carved");
-    if (!prepared) {
-      k_amax_z<<<dim3(kAmaxBlocks, (unsigned)p.P), 256, 0, s>>>(x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.B,
-                                                                x_pstride, b.amax);
-      EX_LAUNCHED("operand bound");
-    }
-  }
+  if (p.scaled && !prepared) EX_TRY(bound_image(p, x, xsub, x_stride, x_row_stride, x_pstride, b, s));
   float *scl = p.scaled ? b.scl : nullptr;
   const float2 *sq = p.comb && !prepared ? b.sq : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
@@ -626,47 +609,15 @@ int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, cons
   const dim3 nb((unsigned)ceil_div(n, 256), (unsigned)p.P);
   u32x4 *ys = reinterpret_cast<u32x4 *>(b.ys);
   const float2 *part = from_partials ? b.part : nullptr;
-  const float *bnd = nullptr, *bnd_meas = nullptr;
-  int nbnd = 0;
-  if (p.scaled) {
-    if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of an fp16 plan are not carved");
-    const dim3 ng(kAmaxBlocks, (unsigned)p.P);
-    const int64_t ny_el = p.T * p.NC;  // [B][T][C] per problem
-    if (!from_partials) {
-      if (!prepared) {
-        k_amax_c<<<ng, 256, 0, s>>>(y_abi, ny_el, ny_el, b.amax);
-        EX_LAUNCHED("operand bound");
-      }
-      bnd = b.amax;
-      nbnd = kAmaxBlocks;
-    } else {
-      if (p.sh) {
-        // the polynomial forward writes its per-wave output maxima
-        bnd = b.wmax;
-        nbnd = p.nwmax;
-      } else {
-        // (the maps-kind forward does not: a pre-pass over its partial sums)
-        const int64_t np = (int64_t)p.fwd_split * p.Tp * p.NCP;
-        k_amax_c<<<ng, 256, 0, s>>>(b.part, np, np, b.amax);
-        EX_LAUNCHED("operand bound");
-        bnd = b.amax;
-        nbnd = kAmaxBlocks;
-      }
-      if (y_meas) {
-        float *am = b.amax + (size_t)p.P * kAmaxBlocks;
-        k_amax_c<<<ng, 256, 0, s>>>(y_meas, ny_el, ny_el, am);
-        EX_LAUNCHED("operand bound");
-        bnd_meas = am;
-      }
-    }
-  }
+  DataBound d;
+  if (p.scaled) EX_TRY(bound_data(p, y_abi, y_meas, b, prepared, &d, s));
   float *scl = p.scaled ? b.scl : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
     k_pack_y_split<true><<<nb, 256, 0, s>>>(y_abi, part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP, ys,
-                                            bnd, nbnd, bnd_meas, scl);
+                                            d.bnd, d.nbnd, d.meas, scl);
   else
     k_pack_y_split<false><<<nb, 256, 0, s>>>(y_abi, part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP, ys,
-                                             bnd, nbnd, bnd_meas, scl);
+                                             d.bnd, d.nbnd, d.meas, scl);
   EX_LAUNCHED("pack_y split");
   return EXPENC_OK;
 }

@@ -71,12 +71,18 @@ __device__ inline void split_pair(float a, float b, uint32_t &hi, uint32_t &lo, 
 __device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Exact bf16 parts (hi, mid, lo) of two FP32 values of any magnitude.
+// bf16 parts (hi, mid, lo) of two FP32 operand values: exact from 2^-110 (the
+// last bit of lo is then at least the smallest bf16, 2^-133) up to the largest
+// value, whose hi must not round to infinity.  An infinity or NaN is kept in lo
+// alone, which meets no part of the other operand but its hi: one product of
+// the right sign, where parts inf, inf - inf give NaN.
 __device__ inline void split3_any(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
-  const bf16x2 hv = {(__bf16)a, (__bf16)b};
+  const bool fa = isfinite(a), fb = isfinite(b);
+  constexpr float kMax = 3.38953139e38f;  // the largest bf16
+  const bf16x2 hv = {(__bf16)(fa ? fminf(fmaxf(a, -kMax), kMax) : 0.f), (__bf16)(fb ? fminf(fmaxf(b, -kMax), kMax) : 0.f)};
   h = __builtin_bit_cast(uint32_t, hv);
   const float ra = a - bf16_lo(h), rb = b - bf16_hi(h);
-  const bf16x2 mv = {(__bf16)ra, (__bf16)rb};
+  const bf16x2 mv = {(__bf16)(fa ? ra : 0.f), (__bf16)(fb ? rb : 0.f)};
   m = __builtin_bit_cast(uint32_t, mv);
   const bf16x2 lv = {(__bf16)(ra - bf16_lo(m)), (__bf16)(rb - bf16_hi(m))};
   l = __builtin_bit_cast(uint32_t, lv);
@@ -105,11 +111,90 @@ __device__ inline f32x16 step6(const u32x4 (&A)[4], const u32x4 *b, f32x16 acc) 
   return acc;
 }
 
+// ---------------------------------------------------------------------------
+// Operand scaling of the fp16 and FP32 forms.  An fp16 hi/lo pair represents
+// |v| up to 65504 and keeps its ~22-bit precision only while the lo half is
+// normal, i.e. for |v| above ~2^-3; three bf16 parts hold all 24 bits from
+// 2^-110.  Both forms therefore multiply each packed operand by a power of two
+// s = 2^(14 - e), where M < 2^e bounds the operand's magnitudes, so that every
+// value lies below 2^14 and values down to 2^-17 (fp16) or 2^-124 (FP32) of the
+// largest keep full precision; the reductions that read the contraction's
+// output divide s out again (exact for powers of two).
+// M comes from a pre-pass over the operand (image operand, or data given at
+// the boundary) or from the forward contraction's per-wave output maxima
+// (the residual operand, summed over nsplit partial sums).
+// ---------------------------------------------------------------------------
+
+__device__ inline float pow2_scale(double m) {
+  if (!(m > 0.0) || !isfinite(m)) return 1.f;  // zero, NaN or infinite: unscaled
+  int e;
+  (void)frexp(m, &e);
+  return ldexpf(1.f, min(126, max(-126, 14 - e)));
+}
+
+// An element's part in a bound M: |Re| + |Im| (l1) or the larger of the two;
+// an element that is not finite has none (its products are not finite at any
+// scale, and the other columns keep theirs).
+__device__ inline float magnitude(float2 u, bool l1) {
+  const float m = l1 ? fabsf(u.x) + fabsf(u.y) : fmaxf(fabsf(u.x), fabsf(u.y));
+  return isfinite(u.x) && isfinite(u.y) ? fminf(m, 3.0e38f) : 0.f;
+}
+
+// Max of v[0..n) over a 256-thread workgroup; every thread returns it.
+__device__ inline float block_max(const float *__restrict__ v, int n) {
+  __shared__ float wm[4];
+  float m = 0.f;
+  int i = threadIdx.x;
+  for (; i + 768 < n; i += 1024) {  // four independent loads in flight
+    const float a = v[i], b = v[i + 256], c = v[i + 512], d = v[i + 768];
+    m = fmaxf(m, fmaxf(fmaxf(a, b), fmaxf(c, d)));
+  }
+  for (; i < n; i += 256) m = fmaxf(m, v[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  __syncthreads();  // an earlier call's readers are done with wm
+  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  __syncthreads();
+  return fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
+}
+
+// Scale of an image operand Z = S u of problem pz from the bounds of u and of
+// the coil maps (amax sections 0 and 2 of P problems), both loaded at once.
+__device__ inline float image_scale(const float *__restrict__ amax, int pz, int P) {
+  __shared__ float wu[4], ws[4];
+  const int tid = threadIdx.x;
+  static_assert(kAmaxBlocks == 256, "one bound per thread");
+  float u = amax[(int64_t)pz * kAmaxBlocks + tid], s = amax[(int64_t)(2 * P + pz) * kAmaxBlocks + tid];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    u = fmaxf(u, __shfl_xor(u, o));
+    s = fmaxf(s, __shfl_xor(s, o));
+  }
+  if ((tid & 63) == 0) {
+    wu[tid >> 6] = u;
+    ws[tid >> 6] = s;
+  }
+  __syncthreads();
+  return pow2_scale((double)fmaxf(fmaxf(wu[0], wu[1]), fmaxf(wu[2], wu[3])) *
+                    fmaxf(fmaxf(ws[0], ws[1]), fmaxf(ws[2], ws[3])));
+}
+
+// Scale of a data operand: the bound of the data itself (bnd: its pre-pass)
+// or, with nsplit > 0, of the forward's nsplit partial sums (bnd:
+// per-wave maxima in units of 1 / inv_z), plus that of the measured data.
+__device__ inline float data_scale(const float *__restrict__ bnd, int nbnd, int nsplit, float inv_z,
+                                   const float *__restrict__ bnd_meas, int pz) {
+  double m = block_max(bnd + (int64_t)pz * nbnd, nbnd);
+  if (nsplit > 0) m *= (double)nsplit * inv_z;
+  if (bnd_meas) m += block_max(bnd_meas + (int64_t)pz * kAmaxBlocks, kAmaxBlocks);
+  return pow2_scale(m);
+}
+
 constexpr int kRec3 = 6 * 64;  // 16-byte words of one FP32-form step and column group
 
 // Operand records of 8 reduction indices (layout: see the packing kernels):
-// hi and lo of b1 and b2 (split forms), three exact bf16 parts (FP32 form; o:
-// the lane's).
+// hi and lo of b1 and b2 (split forms), three bf16 parts (FP32 form; o: the
+// lane's).
 template <bool BF>
 __device__ inline void write_record(u32x4 *out, int64_t q, int g, int NGP, int lane, const float (&b1)[8],
                                     const float (&b2)[8]) {

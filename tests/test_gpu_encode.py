@@ -218,3 +218,98 @@ def test_fp32_form_edges(shape):
     assert rel(yf[0], encoding.forward(x[0] / scale, *args)) <= 1e-6
     xa = ee.adjoint(t(y.astype(np.complex64)), op).cpu().numpy().astype(np.complex128) / scale
     assert rel(xa[0], encoding.adjoint(y[0] / scale, *args)) <= 1e-6
+
+
+def _small_case(sh, scale=1.0, batch=1, seed=90):
+    """A 31 x 29, 8-coil, 9-term operator with its oracle arguments and inputs
+    rounded to complex64 after scaling."""
+    import torch
+    ee = _ee()
+    nx, ny, T, C, L = 31, 29, 300, 8, 9
+    fx, fy, z0 = 0.1, 0.07, 0.003
+    rng = np.random.default_rng(seed)
+    basis = encoding.sh_basis(nx, fx, z0, L, ny=ny, fov_y=fy)
+    coef = rng.normal(0.0, 1.0, (T, L)) * (20.0 / np.maximum(np.abs(basis).max(axis=1), 1e-12))[None, :]
+    time = np.arange(T, dtype=np.float64) * 2e-6
+    dw0 = rng.uniform(-600.0, 600.0, nx * ny)
+    smaps = c64(synth.random_complex((C, nx * ny), 61))
+    x = c64(scale * synth.random_complex((batch, nx * ny), 62))
+    y = c64(scale * synth.random_complex((batch, T, C), 63))
+    dev = torch.device("cuda")
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    op = ee.Operator(nx, ny, t(smaps.astype(np.complex64)), t(coef), t(time), None if sh else t(basis), t(dw0),
+                     sh_grid=(fx, fy, z0) if sh else None)
+    dc = lambda a: t(a.astype(np.complex64))  # noqa: E731
+    return op, (smaps, coef, time, basis, dw0), x, y, dc
+
+
+@pytest.mark.parametrize("sh", [False, True], ids=["maps", "sh"])
+@pytest.mark.parametrize("scale", [1e-37, 1e-35, 1e-33, 1e33])
+def test_fp32_form_keeps_its_accuracy_over_the_fp32_range(scale, sh):
+    """Operands close to the smallest normal FP32 value (and far above 1)
+    reach the result with 24 bits: the same 1e-6 as at scale 1.  Two images,
+    so that columns of one launch share a scale."""
+    ee = _ee()
+    op, args, x, y, dc = _small_case(sh, scale, batch=2)
+    print(f"[case] fp32 range {scale:g} sh={sh}", flush=True)
+    f = ee.forward(dc(x), op).cpu().numpy().astype(np.complex128) / scale
+    a = ee.adjoint(dc(y), op).cpu().numpy().astype(np.complex128) / scale
+    for b in range(2):
+        assert rel(f[b], encoding.forward(x[b] / scale, *args)) <= 1e-6
+        assert rel(a[b], encoding.adjoint(y[b] / scale, *args)) <= 1e-6
+
+
+def test_fp32_normal_equations_keep_their_accuracy_at_small_scale():
+    """The residual operand too: conjugate gradients on data of 1e-34 give the
+    image of scale 1 times 1e-34 (every step is linear in the data; 20 FP32
+    steps on a well-posed system, 1e-5)."""
+    ee = _ee()
+    op, args, _, _, dc = _small_case(True)
+    x = c64(synth.random_complex((1, op.npix), 65))
+    y = encoding.forward(x[0], *args)
+    ref = ee.cg(dc(y), op, 20).cpu().numpy().astype(np.complex128)
+    got = ee.cg(dc(1e-34 * y), op, 20).cpu().numpy().astype(np.complex128)
+    assert np.all(np.isfinite(got)) and rel(got / 1e-34, ref) <= 1e-5
+
+
+@pytest.mark.parametrize("sh", [False, True], ids=["maps", "sh"])
+@pytest.mark.parametrize("value", [3.4e38, np.inf, np.nan])
+def test_fp32_form_extreme_and_non_finite_operands(value, sh):
+    """One element of 3.4e38, infinity or NaN.  The largest values stay finite
+    where the result is; an infinity gives the infinities and NaN that real
+    arithmetic gives (products of the phase's and the maps' signs, NaN where
+    two of opposite sign meet); the other image of the batch is untouched."""
+    ee = _ee()
+    op, (smaps, coef, time, basis, dw0), x, y, dc = _small_case(sh, 0.0, batch=2)
+    x[1] = c64(synth.random_complex((op.npix,), 66))
+    y[1] = c64(synth.random_complex(y.shape[1:], 67))
+    r0, t0, c0 = 500, 7, 2
+    x[0, r0] = y[0, t0, c0] = value
+    ph = encoding.phase(coef, time, basis, dw0)
+    cs, sn = np.cos(ph), np.sin(ph)
+    f = ee.forward(dc(x), op).cpu().numpy()
+    a = ee.adjoint(dc(y), op).cpu().numpy()
+    args = (smaps, coef, time, basis, dw0)
+    # the finite image: 3.4e38 beside it takes the common scale and its bits
+    # (2^-128 of the largest value); beside a non-finite one it keeps them
+    if not np.isfinite(value):
+        assert rel(f[1], encoding.forward(x[1], *args)) <= 1e-6
+        assert rel(a[1], encoding.adjoint(y[1], *args)) <= 1e-6
+    with np.errstate(all="ignore"):
+        z = (smaps[:, r0].real * value, smaps[:, r0].imag * value)
+        fr = cs[:, r0, None] * z[0] - sn[:, r0, None] * z[1]
+        fi = cs[:, r0, None] * z[1] + sn[:, r0, None] * z[0]
+        u = (cs[t0] * value, -sn[t0] * value)
+        s = smaps[c0]
+        ar, ai = s.real * u[0] + s.imag * u[1], s.real * u[1] - s.imag * u[0]
+    clear = np.minimum(np.abs(cs), np.abs(sn)) > 1e-5      # (a sign that a rounded phase cannot change)
+    # (a product S x above the FP32 range is infinite in FP32 arithmetic)
+    zfits = np.broadcast_to(np.maximum(np.abs(z[0]), np.abs(z[1])) < 3.4e38, fr.shape)
+    for got, ref, ok, in_range in ((f[0].real, fr, clear[:, r0], zfits), (f[0].imag, fi, clear[:, r0], zfits),
+                                   (a[0].real, ar, clear[t0], None), (a[0].imag, ai, clear[t0], None)):
+        got, ref = got[ok].astype(np.float64), ref[ok]
+        if np.isfinite(value):
+            fits = (np.abs(ref) < 3.4e38) & (True if in_range is None else in_range[ok])
+            assert np.all(np.abs(got[fits] - ref[fits]) <= 1e-6 * value)
+        else:
+            np.testing.assert_array_equal(got, ref)

@@ -37,8 +37,8 @@ namespace expenc {
 
 // Sum of n float2 values p[k * step], k = 0 .. n - 1, in FP64 and in k
 // order, eight loads in flight per step (a loop that loads and adds one at a
-// time waits for memory once per value).
-__device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, int n, double &sx, double &sy) {
+// time waits for memory once per value).  odd: the sign of every second value.
+__device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, int n, float odd, double &sx, double &sy) {
   int k = 0;
   for (; k + 8 <= n; k += 8) {
     float2 v[8];
@@ -46,21 +46,22 @@ __device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, i
     for (int u = 0; u < 8; ++u) v[u] = p[(k + u) * step];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      sx += v[u].x;
-      sy += v[u].y;
+      sx += (u & 1) ? odd * v[u].x : v[u].x;
+      sy += (u & 1) ? odd * v[u].y : v[u].y;
     }
   }
   for (; k < n; ++k) {
     const float2 v = p[k * step];
-    sx += v.x;
-    sy += v.y;
+    sx += (k & 1) ? odd * v.x : v.x;
+    sy += (k & 1) ? odd * v.y : v.y;
   }
 }
 
-// scl: the scaled form's operand powers of two ([P][2]), or NULL.
+// scl: the scaled form's operand powers of two ([P][2]), or NULL; odd: sign of
+// the odd splits.
 __global__ void k_fwd_reduce_out(const float2 *__restrict__ part, int nsplit, int64_t T,
                                  int64_t Tp, int C, int NC, int NCP, float2 *__restrict__ y,
-                                 const float *__restrict__ scl) {
+                                 const float *__restrict__ scl, float odd) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= T * NC) return;
   const int pz = blockIdx.y;
@@ -69,7 +70,7 @@ __global__ void k_fwd_reduce_out(const float2 *__restrict__ part, int nsplit, in
   int64_t t = i / NC;
   int col = (int)(i % NC);
   double sx = 0.0, sy = 0.0;
-  sum_strided(part + t * NCP + col, Tp * NCP, nsplit, sx, sy);
+  sum_strided(part + t * NCP + col, Tp * NCP, nsplit, odd, sx, sy);
   if (scl) {
     const double inv = 1.0 / scl[2 * pz];
     sx *= inv;
@@ -80,7 +81,8 @@ __global__ void k_fwd_reduce_out(const float2 *__restrict__ part, int nsplit, in
 }
 
 // x_b(r) = alpha * sum_c conj(S_c(r)) sum_split part[split][r][b*C+c].
-// Block: 8 pixels x 32 lanes; lanes stride over coils, then a shuffle sum.
+// Block: 8 pixels x 32 lanes; lanes stride over coils, then a shuffle sum.  odd:
+// sign of the odd splits.
 __global__ __launch_bounds__(256) void k_adj_reduce_out(const float2 *__restrict__ part, int nsplit,
                                                         int R, int Rp, int nx, int C, int B, int NCP,
                                                         const float2 *__restrict__ smaps,
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(256) void k_adj_reduce_out(const float2 *__restrict
                                                         const float2 *__restrict__ add,
                                                         const float2 *__restrict__ base, int nxq,
                                                         int64_t x_pstride, int pad_nx, int pad_ny,
-                                                        const float *__restrict__ scl) {
+                                                        const float *__restrict__ scl, float odd) {
   const int sub = threadIdx.x & 31;
   const int q = blockIdx.x * 8 + (threadIdx.x >> 5);  // pixel of x's grid
   const int npx = pad_nx > 0 ? pad_nx * pad_ny : R;
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(256) void k_adj_reduce_out(const float2 *__restrict
     for (int c = sub; c < C; c += 32) {
       const int col = b * C + c;
       double ux = 0.0, uy = 0.0;
-      sum_strided(part + rq * NCP + col, (int64_t)Rp * NCP, nsplit, ux, uy);
+      sum_strided(part + rq * NCP + col, (int64_t)Rp * NCP, nsplit, odd, ux, uy);
       float2 s = smaps[(int64_t)c * R + r];
       sx += s.x * ux + s.y * uy;  // conj(s) * u
       sy += s.x * uy - s.y * ux;
@@ -417,7 +419,15 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   // (3.8e-6 whatever the chunk; the fp16 forward's 6.6e-7 at 1024 becomes
   // 7.5e-7 at 1480, 148 x 148).
   const bool f32 = precision == EXPENC_FP32;
-  const int32_t longest = f32 ? 64 : kSplitAdjChunkMax;
+  const int32_t longest = f32 ? kF32FoldMax : kSplitAdjChunkMax;
+  // FP32 sums longer than those of kTargetWorkgroups, up to kF32FoldMax, are the
+  // folded ones (f32.hip): 40 x 33, 8 coils, T = 3000 31 / 34 us with 64 indices,
+  // 37 / 45 with the 16 of 2048 workgroups, at 0.86 and 0.8 of the error on the
+  // FP32 instruction with those 16; carried through the matrix instruction 64
+  // indices have 1.2 to 1.4 of it.
+  auto folds = [&](int32_t chunk, int64_t K, int64_t nrb) {
+    return f32 && chunk <= kF32FoldMax && chunk > target_chunk(K, nrb, q.NGY, kTargetWorkgroups, 16, kF32ChunkMax);
+  };
   const double step = (f32 ? 1.0 : q.sh ? 0.5 : 0.6) * (q.GW == 2 ? 1.0 : 0.6);
   // forward: 256 sample rows per workgroup, split over pixels
   {
@@ -430,6 +440,7 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
                                           precision == EXPENC_BF16_SPLIT ? kBf16FwdChunkMax : longest, cap);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
+    q.fwd_fold = folds(q.fwd_chunk, q.Rp, nrb);
   }
   // adjoint: 256 pixel rows per workgroup, split over samples
   {
@@ -450,6 +461,7 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
                           : default_chunk(q.Tp, nrb, q.NGY, q.comb ? q.NGY : q.NCP, slots, step, 1.5, grain,
                                           std::min(longest, cap), cap);
     q.adj_split = (int32_t)ceil_div(q.Tp, q.adj_chunk);
+    q.adj_fold = folds(q.adj_chunk, q.Tp, nrb);
   }
   *p = q;
   return EXPENC_OK;
@@ -475,6 +487,7 @@ int plan_forward_within(const expenc_op *op, int32_t batch, int32_t precision, s
     if (q.prec == EXPENC_FP32) q.fwd_chunk = std::min(q.fwd_chunk, kF32ChunkMax);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
+    q.fwd_fold = q.fwd_fold && q.fwd_chunk <= kF32FoldMax;
   };
   while (enc_operand_bytes(q) > cap && q.fwd_split > min_split)
     set_split(std::max<int32_t>(min_split, q.fwd_split - std::max<int32_t>(1, q.fwd_split / 4)));
@@ -670,9 +683,12 @@ int enc_adjoint_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   return EXPENC_OK;
 }
 
+// (the FP32 form's odd splits are negated)
+static float odd_sign(const EncPlan &p) { return p.prec == EXPENC_FP32 ? -1.f : 1.f; }
+
 int enc_forward_reduce_out(const EncPlan &p, const EncBuffers &b, float2 *y, hipStream_t s) {
   k_fwd_reduce_out<<<grid_p(p.T * p.NC, 256, p.P), 256, 0, s>>>(b.part, p.fwd_split, p.T, p.Tp, p.C, p.NC, p.NCP, y,
-                                                                  p.scaled ? b.scl : nullptr);
+                                                                  p.scaled ? b.scl : nullptr, odd_sign(p));
   EX_LAUNCHED("forward reduce");
   return EXPENC_OK;
 }
@@ -699,7 +715,7 @@ int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *s
   k_adj_reduce_out<<<grid_p(npx, 8, p.P), 256, 0, s>>>(b.part, p.adj_split, p.R, p.Rp, p.nx, p.C, p.B, p.NCP,
                                                        reinterpret_cast<const float2 *>(smaps), x, x_stride,
                                                        x_row_stride, alpha_dev, add, base, p.nxq, x_pstride,
-                                                       pad_nx, pad_ny, p.scaled ? b.scl : nullptr);
+                                                       pad_nx, pad_ny, p.scaled ? b.scl : nullptr, odd_sign(p));
   EX_LAUNCHED("adjoint reduce");
   return EXPENC_OK;
 }

@@ -20,6 +20,21 @@
 // does not grow (adjoint 200 x 200, T = 40000: 4.8e-7 -> 3.9e-7): one matrix
 // instruction adds 16 products to an accumulator, the FP32 one two.
 //
+// The matrix instruction aligns its 16 products and C to the largest of them
+// and cuts what is below, towards minus infinity: a sum carried through it loses
+// the more the larger it has grown, and always to the same side.  So
+//  * the records, and with them the partial sums, of every second split are
+//    negated (split_sign), and the reductions undo it: the losses cancel;
+//  * with FOLD every step's products start from zero and the result is added to
+//    the accumulators outside.  These sums are the more precise ones, which lets
+//    small problems have chunks of 64 where they had 16 (make_plan); on long
+//    chunks it costs 6 to 45 % (16 to 64 more registers, no overlap of a step's
+//    last products with the next phases).
+// Error of the adjoint of random data relative to the FP32 instruction's, before
+// either and now: 148 x 148, 32 coils, T = 16384 1.53 -> 0.83, 128 x 128, 16
+// coils, T = 12000 1.14 -> 0.84, 40 x 33, 8 coils, T = 3000 (64 samples against
+// 16) 1.36 -> 0.82.
+//
 // Layout of one step (K = 16 reduction indices) as in the split forms: lane l
 // holds indices 8*(l/32) .. +7 of row l%32 (A) or column l%32 (B).  Each lane
 // evaluates its OWN row against 16 wave-uniform indices, splits and packs
@@ -62,7 +77,9 @@ __device__ inline void sincos_turns(double p, float &c, float &s) {
 
 // The six products of cos against b1 and of sin against b2, smallest first.
 // A: [c hi, c mid, c lo, s hi, s mid, s lo].
-__device__ inline f32x16 step12(const u32x4 (&A)[6], const u32x4 (&b)[6], f32x16 acc) {
+template <bool FOLD>
+__device__ inline f32x16 step12(const u32x4 (&A)[6], const u32x4 (&b)[6], f32x16 sum) {
+  f32x16 acc = FOLD ? f32x16{} : sum;
 #pragma unroll
   for (int o = 0; o < 6; o += 3) {
     acc = mfma16<true>(A[o + 1], b[o + 1], acc);
@@ -72,7 +89,7 @@ __device__ inline f32x16 step12(const u32x4 (&A)[6], const u32x4 (&b)[6], f32x16
     acc = mfma16<true>(A[o], b[o + 1], acc);
     acc = mfma16<true>(A[o], b[o], acc);
   }
-  return acc;
+  return FOLD ? sum + acc : acc;
 }
 
 // Wave-uniform terms of one reduction index (scalar loads).  The opaque
@@ -96,7 +113,7 @@ struct F32Args {
 // Exchanges the packed words of the lane's own row (w[kind][pair], pairs of
 // reduction indices) into the two blocks' operands and adds the step's
 // products; o: the step's records of the first column group, this lane's.
-template <int GW>
+template <int GW, bool FOLD>
 __device__ inline void contract16(const uint32_t (&w)[6][8], const u32x4 *__restrict__ o, f32x16 (&acc)[2][GW]) {
   u32x4 A[2][6];
 #pragma unroll
@@ -111,8 +128,8 @@ __device__ inline void contract16(const uint32_t (&w)[6][8], const u32x4 *__rest
   for (int g = 0; g < GW; ++g) {
     const u32x4 *og = o + g * kRec3;
     const u32x4 b[6] = {og[0], og[64], og[128], og[192], og[256], og[320]};
-    acc[0][g] = step12(A[0], b, acc[0][g]);
-    acc[1][g] = step12(A[1], b, acc[1][g]);
+    acc[0][g] = step12<FOLD>(A[0], b, acc[0][g]);
+    acc[1][g] = step12<FOLD>(A[1], b, acc[1][g]);
   }
 }
 
@@ -132,10 +149,11 @@ __device__ inline void zero_acc(f32x16 (&acc)[2][GW]) {
 // 148 x 148, 32 coils, T = 16384: 677 -> 640 us, 200 x 200, T = 20000: 1348 ->
 // 1263 (one column group: equal).  The adjoint, which waits for its LDS reads
 // as well, took 705 for 683 us with the same pipeline.
-template <int GW>
+template <int GW, bool FOLD>
 struct Pipe {
   static constexpr int N = 24 * GW;  // MFMAs of a step
   u32x4 A[2][6], b[6];
+  f32x16 t[2];       // FOLD: a column group's sums over the step
   uint32_t w[6][8];  // the next step's words, as for contract16
 
   __device__ inline void load(int h, const u32x4 *__restrict__ rec) {
@@ -167,7 +185,10 @@ struct Pipe {
     for (int k = 0; k < N; ++k)
       if (k >= lo && k < hi) {
         const int g = k / 24, h = k % 24 / 12, q = k % 12 >> 1, blk = k & 1;
-        acc[blk][g] = mfma16<true>(A[blk][3 * h + pa[q]], b[3 * h + pb[q]], acc[blk][g]);
+        f32x16 &c = FOLD ? t[blk] : acc[blk][g];
+        if (FOLD && k % 24 < 2) c = f32x16{};
+        c = mfma16<true>(A[blk][3 * h + pa[q]], b[3 * h + pb[q]], c);
+        if (FOLD && k % 24 >= 22) acc[blk][g] += c;
         if (k % 12 == 11) load(h, g + 1 < GW ? cur + (g + 1) * kRec3 : next);
       }
   }
@@ -193,7 +214,7 @@ struct Pipe {
 constexpr int kIndices = 64;
 constexpr int lds_terms(int nt) { return nt == 17 ? 6 : 0; }
 
-template <int NT, int GW, bool FWD>
+template <int NT, int GW, bool FWD, bool FOLD>
 __device__ inline void f32_body(const double *__restrict__ own, const double *__restrict__ uni,
                                 const u32x4 *__restrict__ opr, float *__restrict__ part, const F32Args &a) {
   static_assert(NT || FWD, "the solid-harmonic adjoint is k_adj_f32_sh");
@@ -204,10 +225,11 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
   const int64_t rows = FWD ? a.Tp : a.Rp, len = FWD ? a.Rp : a.Tp;
   int split, rb;
   const int pz = blockIdx.z;  // problem
-  float *const wmax = FWD ? a.wmax + ((int64_t)(pz * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 4 + wave
-                          : nullptr;
+  auto wmax = [&] {  // this wave's slot
+    return FWD ? a.wmax + ((int64_t)(pz * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 4 + wave : nullptr;
+  };
   if (!split_tile(blockIdx.x, (int)(rows / 256), a.nsplit, &split, &rb)) {
-    if (FWD && lane == 0) *wmax = 0.f;
+    if (FWD && lane == 0) *wmax() = 0.f;
     return;
   }
   const int64_t row0 = (int64_t)rb * 256 + wave * 64;
@@ -235,7 +257,7 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
     __syncthreads();
   }
   if constexpr (NT == 0) {
-    Pipe<GW> pp;
+    Pipe<GW, FOLD> pp;
     RowCubic rc;
     rc.start((int)k0, a.nxq);
     float f[16];
@@ -257,7 +279,7 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
     for (int m = 0; m < 8; ++m) pp.pair(m, f[2 * m], f[2 * m + 1], a.mk);
     pp.exchange();
     for (int64_t k = k0; k + 16 < k1; k += 16, cur += step) {
-      constexpr int N = Pipe<GW>::N;
+      constexpr int N = Pipe<GW, FOLD>::N;
       rc.expand(P, a.nx, a.ny, a.dx, a.dy, dx2, dx3);
       rc.next(a.nxq);
 #pragma unroll
@@ -272,7 +294,7 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
       }
       pp.exchange();
     }
-    pp.products(0, Pipe<GW>::N, cur, cur, acc);
+    pp.products(0, Pipe<GW, FOLD>::N, cur, cur, acc);
   } else {
     for (int64_t k = k0; k < k1; k += 16) {
       uint32_t w[6][8];  // [c hi, mid, lo, s hi, mid, lo][pair of the 16 indices]
@@ -301,28 +323,34 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
         split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
         split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
       }
-      contract16<GW>(w, op + (k >> 4) * NGP * kRec3, acc);
+      contract16<GW, FOLD>(w, op + (k >> 4) * NGP * kRec3, acc);
       if constexpr (NL > 0) {
         if (((k - k0) & (kIndices - 1)) == kIndices - 16) __syncthreads();
       }
     }
   }
   // [problem][split][row][column] complex
-  store_partials<GW>(part + ((int64_t)pz * a.nsplit + split) * rows * a.NCP * 2, row0, a.NCP, g0, lane, acc, wmax, 0);
+  store_partials<GW>(part + ((int64_t)pz * a.nsplit + split) * rows * a.NCP * 2, row0, a.NCP, g0, lane, acc, wmax(),
+                     0);
 }
 
-template <int NT, int GW>
-__global__ __launch_bounds__(256, 2) void k_fwd_f32(const double *__restrict__ own, const double *__restrict__ uni,
+// Waves per SIMD asked for: 17 terms and 32 columns need 169 registers left to
+// the compiler, one more than three waves have (148 x 148, 32 coils, T = 16384
+// forward: two waves 884 us, three 774).
+constexpr int min_waves(int nt, int gw, bool fold) { return nt == 17 && gw == 2 && !fold ? 3 : 2; }
+
+template <int NT, int GW, bool FOLD>
+__global__ __launch_bounds__(256, min_waves(NT, GW, FOLD)) void k_fwd_f32(const double *__restrict__ own, const double *__restrict__ uni,
                                                      const u32x4 *__restrict__ op, float *__restrict__ part,
                                                      F32Args a) {
-  f32_body<NT, GW, true>(own, uni, op, part, a);
+  f32_body<NT, GW, true, FOLD>(own, uni, op, part, a);
 }
 
-template <int NT, int GW>
-__global__ __launch_bounds__(256, 2) void k_adj_f32(const double *__restrict__ own, const double *__restrict__ uni,
+template <int NT, int GW, bool FOLD>
+__global__ __launch_bounds__(256, min_waves(NT, GW, FOLD)) void k_adj_f32(const double *__restrict__ own, const double *__restrict__ uni,
                                                      const u32x4 *__restrict__ op, float *__restrict__ part,
                                                      F32Args a) {
-  f32_body<NT, GW, false>(own, uni, op, part, a);
+  f32_body<NT, GW, false, FOLD>(own, uni, op, part, a);
 }
 
 // The solid-harmonic adjoint (rows: pixels, reduction over samples).  At a
@@ -337,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_f32(const double *__restrict__ o
 // fills bound it: 148 x 148, 32 coils, T = 16384: 806 us.
 constexpr int kSamples = 64;
 
-template <int GW>
+template <int GW, bool FOLD>
 __global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict__ pmono,
                                                        const double *__restrict__ dwq,
                                                        const u32x4 *__restrict__ opr, float *__restrict__ part,
@@ -396,7 +424,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict_
         split3(c[0], c[1], a.mk, w[0][m], w[1][m], w[2][m]);
         split3(s[0], s[1], a.mk, w[3][m], w[4][m], w[5][m]);
       }
-      contract16<GW>(w, op + ((kb + j0) >> 4) * NGP * kRec3, acc);
+      contract16<GW, FOLD>(w, op + ((kb + j0) >> 4) * NGP * kRec3, acc);
     }
     __syncthreads();
   }
@@ -408,6 +436,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict_
 // 16q + 8*(l/32) + i, column col = 16g + l%16, part = (l/16)&1.
 //   forward:  b1 = part ? Zi : Zr,   b2 = part ? Zr : -Zi
 //   adjoint:  b1 = part ? Yi : Yr,   b2 = part ? -Yr : Yi
+// times the operand's scale and the sign of the index's split.
 // ---------------------------------------------------------------------------
 
 // Z[r'][col] = S_c(r) x_b(r), col = b*C + c, row r' = y*nxq + x of pixel
@@ -415,7 +444,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict_
 __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ smaps, const float2 *__restrict__ x,
                                                      int64_t x_stride, int x_row_stride, int nx, int ny, int nxq,
                                                      int Rp, int C, int NC, int NGP, u32x4 *__restrict__ zs,
-                                                     int64_t x_pstride, const float *__restrict__ amax,
+                                                     int64_t x_pstride, int chunk, const float *__restrict__ amax,
                                                      float *__restrict__ scl) {
   const int R = nx * ny;
   const int64_t pz = blockIdx.y;
@@ -449,11 +478,12 @@ __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ 
   const float sc = image_scale(amax, (int)pz, gridDim.y);
   if (blockIdx.x == 0 && threadIdx.x == 0) scl[2 * pz] = sc;
   if (!live) return;
+  const float f = sc * split_sign(16 * (qg / NGP) / chunk);
   float b1[8], b2[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const float2 z = ok[i] ? make_float2((s[i].x * u[i].x - s[i].y * u[i].y) * sc,
-                                         (s[i].x * u[i].y + s[i].y * u[i].x) * sc)
+    const float2 z = ok[i] ? make_float2((s[i].x * u[i].x - s[i].y * u[i].y) * f,
+                                         (s[i].x * u[i].y + s[i].y * u[i].x) * f)
                            : make_float2(0.f, 0.f);
     b1[i] = im ? z.y : z.x;
     b2[i] = im ? z.x : -z.y;
@@ -462,10 +492,10 @@ __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ 
 }
 
 // Adjoint operand: sign * y, y [B][T][C] (src), or the forward's partial sums
-// (part, added in FP64 in the order of the splits) minus y_meas (may be
+// (part, added in FP64 in the order of the splits, their signs undone) minus y_meas (may be
 // NULL).  Padded rows and columns are zero.  The residual is also kept as
 // yop [Tp][NCP] (its norm is the Rayleigh quotient and the data term).
-__global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ src, float sign,
+__global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ src, float sign, int chunk,
                                                     const float2 *__restrict__ part, int nsplit,
                                                     const float2 *__restrict__ y_meas, int64_t T, int64_t Tp, int C,
                                                     int NC, int NCP, u32x4 *__restrict__ ys,
@@ -503,8 +533,8 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
       for (int i = 0; i < 8; ++i) v[i] = p[(int64_t)i * NCP];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        sx[i] += v[i].x;
-        sy[i] += v[i].y;
+        sx[i] += split_sign(k) * v[i].x;
+        sy[i] += split_sign(k) * v[i].y;
       }
     }
 #pragma unroll
@@ -524,6 +554,7 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
   const float sc = data_scale(bnd, nbnd, src ? 0 : nsplit, inv_z, bnd_meas, (int)pz);
   if (blockIdx.x == 0 && threadIdx.x == 0) scl[2 * pz + 1] = sc;
   if (!live) return;
+  const float f = sc * split_sign(16 * (qg / NGP) / chunk);
   if (yop && !im) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) yop[(pz * Tp + t0 + i) * NCP + col] = y[i];
@@ -531,8 +562,8 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
   float b1[8], b2[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    b1[i] = (im ? y[i].y : y[i].x) * sc;
-    b2[i] = (im ? -y[i].x : y[i].y) * sc;
+    b1[i] = (im ? y[i].y : y[i].x) * f;
+    b2[i] = (im ? -y[i].x : y[i].y) * f;
   }
   write_rec3(ys + (pz * (Tp / 16) * NGP + qg) * kRec3 + lane, b1, b2);
 }
@@ -550,22 +581,27 @@ static void launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   const F32Args a{p.Tp, p.Rp, p.NCP, FWD ? p.fwd_chunk : p.adj_chunk, nsplit, p.nxq, p.nx, p.ny, p.dx, p.dy,
                   bf16_masks(), b.wmax};
   const dim3 grid(split_grid((FWD ? p.Tp : p.Rp) / 256 * nsplit), (unsigned)p.NGY, (unsigned)p.P);
-  auto go = [&](auto gw) {
+  auto go = [&](auto gw, auto fold) {
     constexpr int GW = decltype(gw)::value;
-    if constexpr (FWD) k_fwd_f32<NT, GW><<<grid, 256, 0, s>>>(own, uni, op, part, a);
-    else if constexpr (NT > 0) k_adj_f32<NT, GW><<<grid, 256, 0, s>>>(own, uni, op, part, a);
+    constexpr bool FOLD = decltype(fold)::value;
+    if constexpr (FWD) k_fwd_f32<NT, GW, FOLD><<<grid, 256, 0, s>>>(own, uni, op, part, a);
+    else if constexpr (NT > 0) k_adj_f32<NT, GW, FOLD><<<grid, 256, 0, s>>>(own, uni, op, part, a);
     else {
       // image rows that 256 pixels can touch (at most 17: nxq >= 16)
       const int nrow = std::min(256 / p.nxq + 2, (int)ceil_div(p.Rp, p.nxq));
       const size_t lds = (size_t)2 * kSamples * (4 * nrow + 1) * sizeof(double);
       if (lds > 65536)
-        hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_f32_sh<GW>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_f32_sh<GW, FOLD>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      k_adj_f32_sh<GW><<<grid, 256, lds, s>>>(own, uni, op, part, a, nrow);
+      k_adj_f32_sh<GW, FOLD><<<grid, 256, lds, s>>>(own, uni, op, part, a, nrow);
     }
   };
-  if (p.GW == 2) go(std::integral_constant<int, 2>{});
-  else go(std::integral_constant<int, 1>{});
+  auto go_gw = [&](auto fold) {
+    if (p.GW == 2) go(std::integral_constant<int, 2>{}, fold);
+    else go(std::integral_constant<int, 1>{}, fold);
+  };
+  if (FWD ? p.fwd_fold : p.adj_fold) go_gw(std::true_type{});
+  else go_gw(std::false_type{});
 }
 
 template <bool FWD>
@@ -590,7 +626,8 @@ int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x
   if (!prepared) EX_TRY(bound_image(p, x, nullptr, x_stride, x_row_stride, x_pstride, b, s));
   k_build_z_f32<<<record_grid(p.Rp, p), 256, 0, s>>>(reinterpret_cast<const float2 *>(smaps), x, x_stride,
                                                      x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C, p.NC, p.NCP / 16,
-                                                     reinterpret_cast<u32x4 *>(b.zs), x_pstride, b.amax, b.scl);
+                                                     reinterpret_cast<u32x4 *>(b.zs), x_pstride, p.fwd_chunk, b.amax,
+                                                     b.scl);
   EX_LAUNCHED("build_z");
   return EXPENC_OK;
 }
@@ -599,7 +636,7 @@ int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_me
                hipStream_t s, bool prepared) {
   DataBound d;
   EX_TRY(bound_data(p, y, y_meas, b, prepared, &d, s));
-  k_pack_y_f32<<<record_grid(p.Tp, p), 256, 0, s>>>(y, sign, b.part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC,
+  k_pack_y_f32<<<record_grid(p.Tp, p), 256, 0, s>>>(y, sign, p.adj_chunk, b.part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC,
                                                     p.NCP, reinterpret_cast<u32x4 *>(b.ys), y ? nullptr : b.yop,
                                                     d.bnd, d.nbnd, d.meas, b.scl);
   EX_LAUNCHED("pack_y");

@@ -118,6 +118,9 @@ __device__ inline bool split_tile_rows(int b, int nrb, int nsplit, int *split, i
 }
 inline unsigned split_grid(int64_t n) { return (unsigned)((n + 7) / 8 * 8); }
 
+// Sign of split k's records and partial sums (FP32 form, see f32.hip).
+__device__ inline float split_sign(int64_t k) { return k & 1 ? -1.f : 1.f; }
+
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Coil combination in the epilogue of the split adjoint contractions (single
@@ -303,6 +306,7 @@ struct EncPlan {
   int32_t prec = 0;
   int32_t fwd_split = 1, fwd_chunk = 0;   // split-K over pixels
   int32_t adj_split = 1, adj_chunk = 0;   // split-K over samples
+  bool fwd_fold = false, adj_fold = false;  // FP32: steps added up outside the matrix instruction (f32.hip)
   // split forms with a single image (B == 1): the adjoint contraction
   // combines its coils in the epilogue and writes [adj_split][NGY][Rp]
   // partial images instead of [adj_split][Rp][NCP] per-coil partials
@@ -346,6 +350,9 @@ inline unsigned amax_blocks(int64_t n) {
 // contractions; pixels or samples in the FP32 contractions.
 constexpr int32_t kSplitAdjChunkMax = 1024;
 constexpr int32_t kF32ChunkMax = 2048;
+// Longest chunk of the FP32 kernels that add up their steps outside the matrix
+// instruction.
+constexpr int32_t kF32FoldMax = 64;
 
 int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p, int32_t nprob = 1);
 // Indexes per workgroup of a split reduction (see the definition).

@@ -313,3 +313,25 @@ def test_fp32_form_extreme_and_non_finite_operands(value, sh):
             assert np.all(np.abs(got[fits] - ref[fits]) <= 1e-6 * value)
         else:
             np.testing.assert_array_equal(got, ref)
+
+
+@pytest.mark.parametrize("n,coils,T,terms", [(40, 8, 3000, 9), (64, 32, 5000, 16)])
+@pytest.mark.parametrize("sh", [False, True], ids=["maps", "sh"])
+def test_fp32_form_sums_without_bias(n, coils, T, terms, sh):
+    """Random operands, where every output is a sum of many terms that nearly
+    cancel, and coil maps that add up the outputs of neighbouring coils: the
+    losses of the matrix instruction must neither grow with the sums nor add up
+    over splits and coils.  A rounded phase entry is off by 8e-8 (turns rounded
+    to FP32 5e-8, sine and cosine 6e-8), the sums and the result by 5e-8 and
+    3e-8 more: 1e-7, so 1.5e-7."""
+    import torch
+    ee = _ee()
+    w = synth.Workload("bias", n, 0.222, coils, T, 3e-6, 2.0, terms, 120.0, 20.0, 5, "haar", 1, 77)
+    case = Case(w, sh=sh)
+    x = c64(synth.random_complex((1, w.npix), 78))
+    y = c64(synth.random_complex((1, T, coils), 79))
+    args = case.oracle_args()
+    f = rel(ee.forward(case.to_dev(x), case.op).cpu().numpy()[0], encoding.forward(x[0], *args))
+    a = rel(ee.adjoint(case.to_dev(y), case.op).cpu().numpy()[0], encoding.adjoint(y[0], *args))
+    print(f"[case] bias {n} px {coils} coils T={T} sh={sh}: forward {f:.2e}, adjoint {a:.2e}", flush=True)
+    assert f <= 1.5e-7 and a <= 1.5e-7

@@ -131,7 +131,8 @@ int expenc_sh_basis(int32_t nx, int32_t ny, double fov_x, double fov_y, double z
 
 /* Bytes of workspace needed by the call `what` for this operator, batch and
  * precision (for EXPENC_WS_FISTA also the wavelet grid nx_pad x ny_pad; pass
- * 0 for the default).  Returns 0 on invalid arguments. */
+ * 0 for the default).  The forward and the adjoint need the same, so one
+ * workspace serves both.  Returns 0 on invalid arguments. */
 size_t expenc_workspace_size(const expenc_op *op, int32_t batch, int32_t precision,
                              int32_t what, int32_t nx_pad, int32_t ny_pad);
 
@@ -158,8 +159,9 @@ int expenc_adjoint(const expenc_op *op, int32_t batch, int32_t precision,
  * first call on a device until the process ends; the call itself allocates
  * nothing.  The forward's reduction split is lowered as far as needed to fit
  * (not below the FP32 form's chunk limit, so results may differ from
- * expenc_forward by summation order only); an operator whose forward does not
- * fit returns EXPENC_EWORKSPACE.  All calls on one device share the array:
+ * expenc_forward by summation order only), and the FP32 form then holds the
+ * packed operand of fewer splits and column groups at a time; an operator whose
+ * forward does not fit returns EXPENC_EWORKSPACE.  All calls on one device share the array:
  * calls that overlap on one device (different streams, other threads) race,
  * and must be ordered by the caller.  x: [B][R], y: [B][T][C] as in
  * expenc_forward.

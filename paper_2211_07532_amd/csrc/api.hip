@@ -213,7 +213,7 @@ int normal_apply(const EncPlan &p, const expenc_op *op, const EncBuffers &eb, co
 size_t lipschitz_bytes(const EncPlan &p1) {
   Arena a;
   EncBuffers eb;
-  carve_enc(p1, a, &eb);
+  carve_enc(p1, a, &eb, kNeedBoth);
   a.take<float2>((size_t)p1.R * p1.P);
   a.take<float2>((size_t)p1.R * p1.P);
   a.take<double>((size_t)kRedBlocks * p1.P + 8 * p1.P);
@@ -304,7 +304,7 @@ extern "C" int expenc_forward(const expenc_op *op, int32_t batch, int32_t precis
   if (!x || !y) return fail(EXPENC_EINVAL, "x or y is NULL");
   Arena a{static_cast<char *>(ws), ws_bytes, 0};
   EncBuffers eb;
-  if (carve_enc(p, a, &eb) != EXPENC_OK || !ws)
+  if (carve_enc(p, a, &eb, kNeedForward) != EXPENC_OK || !ws)
     return fail(EXPENC_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 enc_operand_bytes(p));
   hipStream_t s = (hipStream_t)stream;
@@ -322,7 +322,7 @@ extern "C" int expenc_adjoint(const expenc_op *op, int32_t batch, int32_t precis
   if (!x || !y) return fail(EXPENC_EINVAL, "x or y is NULL");
   Arena a{static_cast<char *>(ws), ws_bytes, 0};
   EncBuffers eb;
-  if (carve_enc(p, a, &eb) != EXPENC_OK || !ws)
+  if (carve_enc(p, a, &eb, kNeedAdjoint) != EXPENC_OK || !ws)
     return fail(EXPENC_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 enc_operand_bytes(p));
   hipStream_t s = (hipStream_t)stream;
@@ -340,7 +340,7 @@ extern "C" int expenc_lipschitz(const expenc_op *op, int32_t precision, int32_t 
   if (n_iter < 0 || !v0 || !lipschitz_out) return fail(EXPENC_EINVAL, "bad lipschitz arguments");
   Arena a{static_cast<char *>(ws), ws_bytes, 0};
   EncBuffers eb;
-  carve_enc(p1, a, &eb);
+  carve_enc(p1, a, &eb, kNeedBoth);
   float2 *vec = a.take<float2>((size_t)p1.R);
   float2 *tmp = a.take<float2>((size_t)p1.R);
   double *dpart = a.take<double>(kRedBlocks + 8);

@@ -477,7 +477,7 @@ int layout_bal(const expenc_op *op, int32_t batch, const expenc_balanced_opts *o
   L->nb = 3 * o->levels + 1;
   L->B = batch;
   L->N = (int64_t)op->nx * op->ny;
-  carve_enc(L->p, a, &L->eb, {&L->p1, &L->pf});
+  carve_enc(L->p, a, &L->eb, kNeedBoth, {&L->p1, &L->pf});
   const size_t coef = (size_t)batch * L->nb * L->N, img = (size_t)batch * L->N;
   L->a0 = a.take<float2>(coef);
   L->a1 = a.take<float2>(coef);

@@ -408,10 +408,8 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   q.L = op->nbasis;
   q.NT = phase_terms(q.L);
   q.prec = precision;
-  q.has_dw0 = op->dw0 != nullptr;
   q.P = nprob;
   q.scaled = precision != EXPENC_BF16_SPLIT;
-  q.adj_anc = q.sh && precision != EXPENC_FP32;
   // Partial sums of the default splits, unless kTargetWorkgroups makes them
   // longer: at most 64 indexes in the FP32 form, whose error they set (64 x 64
   // to 128 x 128: 1.1 to 2.2 times smaller than with 512, at the same times),
@@ -467,89 +465,100 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   return EXPENC_OK;
 }
 
-size_t enc_operand_bytes(const EncPlan &p) {
+static size_t enc_bytes(const EncPlan &p, int need) {
   Arena a;
   EncBuffers b;
-  carve_enc(p, a, &b);
+  carve_enc(p, a, &b, need);
   return a.used + 256;
 }
+
+// (one size for both directions: a caller may keep one workspace for them)
+size_t enc_operand_bytes(const EncPlan &p) { return std::max(enc_bytes(p, kNeedForward), enc_bytes(p, kNeedAdjoint)); }
 
 int plan_forward_within(const expenc_op *op, int32_t batch, int32_t precision, size_t cap, EncPlan *p) {
   EncPlan q;
   EX_TRY(make_plan(op, batch, precision, &q));
-  // the forward uses no adjoint partial sums: one adjoint split keeps them small
-  q.adj_split = 1;
-  q.adj_anc = false;
-  q.adj_chunk = (int32_t)q.Tp;
   const int32_t min_split = q.prec == EXPENC_FP32 ? (int32_t)ceil_div(q.Rp, kF32ChunkMax) : 1;
   auto set_split = [&](int32_t want) {
     q.fwd_chunk = (int32_t)round_up(ceil_div(q.Rp, want), fwd_grain(q));
     if (q.prec == EXPENC_FP32) q.fwd_chunk = std::min(q.fwd_chunk, kF32ChunkMax);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
-    q.fwd_fold = q.fwd_fold && q.fwd_chunk <= kF32FoldMax;
+    q.fwd_fold = q.prec == EXPENC_FP32;  // (sums longer than the default's: folded, or their error grows)
   };
-  while (enc_operand_bytes(q) > cap && q.fwd_split > min_split)
+  auto fits = [&] { return enc_bytes(q, kNeedForward) <= cap; };
+  while (!fits() && q.fwd_split > min_split)
     set_split(std::max<int32_t>(min_split, q.fwd_split - std::max<int32_t>(1, q.fwd_split / 4)));
-  if (enc_operand_bytes(q) > cap)
+  // the FP32 form's records take three times the operand's bytes: hold those of
+  // fewer splits, then of fewer column blocks (whose phases are evaluated again)
+  if (q.prec == EXPENC_FP32 && !fits()) {
+    q.pass_split = q.fwd_split;
+    q.pass_gy = q.NGY;
+    while (!fits() && q.pass_split > 1) q.pass_split = (q.pass_split + 1) / 2;
+    while (!fits() && q.pass_gy > 1) q.pass_gy = (q.pass_gy + 1) / 2;
+  }
+  if (!fits())
     return fail(EXPENC_EWORKSPACE, "the forward of this operator needs %zu bytes of scratch, more than the %zu "
-                "of the static scratch (use expenc_forward with a workspace)", enc_operand_bytes(q), cap);
+                "of the static scratch (use expenc_forward with a workspace)", enc_bytes(q, kNeedForward), cap);
   *p = q;
   return EXPENC_OK;
 }
 
-size_t enc_part_elems(const EncPlan &p) {
-  const size_t pf = (size_t)p.fwd_split * p.Tp * p.NCP;
-  const size_t pa = (size_t)p.adj_split * p.Rp * (p.comb ? p.NGY : p.NCP);
-  return std::max(pf, pa) * p.P;
-}
-
-int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, std::initializer_list<const EncPlan *> with) {
+int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, int need, std::initializer_list<const EncPlan *> with) {
+  const bool fwd = (need & kNeedForward) != 0, adj = (need & kNeedAdjoint) != 0;
   const size_t P = p.P;
-  size_t part = enc_part_elems(p);
-  int32_t nwmax = p.nwmax;
-  bool scaled = p.scaled;
-  for (const EncPlan *q : with) {
-    part = std::max(part, enc_part_elems(*q));
-    nwmax = std::max(nwmax, q->nwmax);
-    scaled = scaled || q->scaled;
-  }
-  b->kap = a.take<double>(P * p.Tp * p.NT);
-  b->bet = a.take<double>(P * p.Rp * p.NT);
-  // operand records: 384 bytes per step row and 16 columns (FP32 form, three
-  // bf16 parts) hold the split forms' 256 as well
-  // (column groups rounded up to a pair: a solver's FP32 plan shares these
-  // with its split plan, whose column width may be tuned differently)
-  const size_t NG = round_up(p.G, 2);
-  b->zs = a.take<char>(P * p.Rp * NG * 384);
-  b->ys = a.take<char>(P * p.Tp * NG * 384);
-  b->yop = a.take<float2>(P * p.Tp * NG * 16);
-  b->part = a.take<float2>(part);
-  if (p.sh) {
-    // polynomial phase tables (every precision; dpa: the split adjoint's
-    // increment operand)
-    b->pmono = a.take<double>(P * p.Tp * kPolyStride);
-    b->dpa = a.take<float>(P * p.Tp * 16);
-    b->dwq = a.take<double>(P * p.Rp);
-    b->ddw = a.take<float>(P * p.Rp);
-    if (p.adj_anc) b->anc = a.take<float>(P * (p.Tp / 32) * p.Rp);
-  }
-  if (p.prec != EXPENC_FP32) {
-    if (p.comb) b->sq = a.take<float2>(P * p.Rp * p.NCP);
-    if (!p.sh) {
-      b->dbet = a.take<float>(P * p.Rp * round_up(p.NT, 2));
-      b->dkap = a.take<float>(P * p.Tp * round_up(p.NT, 2));
+  size_t part = 0, rec = 0, yop = 0;
+  int32_t nwmax = 0;
+  bool scaled = false, f32 = false;
+  auto plan = [&](const EncPlan &q) {
+    const size_t g = q.NCP / 16 * (q.prec == EXPENC_FP32 ? 384 : 256);  // record bytes per index
+    if (fwd) {
+      part = std::max(part, P * q.fwd_split * q.Tp * q.NCP);
+      rec = std::max(rec, q.pass_split ? (size_t)std::min<int64_t>(q.Rp, (int64_t)q.pass_split * q.fwd_chunk) *
+                                             std::min(q.NCP / 16, q.pass_gy * q.GW) * 384
+                                       : P * q.Rp * g);
+      nwmax = std::max(nwmax, q.nwmax);
     }
+    if (adj) {
+      part = std::max(part, P * q.adj_split * q.Rp * (q.comb ? q.NGY : q.NCP));
+      rec = std::max(rec, P * q.Tp * g);
+    }
+    if (q.prec == EXPENC_FP32) {
+      f32 = true;
+      if (need == kNeedBoth) yop = std::max(yop, P * q.Tp * q.NCP);
+    }
+    scaled = scaled || q.scaled;
+  };
+  plan(p);
+  for (const EncPlan *q : with) plan(*q);
+  b->part = a.take<float2>(part);
+  b->zs = b->ys = a.take<char>(rec);
+  if (yop) b->yop = a.take<float2>(yop);
+  const bool split = p.prec != EXPENC_FP32;
+  if (p.sh) {
+    // polynomial phase tables
+    if (fwd || f32) b->pmono = a.take<double>(P * p.Tp * kPolyStride);
+    b->dwq = a.take<double>(P * p.Rp);
+    if (split && fwd) b->ddw = a.take<float>(P * p.Rp);
+    if (split && adj) {
+      b->dpa = a.take<float>(P * p.Tp * 16);
+      b->anc = a.take<float>(P * (p.Tp / 32) * p.Rp);
+    }
+  } else {
+    b->kap = a.take<double>(P * p.Tp * p.NT);
+    b->bet = a.take<double>(P * p.Rp * p.NT);
+    if (split && fwd) b->dbet = a.take<float>(P * p.Rp * round_up(p.NT, 2));
+    if (split && adj) b->dkap = a.take<float>(P * p.Tp * round_up(p.NT, 2));
   }
+  if (p.comb && adj) b->sq = a.take<float2>(P * p.Rp * p.NCP);
   if (scaled) {
     b->scl = a.take<float>(P * 2);
     b->amax = a.take<float>(P * 3 * kAmaxBlocks);
-    b->wmax = a.take<float>(P * nwmax);
+    b->wmax = a.take<float>(std::max<size_t>(1, P * nwmax));
   }
   return a.ok() ? EXPENC_OK : EXPENC_EWORKSPACE;
 }
 
-static inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)ceil_div(n, bs); }
 static inline dim3 grid_p(int64_t n, int bs, int P) { return dim3((unsigned)ceil_div(n, bs), (unsigned)P); }
 
 int enc_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride,
@@ -670,8 +679,7 @@ int enc_forward_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s, b
 
 int enc_adjoint_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   if (p.comb && !b.sq) return fail(EXPENC_EINVAL, "coil table of a single-image split plan is not carved");
-  if (p.adj_anc && !b.anc) return fail(EXPENC_EINVAL, "anchor table of a split plan is not carved");
-  if (p.sh && p.prec != EXPENC_FP32 && !p.adj_anc) return fail(EXPENC_EINVAL, "forward-only plan");
+  if (p.sh && p.prec != EXPENC_FP32 && !b.anc) return fail(EXPENC_EINVAL, "anchor table of a split plan is not carved");
   timed(1, s, [&] {
     if (p.prec != EXPENC_FP32) {
       split_adjoint_launch(p, b, s);

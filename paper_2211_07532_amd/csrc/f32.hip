@@ -104,7 +104,7 @@ __device__ inline void load_uniform(const double *__restrict__ u, int off, doubl
 
 struct F32Args {
   int64_t Tp;
-  int Rp, NCP, chunk, nsplit, nxq, nx, ny;
+  int Rp, NCP, NGP, chunk, nsplit, nxq, nx, ny, pix0;  // NGP, Rp, pix0: groups, pixels and first pixel of a pass
   double dx, dy;
   Bf16Masks mk;
   float *wmax;  // forward: per-wave maxima of the partial sums
@@ -234,7 +234,7 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
   }
   const int64_t row0 = (int64_t)rb * 256 + wave * 64;
   const int g0 = blockIdx.y * GW;
-  const int NGP = a.NCP / 16;
+  const int NGP = a.NGP;
   constexpr int NP = NT ? NT : 11;
   constexpr int S = NT ? NT : kPolyStride;  // row strides of the tables
   own += pz * (NT ? rows : a.Tp) * S;
@@ -259,7 +259,7 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
   if constexpr (NT == 0) {
     Pipe<GW, FOLD> pp;
     RowCubic rc;
-    rc.start((int)k0, a.nxq);
+    rc.start(a.pix0 + (int)k0, a.nxq);
     float f[16];
     const int64_t step = (int64_t)NGP * kRec3;
     const u32x4 *__restrict__ cur = op + (k0 >> 4) * step;
@@ -440,22 +440,24 @@ __global__ __launch_bounds__(256, 2) void k_adj_f32_sh(const double *__restrict_
 // ---------------------------------------------------------------------------
 
 // Z[r'][col] = S_c(r) x_b(r), col = b*C + c, row r' = y*nxq + x of pixel
-// r = y*nx + x; zero for padded pixels and columns.
+// r = y*nx + x; zero for padded pixels and columns.  npix pixels from pix0 on and
+// NGP column groups from gf on (a pass, or all).
 __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ smaps, const float2 *__restrict__ x,
                                                      int64_t x_stride, int x_row_stride, int nx, int ny, int nxq,
-                                                     int Rp, int C, int NC, int NGP, u32x4 *__restrict__ zs,
-                                                     int64_t x_pstride, int chunk, const float *__restrict__ amax,
+                                                     int npix, int pix0, int C, int NC, int gf, int NGP,
+                                                     u32x4 *__restrict__ zs, int64_t x_pstride, int chunk,
+                                                     const float *__restrict__ amax,
                                                      float *__restrict__ scl) {
   const int R = nx * ny;
   const int64_t pz = blockIdx.y;
   int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const bool live = id < (int64_t)(Rp / 16) * NGP * 64;
+  const bool live = id < (int64_t)(npix / 16) * NGP * 64;
   if (!live) id = 0;
   const int lane = (int)(id & 63);
   const int64_t qg = id >> 6;
-  const int g = (int)(qg % NGP);
+  const int g = gf + (int)(qg % NGP);
   const int col = 16 * g + (lane & 15), im = (lane >> 4) & 1;
-  const int rq0 = (int)(16 * (qg / NGP) + 8 * (lane >> 5));
+  const int rq0 = pix0 + (int)(16 * (qg / NGP) + 8 * (lane >> 5));
   int yy = rq0 / nxq, xx = rq0 - yy * nxq;
   const bool colok = col < NC;
   const int b = colok ? col / C : 0, c = colok ? col % C : 0;
@@ -478,7 +480,7 @@ __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ 
   const float sc = image_scale(amax, (int)pz, gridDim.y);
   if (blockIdx.x == 0 && threadIdx.x == 0) scl[2 * pz] = sc;
   if (!live) return;
-  const float f = sc * split_sign(16 * (qg / NGP) / chunk);
+  const float f = sc * split_sign((pix0 + 16 * (qg / NGP)) / chunk);
   float b1[8], b2[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(256) void k_build_z_f32(const float2 *__restrict__ 
     b1[i] = im ? z.y : z.x;
     b2[i] = im ? z.x : -z.y;
   }
-  write_rec3(zs + (pz * (Rp / 16) * NGP + qg) * kRec3 + lane, b1, b2);
+  write_rec3(zs + (pz * (npix / 16) * NGP + qg) * kRec3 + lane, b1, b2);
 }
 
 // Adjoint operand: sign * y, y [B][T][C] (src), or the forward's partial sums
@@ -572,63 +574,112 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
 // Launchers
 // ---------------------------------------------------------------------------
 
-template <int NT, bool FWD>
-static void launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  const int nsplit = FWD ? p.fwd_split : p.adj_split;
-  const double *own = NT ? (FWD ? b.kap : b.bet) : b.pmono, *uni = NT ? (FWD ? b.bet : b.kap) : b.dwq;
-  const u32x4 *op = reinterpret_cast<const u32x4 *>(FWD ? b.zs : b.ys);
+// Reduction splits and column blocks of a forward launch.
+struct Pass {
+  int split0, nsplit, gy0, ngy;
+};
+static Pass whole(const EncPlan &p) { return Pass{0, p.fwd_split, 0, p.NGY}; }
+static int pass_pixels(const EncPlan &p, const Pass &w) {
+  return (int)std::min<int64_t>(p.Rp - (int64_t)w.split0 * p.fwd_chunk, (int64_t)w.nsplit * p.fwd_chunk);
+}
+
+// go(column groups per wave, FOLD)
+template <class Go>
+static void variant(const EncPlan &p, bool fold, Go go) {
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  if (fold) p.GW == 2 ? go(Two{}, std::true_type{}) : go(One{}, std::true_type{});
+  else p.GW == 2 ? go(Two{}, std::false_type{}) : go(One{}, std::false_type{});
+}
+
+template <int NT>
+static void launch_forward(const EncPlan &p, const EncBuffers &b, const Pass &w, hipStream_t s) {
+  const int pix0 = w.split0 * p.fwd_chunk;
+  const double *own = NT ? b.kap : b.pmono, *uni = NT ? b.bet + (size_t)pix0 * NT : b.dwq + pix0;
+  const u32x4 *op = reinterpret_cast<const u32x4 *>(b.zs);
+  float *part = reinterpret_cast<float *>(b.part + ((int64_t)w.split0 * p.Tp * p.NCP + w.gy0 * p.GW * 16));
+  const F32Args a{p.Tp, pass_pixels(p, w), p.NCP, w.ngy * p.GW, p.fwd_chunk, w.nsplit, p.nxq, p.nx, p.ny, pix0,
+                  p.dx, p.dy, bf16_masks(), b.wmax};
+  const dim3 grid(split_grid(p.Tp / 256 * w.nsplit), (unsigned)w.ngy, (unsigned)p.P);
+  variant(p, p.fwd_fold, [&](auto gw, auto fold) {
+    k_fwd_f32<NT, decltype(gw)::value, decltype(fold)::value><<<grid, 256, 0, s>>>(own, uni, op, part, a);
+  });
+}
+
+template <int NT>
+static void launch_adjoint(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
+  const u32x4 *op = reinterpret_cast<const u32x4 *>(b.ys);
   float *part = reinterpret_cast<float *>(b.part);
-  const F32Args a{p.Tp, p.Rp, p.NCP, FWD ? p.fwd_chunk : p.adj_chunk, nsplit, p.nxq, p.nx, p.ny, p.dx, p.dy,
-                  bf16_masks(), b.wmax};
-  const dim3 grid(split_grid((FWD ? p.Tp : p.Rp) / 256 * nsplit), (unsigned)p.NGY, (unsigned)p.P);
-  auto go = [&](auto gw, auto fold) {
+  const F32Args a{p.Tp, p.Rp, p.NCP, p.NCP / 16, p.adj_chunk, p.adj_split, p.nxq, p.nx, p.ny, 0,
+                  p.dx, p.dy, bf16_masks(), nullptr};
+  const dim3 grid(split_grid((int64_t)p.Rp / 256 * p.adj_split), (unsigned)p.NGY, (unsigned)p.P);
+  variant(p, p.adj_fold, [&](auto gw, auto fold) {
     constexpr int GW = decltype(gw)::value;
     constexpr bool FOLD = decltype(fold)::value;
-    if constexpr (FWD) k_fwd_f32<NT, GW, FOLD><<<grid, 256, 0, s>>>(own, uni, op, part, a);
-    else if constexpr (NT > 0) k_adj_f32<NT, GW, FOLD><<<grid, 256, 0, s>>>(own, uni, op, part, a);
-    else {
+    if constexpr (NT > 0) {
+      k_adj_f32<NT, GW, FOLD><<<grid, 256, 0, s>>>(b.bet, b.kap, op, part, a);
+    } else {
       // image rows that 256 pixels can touch (at most 17: nxq >= 16)
       const int nrow = std::min(256 / p.nxq + 2, (int)ceil_div(p.Rp, p.nxq));
       const size_t lds = (size_t)2 * kSamples * (4 * nrow + 1) * sizeof(double);
       if (lds > 65536)
         hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_f32_sh<GW, FOLD>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      k_adj_f32_sh<GW, FOLD><<<grid, 256, lds, s>>>(own, uni, op, part, a, nrow);
+      k_adj_f32_sh<GW, FOLD><<<grid, 256, lds, s>>>(b.pmono, b.dwq, op, part, a, nrow);
     }
-  };
-  auto go_gw = [&](auto fold) {
-    if (p.GW == 2) go(std::integral_constant<int, 2>{}, fold);
-    else go(std::integral_constant<int, 1>{}, fold);
-  };
-  if (FWD ? p.fwd_fold : p.adj_fold) go_gw(std::true_type{});
-  else go_gw(std::false_type{});
+  });
 }
 
-template <bool FWD>
-static void launch_nt(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  if (p.sh) return launch<0, FWD>(p, b, s);
+static void forward_pass(const EncPlan &p, const EncBuffers &b, const Pass &w, hipStream_t s) {
+  if (p.sh) return launch_forward<0>(p, b, w, s);
   switch (p.NT) {
-    case 4: return launch<4, FWD>(p, b, s);
-    case 10: return launch<10, FWD>(p, b, s);
-    default: return launch<17, FWD>(p, b, s);
+    case 4: return launch_forward<4>(p, b, w, s);
+    case 10: return launch_forward<10>(p, b, w, s);
+    default: return launch_forward<17>(p, b, w, s);
   }
 }
 
-void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) { launch_nt<true>(p, b, s); }
-void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) { launch_nt<false>(p, b, s); }
+void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) { forward_pass(p, b, whole(p), s); }
 
-static dim3 record_grid(int64_t len, const EncPlan &p) {
-  return dim3((unsigned)ceil_div(len / 16 * (p.NCP / 16) * 64, 256), (unsigned)p.P);
+void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
+  if (p.sh) return launch_adjoint<0>(p, b, s);
+  switch (p.NT) {
+    case 4: return launch_adjoint<4>(p, b, s);
+    case 10: return launch_adjoint<10>(p, b, s);
+    default: return launch_adjoint<17>(p, b, s);
+  }
+}
+
+static dim3 record_grid(int64_t len, int groups, const EncPlan &p) {
+  return dim3((unsigned)ceil_div(len / 16 * groups * 64, 256), (unsigned)p.P);
+}
+
+// the records of a pass, of an image that is bounded
+static int build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
+                   const EncBuffers &b, const Pass &w, hipStream_t s, int64_t x_pstride) {
+  const int npix = pass_pixels(p, w), groups = w.ngy * p.GW;
+  k_build_z_f32<<<record_grid(npix, groups, p), 256, 0, s>>>(
+      reinterpret_cast<const float2 *>(smaps), x, x_stride, x_row_stride, p.nx, p.ny, p.nxq, npix,
+      w.split0 * p.fwd_chunk, p.C, p.NC, w.gy0 * p.GW, groups, reinterpret_cast<u32x4 *>(b.zs), x_pstride,
+      p.fwd_chunk, b.amax, b.scl);
+  EX_LAUNCHED("build_z");
+  return EXPENC_OK;
 }
 
 int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
                 const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared) {
   if (!prepared) EX_TRY(bound_image(p, x, nullptr, x_stride, x_row_stride, x_pstride, b, s));
-  k_build_z_f32<<<record_grid(p.Rp, p), 256, 0, s>>>(reinterpret_cast<const float2 *>(smaps), x, x_stride,
-                                                     x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C, p.NC, p.NCP / 16,
-                                                     reinterpret_cast<u32x4 *>(b.zs), x_pstride, p.fwd_chunk, b.amax,
-                                                     b.scl);
-  EX_LAUNCHED("build_z");
+  return build_z(p, smaps, x, x_stride, x_row_stride, b, whole(p), s, x_pstride);
+}
+
+int f32_forward_passes(const EncPlan &p, const float *smaps, const float2 *x, const EncBuffers &b, hipStream_t s) {
+  for (int s0 = 0; s0 < p.fwd_split; s0 += p.pass_split)
+    for (int g0 = 0; g0 < p.NGY; g0 += p.pass_gy) {
+      const Pass w{s0, std::min(p.pass_split, p.fwd_split - s0), g0, std::min(p.pass_gy, p.NGY - g0)};
+      EX_TRY(build_z(p, smaps, x, p.R, p.nx, b, w, s, 0));
+      forward_pass(p, b, w, s);
+      EX_LAUNCHED("forward contraction");
+    }
   return EXPENC_OK;
 }
 
@@ -636,9 +687,9 @@ int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_me
                hipStream_t s, bool prepared) {
   DataBound d;
   EX_TRY(bound_data(p, y, y_meas, b, prepared, &d, s));
-  k_pack_y_f32<<<record_grid(p.Tp, p), 256, 0, s>>>(y, sign, p.adj_chunk, b.part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC,
-                                                    p.NCP, reinterpret_cast<u32x4 *>(b.ys), y ? nullptr : b.yop,
-                                                    d.bnd, d.nbnd, d.meas, b.scl);
+  k_pack_y_f32<<<record_grid(p.Tp, p.NCP / 16, p), 256, 0, s>>>(
+      y, sign, p.adj_chunk, b.part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP,
+      reinterpret_cast<u32x4 *>(b.ys), y ? nullptr : b.yop, d.bnd, d.nbnd, d.meas, b.scl);
   EX_LAUNCHED("pack_y");
   return EXPENC_OK;
 }

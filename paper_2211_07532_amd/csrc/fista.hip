@@ -337,7 +337,7 @@ static int layout_fista(const expenc_op *op, int32_t nprob, int32_t batch, int32
   L->P = nprob;
   L->B = batch;
   // the buffers are shared by all three plans (identical padded geometry)
-  carve_enc(L->p, a, &L->eb, {&L->p1, &L->pf});
+  carve_enc(L->p, a, &L->eb, kNeedBoth, {&L->p1, &L->pf});
   const size_t img = (size_t)nprob * batch * L->nxp * L->nyp;
   L->z = a.take<float2>(img);
   L->v = a.take<float2>(img);
@@ -617,7 +617,7 @@ struct CgLayout {
 static int layout_cg(const expenc_op *op, int32_t batch, int32_t precision, Arena &a, CgLayout *L) {
   EX_TRY(make_plan(op, batch, precision, &L->p));
   L->status = take_status(a);
-  carve_enc(L->p, a, &L->eb);
+  carve_enc(L->p, a, &L->eb, kNeedBoth);
   const size_t n = (size_t)batch * L->p.R;
   L->xv = a.take<float2>(n);
   L->rv = a.take<float2>(n);

@@ -379,9 +379,9 @@ static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLay
     G->pmono = a.take<double>(p.Tp * kPolyStride);
     G->dwq = a.take<double>(p.Rp);
   } else {
+    G->kap = a.take<double>((size_t)p.Tp * p.NT);
     G->bet = a.take<double>((size_t)p.Rp * p.NT);
   }
-  G->kap = a.take<double>(p.Tp * p.NT);
   G->kb = a.take<u32x4>((size_t)p.Tp * G->CK * 12);
   G->za = a.take<u32x4>((size_t)p.Rp * G->CK * 12);
   G->tf = a.take<float>(p.Tp);

@@ -311,11 +311,6 @@ struct EncPlan {
   // combines its coils in the epilogue and writes [adj_split][NGY][Rp]
   // partial images instead of [adj_split][Rp][NCP] per-coil partials
   bool comb = false;
-  // split forms with the solid-harmonic basis: the adjoint contraction reads
-  // its per-tile FP64 phase anchors from a table built at preparation
-  // (EncBuffers::anc); off for forward-only plans
-  bool adj_anc = false;
-  bool has_dw0 = false;
   // Solid-harmonic basis given by grid geometry (EXPENC_BASIS_SH).  Split
   // forms with it lay pixels out row-padded: r' = y*nxq + x, nxq = nx rounded
   // up to 16, so that every 16-pixel step lies inside one image row.
@@ -336,6 +331,9 @@ struct EncPlan {
   // per-wave output maxima (the residual operand's bound).
   bool scaled = false;
   int32_t nwmax = 0;
+  // FP32 forward in passes (plan_forward_within): reduction splits and column
+  // blocks per pass, whose records alone are held at a time; 0: one pass.
+  int32_t pass_split = 0, pass_gy = 0;
 };
 
 constexpr int kPolyStride = 12;  // row stride of the polynomial coefficient table (11 used)
@@ -361,12 +359,14 @@ int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots,
 
 // Device buffers of one operator application, carved from the workspace.
 struct EncBuffers {
-  double *kap = nullptr;   // [Tp][NT] field coefficients in turns (+ time)
-  double *bet = nullptr;   // [Rp][NT] basis values (+ dw0 in turns/s)
+  double *kap = nullptr;   // general basis: [Tp][NT] field coefficients in turns (+ time)
+  double *bet = nullptr;   // general basis: [Rp][NT] basis values (+ dw0 in turns/s)
   float2 *yop = nullptr;   // FP32 form: [Tp][NCP] the residual, beside its packed records
   float2 *part = nullptr;  // split-K partial sums (max of forward and adjoint)
-  void *zs = nullptr;      // packed forward operand [Rp/16][NCP/16][parts][64] x 16 B, parts 4 (split forms) or 6
-  void *ys = nullptr;      // packed adjoint operand [Tp/16][NCP/16][parts][64] x 16 B
+  // packed forward operand [Rp/16][NCP/16][parts][64] x 16 B, parts 4 (split
+  // forms) or 6, and packed adjoint operand [Tp/16] ...: the same memory, as a
+  // forward is done with its records before the data's are written
+  void *zs = nullptr, *ys = nullptr;
   // split forms: bet and kap minus those of index 8 of their 16 (FP32), per 32
   // indexes [pair of terms][term of the pair][index], zero past NT
   float *dbet = nullptr, *dkap = nullptr;
@@ -374,7 +374,7 @@ struct EncBuffers {
   float *dpa = nullptr;    // split + SH: [Tp/32][64][8] adjoint increment coefficients (FP32, per lane)
   double *dwq = nullptr;   // split + SH: [Rp] dw0/2pi in the row-padded pixel layout
   float *ddw = nullptr;    // split + SH: [Rp] dwq minus its 16-pixel tile centre (FP32)
-  float *anc = nullptr;    // split + SH, adj_anc: [Tp/32][Rp] FP64 phase of each 32-sample tile's centre
+  float *anc = nullptr;    // split + SH: [Tp/32][Rp] FP64 phase of each 32-sample tile's centre
                            // sample at each pixel, reduced to turns in [0, 1) (the adjoint's anchors)
   float2 *sq = nullptr;    // split, single image: [Rp][NCP] S_c(r) in the partial-sum layout (0 on padding)
   float *scl = nullptr;    // scaled form: [P][2] powers of two of the forward (0) and adjoint (1) operands
@@ -383,13 +383,12 @@ struct EncBuffers {
   float *wmax = nullptr;   // scaled form: [P][nwmax] per-wave max |partial sum| of the forward contraction
 };
 
+// Workspace of one application (of either direction).
 size_t enc_operand_bytes(const EncPlan &p);
-// Forward-only plan whose buffers (carve_enc) fit in cap bytes: one adjoint
-// split, and the forward split lowered from make_plan's as far as needed
-// (not below the FP32 chunk cap).  EXPENC_EWORKSPACE if even that is larger.
+// Plan whose forward's buffers (carve_enc) fit in cap bytes: the forward split
+// lowered from make_plan's as far as needed (not below the FP32 chunk cap), then
+// (FP32) fewer records at a time.  EXPENC_EWORKSPACE if even that is larger.
 int plan_forward_within(const expenc_op *op, int32_t batch, int32_t precision, size_t cap, EncPlan *p);
-// Split-K partial-sum elements (float2) a plan needs.
-size_t enc_part_elems(const EncPlan &p);
 // Runs body(stream) captured into a cached HIP graph keyed by `key` (or
 // eagerly when graphs are disabled), launched on s.
 int run_captured(uint64_t key, hipStream_t s, const std::function<int(hipStream_t)> &body);
@@ -415,9 +414,12 @@ inline bool anchor_in_fp32(int32_t anchor, int k, int K) {
 int set_tuning(const expenc_op *op, int32_t batch, int32_t precision, int32_t fwd_target, int32_t adj_target,
                int32_t col_groups);
 uint64_t tuning_generation();
-// Carves the buffers of plan p, large enough for the plans in `with` too (the
-// other plans of a solver: same geometry, other precision or batch).
-int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, std::initializer_list<const EncPlan *> with = {});
+// Carves the buffers that the directions in `need` use, of plan p and of the
+// plans in `with` (a solver's other plans: same geometry, other precision or
+// batch).
+enum { kNeedForward = 1, kNeedAdjoint = 2, kNeedBoth = 3 };
+int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, int need,
+              std::initializer_list<const EncPlan *> with = {});
 
 // Kernel launchers (stream-ordered, no synchronisation).
 // Field tables of plan p (prep.hip), one launch: those that the directions in
@@ -427,7 +429,6 @@ int carve_enc(const EncPlan &p, Arena &a, EncBuffers *b, std::initializer_list<c
 // records (bf16) or its magnitude bound (scaled forms, whose records need it)
 // are then written by the same launch, and enc_build_z / enc_pack_y are told so
 // (prepared = true).
-enum { kNeedForward = 1, kNeedAdjoint = 2, kNeedBoth = 3 };
 int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipStream_t s, int need,
                 const float2 *operand = nullptr);
 // Z[r][b*C+c] = S_c(r) x_b(r) from x [B][R] (x_stride elements between problems);
@@ -465,6 +466,9 @@ int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_
 // FP32 kernels (f32.hip).  f32_pack_y: from sign * y, or with y NULL the
 // forward's residual against y_meas (or NULL).
 void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
+// the forward of a plan in passes: records and contraction of each in turn (x
+// bounded by enc_prepare)
+int f32_forward_passes(const EncPlan &p, const float *smaps, const float2 *x, const EncBuffers &b, hipStream_t s);
 void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
                 const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared);

@@ -50,13 +50,17 @@ extern "C" int expenc_forward_static(const expenc_op *op, int32_t batch, int32_t
   EX_TRY(scratch_for_current_device(&base));
   Arena a{static_cast<char *>(base), kStaticScratchBytes, 0};
   EncBuffers eb;
-  if (carve_enc(p, a, &eb) != EXPENC_OK)
+  if (carve_enc(p, a, &eb, kNeedForward) != EXPENC_OK)
     return fail(EXPENC_EWORKSPACE, "forward scratch of %zu bytes exceeds the static %zu", a.used,
                 kStaticScratchBytes);
   hipStream_t s = (hipStream_t)stream;
   const float2 *x2 = reinterpret_cast<const float2 *>(x);
   EX_TRY(enc_prepare(p, op, eb, s, kNeedForward, x2));
-  EX_TRY(enc_build_z(p, op->smaps, x2, p.R, p.nx, eb, s, nullptr, 0, true));
-  EX_TRY(enc_forward_partials(p, eb, s, false));
+  if (p.pass_split) {
+    EX_TRY(f32_forward_passes(p, op->smaps, x2, eb, s));
+  } else {
+    EX_TRY(enc_build_z(p, op->smaps, x2, p.R, p.nx, eb, s, nullptr, 0, true));
+    EX_TRY(enc_forward_partials(p, eb, s, false));
+  }
   return enc_forward_reduce_out(p, eb, reinterpret_cast<float2 *>(y), s);
 }

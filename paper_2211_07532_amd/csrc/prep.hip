@@ -307,11 +307,11 @@ int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipS
   if (p.sh) {
     a.pmono = b.pmono;
     a.dwq = b.dwq;
-    if (fwd || !split) n[kRolePoly] = ceil_div(p.Tp, 256);
+    if (b.pmono) n[kRolePoly] = ceil_div(p.Tp, 256);
     n[kRolePixel] = ceil_div(p.Rp, 256);
     if (split && fwd) a.ddw = b.ddw;
     if (split && adj) {
-      if (!p.adj_anc || !b.anc) return fail(EXPENC_EINVAL, "anchor table of a split plan is not carved");
+      if (!b.anc) return fail(EXPENC_EINVAL, "anchor table of a split plan is not carved");
       a.dpa = b.dpa;
       a.anc = b.anc;
       n[kRoleIncr] = ceil_div(p.Tp * 2, 256);

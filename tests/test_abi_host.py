@@ -236,3 +236,38 @@ def test_size_limits_are_reported_by_planning():
     assert lib.expenc_plan_info(ctypes.byref(ok), 0, 0, 1, out) == b.EXPENC_EINVAL     # batch < 1
     assert lib.expenc_plan_info(ctypes.byref(ok), 1, 0, 0, out) == b.EXPENC_EINVAL     # no problems
     assert lib.expenc_plan_info(ctypes.byref(ok), 1, 0, 65536, out) == b.EXPENC_EINVAL
+
+
+@pytest.mark.parametrize("n,coils,terms,samples,maps,batch,prec", [
+    (148, 32, 16, 34304, False, 1, 0), (148, 32, 16, 38912, True, 1, 0), (168, 32, 16, 27648, False, 1, 0),
+    (200, 32, 16, 19712, False, 1, 0), (200, 16, 16, 39424, False, 1, 0), (128, 16, 16, 89344, False, 1, 0),
+    (600, 16, 9, 256, True, 1, 0),          # many more pixels than samples: the image's records are the bulk
+    (40, 64, 9, 256, True, 64, 0),          # 4096 columns
+    (200, 32, 16, 64512, False, 1, 2), (148, 32, 16, 87040, True, 1, 1),
+])
+def test_static_forward_takes_the_operators_that_fit_unpacked(n, coils, terms, samples, maps, batch, prec):
+    """The forward without allocation accepts every operator whose operand,
+    unpacked in FP32 (8 bytes a pixel and column, and as much again a sample),
+    fits its 128 MiB with the partial sums of the longest chunks, whatever its
+    packed records take.  The plan is made before the arrays are looked at, so
+    NULL arrays tell acceptance from refusal without a device."""
+    b, lib = _lib()
+    op = _op(b, n, coils, samples, terms)
+    op.basis_kind = b.BASIS_MAPS if maps else b.BASIS_SH
+    op.basis = 0x1000
+    st = lib.expenc_forward_static(ctypes.byref(op), batch, prec, None, None, None)
+    assert st == b.EXPENC_EINVAL and b"x or y is NULL" in lib.expenc_last_error()
+    op.nsamples = 8 * samples + (1 << 20)
+    assert lib.expenc_forward_static(ctypes.byref(op), batch, prec, None, None, None) == b.EXPENC_EWORKSPACE
+
+
+def test_forward_and_adjoint_workspaces_are_one_size():
+    """A workspace sized for one direction serves the other."""
+    b, lib = _lib()
+    for prec in (0, 1, 2):
+        for maps in (False, True):
+            op = _op(b, 100, 20, 3000, 16)
+            op.basis_kind = b.BASIS_MAPS if maps else b.BASIS_SH
+            op.basis = 0x1000
+            f = [lib.expenc_workspace_size(ctypes.byref(op), 2, prec, w, 0, 0) for w in (0, 1)]
+            assert f[0] == f[1] > 0

@@ -65,3 +65,33 @@ def test_static_forward_rejects_operators_that_do_not_fit():
                                        ctypes.c_void_p(x.data_ptr()), None)
     assert st == b.EXPENC_EWORKSPACE
     assert b"static scratch" in b.lib().expenc_last_error()
+
+
+@pytest.mark.parametrize("n,coils,samples,batch,sh", [(200, 16, 47616, 1, True), (148, 32, 43776, 1, False),
+                                                      (40, 64, 256, 64, False), (40, 64, 256, 64, True)],
+                         ids=["sh", "maps", "maps-4096-columns", "sh-4096-columns"])
+def test_static_forward_near_its_limit_matches_workspace_forward(n, coils, samples, batch, sh):
+    """FP32 operators whose packed records do not fit the scratch beside the
+    partial sums: the static forward holds those of a few splits (of a few
+    column groups) at a time.  Only the summation order differs from the
+    workspace forward."""
+    import torch
+    import paper_2211_07532_amd as ee
+    from paper_2211_07532_amd import _binding as b
+    g = torch.Generator(device="cuda").manual_seed(n + coils)
+    rnd = lambda *s: torch.randn(s, dtype=torch.complex64, device="cuda", generator=g)  # noqa: E731
+    basis = ee.sh_basis(n, n, 0.2, 0.2, 0.002, 9)
+    coef = torch.randn((samples, 9), dtype=torch.float64, device="cuda", generator=g) * 20.0 / basis.abs().amax(1)
+    dw0 = 600.0 * torch.rand(n * n, dtype=torch.float64, device="cuda", generator=g)
+    time = torch.arange(samples, dtype=torch.float64, device="cuda") * 2e-6
+    op = ee.Operator(n, n, rnd(coils, n * n), coef, time, None if sh else basis, dw0,
+                     sh_grid=(0.2, 0.2, 0.002) if sh else None)
+    x = rnd(batch, n * n)
+    print(f"[case] static forward near its limit {n} px {coils} coils T={samples} B={batch} sh={sh}", flush=True)
+    y = torch.empty((batch, samples, coils), dtype=torch.complex64, device="cuda")
+    st = b.lib().expenc_forward_static(ctypes.byref(op._c), batch, b.FP32, ctypes.c_void_p(x.data_ptr()),
+                                       ctypes.c_void_p(y.data_ptr()),
+                                       ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    b.check(st, "expenc_forward_static")
+    ref = ee.forward(x, op)
+    assert float(torch.linalg.vector_norm(y - ref) / torch.linalg.vector_norm(ref)) <= 1e-6

@@ -9,9 +9,8 @@
 // with 1D filters f(u)[i] = 2^-1/2 sum_k f[k] u[(i + d k) mod n]; the last
 // LL is kept.  Coefficients are laid out [B][3J+1][ny][nx] (level j in
 // bands 3j .. 3j+2, the low pass last).  With orthonormal filters W is a
-// tight frame: W^H W = I.  Each level is one launch over 2D tiles in LDS, one
-// axis after the other with FP64 sums in between; W^H is the gather-form
-// adjoint.
+// tight frame: W^H W = I.  Each level is one launch, with FP64 sums; W^H is the
+// gather-form adjoint.
 //
 // Balanced model on the coefficients alpha:
 //   F = ||A W^H alpha - y||^2 + kappa/2 ||(I - W W^H) alpha||^2 + sum_b lambda_b ||alpha_b||_1,
@@ -46,15 +45,105 @@ __device__ inline int wrap_i(int i, int n) {
   return i;
 }
 
-// One level at tap spacing d works on lattices: the outputs of a tile are
+// One level at tap spacing d, one thread per pixel: the four bands of pixel i
+// from its TAPS x TAPS neighbourhood (FP64 sums in the same order for every
+// band).  The wrapped row and column indices are formed once per pixel.
+// Neighbouring threads read neighbouring pixels at any spacing.
+template <int TAPS>
+__global__ __launch_bounds__(256) void k_swt_direct(const float2 *__restrict__ u, int64_t ustride,
+                                                    float2 *__restrict__ bands, int64_t bstride,
+                                                    float2 *__restrict__ llout, int64_t lstride, int nx, int ny,
+                                                    int d, FilterSet f) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t N = (int64_t)nx * ny;
+  if (i >= N) return;
+  const int b = blockIdx.y;
+  u += b * ustride;
+  bands += b * bstride;
+  llout += b * lstride;
+  const int yy = (int)(i / nx), xx = (int)(i % nx);
+  int cols[TAPS];
+#pragma unroll
+  for (int k = 0; k < TAPS; ++k) cols[k] = wrap_i(xx + d * k, nx);
+  double s0x = 0, s0y = 0, s1x = 0, s1y = 0, s2x = 0, s2y = 0, slx = 0, sly = 0;
+#pragma unroll 1
+  for (int ky = 0; ky < TAPS; ++ky) {
+    const float2 *urow = u + (int64_t)wrap_i(yy + d * ky, ny) * nx;
+    const double hy = f.h[ky], gy = f.g[ky];
+#pragma unroll
+    for (int kx = 0; kx < TAPS; ++kx) {
+      const float2 v = urow[cols[kx]];
+      const double hx = f.h[kx], gx = f.g[kx];
+      const double w0 = gx * hy, w1 = hx * gy, w2 = gx * gy, wl = hx * hy;
+      s0x += w0 * v.x, s0y += w0 * v.y;
+      s1x += w1 * v.x, s1y += w1 * v.y;
+      s2x += w2 * v.x, s2y += w2 * v.y;
+      slx += wl * v.x, sly += wl * v.y;
+    }
+  }
+  bands[i] = make_float2((float)(0.5 * s0x), (float)(0.5 * s0y));
+  bands[N + i] = make_float2((float)(0.5 * s1x), (float)(0.5 * s1y));
+  bands[2 * N + i] = make_float2((float)(0.5 * s2x), (float)(0.5 * s2y));
+  llout[i] = make_float2((float)(0.5 * slx), (float)(0.5 * sly));
+}
+
+// The adjoint of one level: pixel i from the four bands at the TAPS x TAPS
+// neighbours i - d k.
+template <int TAPS>
+__global__ __launch_bounds__(256) void k_iswt_direct(const float2 *__restrict__ bands, int64_t bstride,
+                                                     const float2 *__restrict__ ll, int64_t lstride,
+                                                     float2 *__restrict__ u, int64_t ustride, int nx, int ny, int d,
+                                                     FilterSet f) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t N = (int64_t)nx * ny;
+  if (i >= N) return;
+  const int b = blockIdx.y;
+  bands += b * bstride;
+  ll += b * lstride;
+  u += b * ustride;
+  const int yy = (int)(i / nx), xx = (int)(i % nx);
+  int cols[TAPS];
+#pragma unroll
+  for (int k = 0; k < TAPS; ++k) cols[k] = wrap_i(xx - d * k, nx);
+  double sx = 0.0, sy = 0.0;
+#pragma unroll 1
+  for (int ky = 0; ky < TAPS; ++ky) {
+    const int64_t row = (int64_t)wrap_i(yy - d * ky, ny) * nx;
+    const double hy = f.h[ky], gy = f.g[ky];
+#pragma unroll
+    for (int kx = 0; kx < TAPS; ++kx) {
+      const int64_t o = row + cols[kx];
+      const double hx = f.h[kx], gx = f.g[kx];
+      const float2 a0 = bands[o], a1 = bands[N + o], a2 = bands[2 * N + o], al = ll[o];
+      const double w0 = gx * hy, w1 = hx * gy, w2 = gx * gy, wl = hx * hy;
+      sx += w0 * a0.x + w1 * a1.x + w2 * a2.x + wl * al.x;
+      sy += w0 * a0.y + w1 * a1.y + w2 * a2.y + wl * al.y;
+    }
+  }
+  u[i] = make_float2((float)(0.5 * sx), (float)(0.5 * sy));
+}
+
+// The same for 8 taps over 2D tiles in LDS.  A level at tap spacing d works on
+// lattices: the outputs of a tile are
 // kTX x kTY positions d apart along either axis, so that whatever the spacing
 // a tile needs TAPS - 1 further positions per axis (the periodic wrap may lead
 // to another residue mod d; positions are taken mod n one by one).  Grid:
 // (residues x tiles along x, times the same along y; images).
 // Both axes in turn cost 110 (analysis) and 134 (synthesis) FP64 operations a
-// pixel at 8 taps; one pass over the 64 neighbours cost 768.  36 images of
-// 148 x 148, one level: analysis 77 -> 16 us, synthesis 77 -> 19 us (7 us at
-// the copy rate).  The intermediate sums stay in FP64.
+// pixel; one pass over the 64 neighbours costs 768.  The intermediate sums stay
+// in FP64.
+// Positions d apart are not contiguous, and a tile of few positions is mostly
+// padding, so it is the better kernel only where the spacing is small (analysis)
+// and the tiles are filled; Haar's 4 neighbours need no tile.  Kernel times in us,
+// tiles / direct, by d = 1, 2, 4, ... (fill: positions of all tiles over pixels):
+//   36 x 148 x 148 (fill 1.2 1.4 2.2 2.8 5.1 20): analysis 14/44 18/44 31/45
+//     46/45 50/46 160/47, synthesis 19/107 25/107 38/108 45/109 77/108 260/108
+//   4 x 512 x 512 (1 1 1 1 1 2 8): analysis 14/50 14/48 23/48 40/48 68/48 67/48
+//     74/48, synthesis 20/125 19/122 24/123 36/122 59/123 54/123 129/124
+//   60 x 36 x 36 (2.4 3.2 6.3 20): analysis 6/13 7/13 9/15 21/13, synthesis
+//     7/18 8/19 11/19 28/19
+//   8 x 300 x 40, d = 8, 16 (5.4 9): synthesis 12/20 20/20
+//   Haar, 36 x 148 x 148: analysis 9/9 16/8 30/8, synthesis 12/11 17/13 33/12
 constexpr int kTX = 32, kTY = 16;
 
 // Tile t of the lattice tiling of n positions at spacing d with T per tile:
@@ -68,13 +157,18 @@ __device__ inline void lattice_tile(int t, int n, int d, int T, int &first, int 
 inline int lattice_tiles(int n, int d, int T) {
   return (int)(std::min(d, n) * ceil_div(ceil_div(n, d), T));
 }
+// Whether a level takes the tiles (by the times above).
+inline bool use_tiles(int taps, int nx, int ny, int d, bool synthesis) {
+  const double fill = (double)lattice_tiles(nx, d, kTX) * kTX * lattice_tiles(ny, d, kTY) * kTY / ((double)nx * ny);
+  return taps == 8 && (synthesis || d <= 4 ? fill <= 7 : d == 8 && fill <= 2);
+}
 
 // Analysis: u -> bands (x high, y low), (x low, y high), (high, high) at
 // bands + 0, N, 2N, and the low pass to llout.  Rows first (low and high
 // sums of kTX positions on kTY + TAPS - 1 rows), then columns, two positions
 // per thread.
 template <int TAPS>
-__global__ __launch_bounds__(256) void k_swt_level(const float2 *__restrict__ u, int64_t ustride,
+__global__ __launch_bounds__(256) void k_swt_tiles(const float2 *__restrict__ u, int64_t ustride,
                                                    float2 *__restrict__ bands, int64_t bstride,
                                                    float2 *__restrict__ llout, int64_t lstride, int nx, int ny, int ntx,
                                                    int d, FilterSet f) {
@@ -153,7 +247,7 @@ __global__ __launch_bounds__(256) void k_swt_level(const float2 *__restrict__ u,
 // Columns first (the x-low and x-high sums of kTY rows at kTX + TAPS - 1
 // positions), then rows.
 template <int TAPS>
-__global__ __launch_bounds__(256) void k_iswt_level(const float2 *__restrict__ bands, int64_t bstride,
+__global__ __launch_bounds__(256) void k_iswt_tiles(const float2 *__restrict__ bands, int64_t bstride,
                                                     const float2 *__restrict__ ll, int64_t lstride,
                                                     float2 *__restrict__ u, int64_t ustride, int nx, int ny, int ntx,
                                                     int d, FilterSet f) {
@@ -388,12 +482,16 @@ int swt_forward(const FilterSet &f, int nx, int ny, int J, int B, const float2 *
   for (int j = 0; j < J; ++j) {
     float2 *ll = (j == J - 1) ? w + (int64_t)3 * J * N : tmp + (int64_t)(j % 2) * B * N;
     const int64_t ls = (j == J - 1) ? nb * N : N;
-    const int ntx = lattice_tiles(nx, 1 << j, kTX);
-    const dim3 grid((unsigned)(ntx * (int64_t)lattice_tiles(ny, 1 << j, kTY)), (unsigned)B);
-    if (f.taps == 2)
-      k_swt_level<2><<<grid, 256, 0, s>>>(u, us, w + (int64_t)3 * j * N, nb * N, ll, ls, nx, ny, ntx, 1 << j, f);
+    const int d = 1 << j, ntx = lattice_tiles(nx, d, kTX);
+    float2 *bands = w + (int64_t)3 * j * N;
+    const dim3 tiles((unsigned)(ntx * (int64_t)lattice_tiles(ny, d, kTY)), (unsigned)B);
+    const dim3 grid((unsigned)ceil_div(N, 256), (unsigned)B);
+    if (use_tiles(f.taps, nx, ny, d, false))
+      k_swt_tiles<8><<<tiles, 256, 0, s>>>(u, us, bands, nb * N, ll, ls, nx, ny, ntx, d, f);
+    else if (f.taps == 2)
+      k_swt_direct<2><<<grid, 256, 0, s>>>(u, us, bands, nb * N, ll, ls, nx, ny, d, f);
     else
-      k_swt_level<8><<<grid, 256, 0, s>>>(u, us, w + (int64_t)3 * j * N, nb * N, ll, ls, nx, ny, ntx, 1 << j, f);
+      k_swt_direct<8><<<grid, 256, 0, s>>>(u, us, bands, nb * N, ll, ls, nx, ny, d, f);
     EX_LAUNCHED("undecimated analysis");
     u = ll;
     us = ls;
@@ -410,12 +508,16 @@ int swt_adjoint(const FilterSet &f, int nx, int ny, int J, int B, const float2 *
   int64_t ls = nb * N;
   for (int j = J - 1; j >= 0; --j) {
     float2 *u = (j == 0) ? x : tmp + (int64_t)(j % 2) * B * N;
-    const int ntx = lattice_tiles(nx, 1 << j, kTX);
-    const dim3 grid((unsigned)(ntx * (int64_t)lattice_tiles(ny, 1 << j, kTY)), (unsigned)B);
-    if (f.taps == 2)
-      k_iswt_level<2><<<grid, 256, 0, s>>>(w + (int64_t)3 * j * N, nb * N, ll, ls, u, N, nx, ny, ntx, 1 << j, f);
+    const int d = 1 << j, ntx = lattice_tiles(nx, d, kTX);
+    const float2 *bands = w + (int64_t)3 * j * N;
+    const dim3 tiles((unsigned)(ntx * (int64_t)lattice_tiles(ny, d, kTY)), (unsigned)B);
+    const dim3 grid((unsigned)ceil_div(N, 256), (unsigned)B);
+    if (use_tiles(f.taps, nx, ny, d, true))
+      k_iswt_tiles<8><<<tiles, 256, 0, s>>>(bands, nb * N, ll, ls, u, N, nx, ny, ntx, d, f);
+    else if (f.taps == 2)
+      k_iswt_direct<2><<<grid, 256, 0, s>>>(bands, nb * N, ll, ls, u, N, nx, ny, d, f);
     else
-      k_iswt_level<8><<<grid, 256, 0, s>>>(w + (int64_t)3 * j * N, nb * N, ll, ls, u, N, nx, ny, ntx, 1 << j, f);
+      k_iswt_direct<8><<<grid, 256, 0, s>>>(bands, nb * N, ll, ls, u, N, nx, ny, d, f);
     EX_LAUNCHED("undecimated synthesis");
     ll = u;
     ls = N;

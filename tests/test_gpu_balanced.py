@@ -129,3 +129,51 @@ def test_undecimated_tile_edges(name, shape, levels, batch):
     v = c64(rng.standard_normal(ref.shape) + 1j * rng.standard_normal(ref.shape))
     ref2 = np.stack([bal.iswt2(v[b], levels, name) for b in range(batch)])
     assert rel(ee.swt_inv(_dev(v), levels, name).cpu().numpy(), ref2) <= 3e-7
+
+
+@pytest.mark.parametrize("shape,levels,batch", [((40, 36), 8, 3), ((150, 148), 5, 2), ((9, 260), 6, 2),
+                                                ((96, 64), 4, 1)])
+@pytest.mark.parametrize("name", ["haar", "db4"])
+def test_undecimated_deep_levels(name, shape, levels, batch):
+    """Levels on either side of the change from lattice tiles to one thread per
+    pixel (spacings up to beyond the image), against the oracle at the bar of
+    the tile edges."""
+    import paper_2211_07532_amd as ee
+    rng = np.random.default_rng(sum(shape) + levels)
+    x = c64(rng.standard_normal((batch,) + shape) + 1j * rng.standard_normal((batch,) + shape))
+    ref = np.stack([bal.swt2(x[b], levels, name) for b in range(batch)])
+    print(f"[case] swt deep {name} {shape} J={levels} B={batch}", flush=True)
+    assert rel(ee.swt_fwd(_dev(x), levels, name).cpu().numpy(), ref) <= 3e-7
+    v = c64(rng.standard_normal(ref.shape) + 1j * rng.standard_normal(ref.shape))
+    ref2 = np.stack([bal.iswt2(v[b], levels, name) for b in range(batch)])
+    assert rel(ee.swt_inv(_dev(v), levels, name).cpu().numpy(), ref2) <= 3e-7
+
+
+@pytest.mark.parametrize("name,per_level", [("haar", 4), ("db4", 6)])
+def test_undecimated_deep_levels_cost_no_more_than_shallow_ones(name, per_level):
+    """Every level does the same work at another spacing, so eight levels take
+    about eight times one.  Measured 1.5 (Haar) and 3 times that (8 taps, whose
+    first level runs from LDS tiles); spacings at which tiles are mostly padding
+    took 14 and 22 times.  36 images of 148 x 148; best of five passes."""
+    import torch
+    import paper_2211_07532_amd as ee
+    x = torch.randn((36, 148, 148), dtype=torch.complex64, device="cuda")
+
+    def best(f):
+        f()
+        t = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                f()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t)
+
+    for fn in (lambda j: (lambda: ee.swt_fwd(x, j, name)),
+               lambda j: (lambda w=ee.swt_fwd(x, j, name): ee.swt_inv(w, j, name))):
+        one, eight = best(fn(1)), best(fn(8))
+        print(f"[case] swt levels {name}: 1 level {one / 5 * 1e3:.0f} us, 8 levels {eight / 5 * 1e3:.0f} us", flush=True)
+        assert eight <= per_level * 8 * one

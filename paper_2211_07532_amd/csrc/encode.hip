@@ -35,10 +35,10 @@ namespace expenc {
 // Split-K reductions (fixed summation order)
 // ---------------------------------------------------------------------------
 
-// Sum of n float2 values p[k * step], k = 0 .. n - 1, in FP64 and in k
+// Sum of the n splits' values p[k * step], k = 0 .. n - 1, in FP64 and in k
 // order, eight loads in flight per step (a loop that loads and adds one at a
-// time waits for memory once per value).  odd: the sign of every second value.
-__device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, int n, float odd, double &sx, double &sy) {
+// time waits for memory once per value).
+__device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, int n, double &sx, double &sy) {
   int k = 0;
   for (; k + 8 <= n; k += 8) {
     float2 v[8];
@@ -46,22 +46,21 @@ __device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, i
     for (int u = 0; u < 8; ++u) v[u] = p[(k + u) * step];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      sx += (u & 1) ? odd * v[u].x : v[u].x;
-      sy += (u & 1) ? odd * v[u].y : v[u].y;
+      sx += split_sign(u) * v[u].x;
+      sy += split_sign(u) * v[u].y;
     }
   }
   for (; k < n; ++k) {
     const float2 v = p[k * step];
-    sx += (k & 1) ? odd * v.x : v.x;
-    sy += (k & 1) ? odd * v.y : v.y;
+    sx += split_sign(k) * v.x;
+    sy += split_sign(k) * v.y;
   }
 }
 
-// scl: the scaled form's operand powers of two ([P][2]), or NULL; odd: sign of
-// the odd splits.
+// scl: the scaled form's operand powers of two ([P][2]), or NULL.
 __global__ void k_fwd_reduce_out(const float2 *__restrict__ part, int nsplit, int64_t T,
                                  int64_t Tp, int C, int NC, int NCP, float2 *__restrict__ y,
-                                 const float *__restrict__ scl, float odd) {
+                                 const float *__restrict__ scl) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= T * NC) return;
   const int pz = blockIdx.y;
@@ -70,7 +69,7 @@ __global__ void k_fwd_reduce_out(const float2 *__restrict__ part, int nsplit, in
   int64_t t = i / NC;
   int col = (int)(i % NC);
   double sx = 0.0, sy = 0.0;
-  sum_strided(part + t * NCP + col, Tp * NCP, nsplit, odd, sx, sy);
+  sum_strided(part + t * NCP + col, Tp * NCP, nsplit, sx, sy);
   if (scl) {
     const double inv = 1.0 / scl[2 * pz];
     sx *= inv;
@@ -81,8 +80,7 @@ __global__ void k_fwd_reduce_out(const float2 *__restrict__ part, int nsplit, in
 }
 
 // x_b(r) = alpha * sum_c conj(S_c(r)) sum_split part[split][r][b*C+c].
-// Block: 8 pixels x 32 lanes; lanes stride over coils, then a shuffle sum.  odd:
-// sign of the odd splits.
+// Block: 8 pixels x 32 lanes; lanes stride over coils, then a shuffle sum.
 __global__ __launch_bounds__(256) void k_adj_reduce_out(const float2 *__restrict__ part, int nsplit,
                                                         int R, int Rp, int nx, int C, int B, int NCP,
                                                         const float2 *__restrict__ smaps,
@@ -91,7 +89,7 @@ __global__ __launch_bounds__(256) void k_adj_reduce_out(const float2 *__restrict
                                                         const float2 *__restrict__ add,
                                                         const float2 *__restrict__ base, int nxq,
                                                         int64_t x_pstride, int pad_nx, int pad_ny,
-                                                        const float *__restrict__ scl, float odd) {
+                                                        const float *__restrict__ scl) {
   const int sub = threadIdx.x & 31;
   const int q = blockIdx.x * 8 + (threadIdx.x >> 5);  // pixel of x's grid
   const int npx = pad_nx > 0 ? pad_nx * pad_ny : R;
@@ -122,7 +120,7 @@ __global__ __launch_bounds__(256) void k_adj_reduce_out(const float2 *__restrict
     for (int c = sub; c < C; c += 32) {
       const int col = b * C + c;
       double ux = 0.0, uy = 0.0;
-      sum_strided(part + rq * NCP + col, (int64_t)Rp * NCP, nsplit, odd, ux, uy);
+      sum_strided(part + rq * NCP + col, (int64_t)Rp * NCP, nsplit, ux, uy);
       float2 s = smaps[(int64_t)c * R + r];
       sx += s.x * ux + s.y * uy;  // conj(s) * u
       sy += s.x * uy - s.y * ux;
@@ -155,14 +153,14 @@ __global__ __launch_bounds__(256) void k_adj_reduce_out(const float2 *__restrict
   }
 }
 
-// Single image: x(r) = alpha * (sum over splits and column blocks of the
+// Single image: x(r) = alpha * (sum over splits and ngy column blocks of the
 // coil-combined partial images at row (r / nx) * nxq + r % nx), with the
 // same base / add terms as k_adj_reduce_out.  Four lanes per pixel: lane j
 // sums slices j, j+4, j+8, ... in order (eight loads in flight), then the
 // four partial sums are added in lane order.  With pad_nx > 0 the pixels are
 // those of the pad_nx x pad_ny grid, and those outside the encoded block get
 // add (or 0).
-__global__ __launch_bounds__(256) void k_adj_reduce_comb(const float2 *__restrict__ part, int nslice, int Rp,
+__global__ __launch_bounds__(256) void k_adj_reduce_comb(const float2 *__restrict__ part, int nslice, int ngy, int Rp,
                                                          int nx, int ny, float2 *__restrict__ x, int x_row_stride,
                                                          const double *__restrict__ alpha_dev,
                                                          const float2 *__restrict__ add,
@@ -194,8 +192,9 @@ __global__ __launch_bounds__(256) void k_adj_reduce_comb(const float2 *__restric
     for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(k0 + 4 * u) * Rp + rq];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      sx += v[u].x;
-      sy += v[u].y;
+      const float f = split_sign((k0 + 4 * u) / ngy);
+      sx += f * v[u].x;
+      sy += f * v[u].y;
     }
   }
   if (k0 < nslice) {
@@ -205,8 +204,9 @@ __global__ __launch_bounds__(256) void k_adj_reduce_comb(const float2 *__restric
       v[u] = k0 + 4 * u < nslice ? part[(int64_t)(k0 + 4 * u) * Rp + rq] : make_float2(0.f, 0.f);
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      sx += v[u].x;
-      sy += v[u].y;
+      const float f = split_sign((k0 + 4 * u) / ngy);
+      sx += f * v[u].x;
+      sy += f * v[u].y;
     }
   }
   // lane order: ((s0 + s1) + s2) + s3
@@ -247,7 +247,6 @@ static int phase_terms(int L) {
 }
 
 constexpr int kTargetWorkgroups = 2048;
-constexpr int32_t kBf16FwdChunkMax = 3072;
 constexpr int kMaxWorkgroups = 4608;  // of the default split (scratch grows with the splits)
 
 // EXPENC_TARGET_WG, or 0.
@@ -277,13 +276,17 @@ static int32_t target_chunk(int64_t K, int64_t nrb, int ngy, int target, int gra
 // 16 indexes, and a step takes 0.5 us of a CU (0.6 for the general-basis and
 // 1 for the FP32 kernels, 0.6 times that with 16 columns per wave).  The
 // partial sums cost `width` complex values per row and split at 8 TB/s.
-// Whole calls, at 2048 workgroups and as picked: 100 x 90, T 3000, 16 coils,
-// 4 images, fp16: forward 112 / 84 us (32 splits), adjoint 100 / 84 (9);
-// one image, 16 maps, bf16: 64 / 58 and 71 / 60; 64 x 64, T 4000, 8 coils,
-// bf16: 39 / 34 and 73 / 31; 148 x 148, 32 coils, bf16: 351 / 326 (16
-// splits) and 342 / 331.
-int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, int grain,
-                      int32_t longest, int32_t cap) {
+// Sums longer than those of kTargetWorkgroups take `fold` times as long: they
+// are the ones added up outside the matrix instruction (fwd_fold), or their
+// error would grow by up to 30 % (fp16; carried through the instruction it is
+// rounded at its size 6 or 12 times a step).
+// Whole calls, at 2048 workgroups and as picked (folded): 100 x 90, T 3000, 16
+// coils, 4 images, fp16: forward 101 / 88 us (21 splits), adjoint 98 / 85 (9);
+// 64 x 64, T 4000, 8 coils, bf16: 39 / 32 and 71 / 30, FP32 50 / 46 and 55 / 52;
+// 148 x 148, 32 coils, bf16: 336 us either way (unfolded with 16 splits 323, at
+// an error 0.8 % larger).
+int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, double fold,
+                      int grain, int32_t longest, int32_t cap) {
   const int32_t at_target = target_chunk(K, nrb, ngy, kTargetWorkgroups, grain, cap);
   const int64_t last = std::max<int64_t>(at_target, std::min<int64_t>(longest, round_up(K, grain)));
   const int64_t most = std::max<int64_t>(1, kMaxWorkgroups / (nrb * ngy));
@@ -297,7 +300,8 @@ int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots,
     prev = split;
     const int64_t n = ceil_div(nrb * ngy * split, 256), r = n % slots;
     const double load = (double)(n - r) + (r == 1 ? 1 / 0.85 : r == 2 ? 2 / 0.9 : (double)r) + tail;
-    const double t = load * (double)(chunk / 16 + 8) * step + (double)split * nrb * width * (256 * 8 / 8e6);
+    const double t = load * (double)(chunk / 16 + 8) * step * (chunk > at_target ? fold : 1.0) +
+                     (double)split * nrb * width * (256 * 8 / 8e6);
     if (t < cost) {
       cost = t;
       best = (int32_t)chunk;
@@ -411,20 +415,19 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
   q.P = nprob;
   q.scaled = precision != EXPENC_BF16_SPLIT;
   // Partial sums of the default splits, unless kTargetWorkgroups makes them
-  // longer: at most 64 indexes in the FP32 form, whose error they set (64 x 64
-  // to 128 x 128: 1.1 to 2.2 times smaller than with 512, at the same times),
-  // 1024 in the split forms (below), kBf16FwdChunkMax in the bf16 forward
-  // (3.8e-6 whatever the chunk; the fp16 forward's 6.6e-7 at 1024 becomes
-  // 7.5e-7 at 1480, 148 x 148).
+  // longer: at most 64 indexes in the FP32 form, whose error they set (folded, 64
+  // x 64 with 64: 0.7 of the FP32 instruction's with its 32), 1024 in the split
+  // forms (below), 512 where those are not folded.
   const bool f32 = precision == EXPENC_FP32;
   const int32_t longest = f32 ? kF32FoldMax : kSplitAdjChunkMax;
-  // FP32 sums longer than those of kTargetWorkgroups, up to kF32FoldMax, are the
-  // folded ones (f32.hip): 40 x 33, 8 coils, T = 3000 31 / 34 us with 64 indices,
-  // 37 / 45 with the 16 of 2048 workgroups, at 0.86 and 0.8 of the error on the
-  // FP32 instruction with those 16; carried through the matrix instruction 64
-  // indices have 1.2 to 1.4 of it.
-  auto folds = [&](int32_t chunk, int64_t K, int64_t nrb) {
-    return f32 && chunk <= kF32FoldMax && chunk > target_chunk(K, nrb, q.NGY, kTargetWorkgroups, 16, kF32ChunkMax);
+  // Sums longer than those of kTargetWorkgroups are folded (see default_chunk),
+  // unless a tuned target asks for them; the general-basis split forward's are
+  // not: the order of its phase product leaves it 0.4 to 0.9 of the error that
+  // the phases' vector arithmetic had.
+  const bool fwd_folds = q.sh || f32;
+  const double fold = 1.08;
+  auto folds = [&](int32_t chunk, int64_t K, int64_t nrb, int tuned, int grain, int32_t cap) {
+    return !tuned && chunk > target_chunk(K, nrb, q.NGY, kTargetWorkgroups, grain, cap);
   };
   const double step = (f32 ? 1.0 : q.sh ? 0.5 : 0.6) * (q.GW == 2 ? 1.0 : 0.6);
   // forward: 256 sample rows per workgroup, split over pixels
@@ -434,11 +437,11 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
     const int slots = f32 ? 5 - q.GW : q.sh ? 4 - q.GW : 2;  // workgroups that fit on a CU
     const int grain = fwd_grain(q);
     q.fwd_chunk = tgt_fwd ? target_chunk(q.Rp, nrb, q.NGY, tgt_fwd, grain, cap)
-                          : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, f32 || q.GW == 1 ? 1.5 : 0.3, grain,
-                                          precision == EXPENC_BF16_SPLIT ? kBf16FwdChunkMax : longest, cap);
+                          : default_chunk(q.Rp, nrb, q.NGY, q.NCP, slots, step, f32 || q.GW == 1 ? 1.5 : 0.3,
+                                          fwd_folds ? fold : 1.0, grain, fwd_folds ? longest : 512, cap);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
-    q.fwd_fold = folds(q.fwd_chunk, q.Rp, nrb);
+    q.fwd_fold = fwd_folds && folds(q.fwd_chunk, q.Rp, nrb, tgt_fwd, grain, cap);
   }
   // adjoint: 256 pixel rows per workgroup, split over samples
   {
@@ -456,10 +459,10 @@ int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p,
     const int32_t cap = f32 ? kF32ChunkMax : kSplitAdjChunkMax;
     const int slots = f32 ? 5 - q.GW : q.sh ? 3 : 2;
     q.adj_chunk = tgt_adj ? target_chunk(q.Tp, nrb, q.NGY, tgt_adj, grain, cap)
-                          : default_chunk(q.Tp, nrb, q.NGY, q.comb ? q.NGY : q.NCP, slots, step, 1.5, grain,
+                          : default_chunk(q.Tp, nrb, q.NGY, q.comb ? q.NGY : q.NCP, slots, step, 1.5, fold, grain,
                                           std::min(longest, cap), cap);
     q.adj_split = (int32_t)ceil_div(q.Tp, q.adj_chunk);
-    q.adj_fold = folds(q.adj_chunk, q.Tp, nrb);
+    q.adj_fold = folds(q.adj_chunk, q.Tp, nrb, tgt_adj, grain, cap);
   }
   *p = q;
   return EXPENC_OK;
@@ -484,7 +487,7 @@ int plan_forward_within(const expenc_op *op, int32_t batch, int32_t precision, s
     if (q.prec == EXPENC_FP32) q.fwd_chunk = std::min(q.fwd_chunk, kF32ChunkMax);
     q.fwd_split = (int32_t)ceil_div(q.Rp, q.fwd_chunk);
     q.nwmax = (int32_t)split_grid(q.Tp / 256 * q.fwd_split) * q.NGY * 4;
-    q.fwd_fold = q.prec == EXPENC_FP32;  // (sums longer than the default's: folded, or their error grows)
+    q.fwd_fold = q.sh || q.prec == EXPENC_FP32;
   };
   auto fits = [&] { return enc_bytes(q, kNeedForward) <= cap; };
   while (!fits() && q.fwd_split > min_split)
@@ -691,12 +694,9 @@ int enc_adjoint_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   return EXPENC_OK;
 }
 
-// (the FP32 form's odd splits are negated)
-static float odd_sign(const EncPlan &p) { return p.prec == EXPENC_FP32 ? -1.f : 1.f; }
-
 int enc_forward_reduce_out(const EncPlan &p, const EncBuffers &b, float2 *y, hipStream_t s) {
   k_fwd_reduce_out<<<grid_p(p.T * p.NC, 256, p.P), 256, 0, s>>>(b.part, p.fwd_split, p.T, p.Tp, p.C, p.NC, p.NCP, y,
-                                                                  p.scaled ? b.scl : nullptr, odd_sign(p));
+                                                                  p.scaled ? b.scl : nullptr);
   EX_LAUNCHED("forward reduce");
   return EXPENC_OK;
 }
@@ -714,7 +714,7 @@ int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *s
   if (pad_nx > 0 && (pad_nx < p.nx || pad_ny < p.ny || x_row_stride < pad_nx))
     return fail(EXPENC_EINVAL, "padded grid %dx%d smaller than the image", pad_nx, pad_ny);
   if (p.comb) {
-    k_adj_reduce_comb<<<grid_p(npx * 4, 256, p.P), 256, 0, s>>>(b.part, p.adj_split * p.NGY, p.Rp, p.nx, p.ny, x,
+    k_adj_reduce_comb<<<grid_p(npx * 4, 256, p.P), 256, 0, s>>>(b.part, p.adj_split * p.NGY, p.NGY, p.Rp, p.nx, p.ny, x,
                                                           x_row_stride, alpha_dev, add, base, p.nxq, x_pstride,
                                                           pad_nx, pad_ny, p.scaled ? b.scl : nullptr);
     EX_LAUNCHED("adjoint reduce");
@@ -723,7 +723,7 @@ int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *s
   k_adj_reduce_out<<<grid_p(npx, 8, p.P), 256, 0, s>>>(b.part, p.adj_split, p.R, p.Rp, p.nx, p.C, p.B, p.NCP,
                                                        reinterpret_cast<const float2 *>(smaps), x, x_stride,
                                                        x_row_stride, alpha_dev, add, base, p.nxq, x_pstride,
-                                                       pad_nx, pad_ny, p.scaled ? b.scl : nullptr, odd_sign(p));
+                                                       pad_nx, pad_ny, p.scaled ? b.scl : nullptr);
   EX_LAUNCHED("adjoint reduce");
   return EXPENC_OK;
 }

@@ -20,19 +20,16 @@
 // does not grow (adjoint 200 x 200, T = 40000: 4.8e-7 -> 3.9e-7): one matrix
 // instruction adds 16 products to an accumulator, the FP32 one two.
 //
-// The matrix instruction aligns its 16 products and C to the largest of them
-// and cuts what is below, towards minus infinity: a sum carried through it loses
-// the more the larger it has grown, and always to the same side.  So
-//  * the records, and with them the partial sums, of every second split are
-//    negated (split_sign), and the reductions undo it: the losses cancel;
-//  * with FOLD every step's products start from zero and the result is added to
-//    the accumulators outside.  These sums are the more precise ones, which lets
-//    small problems have chunks of 64 where they had 16 (make_plan); on long
-//    chunks it costs 6 to 45 % (16 to 64 more registers, no overlap of a step's
-//    last products with the next phases).
-// Error of the adjoint of random data relative to the FP32 instruction's, before
-// either and now: 148 x 148, 32 coils, T = 16384 1.53 -> 0.83, 128 x 128, 16
-// coils, T = 12000 1.14 -> 0.84, 40 x 33, 8 coils, T = 3000 (64 samples against
+// A sum carried through the matrix instruction loses the more the larger it has
+// grown, always to the same side (split_sign), and is rounded twelve times a
+// step.  With FOLD every step's products start from zero and the result is added
+// to the accumulators outside.  These sums are the more precise ones, which lets
+// small problems have chunks of 64 where they had 16 (make_plan); on long chunks
+// it costs 6 to 45 % (16 to 64 more registers, no overlap of a step's last
+// products with the next phases).
+// Error of the adjoint of random data relative to the FP32 instruction's, without
+// signs and folds and now: 148 x 148, 32 coils, T = 16384 1.53 -> 0.83, 128 x 128,
+// 16 coils, T = 12000 1.14 -> 0.84, 40 x 33, 8 coils, T = 3000 (64 samples against
 // 16) 1.36 -> 0.82.
 //
 // Layout of one step (K = 16 reduction indices) as in the split forms: lane l

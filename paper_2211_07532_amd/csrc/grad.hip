@@ -373,7 +373,7 @@ static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLay
   // sample, fewer pixels where they hold several groups of 16 coils
   G->CK = (int)ceil_div(p.C, 16);
   const int cap = std::max(64, kGradChunkMax / G->CK / 16 * 16);
-  G->chunk = default_chunk(p.Rp, p.Tp / 256, 1, 8, 2, 1.3, 1.5, 16, cap, cap);
+  G->chunk = default_chunk(p.Rp, p.Tp / 256, 1, 8, 2, 1.3, 1.5, 1.0, 16, cap, cap);
   G->nsplit = (int)ceil_div(p.Rp, G->chunk);
   if (p.sh) {
     G->pmono = a.take<double>(p.Tp * kPolyStride);

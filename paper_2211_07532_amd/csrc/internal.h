@@ -118,7 +118,11 @@ __device__ inline bool split_tile_rows(int b, int nrb, int nsplit, int *split, i
 }
 inline unsigned split_grid(int64_t n) { return (unsigned)((n + 7) / 8 * 8); }
 
-// Sign of split k's records and partial sums (FP32 form, see f32.hip).
+// Sign of split k's operand records and partial sums.  A 16-bit matrix
+// instruction aligns its products and C to the largest of them and cuts what is
+// below, towards minus infinity: all sums are off to the same side, the more the
+// longer they are, and the coil combination adds that up.  With every second
+// split negated (and the reductions undoing it) the losses cancel.
 __device__ inline float split_sign(int64_t k) { return k & 1 ? -1.f : 1.f; }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -306,7 +310,7 @@ struct EncPlan {
   int32_t prec = 0;
   int32_t fwd_split = 1, fwd_chunk = 0;   // split-K over pixels
   int32_t adj_split = 1, adj_chunk = 0;   // split-K over samples
-  bool fwd_fold = false, adj_fold = false;  // FP32: steps added up outside the matrix instruction (f32.hip)
+  bool fwd_fold = false, adj_fold = false;  // steps added up outside the matrix instruction
   // split forms with a single image (B == 1): the adjoint contraction
   // combines its coils in the epilogue and writes [adj_split][NGY][Rp]
   // partial images instead of [adj_split][Rp][NCP] per-coil partials
@@ -354,8 +358,8 @@ constexpr int32_t kF32FoldMax = 64;
 
 int make_plan(const expenc_op *op, int32_t batch, int32_t precision, EncPlan *p, int32_t nprob = 1);
 // Indexes per workgroup of a split reduction (see the definition).
-int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, int grain,
-                      int32_t longest, int32_t cap);
+int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, double fold,
+                      int grain, int32_t longest, int32_t cap);
 
 // Device buffers of one operator application, carved from the workspace.
 struct EncBuffers {

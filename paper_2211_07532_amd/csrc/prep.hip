@@ -38,7 +38,7 @@ struct PrepArgs {
   int64_t T, Tp, nop;  // nop: operand elements per problem
   int R, Rp, L, NT, nx, ny, nxq, C, NC, NCP, op_l1;
   u32x4 *rec;
-  int rec_image, rec_perm;  // records of an image; index order
+  int rec_image, rec_perm, rec_chunk;  // records of an image; index order; indexes per split
   double dx, dy, z0;
   unsigned end[kRoles];  // block index one past each role's range
 };
@@ -154,13 +154,14 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
         sv[e] = make_float2(0.f, 0.f);
       }
     }
+    const float f = split_sign(k0 / a.rec_chunk);
     float b1[8], b2[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float2 z = v[e];
       if (a.rec_image)
         z = make_float2(sv[e].x * v[e].x - sv[e].y * v[e].y, sv[e].x * v[e].y + sv[e].y * v[e].x);
-      if (!ok[e]) z = make_float2(0.f, 0.f);
+      z = ok[e] ? make_float2(z.x * f, z.y * f) : make_float2(0.f, 0.f);
       b1[e] = im ? z.y : z.x;
       b2[e] = im ? z.x : z.y;
       if (im != a.rec_image) b2[e] = -b2[e];
@@ -344,6 +345,7 @@ int enc_prepare(const EncPlan &p, const expenc_op *op, const EncBuffers &b, hipS
     a.rec = reinterpret_cast<u32x4 *>(fwd ? b.zs : b.ys);
     a.rec_image = fwd;
     a.rec_perm = adj || !p.sh;
+    a.rec_chunk = fwd ? p.fwd_chunk : p.adj_chunk;
     n[kRoleRecords] = ceil_div((fwd ? p.Rp : p.Tp) * (p.NCP / 4), 256);
   }
   int64_t tot = 0;

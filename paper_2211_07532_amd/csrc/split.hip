@@ -19,6 +19,9 @@
 // matrix product in that layout).  The B operand is pre-split and packed in
 // exactly the per-lane order (four 16-byte records per lane and step: b1 hi,
 // b1 lo, b2 hi, b2 lo), so the inner loop loads it with dwordx4 loads.
+#include <algorithm>
+#include <vector>
+
 #include "internal.h"
 #include "split_dev.h"
 
@@ -69,7 +72,7 @@ struct FwdShArgs {
 };
 
 // One workgroup of the forward (workgroup bx, by, bz of a gx x gy x P grid).
-template <int GW, bool BF>
+template <int GW, bool BF, bool FOLD>
 __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int bz, int gx, int gy) {
   const double *__restrict__ pmono = a.pmono;
   const double *__restrict__ dwq = a.dwq;
@@ -122,6 +125,7 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
   // row 148 x 148, 32 coils, T = 16384 took 384 us (fp16) so, 360 expanded
   // anew for every tile, and takes 348 pipelined.
   u32x4 A[2][4], bq[GW][4];
+  f32x16 ts[2];      // FOLD: a column group's sums over the tile
   uint32_t w[4][8];  // [kind: c hi, c lo, s hi, s lo][pair of indexes]
   float ph[16], dd[16];
   RowCubic rc;  // of the tile whose phases come next
@@ -185,7 +189,10 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
     for (int k = 0; k < 12 * GW; ++k)
       if (k >= lo && k < hi) {
         const int g = k / 12, q = k % 12 >> 1, blk = k & 1;
-        acc[blk][g] = mfma16<BF>(A[blk][pa[q]], bq[g][pb[q]], acc[blk][g]);
+        f32x16 &c = FOLD ? ts[blk] : acc[blk][g];
+        if (FOLD && k % 12 < 2) c = f32x16{};
+        c = mfma16<BF>(A[blk][pa[q]], bq[g][pb[q]], c);
+        if (FOLD && k % 12 >= 10) acc[blk][g] += c;
       }
   };
   load_dw(r0);
@@ -218,9 +225,9 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
   store_partials<GW>(part + (int64_t)split * Tp * NCP * 2, row0, NCP, g0, lane, acc, wmax, slot);
 }
 
-template <int GW, bool BF>
+template <int GW, bool BF, bool FOLD>
 __global__ __launch_bounds__(256) void k_fwd_split_sh(FwdShArgs a) {
-  fwd_split_sh_body<GW, BF>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x, gridDim.y);
+  fwd_split_sh_body<GW, BF, FOLD>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x, gridDim.y);
 }
 
 // One launch for several problem groups of one shape class (same GW and
@@ -230,7 +237,7 @@ __global__ __launch_bounds__(256) void k_fwd_split_sh(FwdShArgs a) {
 // assigns it and split_tile's L2 locality holds.  (A persistent form, a
 // grid of the resident workgroups walking the tiles with its stride, was
 // slower: its loop raised the adjoint's registers to two waves per SIMD.)
-template <int GW, bool BF>
+template <int GW, bool BF, bool FOLD>
 __global__ __launch_bounds__(256) void k_fwd_split_sh_grouped(GroupedLaunch<FwdShArgs> G) {
   {
     const int64_t t = blockIdx.x;
@@ -240,7 +247,7 @@ __global__ __launch_bounds__(256) void k_fwd_split_sh_grouped(GroupedLaunch<FwdS
     const int64_t l = t - G.off[g];
     const int gx = G.gx[g], gy = G.gy[g];
     const int64_t q = l / gx;
-    fwd_split_sh_body<GW, BF>(G.a[g], (int)(l - q * gx), (int)(q % gy), (int)(q / gy), gx, gy);
+    fwd_split_sh_body<GW, BF, FOLD>(G.a[g], (int)(l - q * gx), (int)(q % gy), (int)(q / gy), gx, gy);
   }
 }
 
@@ -249,6 +256,8 @@ __global__ __launch_bounds__(256) void k_fwd_split_sh_grouped(GroupedLaunch<FwdS
 // 16q + 8*(l/32) + i, column col = 16g + l%16, part = (l/16)&1.
 //   forward:  b1 = part ? Zi : Zr,   b2 = part ? Zr : -Zi
 //   adjoint:  b1 = part ? Yi : Yr,   b2 = part ? -Yr : Yi
+// times the operand's scale and the sign of the index's split.  The adjoints and
+// the general-basis forward read the indices of a step in the order of k_pack_y_split.
 // ---------------------------------------------------------------------------
 
 // Max of m over workgroup blk of nblk into its slots blk, blk + nblk, ... of
@@ -310,7 +319,7 @@ __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict_
                                 const float2 *__restrict__ xsub, int64_t x_stride, int x_row_stride, int nx, int ny,
                                 int nxq, int Rp, int C, int NC, int NGP, u32x4 *__restrict__ zs, int64_t x_pstride,
                                 const float2 *__restrict__ sq, const float *__restrict__ amax,
-                                float *__restrict__ scl, int perm) {
+                                float *__restrict__ scl, int perm, int chunk) {
   const int R = nx * ny;
   const int pz = blockIdx.y;  // problem
   // scaled form: every workgroup derives the same power of two from the pre-pass
@@ -356,6 +365,7 @@ __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict_
       ++yy;
     }
   }
+  const float f = sc * split_sign(16 * q / chunk);
   float b1[8], b2[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -365,7 +375,7 @@ __global__ __launch_bounds__(256) void k_build_z_split(const float2 *__restrict_
       uu.y -= w[i].y;
     }
     const float2 s = sv[i];
-    const float2 z = ok[i] ? make_float2((s.x * uu.x - s.y * uu.y) * sc, (s.x * uu.y + s.y * uu.x) * sc)
+    const float2 z = ok[i] ? make_float2((s.x * uu.x - s.y * uu.y) * f, (s.x * uu.y + s.y * uu.x) * f)
                            : make_float2(0.f, 0.f);
     b1[i] = im ? z.y : z.x;
     b2[i] = im ? z.x : -z.y;
@@ -383,7 +393,8 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
                                                       const float2 *__restrict__ y_meas, int64_t T, int64_t Tp, int C,
                                                       int NC, int NCP, u32x4 *__restrict__ ys,
                                                       const float *__restrict__ bnd, int nbnd,
-                                                      const float *__restrict__ bnd_meas, float *__restrict__ scl) {
+                                                      const float *__restrict__ bnd_meas, float *__restrict__ scl,
+                                                      int chunk) {
   const int NGP = NCP / 16;
   const int pz = blockIdx.y;  // problem
   float sc = 1.f, inv_z = 1.f;
@@ -432,8 +443,8 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
       for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          y[i].x += v[u][i].x;
-          y[i].y += v[u][i].y;
+          y[i].x += split_sign(u) * v[u][i].x;
+          y[i].y += split_sign(u) * v[u][i].y;
         }
     }
     for (; k < nsplit; ++k) {
@@ -441,8 +452,8 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
       for (int i = 0; i < 8; ++i)
         if (ok[i]) {
           const float2 v = src_part[((int64_t)k * Tp + t[i]) * NCP + col];
-          y[i].x += v.x;
-          y[i].y += v.y;
+          y[i].x += split_sign(k) * v.x;
+          y[i].y += split_sign(k) * v.y;
         }
     }
 #pragma unroll
@@ -460,10 +471,11 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
         }
     }
   }
+  const float f = sc * split_sign(16 * q / chunk);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    y[i].x *= sc;
-    y[i].y *= sc;
+    y[i].x *= f;
+    y[i].y *= f;
   }
   float b1[8], b2[8];
 #pragma unroll
@@ -484,14 +496,12 @@ static FwdShArgs fwd_sh_args(const EncPlan &p, const EncBuffers &b) {
                    p.dx, p.dy, bf16_masks()};
 }
 
-template <bool BF>
 static void fwd_split_sh(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   dim3 grid(split_grid(p.Tp / 256 * p.fwd_split), (unsigned)p.NGY, (unsigned)p.P);
   const FwdShArgs a = fwd_sh_args(p, b);
-  if (p.GW == 2)
-    k_fwd_split_sh<2, BF><<<grid, 256, 0, s>>>(a);
-  else
-    k_fwd_split_sh<1, BF><<<grid, 256, 0, s>>>(a);
+  split_variant(p, p.fwd_fold, [&](auto gw, auto bf, auto fold) {
+    k_fwd_split_sh<gw.value, bf.value, fold.value><<<grid, 256, 0, s>>>(a);
+  });
 }
 
 bool split_groupable(const EncPlan &a, const EncPlan &b) {
@@ -499,7 +509,6 @@ bool split_groupable(const EncPlan &a, const EncPlan &b) {
          a.scaled == b.scaled;
 }
 
-template <int GW, bool BF>
 static int fwd_grouped(const EncPlan *const *p, const EncBuffers *const *b, int n, hipStream_t s) {
   GroupedLaunch<FwdShArgs> G{};
   G.ng = n;
@@ -511,33 +520,31 @@ static int fwd_grouped(const EncPlan *const *p, const EncBuffers *const *b, int 
     G.off[g + 1] = G.off[g] + (int64_t)G.gx[g] * G.gy[g] * p[g]->P;
   }
   if (G.off[n] > INT32_MAX) return fail(EXPENC_EUNSUPPORTED, "grouped launch larger than 2^31 workgroups");
-  k_fwd_split_sh_grouped<GW, BF><<<(unsigned)G.off[n], 256, 0, s>>>(G);
+  split_variant(*p[0], p[0]->fwd_fold, [&](auto gw, auto bf, auto fold) {
+    k_fwd_split_sh_grouped<gw.value, bf.value, fold.value><<<(unsigned)G.off[n], 256, 0, s>>>(G);
+  });
   EX_LAUNCHED("grouped forward contraction");
   return EXPENC_OK;
 }
 
 int split_forward_grouped(const EncPlan *const *p, const EncBuffers *const *b, int n, hipStream_t s) {
-  for (int i = 0; i < n; i += kMaxGrouped) {
-    const int m = std::min(kMaxGrouped, n - i);
-    for (int g = i; g < i + m; ++g)
-      if (!split_groupable(*p[i], *p[g])) return fail(EXPENC_EINVAL, "plans of a grouped launch differ in shape");
-    const bool bf = p[i]->prec == EXPENC_BF16_SPLIT;
-    int rc;
-    if (p[i]->GW == 2) rc = bf ? fwd_grouped<2, true>(p + i, b + i, m, s) : fwd_grouped<2, false>(p + i, b + i, m, s);
-    else rc = bf ? fwd_grouped<1, true>(p + i, b + i, m, s) : fwd_grouped<1, false>(p + i, b + i, m, s);
-    EX_TRY(rc);
+  // (groups of folded sums and the others take kernels of their own)
+  std::vector<const EncPlan *> pv[2];
+  std::vector<const EncBuffers *> bv[2];
+  for (int g = 0; g < n; ++g) {
+    if (!split_groupable(*p[0], *p[g])) return fail(EXPENC_EINVAL, "plans of a grouped launch differ in shape");
+    pv[p[g]->fwd_fold].push_back(p[g]);
+    bv[p[g]->fwd_fold].push_back(b[g]);
   }
+  for (int f = 0; f < 2; ++f)
+    for (int i = 0; i < (int)pv[f].size(); i += kMaxGrouped)
+      EX_TRY(fwd_grouped(pv[f].data() + i, bv[f].data() + i, std::min(kMaxGrouped, (int)pv[f].size() - i), s));
   return EXPENC_OK;
 }
 
 void split_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  const bool bf = p.prec == EXPENC_BF16_SPLIT;
-  if (p.sh) {
-    if (bf) fwd_split_sh<true>(p, b, s);
-    else fwd_split_sh<false>(p, b, s);
-  } else {
-    split_maps_launch(p, b, false, s);
-  }
+  if (p.sh) fwd_split_sh(p, b, s);
+  else split_maps_launch(p, b, false, s);
 }
 
 void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
@@ -594,10 +601,10 @@ int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const f
   const float2 *sq = p.comb && !prepared ? b.sq : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
     k_build_z_split<true><<<nb, 256, 0, s>>>(sm, x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C,
-                                             p.NC, NGP, zs, x_pstride, sq, b.amax, scl, p.sh ? 0 : 1);
+                                             p.NC, NGP, zs, x_pstride, sq, b.amax, scl, p.sh ? 0 : 1, p.fwd_chunk);
   else
     k_build_z_split<false><<<nb, 256, 0, s>>>(sm, x, xsub, x_stride, x_row_stride, p.nx, p.ny, p.nxq, p.Rp, p.C,
-                                              p.NC, NGP, zs, x_pstride, sq, b.amax, scl, p.sh ? 0 : 1);
+                                              p.NC, NGP, zs, x_pstride, sq, b.amax, scl, p.sh ? 0 : 1, p.fwd_chunk);
   EX_LAUNCHED("build_z split");
   return EXPENC_OK;
 }
@@ -614,10 +621,10 @@ int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, cons
   float *scl = p.scaled ? b.scl : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
     k_pack_y_split<true><<<nb, 256, 0, s>>>(y_abi, part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP, ys,
-                                            d.bnd, d.nbnd, d.meas, scl);
+                                            d.bnd, d.nbnd, d.meas, scl, p.adj_chunk);
   else
     k_pack_y_split<false><<<nb, 256, 0, s>>>(y_abi, part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP, ys,
-                                             d.bnd, d.nbnd, d.meas, scl);
+                                             d.bnd, d.nbnd, d.meas, scl, p.adj_chunk);
   EX_LAUNCHED("pack_y split");
   return EXPENC_OK;
 }

@@ -38,7 +38,7 @@ struct AdjShArgs {
 // the two rows: E_k = C_k(t, y1) - C_k(t, y0) against (1 | x), (x^2 | 0) on
 // those pixels and 0 on the others (E_3 = 0: C_3 does not depend on y), two
 // more products; CROSS instantiates that case (nxq not a multiple of 32).
-template <int GW, bool BF, bool CROSS>
+template <int GW, bool BF, bool FOLD, bool CROSS>
 __device__ inline void adj_split_sh_body(const AdjShArgs &a, int bx, int by, int bz, int gy) {
   const float *__restrict__ anc = a.anc;
   const float *__restrict__ dpa = a.dpa;
@@ -151,7 +151,7 @@ __device__ inline void adj_split_sh_body(const AdjShArgs &a, int bx, int by, int
         const u32x4 A[4] = {u32x4{w[0][0], w[0][1], w[0][2], w[0][3]}, u32x4{w[1][0], w[1][1], w[1][2], w[1][3]},
                             u32x4{w[2][0], w[2][1], w[2][2], w[2][3]}, u32x4{w[3][0], w[3][1], w[3][2], w[3][3]}};
 #pragma unroll
-        for (int g = 0; g < GW; ++g) acc[blk][g] = step6<BF>(A, b[g], acc[blk][g]);
+        for (int g = 0; g < GW; ++g) acc[blk][g] = step6<BF, FOLD>(A, b[g], acc[blk][g]);
       }
     }
   }
@@ -161,15 +161,15 @@ __device__ inline void adj_split_sh_body(const AdjShArgs &a, int bx, int by, int
 // The bf16 build is held to three waves per SIMD: left to itself the
 // compiler may take a few more registers than that allows, and two waves
 // per SIMD measured 3 % slower.
-template <int GW, bool BF, bool CROSS>
+template <int GW, bool BF, bool FOLD, bool CROSS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF ? 3 : 1))) void k_adj_split_sh(AdjShArgs a) {
-  adj_split_sh_body<GW, BF, CROSS>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
+  adj_split_sh_body<GW, BF, FOLD, CROSS>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
 }
 
 // One launch over several problem groups, one workgroup per tile (the
 // forward's grouped kernel in split.hip describes the numbering and why the
 // XCD mapping holds).
-template <int GW, bool BF, bool CROSS>
+template <int GW, bool BF, bool FOLD, bool CROSS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF ? 3 : 1))) void k_adj_split_sh_grouped(
     GroupedLaunch<AdjShArgs> G) {
   {
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF ? 3 : 1)
     const int64_t l = t - G.off[g];
     const int gx = G.gx[g], gy = G.gy[g];
     const int64_t q = l / gx;
-    adj_split_sh_body<GW, BF, CROSS>(G.a[g], (int)(l - q * gx), (int)(q % gy), (int)(q / gy), gy);
+    adj_split_sh_body<GW, BF, FOLD, CROSS>(G.a[g], (int)(l - q * gx), (int)(q % gy), (int)(q / gy), gy);
   }
 }
 
@@ -194,17 +194,16 @@ static AdjShArgs adj_sh_args(const EncPlan &p, const EncBuffers &b) {
 // length is a multiple of 32.
 static bool adj_cross(const EncPlan &p) { return p.nxq % 32 != 0; }
 
-template <bool BF, bool CROSS>
+template <bool CROSS>
 static void adj_split_sh(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   dim3 grid(split_grid((int64_t)p.Rp / 256 * p.adj_split), (unsigned)p.NGY, (unsigned)p.P);
   const AdjShArgs a = adj_sh_args(p, b);
-  if (p.GW == 2)
-    k_adj_split_sh<2, BF, CROSS><<<grid, 256, 0, s>>>(a);
-  else
-    k_adj_split_sh<1, BF, CROSS><<<grid, 256, 0, s>>>(a);
+  split_variant(p, p.adj_fold, [&](auto gw, auto bf, auto fold) {
+    k_adj_split_sh<gw.value, bf.value, fold.value, CROSS><<<grid, 256, 0, s>>>(a);
+  });
 }
 
-template <int GW, bool BF, bool CROSS>
+template <bool CROSS>
 static int adj_grouped(const EncPlan *const *p, const EncBuffers *const *b, int n, hipStream_t s) {
   GroupedLaunch<AdjShArgs> G{};
   G.ng = n;
@@ -216,7 +215,9 @@ static int adj_grouped(const EncPlan *const *p, const EncBuffers *const *b, int 
     G.off[g + 1] = G.off[g] + (int64_t)G.gx[g] * G.gy[g] * p[g]->P;
   }
   if (G.off[n] > INT32_MAX) return fail(EXPENC_EUNSUPPORTED, "grouped launch larger than 2^31 workgroups");
-  k_adj_split_sh_grouped<GW, BF, CROSS><<<(unsigned)G.off[n], 256, 0, s>>>(G);
+  split_variant(*p[0], p[0]->adj_fold, [&](auto gw, auto bf, auto fold) {
+    k_adj_split_sh_grouped<gw.value, bf.value, fold.value, CROSS><<<(unsigned)G.off[n], 256, 0, s>>>(G);
+  });
   EX_LAUNCHED("grouped adjoint contraction");
   return EXPENC_OK;
 }
@@ -226,37 +227,31 @@ template <bool CROSS>
 static int adj_grouped_class(const EncPlan *const *p, const EncBuffers *const *b, int n, hipStream_t s) {
   for (int i = 0; i < n; i += kMaxGrouped) {
     const int m = std::min(kMaxGrouped, n - i);
-    const bool bf = p[i]->prec == EXPENC_BF16_SPLIT;
-    int rc;
-    if (p[i]->GW == 2)
-      rc = bf ? adj_grouped<2, true, CROSS>(p + i, b + i, m, s) : adj_grouped<2, false, CROSS>(p + i, b + i, m, s);
-    else
-      rc = bf ? adj_grouped<1, true, CROSS>(p + i, b + i, m, s) : adj_grouped<1, false, CROSS>(p + i, b + i, m, s);
-    EX_TRY(rc);
+    EX_TRY(adj_grouped<CROSS>(p + i, b + i, m, s));
   }
   return EXPENC_OK;
 }
 
 int split_adjoint_grouped(const EncPlan *const *p, const EncBuffers *const *b, int n, hipStream_t s) {
-  // groups whose pixel blocks stay inside image rows and the others take
-  // kernel variants of their own
-  std::vector<const EncPlan *> pv[2];
-  std::vector<const EncBuffers *> bv[2];
+  // groups whose pixel blocks stay inside image rows and the others, each with
+  // folded sums or not, take kernel variants of their own
+  std::vector<const EncPlan *> pv[2][2];
+  std::vector<const EncBuffers *> bv[2][2];
   for (int g = 0; g < n; ++g) {
     if (!split_groupable(*p[0], *p[g])) return fail(EXPENC_EINVAL, "plans of a grouped launch differ in shape");
-    pv[adj_cross(*p[g])].push_back(p[g]);
-    bv[adj_cross(*p[g])].push_back(b[g]);
+    pv[adj_cross(*p[g])][p[g]->adj_fold].push_back(p[g]);
+    bv[adj_cross(*p[g])][p[g]->adj_fold].push_back(b[g]);
   }
-  EX_TRY(adj_grouped_class<false>(pv[0].data(), bv[0].data(), (int)pv[0].size(), s));
-  return adj_grouped_class<true>(pv[1].data(), bv[1].data(), (int)pv[1].size(), s);
+  for (int f = 0; f < 2; ++f) {
+    EX_TRY(adj_grouped_class<false>(pv[0][f].data(), bv[0][f].data(), (int)pv[0][f].size(), s));
+    EX_TRY(adj_grouped_class<true>(pv[1][f].data(), bv[1][f].data(), (int)pv[1][f].size(), s));
+  }
+  return EXPENC_OK;
 }
 
 void split_adjoint_sh_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
-  const bool bf = p.prec == EXPENC_BF16_SPLIT;
-  if (adj_cross(p))
-    bf ? adj_split_sh<true, true>(p, b, s) : adj_split_sh<false, true>(p, b, s);
-  else
-    bf ? adj_split_sh<true, false>(p, b, s) : adj_split_sh<false, false>(p, b, s);
+  if (adj_cross(p)) adj_split_sh<true>(p, b, s);
+  else adj_split_sh<false>(p, b, s);
 }
 
 }  // namespace expenc

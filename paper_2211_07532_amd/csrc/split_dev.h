@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace expenc {
@@ -99,16 +101,19 @@ __device__ inline f32x16 mfma16(u32x4 a, u32x4 b, f32x16 c) {
 }
 
 // 6 MFMAs of one step for one 32-row block and one 32-column group:
-// cos against b1, sin against b2, each as hi*hi + hi*lo + lo*hi.
-template <bool BF>
-__device__ inline f32x16 step6(const u32x4 (&A)[4], const u32x4 *b, f32x16 acc) {
+// cos against b1, sin against b2, each as hi*hi + hi*lo + lo*hi.  FOLD: the step's
+// products start from zero and are added up outside the matrix instruction, which
+// rounds a sum that it carries six times a step (EncPlan::fwd_fold).
+template <bool BF, bool FOLD>
+__device__ inline f32x16 step6(const u32x4 (&A)[4], const u32x4 *b, f32x16 sum) {
+  f32x16 acc = FOLD ? f32x16{} : sum;
   acc = mfma16<BF>(A[0], b[0], acc);
   acc = mfma16<BF>(A[0], b[1], acc);
   acc = mfma16<BF>(A[1], b[0], acc);
   acc = mfma16<BF>(A[2], b[2], acc);
   acc = mfma16<BF>(A[2], b[3], acc);
   acc = mfma16<BF>(A[3], b[2], acc);
-  return acc;
+  return FOLD ? sum + acc : acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -188,6 +193,22 @@ __device__ inline float data_scale(const float *__restrict__ bnd, int nbnd, int 
   if (nsplit > 0) m *= (double)nsplit * inv_z;
   if (bnd_meas) m += block_max(bnd_meas + (int64_t)pz * kAmaxBlocks, kAmaxBlocks);
   return pow2_scale(m);
+}
+
+// go(GW, BF) for a split plan, and go(GW, BF, FOLD)
+template <class Go>
+inline void split_variant(const EncPlan &p, Go go) {
+  auto width = [&](auto bf) {
+    if (p.GW == 2) go(std::integral_constant<int, 2>{}, bf);
+    else go(std::integral_constant<int, 1>{}, bf);
+  };
+  if (p.prec == EXPENC_BF16_SPLIT) width(std::true_type{});
+  else width(std::false_type{});
+}
+template <class Go>
+inline void split_variant(const EncPlan &p, bool fold, Go go) {
+  if (fold) split_variant(p, [&](auto gw, auto bf) { go(gw, bf, std::true_type{}); });
+  else split_variant(p, [&](auto gw, auto bf) { go(gw, bf, std::false_type{}); });
 }
 
 constexpr int kRec3 = 6 * 64;  // 16-byte words of one FP32-form step and column group

@@ -31,7 +31,7 @@ namespace expenc {
 // 148 x 148, 32 coils, T = 16384, before / after, forward and adjoint: 16
 // maps fp16 643 / 402 and 682 / 424 us, bf16 645 / 393 and 1215 / 417; 9 maps
 // fp16 430 / 329 and 613 / 353; 3 maps 329 / 294 and 443 / 323.
-template <int NT, int GW, bool BF, bool ADJ>
+template <int NT, int GW, bool BF, bool FOLD, bool ADJ>
 __global__ __launch_bounds__(256) void k_split_maps(const double *__restrict__ own, const double *__restrict__ uni,
                                                     const float *__restrict__ dop, const u32x4 *__restrict__ rec,
                                                     float *__restrict__ part, const float2 *__restrict__ sq,
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_split_maps(const double *__restrict__ o
   for (int64_t k = k0; k < k1; k += 32) {
     float a[NJ];
 #pragma unroll
-    for (int J = 0; J < NJ; ++J) a[J] = dop[((k >> 5) * NJ + J) * 64 + lane];
+    for (int J = NJ - 1; J >= 0; --J) a[J] = dop[((k >> 5) * NJ + J) * 64 + lane];
     const double *u0 = uni + (k + 8) * NT, *u1 = uni + (k + 24) * NT;
     double p0 = 0.0, p1 = 0.0;
 #pragma unroll
@@ -90,8 +90,10 @@ __global__ __launch_bounds__(256) void k_split_maps(const double *__restrict__ o
     for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
       for (int v = 0; v < 16; ++v) ph[blk][v] = 0.f;
+    // (last terms first: a basis lists its low orders, the large increments,
+    // first, and a sum is rounded at its size with every term that follows)
 #pragma unroll
-    for (int J = 0; J < NJ; ++J)
+    for (int J = NJ - 1; J >= 0; --J)
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk)
         ph[blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[J], bt[blk][J], ph[blk], 0, 0, 0);
@@ -130,7 +132,7 @@ __global__ __launch_bounds__(256) void k_split_maps(const double *__restrict__ o
           for (int q = 0; q < 4; ++q) A[q][m] = w[q];
         }
 #pragma unroll
-        for (int g = 0; g < GW; ++g) acc[blk][g] = step6<BF>(A, b[g], acc[blk][g]);
+        for (int g = 0; g < GW; ++g) acc[blk][g] = step6<BF, FOLD>(A, b[g], acc[blk][g]);
       }
     }
   }
@@ -140,36 +142,31 @@ __global__ __launch_bounds__(256) void k_split_maps(const double *__restrict__ o
     store_partials<GW>(part + ((int64_t)pz * nsplit + split) * rows * NCP * 2, row0, NCP, g0, lane, acc, nullptr, 0);
 }
 
-template <int NT, int GW, bool BF>
+template <int NT>
 static void launch_maps(const EncPlan &p, const EncBuffers &b, bool adjoint, hipStream_t s) {
   float *part = reinterpret_cast<float *>(b.part);
   const u32x4 *zs = reinterpret_cast<const u32x4 *>(b.zs), *ys = reinterpret_cast<const u32x4 *>(b.ys);
   const Bf16Masks mk = bf16_masks();
   if (adjoint) {
     const dim3 grid(split_grid((int64_t)p.Rp / 256 * p.adj_split), (unsigned)p.NGY, (unsigned)p.P);
-    k_split_maps<NT, GW, BF, true><<<grid, 256, 0, s>>>(b.bet, b.kap, b.dkap, ys, part, p.comb ? b.sq : nullptr, p.Rp,
-                                                        p.Tp, p.NCP, p.adj_chunk, p.adj_split, mk);
+    split_variant(p, p.adj_fold, [&](auto gw, auto bf, auto fold) {
+      k_split_maps<NT, gw.value, bf.value, fold.value, true><<<grid, 256, 0, s>>>(
+          b.bet, b.kap, b.dkap, ys, part, p.comb ? b.sq : nullptr, p.Rp, p.Tp, p.NCP, p.adj_chunk, p.adj_split, mk);
+    });
   } else {
     const dim3 grid(split_grid(p.Tp / 256 * p.fwd_split), (unsigned)p.NGY, (unsigned)p.P);
-    k_split_maps<NT, GW, BF, false><<<grid, 256, 0, s>>>(b.kap, b.bet, b.dbet, zs, part, nullptr, p.Tp, p.Rp, p.NCP,
-                                                         p.fwd_chunk, p.fwd_split, mk);
+    split_variant(p, [&](auto gw, auto bf) {
+      k_split_maps<NT, gw.value, bf.value, false, false><<<grid, 256, 0, s>>>(
+          b.kap, b.bet, b.dbet, zs, part, nullptr, p.Tp, p.Rp, p.NCP, p.fwd_chunk, p.fwd_split, mk);
+    });
   }
-}
-
-template <int NT>
-static void launch_maps_nt(const EncPlan &p, const EncBuffers &b, bool adjoint, hipStream_t s) {
-  const bool bf = p.prec == EXPENC_BF16_SPLIT;
-  if (p.GW == 2)
-    bf ? launch_maps<NT, 2, true>(p, b, adjoint, s) : launch_maps<NT, 2, false>(p, b, adjoint, s);
-  else
-    bf ? launch_maps<NT, 1, true>(p, b, adjoint, s) : launch_maps<NT, 1, false>(p, b, adjoint, s);
 }
 
 void split_maps_launch(const EncPlan &p, const EncBuffers &b, bool adjoint, hipStream_t s) {
   switch (p.NT) {
-    case 4: launch_maps_nt<4>(p, b, adjoint, s); break;
-    case 10: launch_maps_nt<10>(p, b, adjoint, s); break;
-    default: launch_maps_nt<17>(p, b, adjoint, s); break;
+    case 4: launch_maps<4>(p, b, adjoint, s); break;
+    case 10: launch_maps<10>(p, b, adjoint, s); break;
+    default: launch_maps<17>(p, b, adjoint, s); break;
   }
 }
 

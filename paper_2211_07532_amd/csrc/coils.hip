@@ -450,11 +450,11 @@ int layout_coils(int32_t C, int64_t T, Arena &a, CoilLayout *cl) {
   return a.ok() ? EXPENC_OK : EXPENC_EWORKSPACE;
 }
 
-// Kernels above the default 64 KB of dynamic LDS must ask for it.
-int allow_lds(const void *kernel, size_t bytes) {
-  if (bytes > 65536) EX_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return EXPENC_OK;
-}
+// Dynamic LDS of the kernels for C coils (and nv virtual ones).
+size_t cholesky_lds(int C) { return (size_t)C * (C + 1) * sizeof(double2); }
+size_t whiten_lds(int C) { return (size_t)C * (65 + padded_rows(C)) * sizeof(double2); }
+size_t jacobi_lds(int C) { return 2 * (size_t)C * (C + 1) * sizeof(double2); }
+size_t compress_lds(int C, int nv) { return (size_t)nv * C * sizeof(double2) + (size_t)C * 65 * sizeof(float2); }
 
 }  // namespace
 }  // namespace expenc
@@ -482,9 +482,9 @@ extern "C" int expenc_prewhiten(int32_t ncoils, const double *psi, int64_t nsamp
   EX_TRY(st);
   hipStream_t s = (hipStream_t)stream;
   const int C = ncoils;
-  const size_t clds = (size_t)C * (C + 1) * sizeof(double2), wlds = (size_t)C * (65 + padded_rows(C)) * sizeof(double2);
-  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_cholesky), clds));
-  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_whiten), wlds));
+  const size_t clds = cholesky_lds(C), wlds = whiten_lds(C);
+  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_cholesky), clds, cholesky_lds(kMaxCoils)));
+  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_whiten), wlds, whiten_lds(kMaxCoils)));
   k_cholesky<<<1, 512, clds, s>>>(reinterpret_cast<const double2 *>(psi), C, cl.L, cl.status);
   EX_LAUNCHED("cholesky");
   if (nsamples > 0) {
@@ -520,12 +520,12 @@ extern "C" int expenc_coil_compress(int32_t ncoils, int32_t nvirtual, int64_t ns
   k_gram_sum<<<(unsigned)ceil_div(no, 64), 64, 0, s>>>(cl.part, cl.nblk, C, cl.g);
   EX_LAUNCHED("gram sum");
   double2 *v = eigvec ? reinterpret_cast<double2 *>(eigvec) : cl.v;
-  const size_t jlds = 2 * (size_t)C * (C + 1) * sizeof(double2);
-  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_jacobi), jlds));
+  const size_t jlds = jacobi_lds(C);
+  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_jacobi), jlds, jacobi_lds(kMaxCoils)));
   k_jacobi<<<1, kJacobiThreads, jlds, s>>>(cl.g, C, 40, v, eigval, cl.status);
   EX_LAUNCHED("jacobi");
-  const size_t xlds = (size_t)nvirtual * C * sizeof(double2) + (size_t)C * 65 * sizeof(float2);
-  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_compress), xlds));
+  const size_t xlds = compress_lds(C, nvirtual);
+  EX_TRY(allow_lds(reinterpret_cast<const void *>(k_compress), xlds, compress_lds(kMaxCoils, kMaxCoils)));
   if (y_out) {
     k_compress<<<(unsigned)ceil_div(nsamples, 64), 256, xlds, s>>>(v, C, nvirtual, reinterpret_cast<const float2 *>(y),
                                                                    C, 1, reinterpret_cast<float2 *>(y_out), nvirtual, 1,

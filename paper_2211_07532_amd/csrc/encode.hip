@@ -683,13 +683,15 @@ int enc_forward_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s, b
 int enc_adjoint_partials(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   if (p.comb && !b.sq) return fail(EXPENC_EINVAL, "coil table of a single-image split plan is not carved");
   if (p.sh && p.prec != EXPENC_FP32 && !b.anc) return fail(EXPENC_EINVAL, "anchor table of a split plan is not carved");
+  int st = EXPENC_OK;
   timed(1, s, [&] {
     if (p.prec != EXPENC_FP32) {
       split_adjoint_launch(p, b, s);
       return;
     }
-    f32_adjoint_launch(p, b, s);
+    st = f32_adjoint_launch(p, b, s);
   });
+  EX_TRY(st);
   EX_LAUNCHED("adjoint contraction");
   return EXPENC_OK;
 }

@@ -40,6 +40,7 @@
 // lane order: six 16-byte records per lane and step (b1 hi, mid, lo, b2 hi,
 // mid, lo; b1 against cos, b2 against sin).
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 
 #include "internal.h"
@@ -603,8 +604,17 @@ static void launch_forward(const EncPlan &p, const EncBuffers &b, const Pass &w,
   });
 }
 
+// Image rows that a workgroup's 256 pixels can touch.  Workgroups start at
+// multiples of 256, so in a row at multiples of gcd(256, nxq).
+constexpr int kMaxRows = 16;  // nxq is a multiple of 16
+static int block_rows(const EncPlan &p) {
+  return (int)std::min<int64_t>((p.nxq - std::gcd(256, p.nxq) + 255) / p.nxq + 1, ceil_div(p.Rp, p.nxq));
+}
+static size_t adj_sh_lds(int nrow) { return (size_t)2 * kSamples * (4 * nrow + 1) * sizeof(double); }
+
 template <int NT>
-static void launch_adjoint(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
+static int launch_adjoint(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
+  int st = EXPENC_OK;
   const u32x4 *op = reinterpret_cast<const u32x4 *>(b.ys);
   float *part = reinterpret_cast<float *>(b.part);
   const F32Args a{p.Tp, p.Rp, p.NCP, p.NCP / 16, p.adj_chunk, p.adj_split, p.nxq, p.nx, p.ny, 0,
@@ -616,15 +626,13 @@ static void launch_adjoint(const EncPlan &p, const EncBuffers &b, hipStream_t s)
     if constexpr (NT > 0) {
       k_adj_f32<NT, GW, FOLD><<<grid, 256, 0, s>>>(b.bet, b.kap, op, part, a);
     } else {
-      // image rows that 256 pixels can touch (at most 17: nxq >= 16)
-      const int nrow = std::min(256 / p.nxq + 2, (int)ceil_div(p.Rp, p.nxq));
-      const size_t lds = (size_t)2 * kSamples * (4 * nrow + 1) * sizeof(double);
-      if (lds > 65536)
-        hipFuncSetAttribute(reinterpret_cast<const void *>(k_adj_f32_sh<GW, FOLD>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      k_adj_f32_sh<GW, FOLD><<<grid, 256, lds, s>>>(b.pmono, b.dwq, op, part, a, nrow);
+      const int nrow = block_rows(p);
+      st = allow_lds(reinterpret_cast<const void *>(k_adj_f32_sh<GW, FOLD>), adj_sh_lds(nrow), adj_sh_lds(kMaxRows));
+      if (st == EXPENC_OK)
+        k_adj_f32_sh<GW, FOLD><<<grid, 256, adj_sh_lds(nrow), s>>>(b.pmono, b.dwq, op, part, a, nrow);
     }
   });
+  return st;
 }
 
 static void forward_pass(const EncPlan &p, const EncBuffers &b, const Pass &w, hipStream_t s) {
@@ -638,7 +646,7 @@ static void forward_pass(const EncPlan &p, const EncBuffers &b, const Pass &w, h
 
 void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) { forward_pass(p, b, whole(p), s); }
 
-void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
+int f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s) {
   if (p.sh) return launch_adjoint<0>(p, b, s);
   switch (p.NT) {
     case 4: return launch_adjoint<4>(p, b, s);

@@ -36,6 +36,14 @@ int fail(int status, const char *fmt, ...) __attribute__((format(printf, 2, 3)))
     if (s_ != EXPENC_OK) return s_; \
   } while (0)
 
+// Kernels above 64 KB of dynamic LDS must ask for it.  The limit is the kernel's,
+// shared by all host threads: it is set to the most that any call of the kernel
+// takes, never to a smaller call's own size.
+inline int allow_lds(const void *kernel, size_t bytes, size_t most) {
+  if (bytes > 65536) EX_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
+  return EXPENC_OK;
+}
+
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t v, int64_t m) { return (v + m - 1) / m; }
 
@@ -473,7 +481,7 @@ void f32_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 // the forward of a plan in passes: records and contraction of each in turn (x
 // bounded by enc_prepare)
 int f32_forward_passes(const EncPlan &p, const float *smaps, const float2 *x, const EncBuffers &b, hipStream_t s);
-void f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
+int f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
                 const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared);
 int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_meas, const EncBuffers &b,

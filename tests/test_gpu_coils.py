@@ -113,3 +113,53 @@ def test_coil_tile_edges(C, nv, n, npix):
     yw_ref, sw_ref = coils.prewhiten(psi, y, s)
     assert rel(yd.cpu().numpy(), yw_ref) <= 1e-6 and rel(sd.cpu().numpy(), sw_ref) <= 1e-6
     _compare_compression(y, s, nv)
+
+
+def test_calls_of_different_sizes_from_several_threads():
+    """A kernel's dynamic LDS limit belongs to the kernel, not to a call: host
+    threads whose calls need different sizes (64 and 48 coils, 16-pixel and
+    128-pixel rows) on streams of their own get the results of calls made one
+    after the other."""
+    import threading
+    import torch
+    import paper_2211_07532_amd as ee
+
+    def coil_job(C):
+        y = _dev(c64(synth.random_complex((900, C), 300 + C)))
+        s = _dev(c64(synth.random_complex((C, 500), 301 + C)))
+        psi = _dev(_psi(C, 302 + C), np.complex128)
+
+        def run():
+            yd, sd = y.clone(), s.clone()
+            ee.prewhiten(psi, yd, sd)
+            return [yd, sd, *ee.coil_compress(yd, C - 5, sd)]
+        return run
+
+    def adjoint_job(nx, ny):
+        case = Case(synth.Workload("lds", 16, 0.2, 5, 400, 3e-6, 2.0, 9, 80.0, 20.0, 5, "haar", 1, 91), sh=True)
+        smaps = _dev(c64(synth.random_complex((5, nx * ny), 92)))
+        op = ee.Operator(nx, ny, smaps, case.t_coef, case.t_time, None, None, sh_grid=(0.2, 0.2, 0.0))
+        y = _dev(c64(synth.random_complex((400, 5), 93)))
+        return lambda: [ee.adjoint(y, op)]
+
+    jobs = [coil_job(64), coil_job(48), adjoint_job(5, 200), adjoint_job(128, 16)]
+    ref = [[t.cpu() for t in job()] for job in jobs]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for _ in range(20):
+                out = jobs[i]()
+                stream.synchronize()
+                if not all(torch.equal(a.cpu(), b) for a, b in zip(out, ref[i])):
+                    bad.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    print("[case] threads with calls of different LDS sizes", flush=True)
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad

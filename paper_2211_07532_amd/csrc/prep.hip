@@ -45,12 +45,13 @@ struct PrepArgs {
 
 // The ten monomial coefficients (turns; order 1, x, y, x^2, xy, y^2, x^3,
 // x^2 y, x y^2, y^3) of sum_l k_l(t) b_l(x, y, z) at fixed z, and t: the
-// solid harmonics multiplied out, terms added in the order of l.
+// solid harmonics multiplied out, terms added in the order of l.  Padding repeats
+// the last sample, here and in every table (pixels: the last of their row and
+// the last row): a tile's centre, whose phase the FP32 differences within the tile start
+// from, may be padding.
 __device__ inline void sample_poly(const double *__restrict__ coef, const double *__restrict__ time, int64_t t,
                                    int64_t T, int L, double z, double (&P)[11]) {
-#pragma unroll
-  for (int m = 0; m < 11; ++m) P[m] = 0.0;
-  if (t >= T) return;
+  t = min(t, T - 1);
   const double *c = coef + t * L;
   double k[16];
 #pragma unroll
@@ -69,10 +70,10 @@ __device__ inline void sample_poly(const double *__restrict__ coef, const double
   P[10] = time[t];
 }
 
-// dw0/2pi at padded pixel rq (0 on padding)
+// dw0/2pi at padded pixel rq
 __device__ inline double pixel_dw(const double *__restrict__ dw0, int rq, int nx, int ny, int nxq) {
   const int yy = rq / nxq, xx = rq - yy * nxq;
-  return dw0 && yy < ny && xx < nx ? dw0[(int64_t)yy * nx + xx] * kInv2Pi : 0.0;
+  return dw0 ? dw0[(int64_t)min(yy, ny - 1) * nx + min(xx, nx - 1)] * kInv2Pi : 0.0;
 }
 
 // Element (index i, term j) of a difference table of the split contractions:
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
     const int64_t t = i / a.NT;
     const int j = (int)(i - t * a.NT);
     auto val = [&](int64_t s) -> double {
-      if (s >= a.T) return 0.0;
+      s = min(s, a.T - 1);
       return j < a.L ? coef[s * a.L + j] * kInv2Pi : j == a.L ? time[s] : 0.0;
     };
     const double v = val(t);
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(256) void k_prepare(PrepArgs a) {
     const int r = (int)(i / a.NT), j = (int)(i - (int64_t)r * a.NT);
     const double *basis = a.basis ? a.basis + pz * a.L * a.R : nullptr;
     auto val = [&](int s) -> double {
-      if (s >= a.R) return 0.0;
+      s = min(s, a.R - 1);
       return j < a.L ? basis[(int64_t)j * a.R + s] : j == a.L && dw0 ? dw0[s] * kInv2Pi : 0.0;
     };
     const double v = val(r);

@@ -249,3 +249,38 @@ def test_default_splits_cost_no_accuracy(n, coils, T, terms, sh):
     print(f"[case] splits {n} px {coils} coils sh={sh}: " + ", ".join(f"{a:.2e}/{c:.2e}" for a, c in zip(default, shaped)),
           flush=True)
     assert all(a <= 1.03 * c for a, c in zip(default, shaped))
+
+
+@pytest.mark.parametrize("sh", [False, True], ids=["maps", "sh"])
+@pytest.mark.parametrize("nx,ny,T", [(8, 20, 16), (20, 9, 40), (7, 1, 8), (33, 5, 300)])
+def test_split_phase_at_ragged_ends(nx, ny, T, sh):
+    """Tiles of 16 pixels or 32 samples whose centre lies on padding: the FP32
+    phase differences within such a tile must start from a sample or pixel of it,
+    not from phase zero.  40 turns common to all samples and pixels, 10 of them
+    off-resonance, and a smooth field of a few radians: the differences within a
+    tile are below a turn (6e-8 x 2 pi), fp16 pairs carry 22 bits and drop 2^-22
+    of a product: 1e-6 together; differences from zero would be off by 40 turns'
+    last bits, 1.5e-5."""
+    import torch
+    import paper_2211_07532_amd as ee
+    fx, fy, L, C = 0.2, 0.13, 9, 3
+    rng = np.random.default_rng(nx + 100 * ny + T)
+    basis = encoding.sh_basis(nx, fx, 0.002, L, ny=ny, fov_y=fy)
+    u = np.linspace(0.0, 1.0, T)
+    coef = np.stack([np.cos((l + 1) * u) / max(np.abs(basis[l]).max(), 1e-12) for l in range(L)], 1)
+    coef[:, 0] += 2 * np.pi * 30.0
+    time = 0.05 + np.arange(T) * 2e-6
+    xx = np.arange(nx) - nx / 2
+    dw0 = 2 * np.pi * 200.0 * (1.0 + 0.02 * np.tile(xx / nx, ny))
+    smaps, x = c64(synth.random_complex((C, nx * ny), 81)), c64(synth.random_complex((nx * ny,), 82))
+    y = c64(synth.random_complex((T, C), 83))
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    op = ee.Operator(nx, ny, t(smaps.astype(np.complex64)), t(coef), t(time), None if sh else t(basis), t(dw0),
+                     sh_grid=(fx, fy, 0.002) if sh else None)
+    args = (smaps, coef, time, basis, dw0)
+    f = rel(ee.forward(t(x.astype(np.complex64)), op, precision="fp16").cpu().numpy().reshape(T, C),
+            encoding.forward(x, *args))
+    a = rel(ee.adjoint(t(y.astype(np.complex64)), op, precision="fp16").cpu().numpy().reshape(-1),
+            encoding.adjoint(y, *args))
+    print(f"[case] ragged ends {nx}x{ny} T={T} sh={sh}: forward {f:.2e}, adjoint {a:.2e}", flush=True)
+    assert f <= 1e-6 and a <= 1e-6

@@ -28,14 +28,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kGradChunkMax = 1024;  // pixels one workgroup accumulates in FP32
 constexpr int kGradAmax = 64;        // workgroups of the magnitude pre-pass per array
 
-// Per-workgroup max component magnitude of w [R] (blockIdx.y 0) and kk [n]
-// (blockIdx.y 1) into amax[2][kGradAmax].
+// Per-workgroup max component magnitude of w [R] (blockIdx.y 0), kk [T][C] (1)
+// and smaps [C][R] (2) into amax[3][kGradAmax].
 __global__ __launch_bounds__(256) void k_grad_amax(const float2 *__restrict__ w, int64_t R,
-                                                   const float2 *__restrict__ kk, int64_t n,
+                                                   const float2 *__restrict__ kk, int64_t T,
+                                                   const float2 *__restrict__ smaps, int C,
                                                    float *__restrict__ amax) {
   __shared__ float wm[4];
-  const float2 *v = blockIdx.y ? kk : w;
-  const int64_t m = blockIdx.y ? n : R;
+  const float2 *v = blockIdx.y == 0 ? w : blockIdx.y == 1 ? kk : smaps;
+  const int64_t m = blockIdx.y == 0 ? R : (blockIdx.y == 1 ? T : R) * C;
   float a = 0.f;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m; i += (int64_t)gridDim.x * 256)
     a = fmaxf(a, fmaxf(fabsf(v[i].x), fabsf(v[i].y)));
@@ -47,9 +48,10 @@ __global__ __launch_bounds__(256) void k_grad_amax(const float2 *__restrict__ w,
 }
 
 // Power of two that brings the array's largest component into [1/2, 1) (1
-// for an all-zero or non-finite array): M is a product of kk and w in FP32,
-// and with both scaled it neither overflows nor underflows for any inputs.
-// The reductions divide the scales out in FP64.
+// for an all-zero or non-finite array): M and the sums over it are FP32
+// products of kk, w and the maps, and with all three scaled they are the same
+// bits at any scale of the arrays.  The reductions divide the scales out in
+// FP64.
 __device__ inline float grad_scale(const float *__restrict__ amax) {
   float m = 0.f;
   for (int i = 0; i < kGradAmax; ++i) m = fmaxf(m, amax[i]);
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(256) void k_grad_pack(GradPackArgs g) {
     } else {
       const int r = (int)blk * 16 + e, yy = r / g.nxq, xx = r % g.nxq;
       if (xx < g.nx && yy < g.ny) {
-        const float s = grad_scale(g.amax);
+        const float s = grad_scale(g.amax), sm = grad_scale(g.amax + 2 * kGradAmax);
         const int64_t pix = (int64_t)yy * g.nx + xx, R = (int64_t)g.nx * g.ny;
         float2 w = g.w[pix];
         w.x *= s;
@@ -112,7 +114,9 @@ __global__ __launch_bounds__(256) void k_grad_pack(GradPackArgs g) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           if (c0 + j < g.C) {
-            const float2 c = g.smaps[(c0 + j) * R + pix];
+            float2 c = g.smaps[(c0 + j) * R + pix];
+            c.x *= sm;
+            c.y *= sm;
             v[j] = make_float2(c.x * w.x - c.y * w.y, c.x * w.y + c.y * w.x);
           }
       }
@@ -346,7 +350,8 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const float *__restrict__ g
   int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t nk = gk ? T * L : 0, nd = gd ? (int64_t)nx * ny : 0;
   if (i >= nk + nd) return;
-  const double inv = -1.0 / ((double)grad_scale(amax) * grad_scale(amax + kGradAmax));
+  const double inv =
+      -1.0 / ((double)grad_scale(amax) * grad_scale(amax + kGradAmax) * grad_scale(amax + 2 * kGradAmax));
   const bool coef = i < nk;
   if (!coef) i -= nk;
   const float *p = coef ? gpart + (i / L) * 16 + i % L : dpart + (i / nx) * nxq + i % nx;
@@ -396,7 +401,7 @@ static int layout_grad(const expenc_op *op, int32_t precision, Arena &a, GradLay
   G->za = a.take<u32x4>((size_t)p.Rp * G->CK * 12);
   G->tf = a.take<float>(p.Tp);
   G->bt = a.take<float>((size_t)p.Rp * 16);
-  G->amax = a.take<float>(2 * kGradAmax);
+  G->amax = a.take<float>(3 * kGradAmax);
   G->gpart = a.take<float>((size_t)G->nsplit * p.Tp * 16);
   G->dpart = a.take<float>((size_t)(p.Tp / 256) * p.Rp);
   return a.ok() ? EXPENC_OK : EXPENC_EWORKSPACE;
@@ -435,9 +440,10 @@ extern "C" int expenc_field_grad(const expenc_op *op, int32_t precision, const f
   eb.pmono = G.pmono;
   eb.dwq = G.dwq;
   EX_TRY(enc_prepare(p, op, eb, s, kNeedForward));
-  k_grad_amax<<<dim3(kGradAmax, 2), 256, 0, s>>>(w2, p.R, k2, p.T * p.C, G.amax);
+  const float2 *s2 = reinterpret_cast<const float2 *>(op->smaps);
+  k_grad_amax<<<dim3(kGradAmax, 3), 256, 0, s>>>(w2, p.R, k2, p.T, s2, p.C, G.amax);
   EX_LAUNCHED("gradient operand bounds");
-  const GradPackArgs pa{k2, w2, reinterpret_cast<const float2 *>(op->smaps), op->time, G.bet, G.amax, G.za, G.kb,
+  const GradPackArgs pa{k2, w2, s2, op->time, G.bet, G.amax, G.za, G.kb,
                         G.tf, G.bt, p.T, p.Tp, p.C, G.CK, p.NT, p.L, p.nx, p.ny, p.nxq, p.Rp, p.dx, p.dy, p.z0};
   k_grad_pack<<<(unsigned)ceil_div((p.Tp + p.Rp) * G.CK * 4 + p.Tp + p.Rp, 256), 256, 0, s>>>(pa);
   EX_LAUNCHED("gradient operands");

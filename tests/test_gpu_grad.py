@@ -283,3 +283,22 @@ def test_field_grad_sums_at_full_size():
     e = rel(gc.cpu().numpy()[sub], ref)
     print(f"[case] field grad sums at full size: coef {e:.2e}", flush=True)
     assert e <= 3.5e-7
+
+
+@pytest.mark.parametrize("k", [-120, 120])
+def test_field_grad_is_the_same_bits_at_any_scale_of_the_maps(k):
+    import torch
+    ee, ag = _ee()
+    w = synth.Workload("scale", 20, 0.2, 18, 700, 3e-6, 2.0, 9, 80.0, 20.0, 5, "haar", 1, 87)
+    case = Case(w, sh=True)
+    rng = np.random.default_rng(88)
+    part = lambda: rng.uniform(0.25, 1.0, (18, 400)) * rng.choice([-1.0, 1.0], (18, 400))  # noqa: E731
+    smaps = torch.from_numpy((part() + 1j * part()).astype(np.complex64)).cuda()
+    x, g = case.to_dev(c64(synth.random_complex(400, 89))), case.to_dev(c64(synth.random_complex((700, 18), 90)))
+    out = []
+    for s in (1.0, 2.0 ** k):
+        op = ee.Operator(20, 20, smaps * s, case.t_coef, case.t_time, None, case.t_dw0, sh_grid=(0.2, 0.2, 0.0))
+        out.append([v.cpu().numpy() for v in ag.field_grad(op, x, g)])
+    print(f"[case] field grad, maps at 2^{k}", flush=True)
+    for a, b in zip(*out):
+        assert np.array_equal(a * 2.0 ** k, b) and np.any(a)

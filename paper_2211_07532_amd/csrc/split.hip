@@ -9,7 +9,7 @@
 // 16-bit product.
 //
 // Layout of one MFMA step (K = 16 reduction indices): lane l holds 8
-// consecutive reduction indices 8*(l/32) .. 8*(l/32)+7 of row l%32 for the A
+// reduction indices, in the polynomial forward the consecutive ones 8*(l/32) .. 8*(l/32)+7 of row l%32 for the A
 // operand and of column l%32 for the B operand.  In the polynomial forward, as
 // in the FP32 kernels, each lane first evaluates the phases of ITS OWN row at all 16
 // reduction indices (which are wave-uniform, so their field/basis values
@@ -121,9 +121,9 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
   // indexes.  The vector unit issues in three quarters of the cycles and the
   // matrix cores are busy in half, at a clock of 1.9 GHz that the two share;
   // left to itself the compiler puts the MFMAs behind the phases, the more so
-  // the fewer vector instructions those take: with the cubic moved along the
-  // row 148 x 148, 32 coils, T = 16384 took 384 us (fp16) so, 360 expanded
-  // anew for every tile, and takes 348 pipelined.
+  // the fewer vector instructions those take: against the cubic expanded anew
+  // for every tile, 148 x 148, 32 coils, T = 16384 (fp16) took 7 % more time with
+  // it moved along the row, and takes 3 % less pipelined.
   u32x4 A[2][4], bq[GW][4];
   f32x16 ts[2];      // FOLD: a column group's sums over the tile
   uint32_t w[4][8];  // [kind: c hi, c lo, s hi, s lo][pair of indexes]
@@ -225,8 +225,12 @@ __device__ inline void fwd_split_sh_body(const FwdShArgs &a, int bx, int by, int
   store_partials<GW>(part + (int64_t)split * Tp * NCP * 2, row0, NCP, g0, lane, acc, wmax, slot);
 }
 
+// Waves per SIMD as without folds (three with 16 columns, two with 32): left to
+// itself the compiler gives the folded kernels more registers than that allows.
+// Held to it the one of 16 columns spills 18, and is the faster all the same:
+// 46 us for 50 at 100 x 90, 16 coils, T 3000 (fp16), 82 for 88 with 4 images.
 template <int GW, bool BF, bool FOLD>
-__global__ __launch_bounds__(256) void k_fwd_split_sh(FwdShArgs a) {
+__global__ __launch_bounds__(256, 4 - GW) void k_fwd_split_sh(FwdShArgs a) {
   fwd_split_sh_body<GW, BF, FOLD>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x, gridDim.y);
 }
 
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(256) void k_fwd_split_sh(FwdShArgs a) {
 // grid of the resident workgroups walking the tiles with its stride, was
 // slower: its loop raised the adjoint's registers to two waves per SIMD.)
 template <int GW, bool BF, bool FOLD>
-__global__ __launch_bounds__(256) void k_fwd_split_sh_grouped(GroupedLaunch<FwdShArgs> G) {
+__global__ __launch_bounds__(256, 4 - GW) void k_fwd_split_sh_grouped(GroupedLaunch<FwdShArgs> G) {
   {
     const int64_t t = blockIdx.x;
     if (t >= G.off[G.ng]) return;

@@ -29,8 +29,8 @@ struct AdjShArgs {
 // Phase of a 32-sample x 32-pixel block: the FP64 anchor of the tile's centre
 // sample at each pixel (table anc) plus the increment over the tile.  With
 // the pixels of the block in one image row y the increment is a cubic in x,
-// sum_k C_k(t, y) x^k + d10(t) dw0, whose coefficients are polynomials in y
-//: a rank-6 product, three v_mfma_f32_32x32x2_f32 with terms
+// sum_k C_k(t, y) x^k + d10(t) dw0, whose coefficients are polynomials in y:
+// with the anchor a rank-6 product, three v_mfma_f32_32x32x2_f32 with terms
 // (1 | x), (x^2 | x^3), (dw0 | anchor) against (C_0 | C_1), (C_2 | C_3),
 // (d10 | 1) evaluated at the block's row.  A block that continues into the
 // next row (when the padded row length nxq is not a multiple of 32) adds,
@@ -160,9 +160,12 @@ __device__ inline void adj_split_sh_body(const AdjShArgs &a, int bx, int by, int
 
 // The bf16 build is held to three waves per SIMD: left to itself the
 // compiler may take a few more registers than that allows, and two waves
-// per SIMD measured 3 % slower.
+// per SIMD measured 3 % slower.  Folded and held to them it spills 8 to 12
+// registers: 91 us for 84 at 100 x 90, 16 coils, T 3000, 4 images.
+constexpr int min_waves(bool bf, bool fold) { return bf && !fold ? 3 : 1; }
+
 template <int GW, bool BF, bool FOLD, bool CROSS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF ? 3 : 1))) void k_adj_split_sh(AdjShArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves(BF, FOLD)))) void k_adj_split_sh(AdjShArgs a) {
   adj_split_sh_body<GW, BF, FOLD, CROSS>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
 }
 
@@ -170,7 +173,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF ? 3 : 1)
 // forward's grouped kernel in split.hip describes the numbering and why the
 // XCD mapping holds).
 template <int GW, bool BF, bool FOLD, bool CROSS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF ? 3 : 1))) void k_adj_split_sh_grouped(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves(BF, FOLD)))) void k_adj_split_sh_grouped(
     GroupedLaunch<AdjShArgs> G) {
   {
     const int64_t t = blockIdx.x;

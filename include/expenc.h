@@ -458,8 +458,9 @@ int expenc_coil_compress(int32_t ncoils, int32_t nvirtual, int64_t nsamples, con
  * has about `target` workgroups (the EXPENC_TARGET_WG environment variable;
  * without it, the split that a model of the launch finds shortest, of at
  * most 4608 workgroups and without sums longer than 2048 workgroups' or 64
- * (FP32), 1024 (split forms) and 3072 (bf16 forward) indexes, whichever is
- * longer).
+ * (FP32), 512 (general-basis split forward) and 1024 (other split
+ * contractions) indexes, whichever is longer; sums longer than 2048
+ * workgroups' are added up outside the matrix instruction, at the same error).
  * expenc_set_tuning sets the forward and adjoint
  * targets for every later plan of op's geometry (nx, ny, ncoils, nbasis,
  * nsamples, basis_kind) at this batch and precision; 0 restores the default

@@ -10,8 +10,10 @@
 //   adjoint  X[r, col] = sum_t conj(E(t,r)) Y[t, col],  x_b(r) = sum_c conj(S_c(r)) X[r, b*C+c]
 // Phase in turns: kap[t][.] = (k_l(t)/2pi, t), bet[r][.] = (b_l(r), dw0(r)/2pi);
 // phi/2pi = sum_j kap[t][j] bet[r][j] is accumulated in FP64 (|phi| reaches
-// tens of turns, and the sine needs ~1e-8 turn accuracy), reduced to [0,1)
-// with v_fract_f64, and fed to the hardware v_sin/v_cos (argument in turns).
+// tens of turns, and the sine needs ~1e-8 turn accuracy), reduced by whole turns
+// (to [-1/2, 1/2] in the FP32 form and the field gradient, which then round it to
+// FP32, the split forms' anchors to [0, 1)), and fed to the hardware v_sin/v_cos
+// (argument in turns).
 //
 // The contractions are f32.hip's (FP32 form) and split.hip's / split_adj.hip's
 // (bf16 and fp16 hi/lo forms); the reduction index is split across workgroups
@@ -281,10 +283,10 @@ static int32_t target_chunk(int64_t K, int64_t nrb, int ngy, int target, int gra
 // error would grow by up to 30 % (fp16; carried through the instruction it is
 // rounded at its size 6 or 12 times a step).
 // Whole calls, at 2048 workgroups and as picked (folded): 100 x 90, T 3000, 16
-// coils, 4 images, fp16: forward 101 / 88 us (21 splits), adjoint 98 / 85 (9);
-// 64 x 64, T 4000, 8 coils, bf16: 39 / 32 and 71 / 30, FP32 50 / 46 and 55 / 52;
-// 148 x 148, 32 coils, bf16: 336 us either way (unfolded with 16 splits 323, at
-// an error 0.8 % larger).
+// coils, 4 images, fp16: forward 102 / 85 us (21 splits), adjoint 99 / 88 (9);
+// 64 x 64, T 4000, 8 coils, bf16: 39 / 32 and 72 / 30, FP32 49 / 47 and 55 / 54;
+// 148 x 148, 32 coils, bf16 351 / 349 us (unfolded with 16 splits 335, at an error
+// 0.8 % larger).
 int32_t default_chunk(int64_t K, int64_t nrb, int ngy, int64_t width, int slots, double step, double tail, double fold,
                       int grain, int32_t longest, int32_t cap) {
   const int32_t at_target = target_chunk(K, nrb, ngy, kTargetWorkgroups, grain, cap);

@@ -12,13 +12,12 @@
 // Why: v_mfma_f32_32x32x2_f32 takes 4096 matrix cycles per 16 reduction
 // indices, 64 rows and 32 columns, the six bf16 products 1536, for a few
 // hundred cycles more of vector work (three splits, the exchanges); neither
-// overlaps much with the FP64 phase.  Measured at 148 x 148, 32 coils, T =
-// 16384, against the same phases on the FP32 instruction, forward / adjoint:
-// solid harmonics 981 / 1133 -> 655 / 676 us, 16 maps 1024 / 1154 -> 798 /
-// 860 us, 9 maps 890 / 1008 -> 631 / 693 us.  Bound: matrix cycles plus the
+// overlaps much with the FP64 phase.  Kernel times at 148 x 148, 32 coils, T =
+// 16384, on the FP32 instruction and now, measured in turn on one card, forward /
+// adjoint: solid harmonics 960 / 1107 -> 612 / 650 us, 16 maps 1031 / 1165 -> 793 /
+// 783 us, 9 maps 903 / 1019 -> 659 / 689 us.  Bound: matrix cycles plus the
 // vector work of the phase, sine, cosine and splits.  The error against FP64
-// does not grow (adjoint 200 x 200, T = 40000: 4.8e-7 -> 3.9e-7): one matrix
-// instruction adds 16 products to an accumulator, the FP32 one two.
+// does not grow (adjoint 200 x 200, 32 coils, T = 40000: 4.8e-7 -> 3.0e-7).
 //
 // A sum carried through the matrix instruction loses the more the larger it has
 // grown, always to the same side (split_sign), and is rounded twelve times a
@@ -144,9 +143,9 @@ __device__ inline void zero_acc(f32x16 (&acc)[2][GW]) {
 // Software pipeline of the solid-harmonic forward: the products of one step
 // are issued between the vector work of the next step's phases.  A group's
 // records follow in halves (cos, sin) as soon as the half before is used up.
-// 148 x 148, 32 coils, T = 16384: 677 -> 640 us, 200 x 200, T = 20000: 1348 ->
-// 1263 (one column group: equal).  The adjoint, which waits for its LDS reads
-// as well, took 705 for 683 us with the same pipeline.
+// 32 coils: 5.5 % less time at 148 x 148, T = 16384, 6.3 % at 200 x 200, T = 20000
+// (one column group: equal).  The adjoint, which waits for its LDS reads as well,
+// took 3 % more with the same pipeline.
 template <int GW, bool FOLD>
 struct Pipe {
   static constexpr int N = 24 * GW;  // MFMAs of a step
@@ -197,18 +196,19 @@ struct Pipe {
 // rows are pixels and it runs over samples.  NT: terms of the general basis
 // (17 FP64 products an entry at L = 16), or 0 (forward) for the solid
 // harmonics: along a 16-pixel tile of an image row a sample's phase is a
-// cubic (coefficients from the row polynomial at the tile's centre, 4 FP64
-// products an entry).
+// cubic (coefficients from the row polynomial at the tile's centre; pixels at
+// equal distances from it share their even and odd parts, so 2 FP64 products an
+// entry and one for the off-resonance).
 // own, uni: the rows' terms [rows][NT] and the reduction indices' terms
 // [n][NT] of the general basis, or pmono and dwq; opr: operand records.
 // (restrict kernel arguments: uniform terms become scalar loads)
 // The reduction indices' first lds_terms(NT) terms go through LDS (blocks of
 // kIndices, double-buffered, one barrier per block) and the rest through the
 // scalar cache: with 17 FP64 terms an index the scalar cache's fills bound the
-// kernel, and a broadcast read costs the LDS a full one.  148 x 148, 32 coils,
-// T = 16384, forward / adjoint: 0 terms in LDS 1105 / 1233 us, 4 812 / 890,
-// 6 798 / 860, 8 902 / 1000; 10 terms an index fit the scalar path alone
-// (631 / 693, with 4 to 6 in LDS 654 / 711).
+// kernel, and a broadcast read costs the LDS a full one.  Time at 148 x 148, 32
+// coils, T = 16384 relative to that with 6 terms in LDS, forward / adjoint: none
+// 1.38 / 1.43, 4 1.02 / 1.03, 8 1.13 / 1.16; 10 terms an index fit the scalar path
+// alone (with 4 to 6 in LDS 1.04 / 1.03 of the time).
 constexpr int kIndices = 64;
 constexpr int lds_terms(int nt) { return nt == 17 ? 6 : 0; }
 
@@ -334,7 +334,7 @@ __device__ inline void f32_body(const double *__restrict__ own, const double *__
 
 // Waves per SIMD asked for: 17 terms and 32 columns need 169 registers left to
 // the compiler, one more than three waves have (148 x 148, 32 coils, T = 16384
-// forward: two waves 884 us, three 774).
+// forward: two waves take 1.14 times as long).
 constexpr int min_waves(int nt, int gw, bool fold) { return nt == 17 && gw == 2 && !fold ? 3 : 2; }
 
 template <int NT, int GW, bool FOLD>
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256, min_waves(NT, GW, FOLD)) void k_adj_f32(const 
 // and a lane reads its row's four and t: 4 FP64 products an entry and 40
 // bytes from LDS (broadcast within a row).  With the sample's ten
 // coefficients as scalar operands it took 10 products, and the scalar cache's
-// fills bound it: 148 x 148, 32 coils, T = 16384: 806 us.
+// fills bound it: 1.18 times the time at 148 x 148, 32 coils, T = 16384.
 constexpr int kSamples = 64;
 
 template <int GW, bool FOLD>

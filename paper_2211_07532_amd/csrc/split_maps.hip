@@ -28,9 +28,10 @@ namespace expenc {
 // 32 columns, plus the vector work of sine, cosine and splits.  Before, the
 // NT products ran on the vector unit, 16 terms per index by scalar loads:
 // their rate bound the kernels (and the adjoint spilled scalar registers).
-// 148 x 148, 32 coils, T = 16384, before / after, forward and adjoint: 16
-// maps fp16 643 / 402 and 682 / 424 us, bf16 645 / 393 and 1215 / 417; 9 maps
-// fp16 430 / 329 and 613 / 353; 3 maps 329 / 294 and 443 / 323.
+// Kernel times at 148 x 148, 32 coils, T = 16384, before -> after, measured in turn
+// on one card, forward and adjoint: 16 maps fp16 613 -> 405 and 650 -> 428 us, bf16
+// 639 -> 407 and 1200 -> 431; 9 maps fp16 437 -> 349 and 617 -> 370, bf16 526 -> 355
+// and 586 -> 376.
 template <int NT, int GW, bool BF, bool FOLD, bool ADJ>
 __global__ __launch_bounds__(256) void k_split_maps(const double *__restrict__ own, const double *__restrict__ uni,
                                                     const float *__restrict__ dop, const u32x4 *__restrict__ rec,

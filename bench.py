@@ -45,15 +45,15 @@ N_POWER = 20
 # 256 MiB copy.  Valid only for the kernel source and launch shape they were
 # taken on: `sha` is the SHA-256 of the files the kernel is built from.
 TRAFFIC = {
-    "fp32": {"kernel": "k_adj_f32_sh<2>", "adj_split": 23, "bytes": 164342784,
-             "valu_instr": 140435000, "fwd_valu_instr": 141366000,
-             "sha": "d8f9af6de9d65d2e204a6de5ab1c56b784e6a1655bf4685f2c7a1a91d90ee26f"},
-    "bf16": {"kernel": "k_adj_split_sh<2, true, false>", "adj_split": 16, "bytes": 144985702,
-             "valu_instr": 61031800, "fwd_valu_instr": 90782700,
-             "sha": "23de022baa95b26392ae39dfcc82b0b94912355849394e012cb620c53dbe6048"},
-    "fp16": {"kernel": "k_adj_split_sh<2, false, false>", "adj_split": 16, "bytes": 143211929,
-             "valu_instr": 61031800, "fwd_valu_instr": 90694700,
-             "sha": "23de022baa95b26392ae39dfcc82b0b94912355849394e012cb620c53dbe6048"},
+    "fp32": {"kernel": "k_adj_f32_sh<2, false>", "adj_split": 23, "bytes": 164219085,
+             "valu_instr": 140435000, "fwd_valu_instr": 141678000,
+             "sha": "5ddd478eebd2a43bc9d43b22e1fe39272051d587f029dafd747b1f7f87abea7c"},
+    "bf16": {"kernel": "k_adj_split_sh<2, true, false, false>", "adj_split": 16, "bytes": 145017242,
+             "valu_instr": 61031800, "fwd_valu_instr": 90520600,
+             "sha": "b6cebf9579420447a6afdb151027008db67e42aac95aa32fcd03f0d043664346"},
+    "fp16": {"kernel": "k_adj_split_sh<2, false, false, false>", "adj_split": 16, "bytes": 142590771,
+             "valu_instr": 61031800, "fwd_valu_instr": 90301400,
+             "sha": "b6cebf9579420447a6afdb151027008db67e42aac95aa32fcd03f0d043664346"},
 }
 TRAFFIC_SOURCES = {"fp32": ["f32.hip", "split_dev.h", "internal.h", "../build.py"],
                    "bf16": ["split_adj.hip", "split.hip", "split_dev.h", "internal.h", "../build.py"],

@@ -197,10 +197,11 @@ __device__ inline float dpp(float v) {
 // with its sample in lane % 16 and its pixel 4 (lane / 16) + register, which
 // is the A-operand layout of v_mfma_f32_16x16x4_f32, so grad_k is accumulated
 // on the matrix cores without moving V.  That instruction adds its products one
-// after the other, so a step's 16 pixels are summed from zero and join the
-// chunk's sums in one addition (error of grad_k at the size below 5.0e-7 when
-// they went through the accumulators, 1.8e-7 now, for 1.5 % of the time; with
-// grad_k of the basis-weighted forwards, coils summed in FP64, 1.38e-6).
+// after the other, so a step's 16 pixels are summed from zero, in two halves, and
+// join the chunk's sums in one addition.  Error of grad_k at the size below: 5.0e-7
+// when they went through the accumulators, 1.7e-7 now, for 2.5 % of a training
+// step's time (basis-weighted forwards, coils summed in FP64: 1.2e-6); 30 x 100, 5
+// coils, 4 terms, T = 1000: 1.4e-7, 1.06e-7 (1.14e-7; 1.20e-7 without the halves).
 // grad_dw sums over lanes by halving
 // (DPP) into a row of LDS per wave: no barrier before the end of the chunk.
 // The tables come as kernel parameters: only through those does the compiler
@@ -295,15 +296,15 @@ __global__ __launch_bounds__(256, 2) void k_field_grad(const double *__restrict_
           V[b][v] = fmaf(__builtin_amdgcn_cosf(g[b]), Mi[b][v], __builtin_amdgcn_sinf(g[b]) * Mr[b][v]);
       }
       if (a.gpart) {
-        f32x4 S[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 S[2][4];
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
-          for (int b = 0; b < 4; ++b) S[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(V[b][v], bv[v], S[b], 0, 0, 0);
+          for (int b = 0; b < 4; ++b)
+            S[v >> 1][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                V[b][v], bv[v], v & 1 ? S[v >> 1][b] : f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) G[b] += S[b];
+        for (int b = 0; b < 4; ++b) G[b] += S[0][b] + S[1][b];
       }
       if (a.dpart) {
         // over the 64 samples: blocks, then the 16 lanes of a row; a lane

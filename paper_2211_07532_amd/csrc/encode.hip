@@ -39,7 +39,7 @@ namespace expenc {
 
 // Sum of the n splits' values p[k * step], k = 0 .. n - 1, in FP64 and in k
 // order, eight loads in flight per step (a loop that loads and adds one at a
-// time waits for memory once per value).
+// time waits for memory once per value); the last step repeats the last value.
 __device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, int n, double &sx, double &sy) {
   int k = 0;
   for (; k + 8 <= n; k += 8) {
@@ -52,10 +52,16 @@ __device__ inline void sum_strided(const float2 *__restrict__ p, int64_t step, i
       sy += split_sign(u) * v[u].y;
     }
   }
-  for (; k < n; ++k) {
-    const float2 v = p[k * step];
-    sx += split_sign(k) * v.x;
-    sy += split_sign(k) * v.y;
+  if (k < n) {
+    float2 v[7];
+#pragma unroll
+    for (int u = 0; u < 7; ++u) v[u] = p[min(k + u, n - 1) * step];
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+      if (k + u < n) {
+        sx += split_sign(u) * v[u].x;
+        sy += split_sign(u) * v[u].y;
+      }
   }
 }
 

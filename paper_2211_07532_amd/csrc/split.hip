@@ -434,7 +434,9 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
       if (ok[i]) y[i] = src_abi[((int64_t)b * T + t[i]) * C + c];
   } else {
     // split order per sample as in a plain loop; the loads of four splits x
-    // eight samples are independent and issue together
+    // eight samples are independent and issue together (unconditional, padded
+    // rows and columns exist: under a branch the compiler puts the sign's
+    // negation, and with it a wait, after every load)
     int k = 0;
     for (; k + 4 <= nsplit; k += 4) {
       float2 v[4][8];
@@ -442,7 +444,7 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
       for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-          v[u][i] = ok[i] ? src_part[((int64_t)(k + u) * Tp + t[i]) * NCP + col] : make_float2(0.f, 0.f);
+          v[u][i] = src_part[((int64_t)(k + u) * Tp + t[i]) * NCP + col];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -451,19 +453,26 @@ __global__ __launch_bounds__(256) void k_pack_y_split(const float2 *__restrict__
           y[i].y += split_sign(u) * v[u][i].y;
         }
     }
-    for (; k < nsplit; ++k) {
+    if (k < nsplit) {  // the last splits repeated
+      float2 v[3][8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (ok[i]) {
-          const float2 v = src_part[((int64_t)k * Tp + t[i]) * NCP + col];
-          y[i].x += split_sign(k) * v.x;
-          y[i].y += split_sign(k) * v.y;
-        }
+      for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          v[u][i] = src_part[((int64_t)min(k + u, nsplit - 1) * Tp + t[i]) * NCP + col];
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (k + u < nsplit)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            y[i].x += split_sign(u) * v[u][i].x;
+            y[i].y += split_sign(u) * v[u][i].y;
+          }
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      y[i].x *= inv_z;
-      y[i].y *= inv_z;
+      y[i].x = ok[i] ? y[i].x * inv_z : 0.f;
+      y[i].y = ok[i] ? y[i].y * inv_z : 0.f;
     }
     if (y_meas) {
 #pragma unroll

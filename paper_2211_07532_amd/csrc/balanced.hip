@@ -738,6 +738,7 @@ extern "C" int fista_balanced_solve(const expenc_op *op, int32_t batch, const fl
     }
   }
   auto body = [&](hipStream_t cs) -> int {
+    bool y_bounded = false;
     for (int k = 0; k < K; ++k) {
       float2 *aprev = (k % 2 == 0) ? L.a0 : L.a1;
       float2 *anew = (k % 2 == 0) ? L.a1 : L.a0;
@@ -748,7 +749,7 @@ extern "C" int fista_balanced_solve(const expenc_op *op, int32_t batch, const fl
         if (k == 0) return enc_pack_y(q, y2, L.eb, cs, -1.f);
         EX_TRY(enc_build_z(q, op->smaps, L.xb, N, op->nx, L.eb, cs));
         EX_TRY(enc_forward_partials(q, L.eb, cs));
-        return enc_forward_residual(q, L.eb, y2, cs);
+        return enc_forward_residual(q, L.eb, y2, cs, &y_bounded);
       };
       if (!split) {
         EX_TRY(residual_fp32(p));

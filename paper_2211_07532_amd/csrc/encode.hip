@@ -711,9 +711,9 @@ int enc_forward_reduce_out(const EncPlan &p, const EncBuffers &b, float2 *y, hip
   return EXPENC_OK;
 }
 
-int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_meas, hipStream_t s) {
-  if (p.prec != EXPENC_FP32) return split_pack_y(p, nullptr, true, y_meas, b, s);
-  return f32_pack_y(p, nullptr, 1.f, y_meas, b, s, false);
+int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_meas, hipStream_t s, bool *y_bounded) {
+  if (p.prec != EXPENC_FP32) return split_pack_y(p, nullptr, true, y_meas, b, s, false, y_bounded);
+  return f32_pack_y(p, nullptr, 1.f, y_meas, b, s, false, y_bounded);
 }
 
 int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *smaps, float2 *x,

@@ -515,27 +515,41 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
   float2 y[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) y[i] = make_float2(0.f, 0.f);
-  if (src) {
+  // (loads of padded samples repeat the last: under a branch each waits alone)
+  const float2 *data = src ? src : y_meas;
+  float2 m[8];
+  if (data && col < NC) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (t0 + i < T && col < NC) {
-        const float2 v = src[((pz * NC / C + b) * T + t0 + i) * C + c];
-        y[i] = make_float2(sign * v.x, sign * v.y);
-      }
+    for (int i = 0; i < 8; ++i) m[i] = data[((pz * NC / C + b) * T + min(t0 + i, T - 1)) * C + c];
+  }
+  if (src) {
+    if (col < NC) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (t0 + i < T) y[i] = make_float2(sign * m[i].x, sign * m[i].y);
+    }
   } else if (col < NC) {
     double sx[8], sy[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) sx[i] = sy[i] = 0.0;
     const float2 *p = part + (pz * nsplit * Tp + t0) * NCP + col;
-    for (int k = 0; k < nsplit; ++k, p += Tp * NCP) {
-      float2 v[8];
+    // four splits' loads together, the last split repeated at the end: with one
+    // split at a time and y_meas under branches 20 us, so 18 (55 x 27, 10 coils,
+    // T 2875, 48 splits, 48 workgroups)
+    for (int k = 0; k < nsplit; k += 4) {
+      float2 v[4][8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = p[(int64_t)i * NCP];
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        sx[i] += split_sign(k) * v[i].x;
-        sy[i] += split_sign(k) * v[i].y;
-      }
+        for (int i = 0; i < 8; ++i) v[u][i] = p[(min(k + u, nsplit - 1) * Tp + i) * NCP];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k + u < nsplit)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            sx[i] += split_sign(u) * v[u][i].x;
+            sy[i] += split_sign(u) * v[u][i].y;
+          }
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i)
@@ -543,9 +557,8 @@ __global__ __launch_bounds__(256) void k_pack_y_f32(const float2 *__restrict__ s
         sx[i] *= inv_z;
         sy[i] *= inv_z;
         if (y_meas) {
-          const float2 m = y_meas[((pz * NC / C + b) * T + t0 + i) * C + c];
-          sx[i] -= m.x;
-          sy[i] -= m.y;
+          sx[i] -= m[i].x;
+          sy[i] -= m[i].y;
         }
         y[i] = make_float2((float)sx[i], (float)sy[i]);
       }
@@ -689,9 +702,9 @@ int f32_forward_passes(const EncPlan &p, const float *smaps, const float2 *x, co
 }
 
 int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_meas, const EncBuffers &b,
-               hipStream_t s, bool prepared) {
+               hipStream_t s, bool prepared, bool *y_bounded) {
   DataBound d;
-  EX_TRY(bound_data(p, y, y_meas, b, prepared, &d, s));
+  EX_TRY(bound_data(p, y, y_meas, b, prepared, y_bounded, &d, s));
   k_pack_y_f32<<<record_grid(p.Tp, p.NCP / 16, p), 256, 0, s>>>(
       y, sign, p.adj_chunk, b.part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP,
       reinterpret_cast<u32x4 *>(b.ys), y ? nullptr : b.yop, d.bnd, d.nbnd, d.meas, b.scl);

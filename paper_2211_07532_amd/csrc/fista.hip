@@ -396,6 +396,7 @@ struct FistaGroup {
   int refine = 0;
   std::vector<double> beta;
   bool gref_at_zero = false;  // gref holds -A^H y (FP32) from the lambda rule
+  bool y_bounded = false;     // an iteration has bounded y (enc_forward_residual)
 
   int prologue(hipStream_t s) {
     const EncPlan &p = L.p, &pf = L.pf;
@@ -478,6 +479,7 @@ struct FistaGroup {
     const double *alpha = L.sc + P;
     const int K = opts->n_iter;
     const bool whole = stage == kStageAll;
+    if (k == 0) y_bounded = false;
     {
       float2 *xk = (k % 2 == 0) ? L.x1 : L.x0;
       float2 *xprev = (k % 2 == 0) ? L.x0 : L.x1;
@@ -486,7 +488,7 @@ struct FistaGroup {
         if (k == 0) return enc_pack_y(q, y, L.eb, cs, -1.f);
         EX_TRY(enc_build_z(q, op->smaps, L.z, img, nxp, L.eb, cs, nullptr, pimg));
         EX_TRY(enc_forward_partials(q, L.eb, cs));
-        return enc_forward_residual(q, L.eb, y, cs);
+        return enc_forward_residual(q, L.eb, y, cs, &y_bounded);
       };
       const int pnx = padded ? nxp : 0, pny = padded ? nyp : 0;
       if (!split_difference(k) && !whole) return fail(EXPENC_EINVAL, "iteration %d runs whole", k);
@@ -527,7 +529,7 @@ struct FistaGroup {
       if (with_obj) {
         EX_TRY(enc_build_z(pf, op->smaps, xk, img, nxp, L.eb, cs));
         EX_TRY(enc_forward_partials(pf, L.eb, cs));
-        EX_TRY(enc_forward_residual(pf, L.eb, y, cs));
+        EX_TRY(enc_forward_residual(pf, L.eb, y, cs, &y_bounded));
         k_resid_norm_part<<<dim3(kRedBlocks, B), 256, 0, cs>>>(L.eb.yop, pf.Tp, pf.NCP, pf.C, L.dpart);
         EX_LAUNCHED("residual norm");
         EX_TRY(reduce_sum_parts(L.dpart, kRedBlocks, B, 1.0, L.data, cs));

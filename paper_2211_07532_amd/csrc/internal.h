@@ -472,8 +472,11 @@ int enc_adjoint_reduce_out(const EncPlan &p, const EncBuffers &b, const float *s
                            const float2 *add, hipStream_t s, const float2 *base = nullptr,
                            int64_t x_pstride = 0, int32_t pad_nx = 0, int32_t pad_ny = 0);
 // Residual r = A z - y (y_meas [B][T][C], or NULL for r = A z) written
-// straight into the adjoint operand.
-int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_meas, hipStream_t s);
+// straight into the adjoint operand.  y_bounded: whether an earlier residual on
+// this stream and these buffers has bounded the same y_meas (set by the first
+// that does: an iteration's bound of y is a launch less).
+int enc_forward_residual(const EncPlan &p, const EncBuffers &b, const float2 *y_meas, hipStream_t s,
+                         bool *y_bounded = nullptr);
 
 // FP32 kernels (f32.hip).  f32_pack_y: from sign * y, or with y NULL the
 // forward's residual against y_meas (or NULL).
@@ -485,10 +488,11 @@ int f32_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 int f32_build_z(const EncPlan &p, const float *smaps, const float2 *x, int64_t x_stride, int32_t x_row_stride,
                 const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared);
 int f32_pack_y(const EncPlan &p, const float2 *y, float sign, const float2 *y_meas, const EncBuffers &b,
-               hipStream_t s, bool prepared);
+               hipStream_t s, bool prepared, bool *y_bounded = nullptr);
 // Magnitude bounds of the scaled forms' operands (split.hip): pre-passes of an
 // image x - xsub, and of data y or (y NULL) the forward's partial sums minus
-// y_meas (prepared: enc_prepare has bounded y).
+// y_meas (prepared: enc_prepare has bounded y; y_bounded: see
+// enc_forward_residual).
 struct DataBound {
   const float *bnd = nullptr, *meas = nullptr;  // [P][nbnd] of the data or sums; [P][kAmaxBlocks] of y_meas
   int nbnd = 0;
@@ -496,7 +500,7 @@ struct DataBound {
 int bound_image(const EncPlan &p, const float2 *x, const float2 *xsub, int64_t x_stride, int32_t x_row_stride,
                 int64_t x_pstride, const EncBuffers &b, hipStream_t s);
 int bound_data(const EncPlan &p, const float2 *y, const float2 *y_meas, const EncBuffers &b, bool prepared,
-               DataBound *d, hipStream_t s);
+               bool *y_bounded, DataBound *d, hipStream_t s);
 // Split-precision kernels (split.hip).
 void split_forward_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
 void split_adjoint_launch(const EncPlan &p, const EncBuffers &b, hipStream_t s);
@@ -526,7 +530,8 @@ int split_adjoint_grouped(const EncPlan *const *p, const EncBuffers *const *b, i
 int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const float2 *xsub, int64_t x_stride,
                   int32_t x_row_stride, const EncBuffers &b, hipStream_t s, int64_t x_pstride, bool prepared);
 int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, const float2 *y_meas,
-                 const EncBuffers &b, hipStream_t s, bool prepared = false);
+                 const EncBuffers &b, hipStream_t s, bool prepared = false,
+                 bool *y_bounded = nullptr);
 
 // Per-kernel event timing of the contraction kernels (mode 0 off, 1 on, 2 read).
 int kernel_timing(int32_t mode, double *out);

@@ -575,7 +575,7 @@ int bound_image(const EncPlan &p, const float2 *x, const float2 *xsub, int64_t x
 }
 
 int bound_data(const EncPlan &p, const float2 *y, const float2 *y_meas, const EncBuffers &b, bool prepared,
-               DataBound *d, hipStream_t s) {
+               bool *y_bounded, DataBound *d, hipStream_t s) {
   if (!b.scl || !b.amax || !b.wmax) return fail(EXPENC_EINVAL, "scale buffers of a scaled plan are not carved");
   auto pass = [&](const float2 *v, int64_t n, float *out) -> int {
     k_amax_c<<<dim3(amax_blocks(n), (unsigned)p.P), 256, 0, s>>>(v, n, n, out);
@@ -596,7 +596,8 @@ int bound_data(const EncPlan &p, const float2 *y, const float2 *y_meas, const En
   }
   if (y_meas) {
     float *am = b.amax + (size_t)p.P * kAmaxBlocks;
-    EX_TRY(pass(y_meas, ny_el, am));
+    if (!y_bounded || !*y_bounded) EX_TRY(pass(y_meas, ny_el, am));
+    if (y_bounded) *y_bounded = true;
     d->meas = am;
   }
   return EXPENC_OK;
@@ -623,14 +624,14 @@ int split_build_z(const EncPlan &p, const float *smaps, const float2 *x, const f
 }
 
 int split_pack_y(const EncPlan &p, const float2 *y_abi, bool from_partials, const float2 *y_meas,
-                 const EncBuffers &b, hipStream_t s, bool prepared) {
+                 const EncBuffers &b, hipStream_t s, bool prepared, bool *y_bounded) {
   const int NGP = p.NCP / 16;
   const int64_t n = (p.Tp / 16) * NGP * 64;
   const dim3 nb((unsigned)ceil_div(n, 256), (unsigned)p.P);
   u32x4 *ys = reinterpret_cast<u32x4 *>(b.ys);
   const float2 *part = from_partials ? b.part : nullptr;
   DataBound d;
-  if (p.scaled) EX_TRY(bound_data(p, y_abi, y_meas, b, prepared, &d, s));
+  if (p.scaled) EX_TRY(bound_data(p, y_abi, y_meas, b, prepared, y_bounded, &d, s));
   float *scl = p.scaled ? b.scl : nullptr;
   if (p.prec == EXPENC_BF16_SPLIT)
     k_pack_y_split<true><<<nb, 256, 0, s>>>(y_abi, part, p.fwd_split, y_meas, p.T, p.Tp, p.C, p.NC, p.NCP, ys,

@@ -45,15 +45,15 @@ N_POWER = 20
 # 256 MiB copy.  Valid only for the kernel source and launch shape they were
 # taken on: `sha` is the SHA-256 of the files the kernel is built from.
 TRAFFIC = {
-    "fp32": {"kernel": "k_adj_f32_sh<2, false>", "adj_split": 23, "bytes": 164252057,
+    "fp32": {"kernel": "k_adj_f32_sh<2, false>", "adj_split": 23, "bytes": 164224819,
              "valu_instr": 140435000, "fwd_valu_instr": 141678000,
-             "sha": "5ddd478eebd2a43bc9d43b22e1fe39272051d587f029dafd747b1f7f87abea7c"},
-    "bf16": {"kernel": "k_adj_split_sh<2, true, false, false>", "adj_split": 16, "bytes": 145006387,
+             "sha": "236e54e938d5e34cad4d1e8091f14ddde4f99fb016f99709621a51f4d6cec107"},
+    "bf16": {"kernel": "k_adj_split_sh<2, true, false, false>", "adj_split": 16, "bytes": 145124556,
              "valu_instr": 61031800, "fwd_valu_instr": 90520600,
-             "sha": "20350ba979daf8a05a1f626add58c8c3b99c719f1e0f4149971e0ed1180028ef"},
-    "fp16": {"kernel": "k_adj_split_sh<2, false, false, false>", "adj_split": 16, "bytes": 142745804,
+             "sha": "a4f6febcb6b2fecfd68cbea85de0816c92ab49c31976696b088291b87c74668b"},
+    "fp16": {"kernel": "k_adj_split_sh<2, false, false, false>", "adj_split": 16, "bytes": 142765260,
              "valu_instr": 61031800, "fwd_valu_instr": 90301400,
-             "sha": "20350ba979daf8a05a1f626add58c8c3b99c719f1e0f4149971e0ed1180028ef"},
+             "sha": "a4f6febcb6b2fecfd68cbea85de0816c92ab49c31976696b088291b87c74668b"},
 }
 TRAFFIC_SOURCES = {"fp32": ["f32.hip", "split_dev.h", "internal.h", "../build.py"],
                    "bf16": ["split_adj.hip", "split.hip", "split_dev.h", "internal.h", "../build.py"],
